@@ -60,8 +60,12 @@ size_t kunlun_workspace_bytes(int op, int B, int H, int d, int max_q, int max_kv
                seed_grad_rows_bytes(total_q, H, d, KUNLUN_FP32) + seed_grad_partial_bytes(B, (int64_t)max_q * H * d);
     case KUNLUN_OP_GDPA_BWD:
     case KUNLUN_OP_SWA_BWD:
-        return WS_HEADER_BYTES + order_bytes(B) +
-               mfma_bwd_tiled_workspace(B, H, d, max_q, max_kv, total_q, total_kv, op == KUNLUN_OP_SWA_BWD);
+    {
+        const bool windowed = op == KUNLUN_OP_SWA_BWD;
+        const size_t tiled = mfma_bwd_tiled_workspace(B, H, d, max_q, max_kv, total_q, total_kv, windowed);
+        const size_t wide = windowed ? 0 : tile_table_bytes(B, total_kv) + mfma_bwd_wide_workspace(B, H, d, max_q, max_kv, total_kv);
+        return WS_HEADER_BYTES + order_bytes(B) + (wide > tiled ? wide : tiled);
+    }
     default:
         return 0;
     }
@@ -315,6 +319,9 @@ int gdpa_bwd_checked(const void* q, const void* k, const void* v, const void* o,
             if (e != hipSuccess) return KUNLUN_ERR_LAUNCH;
         }
         e = launch_mfma_bwd(p, (char*)workspace + WS_HEADER_BYTES + order_bytes(B), s);
+    } else if (mfma_bwd_wide_supported(p, dtype)) {
+        char* const tables = (char*)workspace + WS_HEADER_BYTES + order_bytes(B);
+        e = launch_mfma_bwd_wide(p, workspace, (char*)workspace + WS_HEADER_BYTES, tables, tables + tile_table_bytes(B, total_kv), s);
     } else if (mfma_bwd_tiled_supported(p, dtype)) {
         e = launch_mfma_bwd_tiled(p, (char*)workspace + WS_HEADER_BYTES + order_bytes(B), any_softmax, s);
     } else {

@@ -1,0 +1,73 @@
+"""The one-pass backward for 65..256 queries per example at head dimension 128 (whole histories, and ranges of them with
+partial query gradients) against the CPU oracle, at the edges of its tiles, query blocks and ranges."""
+import math
+
+import numpy as np
+import pytest
+import torch
+
+from paper_2602_10016_amd import workloads as W
+from tests.helpers import TOL, assert_close, assert_close_sums, offsets_dev, to_dev, to_np
+
+pytestmark = pytest.mark.gpu
+
+# (B, H, queries, history lengths drawn from lo..hi, first lengths fixed): whole histories when a compute unit has
+# enough work besides the longest one, ranges of 8 tiles (256 keys) else - one key more and less than a range, too
+CASES = [
+    (130, 8, 65, 1, 40, [0, 1, 31, 32, 33, 64]),
+    (64, 4, 256, 20, 60, [0, 33, 60]),
+    (5, 2, 256, 1, 700, [0, 255, 256, 257, 513]),
+    (9, 3, 97, 1, 300, [256, 0, 1, 257]),
+    (3, 1, 129, 500, 1100, [1025]),
+    (4, 2, 255, 33, 64, [33]),
+]
+
+
+@pytest.mark.parametrize("B,H,n,lo,hi,fixed", CASES)
+@pytest.mark.parametrize("act", [0, 3])
+@pytest.mark.parametrize("ragged", [False, True])
+def test_backward_65_to_256_queries(oracle, B, H, n, lo, hi, fixed, act, ragged):
+    from paper_2602_10016_amd import binding as kb
+    rng = np.random.default_rng(1000 * B + n)
+    lengths = np.concatenate([fixed, rng.integers(lo, hi + 1, size=B - len(fixed))]).astype(np.int64)
+    wl = W.make("cfg5", B + n, B=B, H=H, d=128, Nq=n, lengths=("list", lengths), scale=1 / math.sqrt(128))
+    q, d_o, q_off = wl.q, wl.d_o, None
+    if ragged:  # an example without queries, one with a single one, one that ends a block of 32
+        counts = rng.integers(1, n + 1, size=B)
+        counts[:3] = [n, 0, 1]
+        counts[-1] = 64
+        q_off = W.offsets_from_lengths(counts)
+        q, d_o = q[:q_off[-1]], d_o[:q_off[-1]]
+    mk = wl.max_kv
+    qd, k, v, dod = to_dev(q, "bf16"), to_dev(wl.k, "bf16"), to_dev(wl.v, "bf16"), to_dev(d_o, "bf16")
+    kvo, qo = offsets_dev(wl.kv_offsets), offsets_dev(q_off)
+    o, lse = kb.gdpa_fwd(qd, k, v, kvo, wl.scale, act, q_offsets=qo, max_q=n, max_kv=mk)
+    out = tuple(torch.full_like(t, float("nan")) for t in (qd, k, v))
+    got = kb.gdpa_bwd(qd, k, v, dod, kvo, wl.scale, act, o=o, lse=lse, q_offsets=qo, max_q=n, max_kv=mk, out=out)
+    again = kb.gdpa_bwd(qd, k, v, dod, kvo, wl.scale, act, o=o, lse=lse, q_offsets=qo, max_q=n, max_kv=mk)
+    torch.cuda.synchronize()
+    refs = oracle.gdpa_bwd(q, wl.k, wl.v, d_o, wl.kv_offsets, wl.scale, act, q_offsets=q_off, max_q=n)
+    for a, b, ref, name in zip(got, again, refs, ("dQ", "dK", "dV")):
+        what = f"B={B} H={H} n={n} act={act} ragged={ragged} {name}"
+        if name == "dQ" and act == 3 and mk > 512:
+            # Scores of order one without a normaliser: dQ sums ~1000 products with a bf16-rounded dS, each off by at
+            # most 2^-8 of itself and 2^-9 / sqrt(3) = 1.1e-3 RMS, so the sum is off by 1.1e-3 of its RMS (about 4
+            # here: 5 standard deviations are 2.2e-2 absolute, also where the value is near zero), plus its own
+            # rounding 2^-9 |r|: within 2e-2 (rms + |r|) with a factor of three to spare.
+            assert_close_sums(to_np(a), ref, TOL["bf16"], what)
+        else:
+            assert_close(to_np(a), ref, TOL["bf16"], what)
+        assert torch.equal(a, b), f"{name} differs between two runs"
+
+
+@pytest.mark.parametrize("act", [1, 2, 4, 5, 6])
+def test_backward_wide_every_score_function(oracle, act):
+    from paper_2602_10016_amd import binding as kb
+    wl = W.make("cfg5", act, B=6, H=2, d=128, Nq=70, lengths=("list", np.array([300, 0, 40, 257, 31, 64])), scale=0.09)
+    q, k, v, d_o = (to_dev(x, "bf16") for x in (wl.q, wl.k, wl.v, wl.d_o))
+    got = kb.gdpa_bwd(q, k, v, d_o, offsets_dev(wl.kv_offsets), wl.scale, act, max_q=70, max_kv=300)
+    torch.cuda.synchronize()
+    refs = oracle.gdpa_bwd(wl.q, wl.k, wl.v, wl.d_o, wl.kv_offsets, wl.scale, act, max_q=70)
+    for a, ref, name in zip(got, refs, ("dQ", "dK", "dV")):
+        # dQ: up to 300 products with a rounded dS at scores of order one, RMS about 4 - the bound above
+        (assert_close_sums if name == "dQ" else assert_close)(to_np(a), ref, TOL["bf16"], f"act={act} {name}")
