@@ -111,6 +111,11 @@ hipError_t launch_sumkron_fused(const void* x, const void* z, const void* w, voi
                                 hipStream_t stream);
 hipError_t launch_sumkron(const void* x, const void* z, const void* w, void* y, int B, int S, int T, int D, int k,
                           int dtype, void* workspace, hipStream_t stream);
+// Backward in two kernels, for T = 32, S in {128, 256}, D in {128, 256, 384}, k <= 8 (sumkron_bwd_fused.hip)
+bool sumkron_bwd_fused_supported(int S, int T, int D, int k, int dtype);
+size_t sumkron_bwd_fused_workspace(int B, int S, int D, int k);
+hipError_t launch_sumkron_bwd_fused(const void* x, const void* z, const void* w, const void* dy, void* dx, void* dz, void* dw, int B, int S,
+                                    int D, int k, void* workspace, hipStream_t stream);
 bool sumkron_bwd_tiled_supported(int B, int S, int T, int D, int k, int dtype);
 size_t sumkron_bwd_workspace(int B, int S, int T, int D, int k, int dtype);
 hipError_t launch_sumkron_bwd(const void* x, const void* z, const void* w, const void* dy, void* dx, void* dz, void* dw, int B,

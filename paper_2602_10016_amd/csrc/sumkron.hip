@@ -546,7 +546,10 @@ static BwdLayout sumkron_bwd_layout(int B, int S, int T, int D, int k, int dtype
     l.total = l.partial + align_up(p1 > p2 ? p1 : p2, 256);
     return l;
 }
-size_t sumkron_bwd_workspace(int B, int S, int T, int D, int k, int dtype) { return sumkron_bwd_layout(B, S, T, D, k, dtype).total; }
+size_t sumkron_bwd_workspace(int B, int S, int T, int D, int k, int dtype) {
+    if (sumkron_bwd_fused_supported(S, T, D, k, dtype)) return sumkron_bwd_fused_workspace(B, S, D, k);
+    return sumkron_bwd_layout(B, S, T, D, k, dtype).total;
+}
 
 template <typename T_>
 static void launch_bwd_plain(const T_* x, const T_* z, const T_* w, const T_* dy, T_* dx, T_* dz, T_* dw, int B, int S, int T,
@@ -574,6 +577,8 @@ hipError_t launch_sumkron_bwd(const void* x, const void* z, const void* w, const
         }
         return hipGetLastError();
     }
+    if (sumkron_bwd_fused_supported(S, T, D, k, dtype))
+        return launch_sumkron_bwd_fused(x, z, w, dy, dx, dz, dw, B, S, D, k, workspace, stream);
     const BwdLayout l = sumkron_bwd_layout(B, S, T, D, k, dtype);
     char* ws = (char*)workspace;
     if (!sumkron_bwd_tiled_supported(B, S, T, D, k, dtype)) {
