@@ -235,6 +235,8 @@ int kunlun::gdpa_fwd_checked(const void* q, const void* k, const void* v, void* 
             if (e != hipSuccess) return KUNLUN_ERR_LAUNCH;
         }
         e = launch_mfma_fwd(p, s);
+    } else if (fp32_fwd_supported(p, dtype)) {
+        e = launch_fp32_fwd(p, s);
     } else {
         e = launch_scalar_fwd(p, dtype, s);
     }

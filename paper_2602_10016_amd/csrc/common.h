@@ -75,6 +75,9 @@ hipError_t launch_check_offsets(const int32_t* off, int B, int64_t total, int ma
 bool schedule_is_moot(int64_t workgroups, int wgs_per_cu);
 hipError_t launch_scalar_fwd(const AttnParams& p, int dtype, hipStream_t stream);
 hipError_t launch_scalar_bwd(const AttnParams& p, int dtype, hipStream_t stream);
+// fp32 forward, d in {32, 64, 128}, no window (attn_fwd_fp32_mfma.hip)
+bool fp32_fwd_supported(const AttnParams& p, int dtype);
+hipError_t launch_fp32_fwd(const AttnParams& p, hipStream_t stream);
 bool mfma_fwd_supported(const AttnParams& p, int dtype);
 hipError_t launch_mfma_fwd(const AttnParams& p, hipStream_t stream);
 // True when the forward launch walks query tiles (window op, or more than 64 queries per
