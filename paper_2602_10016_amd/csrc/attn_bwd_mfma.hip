@@ -208,18 +208,14 @@ __device__ __forceinline__ void attn_bwd_item(const AttnParams& p, char* smem, i
 #pragma unroll
         for (int qb = 0; qb < NQB; ++qb) {
             float pv[16], dsv[16];
+            if (SOFTMAX) {
 #pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const float s = sacc[qb][v] * sc;
-                float val, der;
-                if (SOFTMAX) {
-                    val = fast_exp2(s - lse2[qb]);
-                    dsv[v] = val * (dpacc[qb][v] - delta[qb]) * p.scale;
-                } else {
-                    act_fast_vd<ACT>(s, val, der);
-                    dsv[v] = dpacc[qb][v] * der * p.scale;
+                for (int v = 0; v < 16; ++v) {
+                    pv[v] = fast_exp2(sacc[qb][v] * sc - lse2[qb]);
+                    dsv[v] = pv[v] * (dpacc[qb][v] - delta[qb]) * p.scale;
                 }
-                pv[v] = val;
+            } else {
+                act_tile_grad<ACT>(sacc[qb], dpacc[qb], sc, pv, dsv);
             }
             if (need_mask) {
 #pragma unroll

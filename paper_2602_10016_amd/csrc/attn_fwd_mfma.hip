@@ -222,7 +222,7 @@ __device__ __forceinline__ void attn_fwd_item(const AttnParams& p, char* lds, in
         bf16x8 pf[NQB][2];
 #pragma unroll
         for (int qb = 0; qb < NQB; ++qb)
-            score_to_weights<ACT, DB, NQB>(sacc[qb], need_mask, (unsigned)(key_base + 4 * g - key_lo), key_span, sc, m_ref[qb],
+            score_to_weights<ACT, DB, NQB, false, true>(sacc[qb], need_mask, (unsigned)(key_base + 4 * g - key_lo), key_span, sc, m_ref[qb],
                                            l_run[qb], oacc, qb, pf[qb]);
         // ---- O^T += V^T P^T
 #pragma unroll

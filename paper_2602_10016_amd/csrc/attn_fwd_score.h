@@ -22,10 +22,11 @@ constexpr float SOFTMAX_LAZY_LOG2 = 8.f;
 // Key k is visible iff (unsigned)(k - key_lo) <= key_span; rel0 = key_base + 4g - key_lo.
 // need_mask (wave-uniform): some (query, key) pair of the tile is not visible.
 // sc = scale (activation heads) or scale * log2(e) (softmax heads; scale > 0).
+// SMALL_FORM: tiles whose scores allow it take the short form of the score function (mfma_tile.h).
 // FRESH: the first tile of a query block under softmax - m_ref = -inf, l_run = 0 and the accumulators hold nothing
 // yet (they need not even be initialised), so the reference simply becomes the tile's maximum and nothing is
 // rescaled; the result is the same, bit for bit, as that of the general path on zeroed accumulators.
-template <int ACT, int DB, int NQB, bool FRESH = false>
+template <int ACT, int DB, int NQB, bool FRESH = false, bool SMALL_FORM = false>
 __device__ __forceinline__ void score_to_weights(const f32x16& sacc, bool need_mask, unsigned rel0, unsigned key_span,
                                                  float sc, float& m_ref, float& l_run, f32x16 (&oacc)[DB][NQB], int qb,
                                                  bf16x8 (&pf)[2]) {
@@ -70,17 +71,13 @@ __device__ __forceinline__ void score_to_weights(const f32x16& sacc, bool need_m
             sum += pv[v];
         }
         l_run += sum;
-    } else if (need_mask) {
-        asm volatile("");  // a branch, as above
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            const bool ok = rel0 + (unsigned)(8 * (v >> 2) + (v & 3)) <= key_span;
-            const float w = act_fast<ACT>(pv[v] * sc);
-            pv[v] = ok ? w : 0.f;
-        }
     } else {
+        act_tile<ACT, SMALL_FORM>(sacc, sc, pv);
+        if (need_mask) {
+            asm volatile("");  // a branch, as above
 #pragma unroll
-        for (int v = 0; v < 16; ++v) pv[v] = act_fast<ACT>(pv[v] * sc);
+            for (int v = 0; v < 16; ++v) pv[v] = rel0 + (unsigned)(8 * (v >> 2) + (v & 3)) <= key_span ? pv[v] : 0.f;
+        }
     }
 #pragma unroll
     for (int c = 0; c < 2; ++c)

@@ -208,6 +208,38 @@ __device__ __forceinline__ float phi_neg_abs(float x, float& gauss) {
     return 0.5f * poly * t * gauss;
 }
 
+// GELU for |x| <= 1 without a transcendental: cdf(x) = 1/2 + x q(x^2) and pdf(x) by near-minimax polynomials of degree
+// 4 and 5 (fits at Chebyshev nodes of x^2 in [0, 1], rounded to fp32; errors 2e-8, where the general form has 7.5e-8).  With the 1/tau scaling of Eq. (GDPA) every score is far inside.  8 (with slope 14) vector operations
+// against 16 (20) and two quarter-rate ones.
+constexpr float GELU_Q0 = 3.9894226193e-01f, GELU_Q1 = -6.6489607096e-02f, GELU_Q2 = 9.9673019722e-03f, GELU_Q3 = -1.1695192661e-03f,
+                GELU_Q4 = 9.4317372714e-05f;
+constexpr float GELU_P0 = 3.9894229174e-01f, GELU_P1 = -1.9947089255e-01f, GELU_P2 = 4.9864895642e-02f, GELU_P3 = -8.2988310605e-03f,
+                GELU_P4 = 1.0143655818e-03f, GELU_P5 = -8.1091340689e-05f;
+__device__ __forceinline__ float gelu_small_cdf(float x, float u) {
+    float q = fmaf(u, GELU_Q4, GELU_Q3);
+    q = fmaf(u, q, GELU_Q2);
+    q = fmaf(u, q, GELU_Q1);
+    q = fmaf(u, q, GELU_Q0);
+    return fmaf(x, q, 0.5f);
+}
+__device__ __forceinline__ float gelu_small_pdf(float u) {
+    float q = fmaf(u, GELU_P5, GELU_P4);
+    q = fmaf(u, q, GELU_P3);
+    q = fmaf(u, q, GELU_P2);
+    q = fmaf(u, q, GELU_P1);
+    return fmaf(u, q, GELU_P0);
+}
+// True when the score function has such a form and all scores of the wave are inside its range.  Wave-uniform.  (The
+// maximum passes over NaN scores; both forms return NaN for them.)
+template <int ACT>
+__device__ __forceinline__ bool scores_are_small(const f32x16& s, float scale) {
+    if constexpr (ACT != KUNLUN_ACT_GELU) return false;
+    float m = 0.f;
+#pragma unroll
+    for (int v = 0; v < 16; v += 2) m = fmaxf(m, fmaxf(fabsf(s[v]), fabsf(s[v + 1])));
+    return __builtin_amdgcn_ballot_w64(!(m * fabsf(scale) <= 1.f)) == 0;
+}
+
 template <int ACT>
 __device__ __forceinline__ float act_fast(float x) {
     if constexpr (ACT == KUNLUN_ACT_IDENTITY) return x;
@@ -260,6 +292,46 @@ __device__ __forceinline__ void act_fast_vd(float x, float& val, float& der) {
         const float cdf = gelu_poly_cdf(x, slope);
         val = x * cdf;
         der = fmaf(x, slope, cdf);
+    }
+}
+
+// Weights of a score tile: raw scores times scale through the score function.  SMALL_FORM: in the short form where it
+// exists and the tile allows it.  For kernels with registers to spare: 1024 items of cfg2's kind (GELU) 37 -> 33 us; in
+// the query-tiled forward the second form costs a wave per SIMD (58 -> 65 us for 32 keys per example), in the one-pass
+// backward for few keys it spills (104 -> 246 us).
+template <int ACT, bool SMALL_FORM>
+__device__ __forceinline__ void act_tile(const f32x16& s, float scale, float (&val)[16]) {
+    if (SMALL_FORM && scores_are_small<ACT>(s, scale)) {
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+            const float x = s[v] * scale;
+            val[v] = x * gelu_small_cdf(x, x * x);
+        }
+    } else {
+#pragma unroll
+        for (int v = 0; v < 16; ++v) val[v] = act_fast<ACT>(s[v] * scale);
+    }
+}
+// ... and the score gradients ds = dp Act'(s scale) scale
+template <int ACT>
+__device__ __forceinline__ void act_tile_grad(const f32x16& s, const f32x16& dp, float scale, float (&val)[16], float (&ds)[16]) {
+    if (scores_are_small<ACT>(s, scale)) {
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+            const float x = s[v] * scale, u = x * x;
+            const float cdf = gelu_small_cdf(x, u);
+            val[v] = x * cdf;
+            ds[v] = dp[v] * fmaf(x, gelu_small_pdf(u), cdf) * scale;
+            if ((v & 3) == 3) __builtin_amdgcn_sched_barrier(0);  // (four at a time: more would cost registers)
+        }
+    } else {
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+            float der;
+            act_fast_vd<ACT>(s[v] * scale, val[v], der);
+            ds[v] = dp[v] * der * scale;
+            if ((v & 3) == 3) __builtin_amdgcn_sched_barrier(0);
+        }
     }
 }
 
