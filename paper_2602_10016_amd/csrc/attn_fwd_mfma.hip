@@ -290,6 +290,7 @@ __device__ __forceinline__ void attn_fwd_item(const AttnParams& p, char* lds, in
         }
         __syncthreads();
         if (split > 0) return;
+#pragma unroll 1
         for (int w = 1; w < KS; ++w) {
             const char* part = lds_all + w * LDS_BYTES;
             float cw[NQB];
@@ -452,7 +453,14 @@ static hipError_t launch_gdpa(const AttnParams& p, hipStream_t stream) {
             if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, (const void*)kern, 64 * NW * KS, bytes) != hipSuccess || n < 1) n = 1;
             return n;
         }();
-        const int64_t resident = (int64_t)per_cu * compute_units();
+        // Fewer workgroups than would fit: every workgroup is a walk of its own through memory, and the memory system
+        // moves the bytes of few walks faster than those of many, as long as the score function keeps up (exponential
+        // forms and GELU on small scores do; GELU on scores beyond 1 gains nothing and loses up to 5 %).  GELU, 8 heads,
+        // log-normal histories, us with 2 / 3 / 4 / all that fit workgroups per compute unit:
+        //   d = 128, 64 queries, 400 examples 348 / 376 / 390 / 390, 30 queries 333 / 363 / 390 / 389;
+        //   d = 64, 64 queries, 400: 221 / 205 / 232 / 246, 32 queries, 600: 320 / 261 / 287 / 325;  d = 32, 900: 368 / 290 / 273 / 285
+        constexpr int walkers = D == 128 ? 2 : D == 64 ? 3 : 4;
+        const int64_t resident = (int64_t)(per_cu < walkers ? per_cu : walkers) * compute_units();
         if (grid > resident) grid = resident;
     }
     hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(64 * NW * KS), bytes, stream, p, n_qtiles, (int)n_items);
@@ -466,15 +474,27 @@ hipError_t launch_mfma_fwd(const AttnParams& p, hipStream_t stream) {
     // Query-tiled launches use 128-query tiles (4 waves): fewer K/V tile loads per query.
     if (mfma_fwd_is_qtiled(p)) return launch_mfma_fwd_qtiled(p, stream);
     // Up to 32 queries per example = one wave per (example, head).  With few work items (every wave has a SIMD to
-    // itself) the longest history and the score function of a single wave would set the time: four waves (two at
-    // d = 128) then share the key tiles of an item.  (cfg2, GELU: 48 -> 40 us cold; the floor of that launch -
-    // identity scores - is 37 us for its 156 MB.)
-    const bool few_items = (int64_t)p.B * p.H <= 2048;
-    if (p.max_q <= 32) {
-        if (p.d == 128) return few_items ? launch_gdpa<128, 1, 1, 2, 1, 2>(p, stream) : launch_gdpa<128, 1, 1, 2, 1>(p, stream);
-        if (p.d == 64) return few_items ? launch_gdpa<64, 1, 1, 2, 2, 4>(p, stream) : launch_gdpa<64, 1, 1, 2, 2>(p, stream);
-        return few_items ? launch_gdpa<32, 1, 1, 2, 2, 4>(p, stream) : launch_gdpa<32, 1, 1, 2, 2>(p, stream);
-    }
+    // itself) the longest history and the score function of a single wave would set the time: four waves, or eight
+    // for histories beyond 1024 keys, then share the key tiles of a block of 32 queries; 33..64 queries make two such
+    // blocks, which read K and V once each (the second time out of the L2), as long as bandwidth is not what counts.
+    // GELU, us per call, one workgroup per item (two waves for 64 queries; the key split of 2 that d = 128 had) against
+    // the split, histories of 64..1024 keys (u) / log-normal up to 4096 (l):
+    //   d = 64, 64 queries, B H = 128: u 34 / 14, l 123 / 33;  512: u 50 / 35, l 179 / 77;  1024: u 53 / 60, l 186 / 136
+    //   d = 128, 64 queries, 128: u 44 / 20, l 162 / 57;  256: u 46 / 36;  512: u 54 / 63, l 183 / 135;  1024: l 224 / 244
+    //   d = 32, 64 queries, 2048: u 80 / 59, l 166 / 122;  d = 128, 24 queries, 1024: u 66 / 61, l 174 / 142
+    //   eight against four waves, 24 queries: d = 64, 512: u 25 / 21, l 48 / 59;  d = 128, 1024: u 66 / 61, l 142 / 151
+    const int64_t blocks = (int64_t)p.B * p.H * ((p.max_q + 31) / 32);
+    const bool long_histories = p.max_kv > 1024;
+    const int64_t few = p.max_q <= 32 ? 2048 : p.d == 32 ? 4096 : p.d == 64 ? (long_histories ? 2048 : 1024) : (long_histories ? 1024 : 512);
+    if (blocks <= few && blocks <= 2048 / (p.max_q <= 32 ? 2 : 1) && long_histories)
+        return p.d == 128 ? launch_gdpa<128, 1, 1, 2, 1, 8>(p, stream)
+               : p.d == 64 ? launch_gdpa<64, 1, 1, 2, 2, 8>(p, stream) : launch_gdpa<32, 1, 1, 2, 2, 8>(p, stream);
+    if (blocks <= few)
+        return p.d == 128 ? launch_gdpa<128, 1, 1, 2, 1, 4>(p, stream)
+               : p.d == 64 ? launch_gdpa<64, 1, 1, 2, 2, 4>(p, stream) : launch_gdpa<32, 1, 1, 2, 2, 4>(p, stream);
+    if (p.max_q <= 32)
+        return p.d == 128 ? launch_gdpa<128, 1, 1, 2, 1>(p, stream)
+               : p.d == 64 ? launch_gdpa<64, 1, 1, 2, 2>(p, stream) : launch_gdpa<32, 1, 1, 2, 2>(p, stream);
     return p.d == 128 ? launch_gdpa<128, 1, 2, 2, 2>(p, stream)
            : p.d == 64 ? launch_gdpa<64, 1, 2, 2, 2>(p, stream) : launch_gdpa<32, 1, 2, 2, 2>(p, stream);
 }
