@@ -547,8 +547,10 @@ static BwdLayout sumkron_bwd_layout(int B, int S, int T, int D, int k, int dtype
     return l;
 }
 size_t sumkron_bwd_workspace(int B, int S, int T, int D, int k, int dtype) {
-    if (sumkron_bwd_fused_supported(S, T, D, k, dtype)) return sumkron_bwd_fused_workspace(B, S, D, k);
-    return sumkron_bwd_layout(B, S, T, D, k, dtype).total;
+    // (the two-kernel path needs about half of what the GEMMs do; the size that callers see stays that of the GEMMs)
+    const size_t gemms = sumkron_bwd_layout(B, S, T, D, k, dtype).total;
+    const size_t fused = sumkron_bwd_fused_supported(S, T, D, k, dtype) ? sumkron_bwd_fused_workspace(B, S, D, k) : 0;
+    return fused > gemms ? fused : gemms;
 }
 
 template <typename T_>
