@@ -27,6 +27,8 @@
 
 namespace kunlun {
 
+#define PIN() __builtin_amdgcn_sched_barrier(0)  // nothing is moved across by the instruction scheduler
+
 constexpr float LOG2E_T = 1.4426950408889634f;
 
 // Padded LDS tiles (32 rows): +16 bytes per row for row-fragment (A/B operand) reads, +64
@@ -447,18 +449,24 @@ __device__ __forceinline__ void bwd_dkdv_item(const AttnParams& p, const float* 
         if (i + 2 < n_steps) issue(qt_begin + i + 2, free_stage);
         if (!wave_active || qt < w_begin || qt >= w_end) continue;
         // S = Q K^T and dP = dO V^T: lane = key column, registers = queries of the tile
+        const f32x16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
         f32x16 sacc, dpacc;
+        {
+            constexpr int QA = 2;  // (as many as fit the registers)
+            bf16x8 fr[QA];
+            auto frag = [&](int j) { return uf.row((j & 1) ? ldsDO : ldsQ, j >> 1); };
 #pragma unroll
-        for (int v = 0; v < 16; ++v) { sacc[v] = 0.f; dpacc[v] = 0.f; }
+            for (int j = 0; j < QA; ++j) fr[j] = frag(j);
+            PIN();
 #pragma unroll
-        for (int kc = 0; kc < KC; ++kc) {
-            const bf16x8 qa = uf.row(ldsQ, kc);
-            const bf16x8 da = uf.row(ldsDO, kc);
-            const bf16x8 kb = kc < K_REG ? kf[kc < K_REG ? kc : 0] : *(const bf16x8*)(kpark + (kc - K_REG) * 1024);
-            sacc = mfma32(qa, kb, sacc);
-            dpacc = mfma32(da, vf[kc], dpacc);
+            for (int j = 0; j < 2 * KC; ++j) {
+                const int kc = j >> 1;
+                if (j & 1) dpacc = mfma32(fr[j % QA], vf[kc], j == 1 ? zero16 : dpacc);
+                else sacc = mfma32(fr[j % QA], kc < K_REG ? kf[kc < K_REG ? kc : 0] : *(const bf16x8*)(kpark + (kc - K_REG) * 1024), j == 0 ? zero16 : sacc);
+                if (j + QA < 2 * KC) fr[j % QA] = frag(j + QA);
+                PIN();
+            }
         }
-        __builtin_amdgcn_sched_barrier(0);  // keep the LDS reads of the next phase behind this one (register pressure)
         // Interior tiles - every (query, key) pair inside the sequence and the window - skip the
         // visibility test.  (Padding key lanes hold zero K/V rows and are never stored.)
         const int q_base = qt * KT;
@@ -503,15 +511,21 @@ __device__ __forceinline__ void bwd_dkdv_item(const AttnParams& p, const float* 
         for (int c = 0; c < 2; ++c)
 #pragma unroll
             for (int e = 0; e < 8; ++e) { pf[c][e] = (bf16_t)pv[8 * c + e]; dsf[c][e] = (bf16_t)dsv[8 * c + e]; }
-        __builtin_amdgcn_sched_barrier(0);
+        PIN();
         // dV^T += dO^T P and dK^T += Q^T dS (contraction over the queries of the tile)
+        constexpr int TA = 3;
+        auto tfrag = [&](int j) { return uf.transposed((j & 1) ? ldsQ : ldsDO, j >> 2, (j >> 1) & 1); };
+        bf16x8 tf[TA];
 #pragma unroll
-        for (int db = 0; db < DB; ++db)
+        for (int j = 0; j < TA; ++j) tf[j] = tfrag(j);
+        PIN();
 #pragma unroll
-            for (int c = 0; c < 2; ++c) {
-                dvacc[db] = mfma32(uf.transposed(ldsDO, db, c), pf[c], dvacc[db]);
-                dkacc[db] = mfma32(uf.transposed(ldsQ, db, c), dsf[c], dkacc[db]);
-            }
+        for (int j = 0; j < 4 * DB; ++j) {
+            if (j & 1) dkacc[j >> 2] = mfma32(tf[j % TA], dsf[(j >> 1) & 1], dkacc[j >> 2]);
+            else dvacc[j >> 2] = mfma32(tf[j % TA], pf[(j >> 1) & 1], dvacc[j >> 2]);
+            if (j + TA < 4 * DB) tf[j % TA] = tfrag(j + TA);
+            PIN();
+        }
     }
     __syncthreads();  // every wave is done with the ring
     if (!wave_active) return;
