@@ -248,6 +248,23 @@ __device__ __forceinline__ float wave_sum(float x) {
     return x;
 }
 
+// Inclusive prefix sum over a workgroup of 1024 threads: shuffles inside a wavefront, then the 16 wave totals (`totals`:
+// 16 ints of LDS, free to reuse after the next barrier).  Three barriers instead of the twenty of a scan through LDS.
+__device__ __forceinline__ int scan1024(int x, int* totals) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const int y = __shfl_up(x, off, 64);
+        x += lane >= off ? y : 0;
+    }
+    if (lane == 63) totals[wave] = x;
+    __syncthreads();
+    int before = 0;
+#pragma unroll
+    for (int w = 0; w < 16; ++w) before += w < wave ? totals[w] : 0;
+    return x + before;
+}
+
 __device__ __forceinline__ float to_float(float x) { return x; }
 __device__ __forceinline__ float to_float(bf16_t x) { return (float)x; }
 template <typename T> __device__ __forceinline__ T from_float(float x);

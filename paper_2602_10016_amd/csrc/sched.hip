@@ -18,7 +18,8 @@ __global__ __launch_bounds__(SCHED_THREADS) void schedule_kernel(const int32_t* 
                                                                   int max_kv, int32_t* __restrict__ order,
                                                                   int32_t* __restrict__ counters) {
     __shared__ int hist[NBINS];
-    __shared__ int scan[NBINS];
+    __shared__ int totals[16];
+    static_assert(NBINS == 2 * SCHED_THREADS && SCHED_THREADS == 1024, "two bins per thread of the scan");
     const int tid = threadIdx.x;
     if (tid < (int)(WS_HEADER_BYTES / sizeof(int32_t))) counters[tid] = 0;
     for (int i = tid; i < NBINS; i += SCHED_THREADS) hist[i] = 0;
@@ -33,21 +34,11 @@ __global__ __launch_bounds__(SCHED_THREADS) void schedule_kernel(const int32_t* 
     };
     for (int b = tid; b < B; b += SCHED_THREADS) atomicAdd(&hist[bin_of(b)], 1);
     __syncthreads();
-    // exclusive scan of hist (Hillis-Steele over NBINS entries, two per thread)
-    for (int i = tid; i < NBINS; i += SCHED_THREADS) scan[i] = hist[i];
-    __syncthreads();
-    for (int off = 1; off < NBINS; off <<= 1) {
-        int v0 = 0, v1 = 0;
-        const int i0 = tid, i1 = tid + SCHED_THREADS;
-        if (i0 >= off) v0 = scan[i0 - off];
-        if (i1 >= off) v1 = scan[i1 - off];
-        __syncthreads();
-        scan[i0] += v0;
-        scan[i1] += v1;
-        __syncthreads();
-    }
-    // scan is inclusive; bucket start = scan - hist.  Reuse hist as the running cursor.
-    for (int i = tid; i < NBINS; i += SCHED_THREADS) hist[i] = scan[i] - hist[i];
+    // exclusive scan of hist, two neighbouring bins per thread; hist becomes the running cursor
+    const int h0 = hist[2 * tid], h1 = hist[2 * tid + 1];
+    const int upto = scan1024(h0 + h1, totals);
+    hist[2 * tid] = upto - h0 - h1;
+    hist[2 * tid + 1] = upto - h1;
     __syncthreads();
     for (int b = tid; b < B; b += SCHED_THREADS) {
         const int pos = atomicAdd(&hist[bin_of(b)], 1);

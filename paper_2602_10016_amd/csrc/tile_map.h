@@ -66,29 +66,22 @@ template <int UNUSED>
 __global__ __launch_bounds__(1024) void tile_prefix_kernel(const int32_t* __restrict__ off, int dense_len, int B,
                                                            int32_t* __restrict__ tile_start,
                                                            int32_t* __restrict__ tile_example, int tile_rows) {
-    __shared__ int part[1024];
+    __shared__ int totals[16];
     const int tid = threadIdx.x;
     const int per = (B + 1023) / 1024;
     const int b0 = tid * per, b1 = (b0 + per < B) ? b0 + per : B;
     auto tiles_of = [&](int b) { return ((off ? off[b + 1] - off[b] : dense_len) + tile_rows - 1) / tile_rows; };
     int sum = 0;
     for (int b = b0; b < b1; ++b) sum += tiles_of(b);
-    part[tid] = sum;
-    __syncthreads();
-    for (int o = 1; o < 1024; o <<= 1) {
-        const int v = tid >= o ? part[tid - o] : 0;
-        __syncthreads();
-        part[tid] += v;
-        __syncthreads();
-    }
-    int run = part[tid] - sum;
+    const int upto = scan1024(sum, totals);
+    int run = upto - sum;
     for (int b = b0; b < b1; ++b) {
         tile_start[b] = run;
         const int n = tiles_of(b);
         for (int t = 0; t < n; ++t) tile_example[run + t] = b;
         run += n;
     }
-    if (tid == 1023) tile_start[B] = part[1023];
+    if (tid == 1023) tile_start[B] = upto;
 }
 #endif  // __HIPCC__
 
