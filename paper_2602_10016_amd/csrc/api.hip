@@ -36,6 +36,17 @@ int fill_acts(AttnParams& p, int H, int act, const int32_t* head_act, bool& any_
     return KUNLUN_OK;
 }
 
+// Whether a forward launch of up to 64 queries per example starts its items longest first (one more kernel, 4 us): when
+// they do not all fit the device at once, and, for histories beyond 1024 keys, already above one workgroup per compute
+// unit.  GELU, us sorted / not: 512 items of up to 4096 keys d = 32, 64, 128 with 24 queries 25 / 30, 40 / 45, 73 / 80, with
+// 64 queries 31 / 37, 65 / 73, 117 / 132; 64..1024 keys d = 64, 24 queries 20 / 19, 768 items with 64 queries 40 / 31, but
+// d = 128, 24 queries, 768 items 45 / 50.
+bool fwd_sorts(int B, int H, int d, int max_q, int max_kv) {
+    const int64_t items = (int64_t)B * H, blocks = items * ((max_q + 31) / 32);
+    return !schedule_is_moot(items, 4) || (max_kv > 1024 && !schedule_is_moot(blocks, 1)) ||
+           (d == 128 && max_q <= 32 && !schedule_is_moot(blocks, 2));
+}
+
 size_t order_bytes(int B) { return align_up((size_t)(B + 1) * sizeof(int32_t), 256); }
 
 int gdpa_bwd_checked(const void* q, const void* k, const void* v, const void* o, const float* lse, const void* d_o, void* dq,
@@ -223,10 +234,9 @@ int kunlun::gdpa_fwd_checked(const void* q, const void* k, const void* v, void* 
     hipError_t e;
     if (mfma_fwd_supported(p, dtype)) {
         int32_t* order = (int32_t*)((char*)workspace + WS_HEADER_BYTES);
-        const int64_t wgs = (int64_t)B * H * ((max_q + 63) / 64);
         if (mfma_fwd_is_qtiled(p)) {
             p.order = order;  // holds the query-tile prefix sums
-        } else if (schedule_is_moot(wgs, 4)) {  // every forward kernel fits 4 workgroups per compute unit
+        } else if (!fwd_sorts(B, H, d, max_q, max_kv)) {
             p.order = nullptr;
         } else {
             p.order = order;
@@ -312,7 +322,10 @@ int gdpa_bwd_checked(const void* q, const void* k, const void* v, const void* o,
     }
     if (mfma_bwd_supported(p, dtype)) {
         int32_t* order = (int32_t*)((char*)workspace + WS_HEADER_BYTES);
-        if (schedule_is_moot((int64_t)B * H, d == 128 ? (max_q > 32 ? 2 : 1) : 4)) {  // workgroups of the kernel per compute unit
+        // Workgroups of the kernel per compute unit (registers); what does not fit at once starts longest first.  1024
+        // items sorted against not, GELU, us: 64..1024 keys, d = 64, 32 queries 69 / 72, 64 queries 94 / 106, d = 32,
+        // 64 queries 47 / 54; log-normal up to 4096 keys 157 / 186, 175 / 251, 95 / 141.
+        if (schedule_is_moot((int64_t)B * H, d == 128 ? (max_q > 32 ? 2 : 1) : d == 64 && max_q > 32 ? 1 : 2)) {
             p.order = nullptr;
         } else {
             p.order = order;
