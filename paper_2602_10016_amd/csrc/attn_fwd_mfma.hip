@@ -459,7 +459,9 @@ static hipError_t launch_gdpa(const AttnParams& p, hipStream_t stream) {
         // log-normal histories, us with 2 / 3 / 4 / all that fit workgroups per compute unit:
         //   d = 128, 64 queries, 400 examples 348 / 376 / 390 / 390, 30 queries 333 / 363 / 390 / 389;
         //   d = 64, 64 queries, 400: 221 / 205 / 232 / 246, 32 queries, 600: 320 / 261 / 287 / 325;  d = 32, 900: 368 / 290 / 273 / 285
-        constexpr int walkers = D == 128 ? 2 : D == 64 ? 3 : 4;
+        // At d = 128 two are the best alone (bench batch 855 / 865 / 873 us), but not next to kernels that draw the clock
+        // down, where two waves of a compute unit cannot keep up: in the benchmark step 887 / 833 / 838 us.
+        constexpr int walkers = D == 32 ? 4 : 3;
         const int64_t resident = (int64_t)(per_cu < walkers ? per_cu : walkers) * compute_units();
         if (grid > resident) grid = resident;
     }
