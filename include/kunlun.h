@@ -251,7 +251,8 @@ size_t kunlun_sumkron_workspace_bytes(int B, int S, int T, int D, int k, int dty
  *   x, z, w  in, device, as in kunlun_sumkron_fwd
  *   dy  in,  device, [B, T, D]   gradient with respect to Y
  *   dx  out, device, [B, S, D];  dz out, device, [k, S, T];  dw out, device, [k, D, D]   fully overwritten
- * KUNLUN_BF16: five matrix-core contractions with fp32 accumulation when, in addition to the forward
+ * KUNLUN_BF16: matrix-core contractions with fp32 accumulation, in two kernels when T = 32, S is 128 or 256, D is
+ * 128, 256 or 384 and k <= 8, else as five matrix products when, in addition to the forward
  * conditions, S is a multiple of 128 and T*k and B*T are multiples of 32; Z_i^T X_b and dY_b W_i^T are
  * recomputed and rounded to bf16 once, the two sums over the batch are accumulated in fp32 partial
  * sums that are added in a fixed order (results are bit-reproducible).  Other shapes and KUNLUN_FP32

@@ -225,7 +225,7 @@ __global__ __launch_bounds__(64 * F32Fwd<D>::MAX_KS) void gdpa_fwd_fp32_kernel(A
 
 bool fp32_fwd_supported(const AttnParams& p, int dtype) {
     // (one workgroup per (example, query block, head) must fit a 1-D grid)
-    return dtype == KUNLUN_FP32 && !p.windowed && (p.d == 32 || p.d == 64 || p.d == 128) &&
+    return dtype == KUNLUN_FP32 && !p.windowed && p.max_q >= 1 && (p.d == 32 || p.d == 64 || p.d == 128) &&
            (int64_t)p.B * p.H * ((p.max_q + 15) / 16) < ((int64_t)1 << 31);
 }
 

@@ -1,8 +1,8 @@
 // Generic (non matrix-core) kernels: fp32 storage and arithmetic, or any head dimension
 // the MFMA kernels do not tile.  One wavefront per output row; lanes run over keys for the
 // score dot products and over channels for the weighted sums.  Exact transcendental
-// functions.  These kernels serve the fp32 data type and the head dimensions other than 32, 64
-// and 128; the bf16 hot path lives in attn_fwd_mfma.hip (streaming forward), attn_fwd_ring_mfma.hip
+// functions.  These kernels serve the head dimensions other than 32, 64 and 128, and of the fp32 data type the
+// backward and the window (its forward at those dimensions: attn_fwd_fp32_mfma.hip); the bf16 hot path lives in attn_fwd_mfma.hip (streaming forward), attn_fwd_ring_mfma.hip
 // (query-tiled forward: sliding window, long query sequences), attn_bwd_pair_mfma.hip /
 // attn_bwd_mfma.hip (fused backward) and attn_bwd_tiled_mfma.hip (two-pass and few-keys backward).
 //
