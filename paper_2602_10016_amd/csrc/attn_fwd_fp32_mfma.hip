@@ -89,7 +89,7 @@ __device__ __forceinline__ void attn_fwd_fp32_item(const AttnParams& p, char* ld
         // ---- weights; keys past the history get none, and their (repeated) V rows count as zero
 #pragma unroll
         for (int qb = 0; qb < QB; ++qb) {
-            float mx = -INFINITY;
+            float mx = -INFINITY, shift = 0.f;
 #pragma unroll
             for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
@@ -101,7 +101,8 @@ __device__ __forceinline__ void attn_fwd_fp32_item(const AttnParams& p, char* ld
                 mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
                 mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
                 const float m_new = fmaxf(m[qb], mx);
-                const float corr = expf(m[qb] - m_new);  // exp(-inf) = 0 in the first step
+                shift = m_new == -INFINITY ? 0.f : m_new;  // only scores of -inf so far: their weights are exp(-inf) = 0
+                const float corr = expf(m[qb] - shift);    // exp(-inf) = 0 in the first step
                 m[qb] = m_new;
                 l[qb] *= corr;
 #pragma unroll
@@ -114,7 +115,7 @@ __device__ __forceinline__ void attn_fwd_fp32_item(const AttnParams& p, char* ld
                     const bool ok = 16 * kb + 4 * c4 + v < left;
                     float w;
                     if (SOFTMAX) {
-                        w = ok ? expf(s[kb][qb][v] - m[qb]) : 0.f;
+                        w = ok ? expf(s[kb][qb][v] - shift) : 0.f;
                         l[qb] += w;
                     } else {
                         w = ok ? act_exact<ACT>(s[kb][qb][v]) : 0.f;
@@ -161,17 +162,17 @@ __device__ __forceinline__ void attn_fwd_fp32_item(const AttnParams& p, char* ld
         }
         __syncthreads();
         if (wave > 0) return;
-        for (int w = 0; w < ks - 1; ++w) {
+        for (int w = 0; w < ks - 1 && 32 * (w + 1) < n_kv; ++w) {  // (a wave past the end of the history saw no key)
             const char* part = lds + w * F::part_bytes(QB) + lane * 16;
 #pragma unroll
             for (int qb = 0; qb < QB; ++qb) {
                 float c0 = 1.f, c1 = 1.f;
                 if (SOFTMAX) {
                     const f4 ml = *(const f4*)(part + (qb * (CB + 1) + CB) * 1024);
-                    if (ml[1] == 0.f && ml[0] == -INFINITY) continue;  // that wave saw no key
                     const float m_new = fmaxf(m[qb], ml[0]);
-                    c0 = expf(m[qb] - m_new);
-                    c1 = expf(ml[0] - m_new);
+                    const float shift = m_new == -INFINITY ? 0.f : m_new;  // as above: a part without a weight counts as zero
+                    c0 = expf(m[qb] - shift);
+                    c1 = expf(ml[0] - shift);
                     l[qb] = l[qb] * c0 + ml[1] * c1;
                     m[qb] = m_new;
                 }

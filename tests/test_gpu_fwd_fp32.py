@@ -45,3 +45,37 @@ def test_fp32_forward_every_score_function_many_items(oracle, act):
     keep = slice(0, int(np.flatnonzero(np.diff(wl.kv_offsets) > 0)[-1]) * 5)
     o_ref, _ = oracle.gdpa_fwd(wl.q, wl.k, wl.v, wl.kv_offsets, wl.scale, act, max_q=5)
     assert_close(to_np(o)[keep], o_ref[keep], TOL["fp32"], f"act={act} O")
+
+
+# (first masked key, one past the last) of the histories below: 32 keys in the middle (the first step of a later wave), the
+# first step of the first wave, every step of the third of sixteen waves (or of eight), all keys but the last, all keys
+MASKS = [(64, 96), (0, 32), (64, 96), (0, 599), (0, 600), (0, 0)]
+
+
+@pytest.mark.parametrize("d", [32, 64, 128])
+@pytest.mark.parametrize("n", [5, 20])
+@pytest.mark.parametrize("infinite", [False, True])
+def test_fp32_softmax_with_scores_of_minus_infinity(oracle, d, n, infinite):
+    """Keys whose scores are -inf (a channel of -inf, or products beyond the fp32 range) have weight 0 wherever they lie;
+    a query with no other key gets a zero row and lse = -inf, as an empty history does."""
+    from paper_2602_10016_amd import binding as kb
+    B, H, L = len(MASKS), 2, 600
+    wl = W.make("cfg1", d + n, B=B, H=H, d=d, Nq=n, lengths=("list", np.full(B, L)), scale=1 / np.sqrt(d))
+    q, k = wl.q.copy(), wl.k.copy()
+    q[:, :, 0] = 1e30
+    k[:, :, 0] = 0
+    masked = np.zeros(B * L, dtype=bool)
+    for b, (lo, hi) in enumerate(MASKS):
+        masked[b * L + lo:b * L + hi] = True
+    masked[2 * L + 64 + 256:2 * L + 96 + 256] = True   # the third of eight waves: its second step ...
+    masked[2 * L + 64 + 512:2 * L + 96 + 512] = True   # ... and its third, which is the second of the third of sixteen
+    k[masked, :, 0] = -1e30
+    kd = to_dev(k, "fp32")
+    if infinite:
+        kd[torch.from_numpy(masked).cuda(), :, 0] = -torch.inf
+    o, lse = kb.gdpa_fwd(to_dev(q, "fp32"), kd, to_dev(wl.v, "fp32"), offsets_dev(wl.kv_offsets), wl.scale, 0, max_q=n, max_kv=L)
+    torch.cuda.synchronize()
+    o_ref, lse_ref = oracle.gdpa_fwd(q, k, wl.v, wl.kv_offsets, wl.scale, 0, max_q=n)
+    o_ref[4 * n:5 * n], lse_ref[:, 4 * n:5 * n] = 0, -np.inf
+    assert_close(to_np(o), o_ref, TOL["fp32"], f"d={d} n={n} O")
+    assert_lse_close(to_np(lse), lse_ref, TOL["fp32"])
