@@ -224,10 +224,21 @@ __global__ __launch_bounds__(64 * F32Fwd<D>::MAX_KS) void gdpa_fwd_fp32_kernel(A
     }
 }
 
+// Queries of a workgroup, and the workgroups of the longest query list the call allows, for every (example, head).
+static int fp32_block_rows(int max_q) { return max_q <= 16 ? 16 : 32; }
+static int64_t fp32_blocks(const AttnParams& p) {
+    const int rows = fp32_block_rows(p.max_q);
+    return (int64_t)p.B * p.H * ((p.max_q + rows - 1) / rows);
+}
+
+// The grid must stay below 2^32 threads (a larger one is cut off without an error).  And with q_offsets many of its
+// workgroups may hold few queries or none, all of those that do perhaps on a quarter of the device: a workgroup has to
+// have two query rows on average (one, in the small blocks), else the scalar kernel takes the call.  Scalar / this, us:
+//   B = 70000, one query each, 2 keys: bound 16 551 / 523, 32 551 / 913, 128 551 / 3570;  B = 20000, 64 keys, bound 512 1105 / 2228;
+//   B = 512, 1..16 queries, 64..512 keys, d = 64: bound 32 1108 / 184, 128 (2.1 rows) 1108 / 478
 bool fp32_fwd_supported(const AttnParams& p, int dtype) {
-    // (one workgroup per (example, query block, head) must fit a 1-D grid)
     return dtype == KUNLUN_FP32 && !p.windowed && p.max_q >= 1 && (p.d == 32 || p.d == 64 || p.d == 128) &&
-           (int64_t)p.B * p.H * ((p.max_q + 15) / 16) < ((int64_t)1 << 31);
+           fp32_blocks(p) < ((int64_t)1 << 26) && fp32_blocks(p) * (fp32_block_rows(p.max_q) / 16) <= p.total_q * p.H;
 }
 
 template <int D, int QB>
@@ -241,7 +252,7 @@ static hipError_t launch(const AttnParams& p, hipStream_t stream) {
         if (raised != hipSuccess) return raised;
     }
     const int n_qtiles = (p.max_q + 16 * QB - 1) / (16 * QB);
-    const int64_t items = (int64_t)p.B * p.H * n_qtiles;
+    const int64_t items = fp32_blocks(p);
     const int steps = (p.max_kv + 31) / 32;
     // as many waves as the longest history has steps, while the waves of all items are fewer than four per SIMD
     int ks = 1;
@@ -251,7 +262,7 @@ static hipError_t launch(const AttnParams& p, hipStream_t stream) {
 }
 
 hipError_t launch_fp32_fwd(const AttnParams& p, hipStream_t stream) {
-    if (p.max_q <= 16)
+    if (fp32_block_rows(p.max_q) == 16)
         return p.d == 32 ? launch<32, 1>(p, stream) : p.d == 64 ? launch<64, 1>(p, stream) : launch<128, 1>(p, stream);
     return p.d == 32 ? launch<32, 2>(p, stream) : p.d == 64 ? launch<64, 2>(p, stream) : launch<128, 2>(p, stream);
 }

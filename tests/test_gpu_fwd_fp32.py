@@ -79,3 +79,18 @@ def test_fp32_softmax_with_scores_of_minus_infinity(oracle, d, n, infinite):
     o_ref[4 * n:5 * n], lse_ref[:, 4 * n:5 * n] = 0, -np.inf
     assert_close(to_np(o), o_ref, TOL["fp32"], f"d={d} n={n} O")
     assert_lse_close(to_np(lse), lse_ref, TOL["fp32"])
+
+
+def test_fp32_forward_with_a_bound_far_above_the_query_counts(oracle):
+    """q_offsets with one query per example under a bound of 4096: one workgroup per block of the bound would be more
+    threads than a launch may have (2^32)."""
+    from paper_2602_10016_amd import binding as kb
+    B, H, d = 70000, 8, 32
+    wl = W.make("cfg1", 5, B=B, H=H, d=d, Nq=1, lengths=("list", np.full(B, 2)), scale=0.2)
+    off = np.arange(B + 1)
+    o, lse = kb.gdpa_fwd(to_dev(wl.q, "fp32"), to_dev(wl.k, "fp32"), to_dev(wl.v, "fp32"), offsets_dev(wl.kv_offsets), wl.scale, 0,
+                         q_offsets=offsets_dev(off), max_q=4096, max_kv=2)
+    torch.cuda.synchronize()
+    o_ref, lse_ref = oracle.gdpa_fwd(wl.q, wl.k, wl.v, wl.kv_offsets, wl.scale, 0, q_offsets=off, max_q=1)
+    assert_close(to_np(o), o_ref, TOL["fp32"], "O")
+    assert_lse_close(to_np(lse), lse_ref, TOL["fp32"])
