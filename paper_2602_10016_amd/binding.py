@@ -76,9 +76,17 @@ def strerror(status: int) -> str:
     return _lib.kunlun_strerror(int(status)).decode()
 
 
-@functools.lru_cache(maxsize=256)  # a pure function of its arguments
+@functools.lru_cache(maxsize=256)
+def _workspace_bytes_of_ints(*args) -> int:
+    return int(_lib.kunlun_workspace_bytes(*args))
+
+
 def workspace_bytes(op, B, H, d, max_q, max_kv, total_q, total_kv) -> int:
-    return int(_lib.kunlun_workspace_bytes(op, B, H, d, max_q, max_kv, total_q, total_kv))
+    args = (op, B, H, d, max_q, max_kv, total_q, total_kv)
+    # a pure function of plain ints; anything else (a tensor that may change, a float equal to an int) is asked anew
+    if set(map(type, args)) == {int}:
+        return _workspace_bytes_of_ints(*args)
+    return int(_lib.kunlun_workspace_bytes(*args))
 
 
 def raw():

@@ -90,3 +90,16 @@ def test_non_tensor_arguments_are_rejected():
         kb.gdpa_fwd(q, k, v, [0, 12], 1.0, kb.ACT_GELU, max_q=8, max_kv=12)
     with pytest.raises(TypeError, match="uint8"):
         kb.gdpa_fwd(q, k, v, off(0, 12), 1.0, kb.ACT_GELU, max_q=8, max_kv=12, workspace=torch.zeros(1024))
+
+
+def test_workspace_query_answers_its_arguments_as_they_are():
+    """Nothing is remembered by the identity of an argument, and what the C entry point refuses stays refused after an
+    equal value of another type was accepted."""
+    import ctypes
+    args = (64, 8, 128, 256, 4096, 64 * 256, 64 * 1000)
+    op = torch.tensor(kb.OP_GDPA_FWD)
+    first = kb.workspace_bytes(op, *args)
+    op.fill_(kb.OP_SEED_BWD)
+    assert kb.workspace_bytes(op, *args) == kb.workspace_bytes(kb.OP_SEED_BWD, *args) != first == kb.workspace_bytes(kb.OP_GDPA_FWD, *args)
+    with pytest.raises(ctypes.ArgumentError):
+        kb.workspace_bytes(kb.OP_GDPA_FWD, 64.0, *args[1:])
