@@ -219,9 +219,14 @@ int kunlun_swa_bwd(const void* q, const void* k, const void* v, const void* o, c
                    int64_t total, int window_left, int window_right, float scale, int dtype, void* workspace,
                    size_t workspace_bytes, void* stream);
 
-/* Bytes of workspace that a call of `op` (kunlun_op) with these sizes needs.  Returns 0 for
- * an unknown op or negative sizes.  For the sliding-window ops pass max_len as max_q and
- * max_kv and total as total_q and total_kv; for the seed ops n_seeds as max_q and B * n_seeds as total_q. */
+/* Bytes of workspace for a call of `op` (kunlun_op) with these sizes.  A workspace of the size for some batch also
+ * serves the calls with the same H, d, max_q and max_kv, no more examples and no more rows - except backward calls with
+ * max_kv <= 32 and max_q > 64, whose partial sums may take more room for a smaller batch: size those for each batch.
+ * (Backward calls with 65..256 queries per example at d = 128 and a history that would set their time alone also have
+ * a larger size for some smaller batches: they add partial sums over ranges of the histories where the workspace has
+ * room for them, and take other kernels, which round differently, where it has not.)  Returns 0 for an unknown op or
+ * negative sizes.  For the sliding-window ops pass max_len as max_q and max_kv and total as total_q and total_kv; for
+ * the seed ops n_seeds as max_q and B * n_seeds as total_q. */
 size_t kunlun_workspace_bytes(int op, int B, int H, int d, int max_q, int max_kv, int64_t total_q,
                               int64_t total_kv);
 

@@ -49,6 +49,18 @@ bool fwd_sorts(int B, int H, int d, int max_q, int max_kv) {
 
 size_t order_bytes(int B) { return align_up((size_t)(B + 1) * sizeof(int32_t), 256); }
 
+// What a backward call cannot do without.  With more than 32 keys or up to 64 queries per example never more for fewer
+// examples or tokens, so that a kept workspace serves smaller batches.
+size_t bwd_bytes(int B, int H, int d, int max_q, int max_kv, int64_t total_q, int64_t total_kv, bool windowed) {
+    return WS_HEADER_BYTES + order_bytes(B) + mfma_bwd_tiled_workspace(B, H, d, max_q, max_kv, total_q, total_kv, windowed);
+}
+// ... of shared seeds: behind that, the per-example query gradients (at most 4 bytes per element) and the partial sums
+// over the batch
+size_t seed_bwd_bytes(int B, int H, int d, int n_seeds, int max_kv, int64_t total_q, int64_t total_kv) {
+    return bwd_bytes(B, H, d, n_seeds, max_kv, total_q, total_kv, false) + seed_grad_rows_bytes(total_q, H, d, KUNLUN_FP32) +
+           seed_grad_partial_bytes(B, (int64_t)n_seeds * H * d);
+}
+
 int gdpa_bwd_checked(const void* q, const void* k, const void* v, const void* o, const float* lse, const void* d_o, void* dq,
                      void* dk, void* dv, const int32_t* q_offsets, const int32_t* kv_offsets, int B, int H, int d, int max_q,
                      int max_kv, int64_t total_q, int64_t total_kv, float scale, int act, const int32_t* head_act, int dtype,
@@ -66,17 +78,13 @@ size_t kunlun_workspace_bytes(int op, int B, int H, int d, int max_q, int max_kv
     case KUNLUN_OP_SWA_FWD:
     case KUNLUN_OP_SEED_FWD:
         return WS_HEADER_BYTES + tile_table_bytes(B, total_q);
-    case KUNLUN_OP_SEED_BWD:  // + the per-example query gradients (at most 4 bytes per element) and the partial sums over the batch
-        return kunlun_workspace_bytes(KUNLUN_OP_GDPA_BWD, B, H, d, max_q, max_kv, total_q, total_kv) +
-               seed_grad_rows_bytes(total_q, H, d, KUNLUN_FP32) + seed_grad_partial_bytes(B, (int64_t)max_q * H * d);
+    // (+ the partial query gradients of the one-pass kernel's ranges, which a call can do without)
+    case KUNLUN_OP_SEED_BWD:
+        return seed_bwd_bytes(B, H, d, max_q, max_kv, total_q, total_kv) + mfma_bwd_wide_workspace(B, H, d, max_q, max_kv, total_kv);
     case KUNLUN_OP_GDPA_BWD:
+        return bwd_bytes(B, H, d, max_q, max_kv, total_q, total_kv, false) + mfma_bwd_wide_workspace(B, H, d, max_q, max_kv, total_kv);
     case KUNLUN_OP_SWA_BWD:
-    {
-        const bool windowed = op == KUNLUN_OP_SWA_BWD;
-        const size_t tiled = mfma_bwd_tiled_workspace(B, H, d, max_q, max_kv, total_q, total_kv, windowed);
-        const size_t wide = windowed ? 0 : tile_table_bytes(B, total_kv) + mfma_bwd_wide_workspace(B, H, d, max_q, max_kv, total_kv);
-        return WS_HEADER_BYTES + order_bytes(B) + (wide > tiled ? wide : tiled);
-    }
+        return bwd_bytes(B, H, d, max_q, max_kv, total_q, total_kv, true);
     default:
         return 0;
     }
@@ -298,10 +306,9 @@ int gdpa_bwd_checked(const void* q, const void* k, const void* v, const void* o,
         !aligned(dq, 16) || !aligned(dk, 16) || !aligned(dv, 16) || !aligned(lse, 4) || !aligned(q_offsets, 4) ||
         !aligned(kv_offsets, 4))
         return KUNLUN_ERR_ALIGN;
-    const size_t base_bytes = kunlun_workspace_bytes(KUNLUN_OP_GDPA_BWD, B, H, d, max_q, max_kv, total_q, total_kv);
-    if (!workspace || workspace_bytes < (q_shared ? kunlun_workspace_bytes(KUNLUN_OP_SEED_BWD, B, H, d, max_q, max_kv, total_q, total_kv)
-                                                  : base_bytes))
-        return KUNLUN_ERR_WORKSPACE;
+    const size_t base_bytes = bwd_bytes(B, H, d, max_q, max_kv, total_q, total_kv, false);
+    const size_t need_bytes = q_shared ? seed_bwd_bytes(B, H, d, max_q, max_kv, total_q, total_kv) : base_bytes;
+    if (!workspace || workspace_bytes < need_bytes) return KUNLUN_ERR_WORKSPACE;
     if (!aligned(workspace, 256)) return KUNLUN_ERR_ALIGN;
 
     p.q = q; p.k = k; p.v = v; p.o = const_cast<void*>(o); p.lse = const_cast<float*>(lse); p.d_o = d_o;
@@ -334,9 +341,12 @@ int gdpa_bwd_checked(const void* q, const void* k, const void* v, const void* o,
             if (e != hipSuccess) return KUNLUN_ERR_LAUNCH;
         }
         e = launch_mfma_bwd(p, (char*)workspace + WS_HEADER_BYTES + order_bytes(B), s);
-    } else if (mfma_bwd_wide_supported(p, dtype)) {
-        char* const tables = (char*)workspace + WS_HEADER_BYTES + order_bytes(B);
-        e = launch_mfma_bwd_wide(p, workspace, (char*)workspace + WS_HEADER_BYTES, tables, tables + tile_table_bytes(B, total_kv), s);
+    } else if (mfma_bwd_wide_supported(p, dtype) &&
+               workspace_bytes - need_bytes >= mfma_bwd_wide_workspace(B, H, d, max_q, max_kv, total_kv)) {
+        // (ranges need room for partial sums at the end; a workspace kept from a larger batch that ran without ranges may
+        // not have it: the two-pass kernels need none)
+        char* const order = (char*)workspace + WS_HEADER_BYTES;
+        e = launch_mfma_bwd_wide(p, workspace, order, order + order_bytes(B), (char*)workspace + need_bytes, s);
     } else if (mfma_bwd_tiled_supported(p, dtype)) {
         e = launch_mfma_bwd_tiled(p, (char*)workspace + WS_HEADER_BYTES + order_bytes(B), any_softmax, s);
     } else {

@@ -97,7 +97,7 @@ hipError_t launch_mfma_bwd_pair(const AttnParams& p, hipStream_t stream);
 // d = 128 with 65..256 queries per example: one pass, every score computed once.
 bool mfma_bwd_wide_supported(const AttnParams& p, int dtype);
 // `counters`: the work counters of the workspace; `order`: B + 1 int32; `tables`: tile_table_bytes(B, total_kv) bytes
-// (tile_map.h); `partial`: mfma_bwd_wide_workspace() bytes
+// (tile_map.h), which the tables of the two-pass kernels cover; `partial`: mfma_bwd_wide_workspace() bytes
 hipError_t launch_mfma_bwd_wide(const AttnParams& p, void* counters, void* order, void* tables, void* partial, hipStream_t stream);
 size_t mfma_bwd_wide_workspace(int B, int H, int d, int max_q, int max_kv, int64_t total_kv);
 // Two-pass matrix-core backward (sliding window, or more than 64 queries per example).

@@ -164,6 +164,27 @@ def test_backward_workspace_covers_the_partial_sums_of_the_few_keys_path(kb):
     assert kb.workspace_bytes(kb.OP_SWA_BWD, B, H, d, 32, 32, B * 32, B * 32) < (1 << 20)
 
 
+def test_a_workspace_for_the_largest_batch_is_accepted_for_smaller_ones(kb):
+    """A program that keeps one workspace, sized for its largest batch, may call with fewer examples and fewer tokens.
+    (The workspace pointer is misaligned: an accepted size ends in that error, and nothing is launched.)"""
+    lib = kb.raw()
+    P, d, max_kv = 0x1000, 128, 4096
+    for H in (1, 2, 4, 8, 16):
+        for n in (8, 64, 65, 100, 256, 257):
+            accepted = {}
+            for B in (1, 3, 16, 32, 64, 100, 128, 200, 256, 1100):
+                for mean in (40, 300, 1016, 1024, 1200, 4096):
+                    accepted[B, mean] = [kb.workspace_bytes(op, B, H, d, n, max_kv, B * n, B * mean) for op in (kb.OP_GDPA_BWD, kb.OP_SEED_BWD)]
+            for (B, mean), largest in accepted.items():
+                for b, m in accepted:
+                    if b <= B and b * m <= B * mean:
+                        gdpa = lib.kunlun_gdpa_bwd(P, P, P, P, P, P, P, P, P, None, P, b, H, d, n, max_kv, b * n, b * m, 0.1, 0, None,
+                                                   kb.BF16, P + 16, largest[0], None)
+                        seed = lib.kunlun_seed_attn_bwd(P, P, P, P, P, P, P, P, P, P, b, H, d, n, max_kv, b * m, 0.1, 0, None, kb.BF16,
+                                                        P + 16, largest[1], None)
+                        assert gdpa == kb.ERR_ALIGN and seed == kb.ERR_ALIGN, (H, n, B, mean, b, m)
+
+
 def test_check_offsets_argument_validation_without_gpu(kb):
     lib = kb.raw()
     call = lambda off=0x1000, B=4, total=100, max_len=64, out=0x1000: lib.kunlun_check_offsets(off, B, total, max_len, out, None)

@@ -71,3 +71,27 @@ def test_backward_wide_every_score_function(oracle, act):
     for a, ref, name in zip(got, refs, ("dQ", "dK", "dV")):
         # dQ: up to 300 products with a rounded dS at scores of order one, RMS about 4 - the bound above
         (assert_close_sums if name == "dQ" else assert_close)(to_np(a), ref, TOL["bf16"], f"act={act} {name}")
+
+
+def test_workspace_of_the_largest_batch_serves_smaller_ones(oracle):
+    """One buffer, sized for the largest batch, for calls with fewer examples and fewer tokens: accepted, and right."""
+    from paper_2602_10016_amd import binding as kb
+    n, H, d, longest = 70, 8, 128, 900
+    ws = torch.empty(kb.workspace_bytes(kb.OP_GDPA_BWD, 150, H, d, n, longest, 150 * n, 150 * longest), dtype=torch.uint8, device="cuda")
+    ws_seed = torch.empty(kb.workspace_bytes(kb.OP_SEED_BWD, 150, H, d, n, longest, 150 * n, 150 * longest), dtype=torch.uint8, device="cuda")
+    for B, lengths in ((3, [900, 40, 1]), (2, [0, 333])):
+        wl = W.make("cfg5", B, B=B, H=H, d=d, Nq=n, lengths=("list", np.array(lengths)), scale=1 / math.sqrt(d))
+        q, k, v, d_o = (to_dev(x, "bf16") for x in (wl.q, wl.k, wl.v, wl.d_o))
+        kvo = offsets_dev(wl.kv_offsets)
+        o, lse = kb.gdpa_fwd(q, k, v, kvo, wl.scale, 0, max_q=n, max_kv=longest)
+        got = kb.gdpa_bwd(q, k, v, d_o, kvo, wl.scale, 0, o=o, lse=lse, max_q=n, max_kv=longest, workspace=ws)
+        refs = oracle.gdpa_bwd(wl.q, wl.k, wl.v, wl.d_o, wl.kv_offsets, wl.scale, 0, max_q=n)
+        seeds = q[:n].contiguous()
+        o, lse = kb.seed_attn_fwd(seeds, k, v, kvo, wl.scale, 0, max_kv=longest)
+        got_seed = kb.seed_attn_bwd(seeds, k, v, d_o, kvo, wl.scale, 0, o=o, lse=lse, max_kv=longest, workspace=ws_seed)
+        torch.cuda.synchronize()
+        for a, ref, name in zip(got, refs, ("dQ", "dK", "dV")):
+            assert_close(to_np(a), ref, TOL["bf16"], f"B={B} {name}")
+        refs = oracle.gdpa_bwd(np.tile(wl.q[:n], (B, 1, 1)), wl.k, wl.v, wl.d_o, wl.kv_offsets, wl.scale, 0, max_q=n)
+        for a, ref, name in zip(got_seed, (refs[0].reshape(B, n, H, d).sum(axis=0), *refs[1:]), ("dE", "dK", "dV")):
+            (assert_close_sums if name == "dE" else assert_close)(to_np(a), ref, TOL["bf16"], f"B={B} seeds {name}")
