@@ -257,7 +257,7 @@ size_t kunlun_sumkron_workspace_bytes(int B, int S, int T, int D, int k, int dty
  *   dy  in,  device, [B, T, D]   gradient with respect to Y
  *   dx  out, device, [B, S, D];  dz out, device, [k, S, T];  dw out, device, [k, D, D]   fully overwritten
  * KUNLUN_BF16: matrix-core contractions with fp32 accumulation, in two kernels when T = 32, S is 128 or 256, D is
- * 128, 256 or 384 and k <= 8, else as five matrix products when, in addition to the forward
+ * 128, 256 or 384 and k <= 8 (and the workspace has room), else as five matrix products when, in addition to the forward
  * conditions, S is a multiple of 128 and T*k and B*T are multiples of 32; Z_i^T X_b and dY_b W_i^T are
  * recomputed and rounded to bf16 once, the two sums over the batch are accumulated in fp32 partial
  * sums that are added in a fixed order (results are bit-reproducible).  Other shapes and KUNLUN_FP32
@@ -267,7 +267,8 @@ size_t kunlun_sumkron_workspace_bytes(int B, int S, int T, int D, int k, int dty
 int kunlun_sumkron_bwd(const void* x, const void* z, const void* w, const void* dy, void* dx, void* dz, void* dw, int B, int S,
                        int T, int D, int k, int dtype, void* workspace, size_t workspace_bytes, void* stream);
 
-/* Bytes of workspace that kunlun_sumkron_bwd needs for these sizes (0 for invalid sizes). */
+/* Bytes of workspace for kunlun_sumkron_bwd with these sizes (0 for invalid sizes).  (Small batches of the two-kernel
+ * shapes ask for somewhat more than the five products use; with a workspace for those the call takes them.) */
 size_t kunlun_sumkron_bwd_workspace_bytes(int B, int S, int T, int D, int k, int dtype);
 
 /*

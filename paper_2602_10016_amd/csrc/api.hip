@@ -129,10 +129,10 @@ int kunlun_sumkron_bwd(const void* x, const void* z, const void* w, const void* 
         !aligned(dw, 16))
         return KUNLUN_ERR_ALIGN;
     if (B > 0) {
-        if (!workspace || workspace_bytes < kunlun_sumkron_bwd_workspace_bytes(B, S, T, D, k, dtype)) return KUNLUN_ERR_WORKSPACE;
+        if (!workspace || workspace_bytes < sumkron_bwd_need(B, S, T, D, k, dtype) + 256) return KUNLUN_ERR_WORKSPACE;
         if (!aligned(workspace, 256)) return KUNLUN_ERR_ALIGN;
     }
-    const hipError_t e = launch_sumkron_bwd(x, z, w, dy, dx, dz, dw, B, S, T, D, k, dtype, workspace, (hipStream_t)stream);
+    const hipError_t e = launch_sumkron_bwd(x, z, w, dy, dx, dz, dw, B, S, T, D, k, dtype, workspace, workspace_bytes, (hipStream_t)stream);
     return e == hipSuccess ? KUNLUN_OK : KUNLUN_ERR_LAUNCH;
 }
 

@@ -120,9 +120,11 @@ size_t sumkron_bwd_fused_workspace(int B, int S, int D, int k);
 hipError_t launch_sumkron_bwd_fused(const void* x, const void* z, const void* w, const void* dy, void* dx, void* dz, void* dw, int B, int S,
                                     int D, int k, void* workspace, hipStream_t stream);
 bool sumkron_bwd_tiled_supported(int B, int S, int T, int D, int k, int dtype);
+// Bytes with which the call takes its fastest path, and bytes that it cannot do without (the five GEMMs')
 size_t sumkron_bwd_workspace(int B, int S, int T, int D, int k, int dtype);
+size_t sumkron_bwd_need(int B, int S, int T, int D, int k, int dtype);
 hipError_t launch_sumkron_bwd(const void* x, const void* z, const void* w, const void* dy, void* dx, void* dz, void* dw, int B,
-                              int S, int T, int D, int k, int dtype, void* workspace, hipStream_t stream);
+                              int S, int T, int D, int k, int dtype, void* workspace, size_t workspace_bytes, hipStream_t stream);
 
 #ifdef __HIPCC__
 // ---- device helpers ----

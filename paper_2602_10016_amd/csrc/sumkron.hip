@@ -546,9 +546,10 @@ static BwdLayout sumkron_bwd_layout(int B, int S, int T, int D, int k, int dtype
     l.total = l.partial + align_up(p1 > p2 ? p1 : p2, 256);
     return l;
 }
+size_t sumkron_bwd_need(int B, int S, int T, int D, int k, int dtype) { return sumkron_bwd_layout(B, S, T, D, k, dtype).total; }
 size_t sumkron_bwd_workspace(int B, int S, int T, int D, int k, int dtype) {
-    // (the two-kernel path needs about half of what the GEMMs do; the size that callers see stays that of the GEMMs)
-    const size_t gemms = sumkron_bwd_layout(B, S, T, D, k, dtype).total;
+    // (the two-kernel path takes about half of what the GEMMs do for large batches, and more for small ones)
+    const size_t gemms = sumkron_bwd_need(B, S, T, D, k, dtype);
     const size_t fused = sumkron_bwd_fused_supported(S, T, D, k, dtype) ? sumkron_bwd_fused_workspace(B, S, D, k) : 0;
     return fused > gemms ? fused : gemms;
 }
@@ -566,7 +567,7 @@ static void launch_bwd_plain(const T_* x, const T_* z, const T_* w, const T_* dy
 }
 
 hipError_t launch_sumkron_bwd(const void* x, const void* z, const void* w, const void* dy, void* dx, void* dz, void* dw, int B,
-                              int S, int T, int D, int k, int dtype, void* workspace, hipStream_t stream) {
+                              int S, int T, int D, int k, int dtype, void* workspace, size_t workspace_bytes, hipStream_t stream) {
     const int64_t nz = (int64_t)k * S * T, nw = (int64_t)k * D * D;
     auto blocks = [](int64_t n) { return dim3((unsigned)((n + 255) / 256)); };
     if (B == 0) {  // no example: the weight gradients are zero
@@ -579,7 +580,7 @@ hipError_t launch_sumkron_bwd(const void* x, const void* z, const void* w, const
         }
         return hipGetLastError();
     }
-    if (sumkron_bwd_fused_supported(S, T, D, k, dtype))
+    if (sumkron_bwd_fused_supported(S, T, D, k, dtype) && workspace_bytes >= sumkron_bwd_fused_workspace(B, S, D, k))
         return launch_sumkron_bwd_fused(x, z, w, dy, dx, dz, dw, B, S, D, k, workspace, stream);
     const BwdLayout l = sumkron_bwd_layout(B, S, T, D, k, dtype);
     char* ws = (char*)workspace;

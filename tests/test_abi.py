@@ -185,6 +185,19 @@ def test_a_workspace_for_the_largest_batch_is_accepted_for_smaller_ones(kb):
                         assert gdpa == kb.ERR_ALIGN and seed == kb.ERR_ALIGN, (H, n, B, mean, b, m)
 
 
+@pytest.mark.parametrize("B,bytes_of_the_products", [(1, 5_374_208), (32, 50_594_048)])
+def test_sumkron_bwd_accepts_the_workspace_of_the_five_products(kb, B, bytes_of_the_products):
+    """S = 256, T = 32, D = 384, k = 8: two copies of Z (131 072 bytes each), U and G (196 608 bytes per example each) and
+    the dW partial sums (4 718 592 bytes per split, one for B = 1, eight for B = 32), 256 bytes more, are enough for the call, also where
+    the two kernels would use more.  (Misaligned workspace pointer, as above.)"""
+    P = 0x1000
+    lib = kb.raw()
+    call = lambda n: lib.kunlun_sumkron_bwd(P, P, P, P, P, P, P, B, 256, 32, 384, 8, kb.BF16, P + 16, n, None)
+    assert call(bytes_of_the_products) == kb.ERR_ALIGN
+    assert call(bytes_of_the_products - 1) == kb.ERR_WORKSPACE
+    assert kb.sumkron_bwd_workspace_bytes(B, 256, 32, 384, 8) >= bytes_of_the_products
+
+
 def test_check_offsets_argument_validation_without_gpu(kb):
     lib = kb.raw()
     call = lambda off=0x1000, B=4, total=100, max_len=64, out=0x1000: lib.kunlun_check_offsets(off, B, total, max_len, out, None)
