@@ -234,8 +234,8 @@ __device__ __forceinline__ void attn_bwd_wide_item(const AttnParams& p, char* sm
             const int db = j >> 1, c = j & 1;
             return tr_read((uint32_t)(ktA ^ (db << 6)) + kv + c * 16 * L::ROW_BYTES, (uint32_t)(ktB ^ (db << 6)) + kv + c * 16 * L::ROW_BYTES);
         };
-        if (key_base + KT > n_kv) {
-            const int keys_left = n_kv - key_base - 4 * g;
+        if (key_base + KT > n_kv || 32 * wave + 32 > nq) {  // keys past the history, and the queries that pad the block
+            const int keys_left = r < nq - 32 * wave ? n_kv - key_base - 4 * g : 0;
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
                 const bool ok = 8 * (v >> 2) + (v & 3) < keys_left;

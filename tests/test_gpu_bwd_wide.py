@@ -95,3 +95,24 @@ def test_workspace_of_the_largest_batch_serves_smaller_ones(oracle):
         refs = oracle.gdpa_bwd(np.tile(wl.q[:n], (B, 1, 1)), wl.k, wl.v, wl.d_o, wl.kv_offsets, wl.scale, 0, max_q=n)
         for a, ref, name in zip(got_seed, (refs[0].reshape(B, n, H, d).sum(axis=0), *refs[1:]), ("dE", "dK", "dV")):
             (assert_close_sums if name == "dE" else assert_close)(to_np(a), ref, TOL["bf16"], f"B={B} seeds {name}")
+
+
+@pytest.mark.parametrize("n", [65, 97, 250])
+def test_padding_queries_add_nothing_at_keys_masked_by_infinity(n):
+    """A key whose scores are -inf (a channel of -inf) has weight 0 for every query of the example, and so zero dK and dV:
+    the rows that pad the queries to whole blocks, whose scores there are 0 * -inf, must not reach them.  (dQ is not
+    compared: it adds 0 * -inf.)"""
+    from paper_2602_10016_amd import binding as kb
+    B, H, L = 3, 2, 70
+    wl = W.make("cfg5", n, B=B, H=H, d=128, Nq=n, lengths=("list", np.full(B, L)), scale=1 / math.sqrt(128))
+    q, k, v, d_o = (to_dev(x, "bf16") for x in (wl.q, wl.k, wl.v, wl.d_o))
+    q[:, :, 0] = 1
+    masked = torch.zeros(B * L, dtype=torch.bool, device="cuda")
+    masked[[3, 40, L + 69, 2 * L]] = True
+    k[masked, :, 0] = -torch.inf
+    kvo = offsets_dev(wl.kv_offsets)
+    o, lse = kb.gdpa_fwd(q, k, v, kvo, wl.scale, 0, max_q=n, max_kv=L)
+    _, dk, dv = kb.gdpa_bwd(q, k, v, d_o, kvo, wl.scale, 0, o=o, lse=lse, max_q=n, max_kv=L)
+    torch.cuda.synchronize()
+    assert torch.isfinite(o).all() and torch.isfinite(dk).all() and torch.isfinite(dv).all()
+    assert (dk[masked] == 0).all() and (dv[masked] == 0).all() and (dv[~masked] != 0).any()
