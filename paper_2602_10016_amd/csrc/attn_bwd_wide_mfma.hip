@@ -9,6 +9,9 @@
 //     gradient phase, one tile later: wave w owns one of the 8 output blocks, dV^T or dK^T of 32 channels:
 //         dV^T[block] = dO^T[block] P,   dK^T[block] = Q^T[block] dS,   over all 256 queries;
 //         the dO^T / Q^T operand of a block does not change over the key tiles: its 16 fragments stay in registers
+// Blocks of 32 queries that an example does not have take no part: their waves compute no scores, and the gradient phase
+// skips their share of the contraction (65 queries, H = 8, GELU, 256 histories of 64..256 keys 184 -> 154 us, log-normal
+// 915 -> 657 us; the two-pass kernels 157 and 987 us).
 // The P / dS images are double-buffered, so the gradient phase of a tile and the score phase of the next lie
 // between the same two barriers (one barrier per tile).
 // K/V tiles travel by buffer-load-to-LDS through a ring of three stages (lds_ring.h), two tiles ahead.
@@ -273,14 +276,27 @@ __device__ __forceinline__ void attn_bwd_wide_item(const AttnParams& p, char* sm
         const uint32_t src = img + out_which * SM::P_BYTES;
         f32x16 acc;
         bf16x8 fr[4];  // four matrix instructions ahead
+        auto frag = [&](int j) { return tr_read(ptA + src + j * 16 * 64, ptB + src + j * 16 * 64); };
+        if (nq > SM::NQ - 32) {
 #pragma unroll
-        for (int j = 0; j < 4; ++j) fr[j] = tr_read(ptA + src + j * 16 * 64, ptB + src + j * 16 * 64);
-        PIN();
-#pragma unroll
-        for (int j = 0; j < 16; ++j) {
-            acc = mfma32(outf[j], fr[j & 3], j == 0 ? zero16 : acc);
-            if (j + 4 < 16) fr[j & 3] = tr_read(ptA + src + (j + 4) * 16 * 64, ptB + src + (j + 4) * 16 * 64);
+            for (int j = 0; j < 4; ++j) fr[j] = frag(j);
             PIN();
+#pragma unroll
+            for (int j = 0; j < 16; ++j) {
+                acc = mfma32(outf[j], fr[j & 3], j == 0 ? zero16 : acc);
+                if (j + 4 < 16) fr[j & 3] = frag(j + 4);
+                PIN();
+            }
+        } else {  // the blocks that hold queries, two matrix instructions each
+            acc = zero16;
+#pragma unroll
+            for (int j = 0; j < 14; j += 2) {
+                if (16 * j >= nq) break;
+                fr[0] = frag(j);
+                fr[1] = frag(j + 1);
+                acc = mfma32(outf[j], fr[0], acc);
+                acc = mfma32(outf[j + 1], fr[1], acc);
+            }
         }
         // lane: key r, channels 8 vg + 4g + 0..3 of the block -> whole rows of the block, 16 bytes per lane (the
         // region is the wave's own, and the LDS operations of a wave complete in order)
@@ -317,7 +333,7 @@ __device__ __forceinline__ void attn_bwd_wide_item(const AttnParams& p, char* sm
         const uint32_t img = lds0 + SM::RING + (i & 1) * 2 * SM::P_BYTES;
         const uint32_t img_prev = lds0 + SM::RING + ((i & 1) ^ 1) * 2 * SM::P_BYTES;
         stage = stage == 2 ? 0 : stage + 1;
-        if (i < n_steps) score_phase(kv, img, kt0 + i);
+        if (i < n_steps && 32 * wave < nq) score_phase(kv, img, kt0 + i);
         PIN();
         if (i > 0) gradient_phase(img_prev, kt0 + i - 1);
     }
