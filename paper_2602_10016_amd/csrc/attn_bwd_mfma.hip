@@ -331,9 +331,12 @@ __device__ __forceinline__ void attn_bwd_item(const AttnParams& p, char* smem, i
 
 // Work items = (example, head), examples in scheduler order (longest history first); consecutive examples take
 // consecutive item numbers modulo 8 (workgroup i runs on XCD i % 8), and all heads of eight examples come before the
-// next eight, so all L2 channels stay in use.  At d = 128, where one workgroup fills a compute unit, launches with a work
-// counter (p.queue: more items than compute units) are persistent, as in the pair kernel: 30 queries, 1600 items, 408 ->
-// 393 us log-normal, 218 -> 197 us for 64..1024 keys.  The smaller head dimensions keep one workgroup per item: the
+// next eight, so all L2 channels stay in use.  At d = 128, where one workgroup fills a compute unit, launches of four and
+// more items per compute unit with a work counter (p.queue) are persistent.  A workgroup claims its next item when it
+// is done, not ahead: claimed at the start of an item, the longest items left would go to the workgroups with the longest
+// items in hand.  20 queries, GELU, one workgroup per item / claim ahead / claim when done, us: 64..1024 keys, 1024 items
+// 138 / 128 / 123, 3072 items 379 / 352 / 351; log-normal histories 263 / 287 / 248, 778 / 725 / 724; below four items
+// per compute unit, 768 log-normal ones 210 / 252 / 219.  The smaller head dimensions keep one workgroup per item: the
 // persistent loop costs them 50 registers, that is, resident waves (d = 32, 64 queries: 373 -> 451 us).
 template <int D, int NQB, int NW>
 __global__ __launch_bounds__(64 * NW) void gdpa_bwd_mfma_kernel(AttnParams p, int n_items) {
@@ -341,8 +344,6 @@ __global__ __launch_bounds__(64 * NW) void gdpa_bwd_mfma_kernel(AttnParams p, in
     constexpr bool PERSISTENT = D == 128;
     int item = blockIdx.x;
     while (item < n_items) {
-        int claimed = 0;
-        if (PERSISTENT && p.queue && threadIdx.x == 0) claimed = atomicAdd(p.queue, 1);
         const int64_t j = item >> 3;
         const int h = (int)(j % p.H);
         const int64_t e = (j / p.H) * 8 + (item & 7);
@@ -378,7 +379,7 @@ __global__ __launch_bounds__(64 * NW) void gdpa_bwd_mfma_kernel(AttnParams p, in
             __shared__ int next_item;
             if (!p.queue) break;
             __syncthreads();  // the item's last LDS reads are done
-            if (threadIdx.x == 0) next_item = claimed + (int)gridDim.x;
+            if (threadIdx.x == 0) next_item = atomicAdd(p.queue, 1) + (int)gridDim.x;
             __syncthreads();
             item = __builtin_amdgcn_readfirstlane(next_item);
         }
@@ -392,7 +393,8 @@ bool mfma_bwd_supported(const AttnParams& p, int dtype) {
 size_t mfma_bwd_workspace_tail(int, int, int, int, int64_t) { return 0; }
 
 template <int D, int NQB, int NW>
-static hipError_t launch_bwd(const AttnParams& p, hipStream_t stream) {
+static hipError_t launch_bwd(const AttnParams& params, hipStream_t stream) {
+    AttnParams p = params;
     constexpr int bytes = BwdSmem<D, NQB, NW>::TOTAL;
     auto kern = gdpa_bwd_mfma_kernel<D, NQB, NW>;
     if (bytes > 64 * 1024) {
@@ -404,7 +406,9 @@ static hipError_t launch_bwd(const AttnParams& p, hipStream_t stream) {
         if (raised != hipSuccess) return raised;
     }
     const int64_t n_items = (((int64_t)p.B + 7) / 8) * 8 * p.H;
-    const int64_t grid = D == 128 && p.queue && n_items > compute_units() ? compute_units() : n_items;
+    const bool persistent = D == 128 && p.queue && n_items >= 4 * (int64_t)compute_units();
+    if (!persistent) p.queue = nullptr;
+    const int64_t grid = persistent ? compute_units() : n_items;
     hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(64 * NW), bytes, stream, p, (int)n_items);
     return hipGetLastError();
 }
