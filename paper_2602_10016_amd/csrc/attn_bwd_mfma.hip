@@ -338,8 +338,10 @@ __device__ __forceinline__ void attn_bwd_item(const AttnParams& p, char* smem, i
 // 138 / 128 / 123, 3072 items 379 / 352 / 351; log-normal histories 263 / 287 / 248, 778 / 725 / 724; below four items
 // per compute unit, 768 log-normal ones 210 / 252 / 219.  The smaller head dimensions keep one workgroup per item: the
 // persistent loop costs them 50 registers, that is, resident waves (d = 32, 64 queries: 373 -> 451 us).
+// (three workgroups per compute unit at D = 32 with one query block: without the bound the two forms of GELU take 185
+// registers where 168 allow the third; 4096 items of 64..256 keys 52 -> 41 us)
 template <int D, int NQB, int NW>
-__global__ __launch_bounds__(64 * NW) void gdpa_bwd_mfma_kernel(AttnParams p, int n_items) {
+__global__ __launch_bounds__(64 * NW, D == 32 && NQB == 1 ? 3 : 1) void gdpa_bwd_mfma_kernel(AttnParams p, int n_items) {
     extern __shared__ __attribute__((aligned(1024))) char smem[];
     constexpr bool PERSISTENT = D == 128;
     int item = blockIdx.x;
