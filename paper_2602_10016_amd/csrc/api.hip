@@ -47,6 +47,19 @@ bool fwd_sorts(int B, int H, int d, int max_q, int max_kv) {
            (d == 128 && max_q <= 32 && !schedule_is_moot(blocks, 2));
 }
 
+// Whether a backward launch of up to 64 queries per example starts its items longest first: when they do not all fit the
+// device at once.  That is one, two or three workgroups per compute unit by registers; at d = 32 and 64 the sorting kernel
+// pays up to four per compute unit only with long histories and an eighth more items than fit.  us, sorted / not:
+//   d = 64, 64 queries: softmax, 320 items 64..256 keys 24 / 21, 64..1024 keys 35 / 44; 264 log-normal items 104 / 101;
+//   GELU, 768 log-normal items 134 / 240;  d = 64, 20 queries, softmax: 520 items 64..1024 keys 41 / 40, 1024 items
+//   64..512 keys 41 / 38, log-normal 153 / 180;  d = 32, 64 queries, ReLU: 640 items 64..512 keys 21 / 18, 1024 log-normal 77 / 107
+bool bwd_sorts(int B, int H, int d, int max_q, int max_kv) {
+    const int64_t items = (int64_t)B * H;
+    if (d == 128) return !schedule_is_moot(items, max_q > 32 ? 2 : 1);
+    const int per_cu = d == 64 ? (max_q > 32 ? 1 : 2) : (max_q > 32 ? 2 : 3);
+    return !schedule_is_moot(items, 4) || (max_kv > 512 && !schedule_is_moot(items * 8 / 9, per_cu));
+}
+
 size_t order_bytes(int B) { return align_up((size_t)(B + 1) * sizeof(int32_t), 256); }
 
 // What a backward call cannot do without.  With more than 32 keys or up to 64 queries per example never more for fewer
@@ -329,10 +342,7 @@ int gdpa_bwd_checked(const void* q, const void* k, const void* v, const void* o,
     }
     if (mfma_bwd_supported(p, dtype)) {
         int32_t* order = (int32_t*)((char*)workspace + WS_HEADER_BYTES);
-        // Workgroups of the kernel per compute unit (registers); what does not fit at once starts longest first.  1024
-        // items sorted against not, GELU, us: 64..1024 keys, d = 64, 32 queries 69 / 72, 64 queries 94 / 106, d = 32,
-        // 64 queries 47 / 54; log-normal up to 4096 keys 157 / 186, 175 / 251, 95 / 141.
-        if (schedule_is_moot((int64_t)B * H, d == 128 ? (max_q > 32 ? 2 : 1) : d == 64 && max_q > 32 ? 1 : 2)) {
+        if (!bwd_sorts(B, H, d, max_q, max_kv)) {
             p.order = nullptr;
         } else {
             p.order = order;
