@@ -332,7 +332,7 @@ __device__ __forceinline__ void attn_bwd_item(const AttnParams& p, char* smem, i
 // Work items = (example, head), examples in scheduler order (longest history first); consecutive examples take
 // consecutive item numbers modulo 8 (workgroup i runs on XCD i % 8), and all heads of eight examples come before the
 // next eight, so all L2 channels stay in use.  At d = 128, where one workgroup fills a compute unit, launches of four and
-// more items per compute unit with a work counter (p.queue) are persistent.  A workgroup claims its next item when it
+// more items per compute unit (six with histories up to 512 keys) with a work counter (p.queue) are persistent.  A workgroup claims its next item when it
 // is done, not ahead: claimed at the start of an item, the longest items left would go to the workgroups with the longest
 // items in hand.  20 queries, GELU, one workgroup per item / claim ahead / claim when done, us: 64..1024 keys, 1024 items
 // 138 / 128 / 123, 3072 items 379 / 352 / 351; log-normal histories 263 / 287 / 248, 778 / 725 / 724; below four items
@@ -408,7 +408,7 @@ static hipError_t launch_bwd(const AttnParams& params, hipStream_t stream) {
         if (raised != hipSuccess) return raised;
     }
     const int64_t n_items = (((int64_t)p.B + 7) / 8) * 8 * p.H;
-    const bool persistent = D == 128 && p.queue && n_items >= 4 * (int64_t)compute_units();
+    const bool persistent = D == 128 && p.queue && n_items >= (p.max_kv > 512 ? 4 : 6) * (int64_t)compute_units();
     if (!persistent) p.queue = nullptr;
     const int64_t grid = persistent ? compute_units() : n_items;
     hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(64 * NW), bytes, stream, p, (int)n_items);

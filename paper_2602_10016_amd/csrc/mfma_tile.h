@@ -330,7 +330,7 @@ __device__ __forceinline__ void act_tile_grad(const f32x16& s, const f32x16& dp,
             float der;
             act_fast_vd<ACT>(s[v] * scale, val[v], der);
             ds[v] = dp[v] * der * scale;
-            if ((v & 3) == 3) __builtin_amdgcn_sched_barrier(0);
+            if (ACT == KUNLUN_ACT_GELU && (v & 3) == 3) __builtin_amdgcn_sched_barrier(0);  // (as above)
         }
     }
 }

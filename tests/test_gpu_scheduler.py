@@ -164,7 +164,7 @@ def bwd_case(kb, oracle, B, H, d, Nq, lo, hi, act, seed):
 # B*H against 1024 (d = 64, 32), 512 (d = 128, > 32 queries), 256 (d = 128, <= 32 queries); 2048: few-items switch
 @pytest.mark.parametrize("B,H,d,Nq", [(256, 4, 64, 32), (260, 4, 64, 32), (512, 4, 64, 32), (516, 4, 64, 32), (300, 4, 64, 64), (520, 4, 64, 40),
                                       (64, 8, 128, 64), (65, 8, 128, 64), (90, 8, 128, 40),
-                                      (32, 8, 128, 32), (33, 8, 128, 24), (120, 8, 128, 24), (130, 8, 128, 24),
+                                      (32, 8, 128, 32), (33, 8, 128, 24), (120, 8, 128, 24), (190, 8, 128, 24), (200, 8, 128, 24),
                                       (260, 4, 32, 64), (520, 4, 32, 20)])
 @pytest.mark.parametrize("act", [3, 0])
 def test_backward_parity_around_the_dispatch_thresholds(kb, oracle, B, H, d, Nq, act):
