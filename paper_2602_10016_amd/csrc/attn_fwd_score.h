@@ -71,13 +71,24 @@ __device__ __forceinline__ void score_to_weights(const f32x16& sacc, bool need_m
             sum += pv[v];
         }
         l_run += sum;
-    } else {
-        act_tile<ACT, SMALL_FORM>(sacc, sc, pv);
+    } else if (SMALL_FORM && ACT == KUNLUN_ACT_GELU) {
+        gelu_tile(sacc, sc, pv);
         if (need_mask) {
             asm volatile("");  // a branch, as above
 #pragma unroll
             for (int v = 0; v < 16; ++v) pv[v] = rel0 + (unsigned)(8 * (v >> 2) + (v & 3)) <= key_span ? pv[v] : 0.f;
         }
+    } else if (need_mask) {  // (the masking inside the loop: behind it, as for GELU, tanh GELU at d = 64 loses up to 12 %)
+        asm volatile("");  // a branch, as above
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+            const bool ok = rel0 + (unsigned)(8 * (v >> 2) + (v & 3)) <= key_span;
+            const float w = act_fast<ACT>(pv[v] * sc);
+            pv[v] = ok ? w : 0.f;
+        }
+    } else {
+#pragma unroll
+        for (int v = 0; v < 16; ++v) pv[v] = act_fast<ACT>(pv[v] * sc);
     }
 #pragma unroll
     for (int c = 0; c < 2; ++c)

@@ -295,13 +295,12 @@ __device__ __forceinline__ void act_fast_vd(float x, float& val, float& der) {
     }
 }
 
-// Weights of a score tile: raw scores times scale through the score function.  SMALL_FORM: in the short form where it
-// exists and the tile allows it.  For kernels with registers to spare: 1024 items of cfg2's kind (GELU) 37 -> 33 us; in
-// the query-tiled forward the second form costs a wave per SIMD (58 -> 65 us for 32 keys per example), in the one-pass
-// backward for few keys it spills (104 -> 246 us).
-template <int ACT, bool SMALL_FORM>
-__device__ __forceinline__ void act_tile(const f32x16& s, float scale, float (&val)[16]) {
-    if (SMALL_FORM && scores_are_small<ACT>(s, scale)) {
+// GELU weights of a score tile: raw scores times scale through the score function, in the short form where the tile allows
+// it.  For kernels with registers to spare: 1024 items of cfg2's kind 37 -> 33 us; in the query-tiled forward the second
+// form costs a wave per SIMD (58 -> 65 us for 32 keys per example), in the one-pass backward for few keys it spills (104 ->
+// 246 us).
+__device__ __forceinline__ void gelu_tile(const f32x16& s, float scale, float (&val)[16]) {
+    if (scores_are_small<KUNLUN_ACT_GELU>(s, scale)) {
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
             const float x = s[v] * scale;
@@ -309,10 +308,10 @@ __device__ __forceinline__ void act_tile(const f32x16& s, float scale, float (&v
         }
     } else {
 #pragma unroll
-        for (int v = 0; v < 16; ++v) val[v] = act_fast<ACT>(s[v] * scale);
+        for (int v = 0; v < 16; ++v) val[v] = act_fast<KUNLUN_ACT_GELU>(s[v] * scale);
     }
 }
-// ... and the score gradients ds = dp Act'(s scale) scale
+// Weights of any score function, and the score gradients ds = dp Act'(s scale) scale
 template <int ACT>
 __device__ __forceinline__ void act_tile_grad(const f32x16& s, const f32x16& dp, float scale, float (&val)[16], float (&ds)[16]) {
     if (scores_are_small<ACT>(s, scale)) {
