@@ -36,17 +36,6 @@ int fill_acts(AttnParams& p, int H, int act, const int32_t* head_act, bool& any_
     return KUNLUN_OK;
 }
 
-// Whether a forward launch of up to 64 queries per example starts its items longest first (one more kernel, 4 us): when
-// they do not all fit the device at once, and, for histories beyond 1024 keys, already above one workgroup per compute
-// unit.  GELU, us sorted / not: 512 items of up to 4096 keys d = 32, 64, 128 with 24 queries 25 / 30, 40 / 45, 73 / 80, with
-// 64 queries 31 / 37, 65 / 73, 117 / 132; 64..1024 keys d = 64, 24 queries 20 / 19, 768 items with 64 queries 40 / 31, but
-// d = 128, 24 queries, 768 items 45 / 50.
-bool fwd_sorts(int B, int H, int d, int max_q, int max_kv) {
-    const int64_t items = (int64_t)B * H, blocks = items * ((max_q + 31) / 32);
-    return !schedule_is_moot(items, 4) || (max_kv > 1024 && !schedule_is_moot(blocks, 1)) ||
-           (d == 128 && max_q <= 32 && !schedule_is_moot(blocks, 2));
-}
-
 // Whether a backward launch of up to 64 queries per example starts its items longest first: when they do not all fit the
 // device at once.  That is one, two or three workgroups per compute unit by registers; at d = 32 and 64 the sorting kernel
 // pays up to four per compute unit only with long histories and an eighth more items than fit.  us, sorted / not:
@@ -257,7 +246,7 @@ int kunlun::gdpa_fwd_checked(const void* q, const void* k, const void* v, void* 
         int32_t* order = (int32_t*)((char*)workspace + WS_HEADER_BYTES);
         if (mfma_fwd_is_qtiled(p)) {
             p.order = order;  // holds the query-tile prefix sums
-        } else if (!fwd_sorts(B, H, d, max_q, max_kv)) {
+        } else if (!mfma_fwd_plan(p).sorted) {
             p.order = nullptr;
         } else {
             p.order = order;

@@ -94,12 +94,13 @@ struct CoopTile {
     }
 };
 
+// SMALL: GELU in its short form where the scores allow it (mfma_tile.h).
 // One work item.  q_row0 / nq_wg: first query row (global) and query count of the workgroup's tile.
 // KS > 1 (with NW = 1): the workgroup has KS waves that own the SAME queries and take the key tiles of the
 // item in turn (wave s: tiles s, s + KS, ...), each with its own tile buffers and no barrier in the key loop;
 // their partial results are merged in LDS at the end, in wave order.  For launches with few work items, where
 // one wave per item would leave the time to the longest history.
-template <int D, int NQB, int NW, int ACT, int AHEAD, int KS>
+template <int D, int NQB, int NW, int ACT, int AHEAD, int KS, bool SMALL>
 __device__ __forceinline__ void attn_fwd_item(const AttnParams& p, char* lds, int h, int64_t q_row0, int nq_wg,
                                               int64_t k0, int n_kv) {
     using SM = FwdSmem<D>;
@@ -222,7 +223,7 @@ __device__ __forceinline__ void attn_fwd_item(const AttnParams& p, char* lds, in
         bf16x8 pf[NQB][2];
 #pragma unroll
         for (int qb = 0; qb < NQB; ++qb)
-            score_to_weights<ACT, DB, NQB, false, true>(sacc[qb], need_mask, (unsigned)(key_base + 4 * g - key_lo), key_span, sc, m_ref[qb],
+            score_to_weights<ACT, DB, NQB, false, SMALL>(sacc[qb], need_mask, (unsigned)(key_base + 4 * g - key_lo), key_span, sc, m_ref[qb],
                                            l_run[qb], oacc, qb, pf[qb]);
         // ---- O^T += V^T P^T
 #pragma unroll
@@ -364,17 +365,17 @@ __device__ __forceinline__ void attn_fwd_item(const AttnParams& p, char* lds, in
     }
 }
 
-template <int D, int NQB, int NW, int AHEAD, int KS>
+template <int D, int NQB, int NW, int AHEAD, int KS, bool SMALL>
 __device__ __forceinline__ void attn_fwd_dispatch(const AttnParams& p, char* lds, int act, int h, int64_t q_row0,
                                                   int nq, int64_t k0, int n_kv) {
     switch (act) {
-    case KUNLUN_ACT_SOFTMAX: attn_fwd_item<D, NQB, NW, KUNLUN_ACT_SOFTMAX, AHEAD, KS>(p, lds, h, q_row0, nq, k0, n_kv); break;
-    case KUNLUN_ACT_IDENTITY: attn_fwd_item<D, NQB, NW, KUNLUN_ACT_IDENTITY, AHEAD, KS>(p, lds, h, q_row0, nq, k0, n_kv); break;
-    case KUNLUN_ACT_RELU: attn_fwd_item<D, NQB, NW, KUNLUN_ACT_RELU, AHEAD, KS>(p, lds, h, q_row0, nq, k0, n_kv); break;
-    case KUNLUN_ACT_GELU: attn_fwd_item<D, NQB, NW, KUNLUN_ACT_GELU, AHEAD, KS>(p, lds, h, q_row0, nq, k0, n_kv); break;
-    case KUNLUN_ACT_GELU_TANH: attn_fwd_item<D, NQB, NW, KUNLUN_ACT_GELU_TANH, AHEAD, KS>(p, lds, h, q_row0, nq, k0, n_kv); break;
-    case KUNLUN_ACT_SILU: attn_fwd_item<D, NQB, NW, KUNLUN_ACT_SILU, AHEAD, KS>(p, lds, h, q_row0, nq, k0, n_kv); break;
-    default: attn_fwd_item<D, NQB, NW, KUNLUN_ACT_GELU_POLY, AHEAD, KS>(p, lds, h, q_row0, nq, k0, n_kv); break;
+    case KUNLUN_ACT_SOFTMAX: attn_fwd_item<D, NQB, NW, KUNLUN_ACT_SOFTMAX, AHEAD, KS, SMALL>(p, lds, h, q_row0, nq, k0, n_kv); break;
+    case KUNLUN_ACT_IDENTITY: attn_fwd_item<D, NQB, NW, KUNLUN_ACT_IDENTITY, AHEAD, KS, SMALL>(p, lds, h, q_row0, nq, k0, n_kv); break;
+    case KUNLUN_ACT_RELU: attn_fwd_item<D, NQB, NW, KUNLUN_ACT_RELU, AHEAD, KS, SMALL>(p, lds, h, q_row0, nq, k0, n_kv); break;
+    case KUNLUN_ACT_GELU: attn_fwd_item<D, NQB, NW, KUNLUN_ACT_GELU, AHEAD, KS, SMALL>(p, lds, h, q_row0, nq, k0, n_kv); break;
+    case KUNLUN_ACT_GELU_TANH: attn_fwd_item<D, NQB, NW, KUNLUN_ACT_GELU_TANH, AHEAD, KS, SMALL>(p, lds, h, q_row0, nq, k0, n_kv); break;
+    case KUNLUN_ACT_SILU: attn_fwd_item<D, NQB, NW, KUNLUN_ACT_SILU, AHEAD, KS, SMALL>(p, lds, h, q_row0, nq, k0, n_kv); break;
+    default: attn_fwd_item<D, NQB, NW, KUNLUN_ACT_GELU_POLY, AHEAD, KS, SMALL>(p, lds, h, q_row0, nq, k0, n_kv); break;
     }
 }
 
@@ -388,7 +389,7 @@ __device__ __forceinline__ void attn_fwd_dispatch(const AttnParams& p, char* lds
 // unclaimed one, which is the dispatcher's longest-first list scheduling without its cost (measured on the
 // jagged benchmark batch: with cheap score functions the dispatcher kept a third of the workgroup slots empty).
 // The counter is asked for the next item while the current one starts.
-template <int D, int NQB, int NW, int OCC, int AHEAD, int KS>
+template <int D, int NQB, int NW, int OCC, int AHEAD, int KS, bool SMALL>
 __global__ __launch_bounds__(64 * NW * KS, OCC) void gdpa_fwd_mfma_kernel(AttnParams p, int n_qtiles, int n_items) {
     extern __shared__ __attribute__((aligned(1024))) char lds[];  // KS * FwdSmem<D>::bytes(KS) bytes
     constexpr int QT = 32 * NQB * NW;
@@ -413,7 +414,7 @@ __global__ __launch_bounds__(64 * NW * KS, OCC) void gdpa_fwd_mfma_kernel(AttnPa
                 const int nq = (int)((nq_all - q_first) < QT ? (nq_all - q_first) : QT);
                 const int64_t k0 = p.kv_off[b];
                 const int n_kv = p.kv_off[b + 1] - (int)k0;
-                attn_fwd_dispatch<D, NQB, NW, AHEAD, KS>(p, lds, p.head_act[h], h, qb0 + q_first, nq, k0, n_kv);
+                attn_fwd_dispatch<D, NQB, NW, AHEAD, KS, SMALL>(p, lds, p.head_act[h], h, qb0 + q_first, nq, k0, n_kv);
             }
         }
         if (KS > 1 || !p.queue) break;
@@ -433,11 +434,17 @@ bool mfma_fwd_supported(const AttnParams& p, int dtype) {
     return true;
 }
 
-template <int D, int NQB, int NW, int OCC, int AHEAD, int KS = 1>
+static bool has_act(const AttnParams& p, int act) {
+    for (int h = 0; h < p.H; ++h)
+        if (p.head_act[h] == act) return true;
+    return false;
+}
+
+template <int D, int NQB, int NW, int OCC, int AHEAD, int KS = 1, bool SMALL = true>
 static hipError_t launch_gdpa(const AttnParams& p, hipStream_t stream) {
     constexpr int QT = 32 * NQB * NW;
     constexpr int bytes = KS * FwdSmem<D>::bytes(KS);
-    auto kern = gdpa_fwd_mfma_kernel<D, NQB, NW, OCC, AHEAD, KS>;
+    auto kern = gdpa_fwd_mfma_kernel<D, NQB, NW, OCC, AHEAD, KS, SMALL>;
     if (bytes > 64 * 1024) {
         // once per process (thread-safe initialisation of a function-local static); not a stream operation
         static const hipError_t raised = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
@@ -461,7 +468,9 @@ static hipError_t launch_gdpa(const AttnParams& p, hipStream_t stream) {
         //   d = 64, 64 queries, 400: 221 / 205 / 232 / 246, 32 queries, 600: 320 / 261 / 287 / 325;  d = 32, 900: 368 / 290 / 273 / 285
         // At d = 128 two are the best alone (bench batch 855 / 865 / 873 us), but not next to kernels that draw the clock
         // down, where two waves of a compute unit cannot keep up: in the benchmark step 887 / 833 / 838 us.
-        constexpr int walkers = D == 32 ? 4 : 3;
+        // At d = 32 with 33..64 queries the tanh and the polynomial form need all that fit: 900 examples of 64..1024 keys 157 / 161 us.
+        const bool needs_waves = NW == 2 && (has_act(p, KUNLUN_ACT_GELU_TANH) || has_act(p, KUNLUN_ACT_GELU_POLY));
+        const int walkers = D == 32 ? (!SMALL && needs_waves ? per_cu : 4) : 3;
         const int64_t resident = (int64_t)(per_cu < walkers ? per_cu : walkers) * compute_units();
         if (grid > resident) grid = resident;
     }
@@ -471,34 +480,74 @@ static hipError_t launch_gdpa(const AttnParams& p, hipStream_t stream) {
 
 bool mfma_fwd_is_qtiled(const AttnParams& p) { return p.windowed || p.max_q > 64; }
 
+// Up to 32 queries per example = one wave per (example, head).  With few work items (every wave has a SIMD to itself) the
+// longest history and the score function of a single wave would set the time: two, four or, for histories beyond 1024
+// keys, eight waves then share the key tiles of a block of 32 queries; 33..64 queries make two such blocks, which read K
+// and V once each (the second time out of the L2), as long as bandwidth is not what counts.  Where the lines lie depends
+// on the score function: all but GELU (its general form) keep up with memory for longer.
+// Longest first (one more kernel, 4 us): when the items do not all fit the device at once, and earlier with long histories.
+// us, one wave per item (64 queries: a workgroup of two) / 4 waves / 8 waves, unsorted, then sorted; histories of 64..512
+// (t), 64..1024 (u) and log-normal up to 4096 keys (l):
+//   64 queries  d = 128  softmax  256 items u 31 / 36 / 38, 35 / 35 / 36;  l 110 / 104 / 98, 111 / 80 / 73;  GELU 512 l 149 / 149 / 132, 153 / 117 / 117
+//               d = 64   softmax  384 u 23 / 26 / 31, 29 / 26 / 32;  512 l 82 / 77 / 74, 88 / 62 / 67;  768 l 89 / 107 / 110, 97 / 87 / 97
+//                        GELU     512 u 32 / 33 / 39, 37 / 32 / 39;  1024 l 122 / 129 / 131, 125 / 112 / 124
+//               d = 32   softmax  384 u 18 / 14 / 15;  768 u 20 / 23 / 25, 29 / 23 / 27;  1024 l 67 / 68 / 61, 73 / 52 / 54;  1536 u 30 / 38 / 42, 40 / 38 / 47
+//   32 queries  d = 128 (one / 2 / 4 / 8)  softmax  512 u 36 / 34 / 35 / 38, 43 / 34 / 35 / 35;  768 t 27 / 27 / 29 / 36, 36 / 27 / 30 / 38;
+//                        768 u 50 / 50 / 54 / 55, 58 / 48 / 47 / 53;  256 t 17 / 12 / 12 / 13
+//               d = 64   softmax  256 l 76 / 29 / 31, 82 / 33 / 34;  384 l 79 / 44 / 37, 85 / 39 / 37
+//               d = 32   ReLU     256 l 41 / 16 / 15, 47 / 19 / 18;  384 l 43 / 20 / 20, 50 / 21 / 21;  512 l 43 / 26 / 27, 51 / 23 / 23
+FwdPlan mfma_fwd_plan(const AttnParams& p) {
+    const bool cheap = !has_act(p, KUNLUN_ACT_GELU);
+    const int d = p.d;
+    const int64_t items = (int64_t)p.B * p.H, blocks = items * ((p.max_q + 31) / 32);
+    const bool long_histories = p.max_kv > 1024;
+    const bool all_fit = schedule_is_moot(items, 4);
+    FwdPlan plan = {1, !all_fit || (long_histories && !schedule_is_moot(blocks, 1))};
+    if (p.max_q <= 32) {
+        if (blocks > 2048) return plan;
+        plan.key_split = long_histories && blocks <= 1024 ? 8 : 4;
+        if (d == 128 && !long_histories) {
+            const bool worth = p.max_kv > 512 && blocks > 512;  // (four waves crowd each other out below)
+            plan.key_split = worth || blocks <= 256 ? 4 : 2;
+            plan.sorted = plan.sorted || worth;
+        }
+        if (cheap && long_histories && (d == 64 ? blocks <= 256 : d == 32 && blocks > 256 && blocks <= 384)) plan = {4, false};
+        return plan;
+    }
+    const int64_t dear_limit = d == 32 ? 4096 : d == 64 ? (long_histories ? 2048 : 1024) : (long_histories ? 1024 : 512);
+    const int64_t cheap_limit = d == 32 ? (long_histories || !all_fit ? 4096 : 768) : d == 64 ? (long_histories ? 1024 : 512) : (long_histories ? 1024 : 256);
+    if (blocks <= (cheap ? cheap_limit : dear_limit))
+        plan.key_split = long_histories && blocks <= (d == 32 ? 1536 : 2048) ? 8 : 4;
+    else
+        plan.sorted = !all_fit || (long_histories && (d == 128 ? items > 896 : !cheap));
+    return plan;
+}
+
 hipError_t launch_mfma_fwd(const AttnParams& p, hipStream_t stream) {
     // 32 queries per wave, up to 255 registers per wave, two or three waves per SIMD.
     // Query-tiled launches use 128-query tiles (4 waves): fewer K/V tile loads per query.
     if (mfma_fwd_is_qtiled(p)) return launch_mfma_fwd_qtiled(p, stream);
-    // Up to 32 queries per example = one wave per (example, head).  With few work items (every wave has a SIMD to
-    // itself) the longest history and the score function of a single wave would set the time: four waves, or eight
-    // for histories beyond 1024 keys, then share the key tiles of a block of 32 queries; 33..64 queries make two such
-    // blocks, which read K and V once each (the second time out of the L2), as long as bandwidth is not what counts.
-    // GELU, us per call, one workgroup per item (two waves for 64 queries; the key split of 2 that d = 128 had) against
-    // the split, histories of 64..1024 keys (u) / log-normal up to 4096 (l):
-    //   d = 64, 64 queries, B H = 128: u 34 / 14, l 123 / 33;  512: u 50 / 35, l 179 / 77;  1024: u 53 / 60, l 186 / 136
-    //   d = 128, 64 queries, 128: u 44 / 20, l 162 / 57;  256: u 46 / 36;  512: u 54 / 63, l 183 / 135;  1024: l 224 / 244
-    //   d = 32, 64 queries, 2048: u 80 / 59, l 166 / 122;  d = 128, 24 queries, 1024: u 66 / 61, l 174 / 142
-    //   eight against four waves, 24 queries: d = 64, 512: u 25 / 21, l 48 / 59;  d = 128, 1024: u 66 / 61, l 142 / 151
-    const int64_t blocks = (int64_t)p.B * p.H * ((p.max_q + 31) / 32);
-    const bool long_histories = p.max_kv > 1024;
-    const int64_t few = p.max_q <= 32 ? 2048 : p.d == 32 ? 4096 : p.d == 64 ? (long_histories ? 2048 : 1024) : (long_histories ? 1024 : 512);
-    if (blocks <= few && blocks <= 2048 / (p.max_q <= 32 ? 2 : 1) && long_histories)
-        return p.d == 128 ? launch_gdpa<128, 1, 1, 2, 1, 8>(p, stream)
-               : p.d == 64 ? launch_gdpa<64, 1, 1, 2, 2, 8>(p, stream) : launch_gdpa<32, 1, 1, 2, 2, 8>(p, stream);
-    if (blocks <= few)
-        return p.d == 128 ? launch_gdpa<128, 1, 1, 2, 1, 4>(p, stream)
-               : p.d == 64 ? launch_gdpa<64, 1, 1, 2, 2, 4>(p, stream) : launch_gdpa<32, 1, 1, 2, 2, 4>(p, stream);
-    if (p.max_q <= 32)
-        return p.d == 128 ? launch_gdpa<128, 1, 1, 2, 1>(p, stream)
-               : p.d == 64 ? launch_gdpa<64, 1, 1, 2, 2>(p, stream) : launch_gdpa<32, 1, 1, 2, 2>(p, stream);
-    return p.d == 128 ? launch_gdpa<128, 1, 2, 2, 2>(p, stream)
-           : p.d == 64 ? launch_gdpa<64, 1, 2, 2, 2>(p, stream) : launch_gdpa<32, 1, 2, 2, 2>(p, stream);
+    const int ks = mfma_fwd_plan(p).key_split;
+    if (p.d == 128) {
+        if (ks == 8) return launch_gdpa<128, 1, 1, 2, 1, 8>(p, stream);
+        if (ks == 4) return launch_gdpa<128, 1, 1, 2, 1, 4>(p, stream);
+        if (ks == 2) return launch_gdpa<128, 1, 1, 2, 1, 2>(p, stream);
+        return p.max_q <= 32 ? launch_gdpa<128, 1, 1, 2, 1>(p, stream) : launch_gdpa<128, 1, 2, 2, 2>(p, stream);
+    }
+    if (p.d == 64) {
+        if (ks == 8) return launch_gdpa<64, 1, 1, 2, 2, 8>(p, stream);
+        // Four waves: with the short form of GELU a kernel of 177 registers, two workgroups per compute unit; without it 168
+        // and three, which is what counts for the other score functions and for short histories (softmax, 2048 items of
+        // 32 queries, 64..256 keys 29 / 27 us; GELU, 1536 items of 64..1024 keys 44 / 45 us, 768 of 64..512 keys 17 / 16 us)
+        if (ks == 4 && (p.max_kv <= 512 || !has_act(p, KUNLUN_ACT_GELU))) return launch_gdpa<64, 1, 1, 3, 2, 4, false>(p, stream);
+        if (ks == 4) return launch_gdpa<64, 1, 1, 2, 2, 4>(p, stream);
+        return p.max_q <= 32 ? launch_gdpa<64, 1, 1, 2, 2>(p, stream) : launch_gdpa<64, 1, 2, 2, 2>(p, stream);
+    }
+    if (ks == 8) return launch_gdpa<32, 1, 1, 2, 2, 8>(p, stream);
+    if (ks == 4) return launch_gdpa<32, 1, 1, 2, 2, 4>(p, stream);
+    if (p.max_q <= 32) return launch_gdpa<32, 1, 1, 2, 2>(p, stream);
+    // (the short form of GELU makes the compiler schedule the others worse: tanh GELU, 900 log-normal examples 287 / 292 us)
+    return has_act(p, KUNLUN_ACT_GELU) ? launch_gdpa<32, 1, 2, 2, 2>(p, stream) : launch_gdpa<32, 1, 2, 2, 2, 1, false>(p, stream);
 }
 
 }  // namespace kunlun

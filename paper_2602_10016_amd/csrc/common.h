@@ -79,6 +79,13 @@ hipError_t launch_scalar_bwd(const AttnParams& p, int dtype, hipStream_t stream)
 bool fp32_fwd_supported(const AttnParams& p, int dtype);
 hipError_t launch_fp32_fwd(const AttnParams& p, hipStream_t stream);
 bool mfma_fwd_supported(const AttnParams& p, int dtype);
+// How a streaming forward launch (up to 64 queries per example) is cut: waves that share the key tiles of a block of 32
+// queries (1: none do), and whether it starts its items longest first (p.order and p.queue are then set).
+struct FwdPlan {
+    int key_split;
+    bool sorted;
+};
+FwdPlan mfma_fwd_plan(const AttnParams& p);
 hipError_t launch_mfma_fwd(const AttnParams& p, hipStream_t stream);
 // True when the forward launch walks query tiles (window op, or more than 64 queries per
 // example): the workspace then holds query-tile prefix sums instead of the sorted example order.

@@ -34,19 +34,43 @@ def test_key_split_forward(oracle, d, n, longest, act):
         assert_lse_close(to_np(lse), lse_ref, 1e-2)
 
 
-@pytest.mark.parametrize("d,n,blocks", [(128, 64, 512), (64, 64, 1024), (32, 64, 4096), (64, 20, 2048), (128, 20, 2048)])
+# The largest launch that shares key tiles among four waves, for GELU (act 3) and for the others; at d = 128 with up to 32
+# queries the line between four and two.
+@pytest.mark.parametrize("d,n,blocks,act", [(128, 64, 512, 3), (64, 64, 1024, 3), (32, 64, 4096, 3), (128, 64, 256, 0), (64, 64, 512, 0),
+                                            (32, 64, 768, 0), (64, 20, 2048, 0), (64, 20, 2048, 3), (128, 20, 256, 0), (128, 20, 2048, 0)])
 @pytest.mark.parametrize("above", [False, True])
-def test_both_sides_of_the_few_items_rule(oracle, d, n, blocks, above):
+def test_both_sides_of_the_few_items_rule(oracle, d, n, blocks, act, above):
     """`blocks` = examples x heads x blocks of 32 queries is the largest launch that shares key tiles among waves."""
     from paper_2602_10016_amd import binding as kb
     H = 4
     B = blocks // H // ((n + 31) // 32) + (1 if above else 0)
     wl = W.make("cfg5", blocks, B=B, H=H, d=d, Nq=n, lengths=("uniform", 0, 50), scale=0.1)
     q, k, v = (to_dev(x, "bf16") for x in (wl.q, wl.k, wl.v))
-    o, _ = kb.gdpa_fwd(q, k, v, offsets_dev(wl.kv_offsets), wl.scale, 0, max_q=n, max_kv=50)
+    o, _ = kb.gdpa_fwd(q, k, v, offsets_dev(wl.kv_offsets), wl.scale, act, max_q=n, max_kv=50)
     torch.cuda.synchronize()
-    o_ref, _ = oracle.gdpa_fwd(wl.q, wl.k, wl.v, wl.kv_offsets, wl.scale, 0, max_q=n)
-    assert_close(to_np(o), o_ref, TOL["bf16"], f"d={d} n={n} B={B}")
+    o_ref, _ = oracle.gdpa_fwd(wl.q, wl.k, wl.v, wl.kv_offsets, wl.scale, act, max_q=n)
+    assert_close(to_np(o), o_ref, TOL["bf16"], f"d={d} n={n} B={B} act={act}")
+
+
+@pytest.mark.parametrize("d,n,act", [(32, 20, 0), (32, 64, 3), (64, 20, 3), (64, 20, 0), (64, 64, 0), (128, 20, 0), (128, 40, 3)])
+def test_key_split_of_sorted_items(oracle, d, n, act):
+    """Long histories above one item per compute unit: eight waves share the key tiles of items in sorted order."""
+    from paper_2602_10016_amd import binding as kb
+    B, H = 100, 4
+    rng = np.random.default_rng(d + n)
+    lengths = rng.integers(0, 60, size=B)
+    lengths[[5, 50, 99]] = [1100, 300, 700]
+    wl = W.make("cfg5", d + n, B=B, H=H, d=d, Nq=n, lengths=("list", lengths), scale=1 / math.sqrt(d) if act == 0 else 1 / 1100)
+    q, k, v = (to_dev(x, "bf16") for x in (wl.q, wl.k, wl.v))
+    ws = torch.full((kb.workspace_bytes(kb.OP_GDPA_FWD, B, H, d, n, 1100, B * n, k.shape[0]),), 0xEE, dtype=torch.uint8, device="cuda")
+    o, lse = kb.gdpa_fwd(q, k, v, offsets_dev(wl.kv_offsets), wl.scale, act, max_q=n, max_kv=1100, workspace=ws)
+    torch.cuda.synchronize()
+    order = ws[256:256 + 4 * B].cpu().numpy().view(np.int32)
+    assert order[0] == 5 and np.array_equal(np.sort(order), np.arange(B)), "the items were not sorted"
+    o_ref, lse_ref = oracle.gdpa_fwd(wl.q, wl.k, wl.v, wl.kv_offsets, wl.scale, act, max_q=n)
+    assert_close(to_np(o), o_ref, TOL["bf16"], f"d={d} n={n} act={act}")
+    if act == 0:
+        assert_lse_close(to_np(lse), lse_ref, 1e-2)
 
 
 def test_gelu_of_small_and_large_scores_is_the_function_rounded_once():
