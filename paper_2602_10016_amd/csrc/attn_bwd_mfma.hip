@@ -411,7 +411,11 @@ static hipError_t launch_bwd(const AttnParams& params, hipStream_t stream) {
     const bool persistent = D == 128 && p.queue && n_items >= (p.max_kv > 512 ? 4 : 6) * (int64_t)compute_units();
     if (!persistent) p.queue = nullptr;
     const int64_t grid = persistent ? compute_units() : n_items;
-    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(64 * NW), bytes, stream, p, (int)n_items);
+    // Many long histories at D = 32 with one query block: two workgroups per compute unit move their bytes faster than three
+    // (the memory system prefers fewer walks); LDS that is not used keeps the third away.  Softmax, 32 queries, 4096
+    // log-normal items 335 -> 323 us; 64..1024 keys, 2048 items, 57 us with three, 59 with two.
+    const int lds = D == 32 && NQB == 1 && p.max_kv > 1024 && n_items > 1024 ? 56 * 1024 : bytes;
+    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(64 * NW), lds, stream, p, (int)n_items);
     return hipGetLastError();
 }
 

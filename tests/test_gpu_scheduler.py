@@ -171,6 +171,27 @@ def test_backward_parity_around_the_dispatch_thresholds(kb, oracle, B, H, d, Nq,
     bwd_case(kb, oracle, B, H, d, Nq, 1, 96, act, seed=B + Nq + 1)
 
 
+@pytest.mark.parametrize("B,H,d,Nq", [(260, 4, 32, 20), (260, 4, 128, 20), (75, 4, 64, 40), (225, 4, 32, 32)])
+@pytest.mark.parametrize("act", [3, 0])
+def test_backward_parity_of_many_items_with_a_long_history(kb, oracle, B, H, d, Nq, act):
+    """max_kv beyond 1024: two workgroups per compute unit at d = 32, the persistent launch at d = 128, sorting from one
+    item per workgroup that fits the device."""
+    rng = np.random.default_rng(B + d)
+    lengths = make_lengths(rng, B, 1, 70)
+    lengths[[2, B - 1]] = [1100, 640]
+    wl = W.make("cfg5", B, B=B, H=H, d=d, Nq=Nq, lengths=("list", lengths), scale=0.5 / math.sqrt(d) if act == 0 else 1 / 1100)
+    q, k, v, d_o = [to_dev(a, "bf16") for a in (wl.q, wl.k, wl.v, wl.d_o)]
+    kvo = offsets_dev(wl.kv_offsets)
+    o, lse = kb.gdpa_fwd(q, k, v, kvo, wl.scale, act, max_q=Nq, max_kv=1100)
+    ws = torch.full((kb.workspace_bytes(kb.OP_GDPA_BWD, B, H, d, Nq, 1100, B * Nq, k.shape[0]),), 0xEE, dtype=torch.uint8, device="cuda")
+    got = kb.gdpa_bwd(q, k, v, d_o, kvo, wl.scale, act, o=o, lse=lse, max_q=Nq, max_kv=1100, workspace=ws)
+    torch.cuda.synchronize()
+    check_order(read_i32(ws, 256, B), lengths, 1100)
+    refs = oracle.gdpa_bwd(wl.q, wl.k, wl.v, wl.d_o, wl.kv_offsets, wl.scale, act, max_q=Nq)
+    for a, ref, name in zip(got, refs, ("dQ", "dK", "dV")):
+        assert_close(to_np(a), ref, TOL["bf16"], f"bwd B={B} H={H} d={d} Nq={Nq} act={act} {name}")
+
+
 def test_many_more_examples_than_scheduler_threads(kb, oracle):
     """B = 5000 short examples: the sorting kernel and the prefix kernel walk several examples per thread."""
     fwd_case(kb, oracle, 5000, 1, 64, 8, 0, 40, 3, seed=77)
