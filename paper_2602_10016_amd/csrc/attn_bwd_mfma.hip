@@ -42,7 +42,7 @@ __device__ __forceinline__ int r_offset(int row, int chunk) {
     return row * D * 4 + ((chunk ^ (row & (D / 4 - 1))) << 4);
 }
 
-template <int D, int NQB, int NW, int ACT>
+template <int D, int NQB, int NW, int ACT, bool SMALL>
 __device__ __forceinline__ void attn_bwd_item(const AttnParams& p, char* smem, int h, int64_t q_row0, int nq,
                                               int64_t k0, int n_kv) {
     using L = TileLayout<D>;
@@ -209,14 +209,22 @@ __device__ __forceinline__ void attn_bwd_item(const AttnParams& p, char* smem, i
 #pragma unroll
         for (int qb = 0; qb < NQB; ++qb) {
             float pv[16], dsv[16];
-            if (SOFTMAX) {
+            if (SMALL && ACT == KUNLUN_ACT_GELU) {
+                gelu_tile_grad(sacc[qb], dpacc[qb], sc, pv, dsv);
+            } else {
 #pragma unroll
                 for (int v = 0; v < 16; ++v) {
-                    pv[v] = fast_exp2(sacc[qb][v] * sc - lse2[qb]);
-                    dsv[v] = pv[v] * (dpacc[qb][v] - delta[qb]) * p.scale;
+                    const float s = sacc[qb][v] * sc;
+                    float val, der;
+                    if (SOFTMAX) {
+                        val = fast_exp2(s - lse2[qb]);
+                        dsv[v] = val * (dpacc[qb][v] - delta[qb]) * p.scale;
+                    } else {
+                        act_fast_vd<ACT>(s, val, der);
+                        dsv[v] = dpacc[qb][v] * der * p.scale;
+                    }
+                    pv[v] = val;
                 }
-            } else {
-                act_tile_grad<ACT>(sacc[qb], dpacc[qb], sc, pv, dsv);
             }
             if (need_mask) {
 #pragma unroll
@@ -340,7 +348,7 @@ __device__ __forceinline__ void attn_bwd_item(const AttnParams& p, char* smem, i
 // persistent loop costs them 50 registers, that is, resident waves (d = 32, 64 queries: 373 -> 451 us).
 // (three workgroups per compute unit at D = 32 with one query block: without the bound the two forms of GELU take 185
 // registers where 168 allow the third; 4096 items of 64..256 keys 52 -> 41 us)
-template <int D, int NQB, int NW>
+template <int D, int NQB, int NW, bool SMALL>
 __global__ __launch_bounds__(64 * NW, D == 32 && NQB == 1 ? 3 : 1) void gdpa_bwd_mfma_kernel(AttnParams p, int n_items) {
     extern __shared__ __attribute__((aligned(1024))) char smem[];
     constexpr bool PERSISTENT = D == 128;
@@ -366,13 +374,13 @@ __global__ __launch_bounds__(64 * NW, D == 32 && NQB == 1 ? 3 : 1) void gdpa_bwd
                 }
             } else {
                 switch (p.head_act[h]) {
-                case KUNLUN_ACT_SOFTMAX: attn_bwd_item<D, NQB, NW, KUNLUN_ACT_SOFTMAX>(p, smem, h, q0, nq, k0, n_kv); break;
-                case KUNLUN_ACT_IDENTITY: attn_bwd_item<D, NQB, NW, KUNLUN_ACT_IDENTITY>(p, smem, h, q0, nq, k0, n_kv); break;
-                case KUNLUN_ACT_RELU: attn_bwd_item<D, NQB, NW, KUNLUN_ACT_RELU>(p, smem, h, q0, nq, k0, n_kv); break;
-                case KUNLUN_ACT_GELU: attn_bwd_item<D, NQB, NW, KUNLUN_ACT_GELU>(p, smem, h, q0, nq, k0, n_kv); break;
-                case KUNLUN_ACT_GELU_TANH: attn_bwd_item<D, NQB, NW, KUNLUN_ACT_GELU_TANH>(p, smem, h, q0, nq, k0, n_kv); break;
-                case KUNLUN_ACT_SILU: attn_bwd_item<D, NQB, NW, KUNLUN_ACT_SILU>(p, smem, h, q0, nq, k0, n_kv); break;
-                default: attn_bwd_item<D, NQB, NW, KUNLUN_ACT_GELU_POLY>(p, smem, h, q0, nq, k0, n_kv); break;
+                case KUNLUN_ACT_SOFTMAX: attn_bwd_item<D, NQB, NW, KUNLUN_ACT_SOFTMAX, SMALL>(p, smem, h, q0, nq, k0, n_kv); break;
+                case KUNLUN_ACT_IDENTITY: attn_bwd_item<D, NQB, NW, KUNLUN_ACT_IDENTITY, SMALL>(p, smem, h, q0, nq, k0, n_kv); break;
+                case KUNLUN_ACT_RELU: attn_bwd_item<D, NQB, NW, KUNLUN_ACT_RELU, SMALL>(p, smem, h, q0, nq, k0, n_kv); break;
+                case KUNLUN_ACT_GELU: attn_bwd_item<D, NQB, NW, KUNLUN_ACT_GELU, SMALL>(p, smem, h, q0, nq, k0, n_kv); break;
+                case KUNLUN_ACT_GELU_TANH: attn_bwd_item<D, NQB, NW, KUNLUN_ACT_GELU_TANH, SMALL>(p, smem, h, q0, nq, k0, n_kv); break;
+                case KUNLUN_ACT_SILU: attn_bwd_item<D, NQB, NW, KUNLUN_ACT_SILU, SMALL>(p, smem, h, q0, nq, k0, n_kv); break;
+                default: attn_bwd_item<D, NQB, NW, KUNLUN_ACT_GELU_POLY, SMALL>(p, smem, h, q0, nq, k0, n_kv); break;
                 }
             }
         }
@@ -394,11 +402,11 @@ bool mfma_bwd_supported(const AttnParams& p, int dtype) {
 
 size_t mfma_bwd_workspace_tail(int, int, int, int, int64_t) { return 0; }
 
-template <int D, int NQB, int NW>
-static hipError_t launch_bwd(const AttnParams& params, hipStream_t stream) {
+template <int D, int NQB, int NW, bool SMALL>
+static hipError_t launch_bwd_form(const AttnParams& params, hipStream_t stream) {
     AttnParams p = params;
     constexpr int bytes = BwdSmem<D, NQB, NW>::TOTAL;
-    auto kern = gdpa_bwd_mfma_kernel<D, NQB, NW>;
+    auto kern = gdpa_bwd_mfma_kernel<D, NQB, NW, SMALL>;
     if (bytes > 64 * 1024) {
         // raise the kernel's dynamic LDS limit once per process (initialisation of a function-local
         // static is thread-safe; not a stream operation, so a later call under graph capture
@@ -417,6 +425,11 @@ static hipError_t launch_bwd(const AttnParams& params, hipStream_t stream) {
     const int lds = D == 32 && NQB == 1 && p.max_kv > 1024 && n_items > 1024 ? 56 * 1024 : bytes;
     hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(64 * NW), lds, stream, p, (int)n_items);
     return hipGetLastError();
+}
+
+template <int D, int NQB, int NW>
+static hipError_t launch_bwd(const AttnParams& p, hipStream_t stream) {
+    return short_gelu(p) ? launch_bwd_form<D, NQB, NW, true>(p, stream) : launch_bwd_form<D, NQB, NW, false>(p, stream);
 }
 
 hipError_t launch_mfma_bwd(const AttnParams& p, void*, hipStream_t stream) {

@@ -94,7 +94,7 @@ struct CoopTile {
     }
 };
 
-// SMALL: GELU in its short form where the scores allow it (mfma_tile.h).
+// SMALL: GELU in its short form where the scores of a tile allow it (short_gelu()).
 // One work item.  q_row0 / nq_wg: first query row (global) and query count of the workgroup's tile.
 // KS > 1 (with NW = 1): the workgroup has KS waves that own the SAME queries and take the key tiles of the
 // item in turn (wave s: tiles s, s + KS, ...), each with its own tile buffers and no barrier in the key loop;
@@ -434,13 +434,7 @@ bool mfma_fwd_supported(const AttnParams& p, int dtype) {
     return true;
 }
 
-static bool has_act(const AttnParams& p, int act) {
-    for (int h = 0; h < p.H; ++h)
-        if (p.head_act[h] == act) return true;
-    return false;
-}
-
-template <int D, int NQB, int NW, int OCC, int AHEAD, int KS = 1, bool SMALL = true>
+template <bool SMALL, int D, int NQB, int NW, int OCC, int AHEAD, int KS = 1>
 static hipError_t launch_gdpa(const AttnParams& p, hipStream_t stream) {
     constexpr int QT = 32 * NQB * NW;
     constexpr int bytes = KS * FwdSmem<D>::bytes(KS);
@@ -461,16 +455,18 @@ static hipError_t launch_gdpa(const AttnParams& p, hipStream_t stream) {
             return n;
         }();
         // Fewer workgroups than would fit: every workgroup is a walk of its own through memory, and the memory system
-        // moves the bytes of few walks faster than those of many, as long as the score function keeps up (exponential
-        // forms and GELU on small scores do; GELU on scores beyond 1 gains nothing and loses up to 5 %).  GELU, 8 heads,
-        // log-normal histories, us with 2 / 3 / 4 / all that fit workgroups per compute unit:
+        // moves the bytes of few walks faster than those of many, as long as the score function keeps up: exponential
+        // forms and the short form of GELU do, its general form does not.  GELU on small scores, 8 heads, log-normal
+        // histories, us with 2 / 3 / 4 / all that fit workgroups per compute unit:
         //   d = 128, 64 queries, 400 examples 348 / 376 / 390 / 390, 30 queries 333 / 363 / 390 / 389;
         //   d = 64, 64 queries, 400: 221 / 205 / 232 / 246, 32 queries, 600: 320 / 261 / 287 / 325;  d = 32, 900: 368 / 290 / 273 / 285
+        // (scores around 2, d = 64, 64 queries, 4096 items: 313 us with three, 283 with all).
         // At d = 128 two are the best alone (bench batch 855 / 865 / 873 us), but not next to kernels that draw the clock
         // down, where two waves of a compute unit cannot keep up: in the benchmark step 887 / 833 / 838 us.
         // At d = 32 with 33..64 queries the tanh and the polynomial form need all that fit: 900 examples of 64..1024 keys 157 / 161 us.
-        const bool needs_waves = NW == 2 && (has_act(p, KUNLUN_ACT_GELU_TANH) || has_act(p, KUNLUN_ACT_GELU_POLY));
-        const int walkers = D == 32 ? (!SMALL && needs_waves ? per_cu : 4) : 3;
+        const bool needs_waves = (!SMALL && has_act(p, KUNLUN_ACT_GELU)) ||
+                                 (D == 32 && NW == 2 && (has_act(p, KUNLUN_ACT_GELU_TANH) || has_act(p, KUNLUN_ACT_GELU_POLY)));
+        const int walkers = needs_waves ? per_cu : D == 32 ? 4 : 3;
         const int64_t resident = (int64_t)(per_cu < walkers ? per_cu : walkers) * compute_units();
         if (grid > resident) grid = resident;
     }
@@ -523,31 +519,34 @@ FwdPlan mfma_fwd_plan(const AttnParams& p) {
     return plan;
 }
 
-hipError_t launch_mfma_fwd(const AttnParams& p, hipStream_t stream) {
+template <bool SMALL>
+static hipError_t launch_streaming(const AttnParams& p, int ks, hipStream_t stream) {
     // 32 queries per wave, up to 255 registers per wave, two or three waves per SIMD.
+    if (p.d == 128) {
+        if (ks == 8) return launch_gdpa<SMALL, 128, 1, 1, 2, 1, 8>(p, stream);
+        if (ks == 4) return launch_gdpa<SMALL, 128, 1, 1, 2, 1, 4>(p, stream);
+        if (ks == 2) return launch_gdpa<SMALL, 128, 1, 1, 2, 1, 2>(p, stream);
+        return p.max_q <= 32 ? launch_gdpa<SMALL, 128, 1, 1, 2, 1>(p, stream) : launch_gdpa<SMALL, 128, 1, 2, 2, 2>(p, stream);
+    }
+    if (p.d == 64) {
+        if (ks == 8) return launch_gdpa<SMALL, 64, 1, 1, 2, 2, 8>(p, stream);
+        // Four waves: with the short form of GELU a kernel of 177 registers, two workgroups per compute unit; without it 162
+        // and three, which is what counts for short histories (GELU, 768 items of 32 queries, 64..512 keys 17.2 / 15.9 us;
+        // 1536 of 64..1024 keys 43.9 / 45.4 us)
+        if (ks == 4 && SMALL && p.max_kv > 512) return launch_gdpa<SMALL, 64, 1, 1, 2, 2, 4>(p, stream);
+        if (ks == 4) return launch_gdpa<false, 64, 1, 1, 2, 2, 4>(p, stream);
+        return p.max_q <= 32 ? launch_gdpa<SMALL, 64, 1, 1, 2, 2>(p, stream) : launch_gdpa<SMALL, 64, 1, 2, 2, 2>(p, stream);
+    }
+    if (ks == 8) return launch_gdpa<SMALL, 32, 1, 1, 2, 2, 8>(p, stream);
+    if (ks == 4) return launch_gdpa<SMALL, 32, 1, 1, 2, 2, 4>(p, stream);
+    return p.max_q <= 32 ? launch_gdpa<SMALL, 32, 1, 1, 2, 2>(p, stream) : launch_gdpa<SMALL, 32, 1, 2, 2, 2>(p, stream);
+}
+
+hipError_t launch_mfma_fwd(const AttnParams& p, hipStream_t stream) {
     // Query-tiled launches use 128-query tiles (4 waves): fewer K/V tile loads per query.
     if (mfma_fwd_is_qtiled(p)) return launch_mfma_fwd_qtiled(p, stream);
     const int ks = mfma_fwd_plan(p).key_split;
-    if (p.d == 128) {
-        if (ks == 8) return launch_gdpa<128, 1, 1, 2, 1, 8>(p, stream);
-        if (ks == 4) return launch_gdpa<128, 1, 1, 2, 1, 4>(p, stream);
-        if (ks == 2) return launch_gdpa<128, 1, 1, 2, 1, 2>(p, stream);
-        return p.max_q <= 32 ? launch_gdpa<128, 1, 1, 2, 1>(p, stream) : launch_gdpa<128, 1, 2, 2, 2>(p, stream);
-    }
-    if (p.d == 64) {
-        if (ks == 8) return launch_gdpa<64, 1, 1, 2, 2, 8>(p, stream);
-        // Four waves: with the short form of GELU a kernel of 177 registers, two workgroups per compute unit; without it 168
-        // and three, which is what counts for the other score functions and for short histories (softmax, 2048 items of
-        // 32 queries, 64..256 keys 29 / 27 us; GELU, 1536 items of 64..1024 keys 44 / 45 us, 768 of 64..512 keys 17 / 16 us)
-        if (ks == 4 && (p.max_kv <= 512 || !has_act(p, KUNLUN_ACT_GELU))) return launch_gdpa<64, 1, 1, 3, 2, 4, false>(p, stream);
-        if (ks == 4) return launch_gdpa<64, 1, 1, 2, 2, 4>(p, stream);
-        return p.max_q <= 32 ? launch_gdpa<64, 1, 1, 2, 2>(p, stream) : launch_gdpa<64, 1, 2, 2, 2>(p, stream);
-    }
-    if (ks == 8) return launch_gdpa<32, 1, 1, 2, 2, 8>(p, stream);
-    if (ks == 4) return launch_gdpa<32, 1, 1, 2, 2, 4>(p, stream);
-    if (p.max_q <= 32) return launch_gdpa<32, 1, 1, 2, 2>(p, stream);
-    // (the short form of GELU makes the compiler schedule the others worse: tanh GELU, 900 log-normal examples 287 / 292 us)
-    return has_act(p, KUNLUN_ACT_GELU) ? launch_gdpa<32, 1, 2, 2, 2>(p, stream) : launch_gdpa<32, 1, 2, 2, 2, 1, false>(p, stream);
+    return short_gelu(p) ? launch_streaming<true>(p, ks, stream) : launch_streaming<false>(p, ks, stream);
 }
 
 }  // namespace kunlun

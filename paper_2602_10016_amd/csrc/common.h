@@ -79,6 +79,20 @@ hipError_t launch_scalar_bwd(const AttnParams& p, int dtype, hipStream_t stream)
 bool fp32_fwd_supported(const AttnParams& p, int dtype);
 hipError_t launch_fp32_fwd(const AttnParams& p, hipStream_t stream);
 bool mfma_fwd_supported(const AttnParams& p, int dtype);
+// Whether some head uses a score function, and whether queries and keys of unit variance give scores within [-1, 1] (four
+// standard deviations of scale sqrt(d)), as the 1/tau scaling of Eq. (GDPA) does.
+inline bool has_act(const AttnParams& p, int act) {
+    for (int h = 0; h < p.H; ++h)
+        if (p.head_act[h] == act) return true;
+    return false;
+}
+inline bool small_scores_expected(const AttnParams& p) { return p.scale * p.scale * (float)p.d <= 1.f / 16; }
+// Kernels in which GELU has its short form beside the general one (mfma_tile.h): a matter of speed, both are right for any
+// score.  Not for large scores: the branch between the forms costs what surrounds it 3 to 6 % (scores around 2, 64
+// queries: backward, d = 64, 4096 log-normal items 645 / 668 us without / with it, forward, d = 128, 512 items of
+// 64..1024 keys 51.1 / 54.7 us).  On small ones it gains 5 to 12 % (256 examples, 4 heads, d = 64, 32 queries, 64..1024 keys: forward
+// 36.7 / 33.4 us, backward 74.5 / 71.1 us).
+inline bool short_gelu(const AttnParams& p) { return has_act(p, KUNLUN_ACT_GELU) && small_scores_expected(p); }
 // How a streaming forward launch (up to 64 queries per example) is cut: waves that share the key tiles of a block of 32
 // queries (1: none do), and whether it starts its items longest first (p.order and p.queue are then set).
 struct FwdPlan {

@@ -229,11 +229,9 @@ __device__ __forceinline__ float gelu_small_pdf(float u) {
     q = fmaf(u, q, GELU_P1);
     return fmaf(u, q, GELU_P0);
 }
-// True when the score function has such a form and all scores of the wave are inside its range.  Wave-uniform.  (The
-// maximum passes over NaN scores; both forms return NaN for them.)
-template <int ACT>
+// True when all scores of the wave are inside that range.  Wave-uniform.  (The maximum passes over NaN scores; both
+// forms return NaN for them.)
 __device__ __forceinline__ bool scores_are_small(const f32x16& s, float scale) {
-    if constexpr (ACT != KUNLUN_ACT_GELU) return false;
     float m = 0.f;
 #pragma unroll
     for (int v = 0; v < 16; v += 2) m = fmaxf(m, fmaxf(fabsf(s[v]), fabsf(s[v + 1])));
@@ -300,7 +298,7 @@ __device__ __forceinline__ void act_fast_vd(float x, float& val, float& der) {
 // form costs a wave per SIMD (58 -> 65 us for 32 keys per example), in the one-pass backward for few keys it spills (104 ->
 // 246 us).
 __device__ __forceinline__ void gelu_tile(const f32x16& s, float scale, float (&val)[16]) {
-    if (scores_are_small<KUNLUN_ACT_GELU>(s, scale)) {
+    if (scores_are_small(s, scale)) {
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
             const float x = s[v] * scale;
@@ -311,10 +309,9 @@ __device__ __forceinline__ void gelu_tile(const f32x16& s, float scale, float (&
         for (int v = 0; v < 16; ++v) val[v] = act_fast<KUNLUN_ACT_GELU>(s[v] * scale);
     }
 }
-// Weights of any score function, and the score gradients ds = dp Act'(s scale) scale
-template <int ACT>
-__device__ __forceinline__ void act_tile_grad(const f32x16& s, const f32x16& dp, float scale, float (&val)[16], float (&ds)[16]) {
-    if (scores_are_small<ACT>(s, scale)) {
+// GELU weights and the score gradients ds = dp GELU'(s scale) scale, likewise
+__device__ __forceinline__ void gelu_tile_grad(const f32x16& s, const f32x16& dp, float scale, float (&val)[16], float (&ds)[16]) {
+    if (scores_are_small(s, scale)) {
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
             const float x = s[v] * scale, u = x * x;
@@ -327,9 +324,9 @@ __device__ __forceinline__ void act_tile_grad(const f32x16& s, const f32x16& dp,
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
             float der;
-            act_fast_vd<ACT>(s[v] * scale, val[v], der);
+            act_fast_vd<KUNLUN_ACT_GELU>(s[v] * scale, val[v], der);
             ds[v] = dp[v] * der * scale;
-            if (ACT == KUNLUN_ACT_GELU && (v & 3) == 3) __builtin_amdgcn_sched_barrier(0);  // (as above)
+            if ((v & 3) == 3) __builtin_amdgcn_sched_barrier(0);
         }
     }
 }

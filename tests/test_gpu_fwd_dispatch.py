@@ -73,9 +73,11 @@ def test_key_split_of_sorted_items(oracle, d, n, act):
         assert_lse_close(to_np(lse), lse_ref, 1e-2)
 
 
-def test_gelu_of_small_and_large_scores_is_the_function_rounded_once():
-    """One key e_0, value e_0, queries x e_0: O[0] = bf16(gelu(x)) and, with dO = e_0, dQ[0] = bf16(gelu'(x)).  Examples
-    whose scores all lie inside [-1, 1] take the short form, the others (also with one score just outside) the general."""
+@pytest.mark.parametrize("scale", [1.0, 1 / 32])
+def test_gelu_of_small_and_large_scores_is_the_function_rounded_once(scale):
+    """One key e_0, value e_0, queries (x / scale) e_0: O[0] = bf16(gelu(x)) and, with dO = e_0, dQ[0] = bf16(gelu'(x)) scale.
+    With the small scale, examples whose scores all lie inside [-1, 1] take the short form, the others (also with one score
+    just outside) the general."""
     from paper_2602_10016_amd import binding as kb
     n, d = 64, 32
     inside = torch.linspace(-1, 1, 40 * n).view(40, n)
@@ -85,18 +87,18 @@ def test_gelu_of_small_and_large_scores_is_the_function_rounded_once():
     x = torch.cat([inside, wide, edge]).to(torch.bfloat16).cuda()
     B = x.shape[0]
     q = torch.zeros((B * n, 1, d), dtype=torch.bfloat16, device="cuda")
-    q[:, 0, 0] = x.reshape(-1)
+    q[:, 0, 0] = x.reshape(-1) / scale  # a power of two: exact
     k = torch.zeros((B, 1, d), dtype=torch.bfloat16, device="cuda")
     k[:, 0, 0] = 1
     d_o = torch.zeros_like(q)
     d_o[:, 0, 0] = 1
     off = torch.arange(B + 1, dtype=torch.int32, device="cuda")
-    o, _ = kb.gdpa_fwd(q, k, k.clone(), off, 1.0, kb.ACT_GELU, max_q=n, max_kv=1)
-    dq, _, _ = kb.gdpa_bwd(q, k, k.clone(), d_o, off, 1.0, kb.ACT_GELU, max_q=n, max_kv=1)
+    o, _ = kb.gdpa_fwd(q, k, k.clone(), off, scale, kb.ACT_GELU, max_q=n, max_kv=1)
+    dq, _, _ = kb.gdpa_bwd(q, k, k.clone(), d_o, off, scale, kb.ACT_GELU, max_q=n, max_kv=1)
     torch.cuda.synchronize()
     t = x.double().reshape(-1)
     cdf = 0.5 * (1 + torch.erf(t / math.sqrt(2)))
-    for got, want in ((o[:, 0, 0].double(), t * cdf), (dq[:, 0, 0].double(), cdf + t * torch.exp(-t * t / 2) / math.sqrt(2 * math.pi))):
+    for got, want in ((o[:, 0, 0].double(), t * cdf), (dq[:, 0, 0].double() / scale, cdf + t * torch.exp(-t * t / 2) / math.sqrt(2 * math.pi))):
         # half a unit in the last place of bf16 (2^-9 of the value, rounded up to the next power of two: 2^-8), plus the
         # stated error 7.5e-8 of the general form's cdf times |x| <= 6 and fp32 rounding
         assert torch.all((got - want).abs() <= 2.0 ** -8 * want.abs() + 6e-7)
