@@ -69,9 +69,10 @@ __global__ __launch_bounds__(64) void scalar_fwd_kernel(AttnParams p) {
         if (valid) s = p.scale * row_dot(sq, K + (k0 + j) * hd + (int64_t)h * d, d);
         float pj;
         if (act == KUNLUN_ACT_SOFTMAX) {
-            const float m_new = fmaxf(m, wave_max(s));  // finite: the chunk holds at least one key
-            const float corr = expf(m - m_new);         // exp(-inf) = 0 on the first chunk
-            pj = valid ? expf(s - m_new) : 0.f;
+            const float m_new = fmaxf(m, wave_max(s));
+            const float shift = m_new == -INFINITY ? 0.f : m_new;  // only scores of -inf so far: their weights are exp(-inf) = 0
+            const float corr = expf(m - shift);                    // exp(-inf) = 0 on the first chunk
+            pj = valid ? expf(s - shift) : 0.f;
             l = l * corr + wave_sum(pj);
 #pragma unroll
             for (int i = 0; i < CH; ++i) acc[i] *= corr;

@@ -52,7 +52,7 @@ def test_fp32_forward_every_score_function_many_items(oracle, act):
 MASKS = [(64, 96), (0, 32), (64, 96), (0, 599), (0, 600), (0, 0)]
 
 
-@pytest.mark.parametrize("d", [32, 64, 128])
+@pytest.mark.parametrize("d", [32, 64, 128, 40])  # (40: the scalar kernel, 64 keys at a time)
 @pytest.mark.parametrize("n", [5, 20])
 @pytest.mark.parametrize("infinite", [False, True])
 def test_fp32_softmax_with_scores_of_minus_infinity(oracle, d, n, infinite):
