@@ -20,6 +20,11 @@ CASES = [
     (9, 3, 97, 1, 300, [256, 0, 1, 257]),
     (3, 1, 129, 500, 1100, [1025]),
     (4, 2, 255, 33, 64, [33]),
+    # whole histories of several tiles (the ring of three stages wraps, items follow long ones): 1024 items and more
+    (129, 8, 65, 0, 300, [97, 128, 129, 257, 0, 1]),
+    (128, 8, 256, 0, 300, [300, 96, 128, 129, 0, 257]),
+    # ranges of nine tiles (more than 4608 tiles in all)
+    (40, 8, 100, 400, 450, [2300, 288, 289, 0, 577]),
 ]
 
 
@@ -55,6 +60,12 @@ def test_backward_65_to_256_queries(oracle, B, H, n, lo, hi, fixed, act, ragged)
             # here: 5 standard deviations are 2.2e-2 absolute, also where the value is near zero), plus its own
             # rounding 2^-9 |r|: within 2e-2 (rms + |r|) with a factor of three to spare.
             assert_close_sums(to_np(a), ref, TOL["bf16"], what)
+        elif n == 256 and B == 128 and (act == 3 or name != "dQ"):
+            # 256 terms per dK and dV element (histories of one key: weights of one, dV of order 16), 300 per dQ element, each
+            # with a bf16-rounded factor, in tens of millions of elements: off by 1.1e-3 of the RMS of its sums (as above),
+            # here per example and head for dK and dV, so 2e-2 (rms + |r|) are 18 standard deviations, where
+            # 2e-2 (1 + |r|) are 2.5 of the largest sums.  (The two-pass kernels have the same errors: 5.24e-4 RMS in dV.)
+            assert_close_sums(to_np(a), ref, TOL["bf16"], what, offsets=None if name == "dQ" else wl.kv_offsets)
         else:
             assert_close(to_np(a), ref, TOL["bf16"], what)
         assert torch.equal(a, b), f"{name} differs between two runs"

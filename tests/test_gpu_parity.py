@@ -517,11 +517,15 @@ def _check_sumkron_bwd(kb, oracle, B, S, T, D, k, dtype, tol, seed):
                                        (3, 128, 32, 128, 2),     # one tile in most directions
                                        (4, 128, 16, 256, 2),     # k*T = 32: a ragged row tile in the dZ contraction
                                        (2, 256, 48, 128, 2),     # T*k = 96, k*T = 96
-                                       (3, 128, 32, 128, 3),     # k*D = 384: 128-row tiles in the dW contraction
+                                       (3, 128, 32, 128, 3),
                                        (2, 128, 16, 128, 6),
-                                       (16, 128, 32, 128, 2)])   # enough rows for several split-K ranges
+                                       (4, 128, 16, 128, 3),     # k*D = 384: 128-row tiles in the dW contraction
+                                       (3, 128, 32, 128, 9),     # more factors than the two kernels take
+                                       (32, 128, 16, 128, 2),    # enough rows for several split-K ranges
+                                       (16, 128, 32, 128, 2)])
 def test_sumkron_backward_tiled(kb, oracle, B, S, T, D, k):
-    """bf16 matrix-core path (five tiled GEMMs, two of them split-K).  The intermediates Z^T X and
+    """bf16 matrix-core paths: the two kernels (T = 32, k <= 8, S and D of their list) and five tiled GEMMs, two of them
+    split-K (T = 16 and 48, k = 9).  The intermediates Z^T X and
     dY W^T (O(1) values) are rounded to bf16 once; sums over the batch are accumulated in fp32."""
     _check_sumkron_bwd(kb, oracle, B, S, T, D, k, "bf16", TOL["bf16"], 70 + B)
 
