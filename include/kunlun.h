@@ -159,6 +159,11 @@ int kunlun_gdpa_fwd_static(const void* q, const void* k, const void* v, void* o,
  *     softmax heads: ds = p (dp - rowsum(dO * O)) scale;   dQ += ds K;   dK += ds Q.
  * o and lse (in, device) are the forward outputs; they are read for softmax heads only and
  * may be NULL when no head uses softmax.  Other arguments as in kunlun_gdpa_fwd.
+ *
+ * Forward and backward repeat their results bit for bit for the same call.  The results of an example depend on that
+ * example alone up to rounding: how a launch is cut (which waves share a history, in which ranges partial sums are
+ * added) follows from B, H, max_q, max_kv and total_kv, so the last bits of an example's o, lse and dq may differ
+ * between batches of different sizes.
  */
 int kunlun_gdpa_bwd(const void* q, const void* k, const void* v, const void* o, const float* lse, const void* d_o,
                     void* dq, void* dk, void* dv, const int32_t* q_offsets, const int32_t* kv_offsets, int B, int H,

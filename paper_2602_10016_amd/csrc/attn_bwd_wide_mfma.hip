@@ -400,7 +400,7 @@ __device__ __forceinline__ void zero_key_gradients(const AttnParams& p, int h, i
 // (attn_bwd_pair_mfma.hip).
 __global__ __launch_bounds__(512, 2) void gdpa_bwd_wide_kernel(AttnParams p, int n_items) {
     extern __shared__ __attribute__((aligned(1024))) char smem[];
-    // hand-over word of the next item: the last word of the output blocks, dead between items
+    // hand-over word of the next item: the last word of the last wave's parked fragments, dead between items
     volatile int* const next_word = (volatile int*)(smem + WideSmem::TOTAL - 4);
     int item = blockIdx.x;
     while (item < n_items) {
@@ -422,7 +422,7 @@ __global__ __launch_bounds__(512, 2) void gdpa_bwd_wide_kernel(AttnParams p, int
         __syncthreads();  // the item's last LDS reads (dQ rows) are done
         if (threadIdx.x == 0) *next_word = claimed + (int)gridDim.x;
         __syncthreads();
-        item = __builtin_amdgcn_readfirstlane(*next_word);  // (next written in the next item's gradient phase, behind its barriers)
+        item = __builtin_amdgcn_readfirstlane(*next_word);  // (next written in the next item's prologue, where the last wave parks its fragments behind the barriers of the staging)
     }
 }
 

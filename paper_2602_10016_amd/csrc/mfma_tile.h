@@ -209,8 +209,11 @@ __device__ __forceinline__ float phi_neg_abs(float x, float& gauss) {
 }
 
 // GELU for |x| <= 1 without a transcendental: cdf(x) = 1/2 + x q(x^2) and pdf(x) by near-minimax polynomials of degree
-// 4 and 5 (fits at Chebyshev nodes of x^2 in [0, 1], rounded to fp32; errors 2e-8, where the general form has 7.5e-8).  With the 1/tau scaling of Eq. (GDPA) every score is far inside.  8 (with slope 14) vector operations
-// against 16 (20) and two quarter-rate ones.
+// 4 and 5 (fits at Chebyshev nodes of x^2 in [0, 1], rounded to fp32).  Approximation errors 2e-8, where the general form
+// has 7.5e-8; evaluation in fp32 adds up to 6e-8 to either (a cdf in [1/2, 1) is rounded by up to 3e-8).  8 (with slope 14)
+// vector operations against 16 (20) and two quarter-rate ones.  The streaming forward and the one-wave-per-tile backward
+// (up to 64 queries; d = 128: up to 32) use it where small scores are expected (short_gelu()); the pair, long-query,
+// two-pass, few-keys and query-tiled kernels have no registers for a second form.
 constexpr float GELU_Q0 = 3.9894226193e-01f, GELU_Q1 = -6.6489607096e-02f, GELU_Q2 = 9.9673019722e-03f, GELU_Q3 = -1.1695192661e-03f,
                 GELU_Q4 = 9.4317372714e-05f;
 constexpr float GELU_P0 = 3.9894229174e-01f, GELU_P1 = -1.9947089255e-01f, GELU_P2 = 4.9864895642e-02f, GELU_P3 = -8.2988310605e-03f,

@@ -23,7 +23,7 @@
 //               dZ rows of the S/4 rows of X that begin at q S/4: X rows and G fragments as stored
 //     phase 2:  dW[64 channels, n block q of D/4] += U^T dY: U from the image, dY read transposed
 // Workgroups that share X and dY rows (same examples and channels, other factors) run on one XCD.
-// Measured at B = 1024, S = 256, D = 384, k = 8: 140 us (128 GFLOP) and 215 us (180 GFLOP), clocks at 2.0-2.1 GHz, in
+// Measured at B = 1024, S = 256, D = 384, k = 8: 140 us (128 GFLOP) and 215 to 244 us (180 GFLOP), clocks at 2.0-2.1 GHz, in
 // place of five GEMMs with U and G through HBM (100 + 121 + 100 + 147 + 134 us).  What bounds them: the writes of G and
 // dX (400 MB: without the stores of dX the pair takes 55 us less; pairs of blocks stored as whole 128-byte lines, or
 // non-temporal: no change); in the second kernel LDS, 328 KB per example = 2560 cycles against 1792 cycles of matrix

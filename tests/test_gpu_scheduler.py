@@ -7,9 +7,11 @@ Workspace layout relied on here (csrc/common.h, csrc/tile_map.h): a 256-byte hea
                           bucket floor(len * 2048 / (max_kv + 1)); the order inside a bucket is free
   query-tiled launches    int32 tile_start[B+1] (exclusive prefix sums of ceil(n_b / 128)), padded to 256
                           bytes, then int32 tile_example[tile] = example of every tile.
-The sorting kernel runs only when the launch has more workgroups than are resident at once: forward more
-than 1024 (example, head, 64-query tile) items; backward B*H above 1024 (d = 32, 64), 512 (d = 128, more than
-32 queries) or 256 (d = 128, up to 32 queries).  B*H <= 2048 additionally selects the few-items kernels."""
+The sorting kernel runs when the launch has more workgroups than are resident at once: forward more than 1024
+(example, head) items, or, with histories beyond 1024 keys, more than 256 blocks of 32 queries (d = 128, up to 32 queries:
+more than 512 with histories beyond 512 keys); backward more than 1024 items, or, with histories beyond 512 keys, an eighth
+more than fit (d = 64, 33..64 queries: 256; d = 32, up to 32 queries: 768; else 512), and at d = 128 more than 512 (more
+than 32 queries) or 256 items whatever the histories.  Few items additionally share their key tiles among waves."""
 import math
 
 import numpy as np
@@ -136,7 +138,7 @@ def fwd_case(kb, oracle, B, H, d, Nq, lo, hi, act, seed):
         assert_lse_close(to_np(lse), lse_ref, 1e-2)
 
 
-# B*H*ceil(Nq/64): 1024 = all resident (no sorting kernel), above = scheduled; B*H 2048 / 2052: few-items switch
+# histories up to 96 keys: B*H 1024 = all resident (no sorting kernel), above = scheduled; B*H 2048 / 2052: few-items switch
 @pytest.mark.parametrize("B,H,d,Nq", [(256, 4, 64, 32), (257, 4, 64, 32), (320, 4, 64, 32), (512, 4, 64, 32), (513, 4, 64, 32),
                                       (128, 8, 128, 64), (129, 8, 128, 64), (140, 8, 128, 33),
                                       (257, 8, 128, 24), (130, 8, 128, 24),
@@ -161,14 +163,30 @@ def bwd_case(kb, oracle, B, H, d, Nq, lo, hi, act, seed):
         assert_close(to_np(got), ref, TOL["bf16"], f"bwd B={B} H={H} d={d} Nq={Nq} act={act} {name}")
 
 
-# B*H against 1024 (d = 64, 32), 512 (d = 128, > 32 queries), 256 (d = 128, <= 32 queries); 2048: few-items switch
-@pytest.mark.parametrize("B,H,d,Nq", [(256, 4, 64, 32), (260, 4, 64, 32), (512, 4, 64, 32), (516, 4, 64, 32), (300, 4, 64, 64), (520, 4, 64, 40),
+# B*H against 256, 512 and 1024 (d = 64, 32), 512 (d = 128, > 32 queries), 256 and 1536 (d = 128, <= 32 queries: sorted,
+# persistent); 2048: few-items switch
+@pytest.mark.parametrize("B,H,d,Nq", [(64, 4, 64, 64), (66, 4, 64, 64), (128, 4, 64, 32), (130, 4, 64, 32), (128, 4, 32, 64), (130, 4, 32, 40),
+                                      (256, 4, 64, 32), (260, 4, 64, 32), (512, 4, 64, 32), (516, 4, 64, 32), (300, 4, 64, 64), (520, 4, 64, 40),
                                       (64, 8, 128, 64), (65, 8, 128, 64), (90, 8, 128, 40),
                                       (32, 8, 128, 32), (33, 8, 128, 24), (120, 8, 128, 24), (190, 8, 128, 24), (200, 8, 128, 24),
                                       (260, 4, 32, 64), (520, 4, 32, 20)])
 @pytest.mark.parametrize("act", [3, 0])
 def test_backward_parity_around_the_dispatch_thresholds(kb, oracle, B, H, d, Nq, act):
     bwd_case(kb, oracle, B, H, d, Nq, 1, 96, act, seed=B + Nq + 1)
+
+
+@pytest.mark.parametrize("B,H,d,Nq,sorted_", [(72, 4, 64, 40, False), (73, 4, 64, 40, True), (144, 4, 64, 20, False), (145, 4, 64, 20, True),
+                                              (144, 4, 32, 40, False), (145, 4, 32, 40, True), (216, 4, 32, 20, False), (217, 4, 32, 20, True)])
+def test_backward_sorts_an_eighth_above_what_fits(kb, B, H, d, Nq, sorted_):
+    lengths = np.full(B, 5)
+    lengths[7] = 600
+    wl = W.make("cfg5", B, B=B, H=H, d=d, Nq=Nq, lengths=("list", lengths))
+    q, k, v, d_o = [to_dev(a, "bf16") for a in (wl.q, wl.k, wl.v, wl.d_o)]
+    ws = torch.full((kb.workspace_bytes(kb.OP_GDPA_BWD, B, H, d, Nq, 600, B * Nq, k.shape[0]),), 0xEE, dtype=torch.uint8, device="cuda")
+    kb.gdpa_bwd(q, k, v, d_o, offsets_dev(wl.kv_offsets), wl.scale, 3, max_q=Nq, max_kv=600, workspace=ws)
+    torch.cuda.synchronize()
+    order = read_i32(ws, 256, B)
+    assert (order[0] == 7 and np.array_equal(np.sort(order), np.arange(B))) == sorted_
 
 
 @pytest.mark.parametrize("B,H,d,Nq", [(260, 4, 32, 20), (260, 4, 128, 20), (75, 4, 64, 40), (225, 4, 32, 32)])
