@@ -480,8 +480,9 @@ bool mfma_bwd_wide_supported(const AttnParams& p, int dtype) {
 // lasts at least as long as its longest history; ranges lift that for the price of the partial sums (128 KB written
 // and read per range and head).  Whole backward and forward call with 256 queries, H = 4, whole against ranges: 64
 // histories of 64..1024 keys (longest = 1.9 times the mean work of a compute unit) 132 / 153 us, 16 x 8 heads of them
-// (3.8 times) 120 / 108 us, 64 log-normal histories up to 4096 (3.7 times) 392 / 307 us; with 100 queries, where
-// half of the waves have no scores to compute, 128 log-normal histories (1.8 times) 471 / 405 us.
+// (3.8 times) 120 / 108 us, 64 log-normal histories up to 4096 (3.7 times) 392 / 307 us; with 100 queries,
+// where half of the waves have no scores to compute, the backward alone of 128 log-normal histories (1.9 times) takes
+// 252 / 219 us, of 64 histories of 64..1024 keys (1.9 times) 62 / 73 us.
 // Two ranges per compute unit, of at least 8 tiles.
 static int wide_chunk(int B, int H, int max_q, int max_kv, int64_t total_kv) {
     const int64_t tiles = total_kv * H / KT;
