@@ -39,8 +39,9 @@ struct FwdSmem {
     static constexpr int TOTAL = 2 * BUF_BYTES;        // double buffer (workgroups of several waves)
     // A wave that streams alone needs no second buffer (it writes a tile, reads it, and writes the next one in
     // program order); the key-split launches use that to fit four waves' buffers, the others keep two buffers
-    // (the store of the next tile can then be scheduled before the reads of the current one end).
-    static constexpr int bytes(int ks) { return ks > 1 ? BUF_BYTES : TOTAL; }
+    // (the store of the next tile can then be scheduled before the reads of the current one end).  With both query
+    // blocks in a wave (nqb = 2) its partial results, which pass through the same bytes, are what takes the room.
+    static constexpr int bytes(int ks, int nqb) { return ks == 1 ? TOTAL : nqb == 1 ? BUF_BYTES : D / 32 * nqb * 4096 + 2048; }
 };
 
 // Cooperative global -> register -> LDS staging of one 32-row tile by a workgroup of 64*NW
@@ -95,20 +96,24 @@ struct CoopTile {
 };
 
 // SMALL: GELU in its short form where the scores of a tile allow it (short_gelu()).
+// HP = 2: the item is a PAIR of neighbouring heads of D / 2 channels each, whose row pieces are one piece of D channels; the
+// wave forms the scores and outputs of both from the same tiles.
 // One work item.  q_row0 / nq_wg: first query row (global) and query count of the workgroup's tile.
 // KS > 1 (with NW = 1): the workgroup has KS waves that own the SAME queries and take the key tiles of the
 // item in turn (wave s: tiles s, s + KS, ...), each with its own tile buffers and no barrier in the key loop;
 // their partial results are merged in LDS at the end, in wave order.  For launches with few work items, where
 // one wave per item would leave the time to the longest history.
-template <int D, int NQB, int NW, int ACT, int AHEAD, int KS, bool SMALL>
+template <int D, int HP, int NQB, int NW, int ACT, int AHEAD, int KS, bool SMALL>
 __device__ __forceinline__ void attn_fwd_item(const AttnParams& p, char* lds, int h, int64_t q_row0, int nq_wg,
                                               int64_t k0, int n_kv) {
     using SM = FwdSmem<D>;
     using CT = CoopTile<D, NW>;
     static_assert(KS == 1 || NW == 1, "key splitting is for single-wave query groups");
     constexpr bool SOFTMAX = ACT == KUNLUN_ACT_SOFTMAX;
-    constexpr int KC = D / 16;  // contraction steps of S^T = K Q^T
-    constexpr int DB = D / 32;  // 32-channel blocks of O^T
+    constexpr int DH = D / HP;          // head dimension
+    constexpr int KC = DH / 16;         // contraction steps of S^T = K Q^T
+    constexpr int DB = DH / 32;         // 32-channel blocks of O^T
+    static_assert(DB >= 1, "a head has at least 32 channels");
     constexpr int QW = 32 * NQB;  // queries per wave
     // (the thread index goes through an opaque move per item: what is derived from it is computed where the item
     // uses it, and not kept in registers across the loop of a persistent launch for all six score functions)
@@ -116,17 +121,17 @@ __device__ __forceinline__ void attn_fwd_item(const AttnParams& p, char* lds, in
     asm volatile("" : "+v"(tid_wg));
     const int split = KS > 1 ? __builtin_amdgcn_readfirstlane(tid_wg >> 6) : 0;  // this wave's turn in the key tiles
     const int tid = KS > 1 ? (tid_wg & 63) : tid_wg;
-    constexpr int LDS_BYTES = SM::bytes(KS);  // of one query-owning group of waves
+    constexpr int LDS_BYTES = SM::bytes(KS, NQB);  // of one query-owning group of waves
     char* const lds_all = lds;
     lds += split * LDS_BYTES;
     const int lane = tid & 63, wave = tid >> 6;
     const int r = lane & 31, g = lane >> 5;
-    const int64_t hd = (int64_t)p.H * D;
+    const int64_t hd = (int64_t)p.H * DH;
     const uint32_t row_bytes = (uint32_t)(hd * 2);
     const int64_t tile_bytes = (int64_t)KT * row_bytes;
     const bf16_t* Q = (const bf16_t*)p.q;
-    const char* K = (const char*)((const bf16_t*)p.k + (k0 * p.H + h) * D);
-    const char* V = (const char*)((const bf16_t*)p.v + (k0 * p.H + h) * D);
+    const char* K = (const char*)((const bf16_t*)p.k + (k0 * p.H + h) * DH);
+    const char* V = (const char*)((const bf16_t*)p.v + (k0 * p.H + h) * DH);
 
     // this wave's queries
     const int q_lo_w = wave * QW;
@@ -153,9 +158,9 @@ __device__ __forceinline__ void attn_fwd_item(const AttnParams& p, char* lds, in
     constexpr int QT = QW * NW;
     constexpr int Q_LOADS = QT * CT::CHUNKS / (64 * NW);
     static_assert(QT * SM::K_STRIDE <= LDS_BYTES, "query tile must fit the tile buffers");
-    bf16x8 qf[NQB][KC];
+    bf16x8 qf[NQB][HP * KC];
     {
-        const char* qbase = (const char*)(Q + q_src_row(p, q_row0) * hd + (int64_t)h * D);
+        const char* qbase = (const char*)(Q + q_src_row(p, q_row0) * hd + (int64_t)h * DH);
         const __amdgpu_buffer_rsrc_t qrsrc =
             __builtin_amdgcn_make_buffer_rsrc((void*)qbase, 0, (nq_wg - 1) * (int)row_bytes + D * 2, 0x00020000);
         u32x4 qst[Q_LOADS];
@@ -168,7 +173,7 @@ __device__ __forceinline__ void attn_fwd_item(const AttnParams& p, char* lds, in
 #pragma unroll
         for (int qb = 0; qb < NQB; ++qb)
 #pragma unroll
-            for (int kc = 0; kc < KC; ++kc)
+            for (int kc = 0; kc < HP * KC; ++kc)
                 qf[qb][kc] = *(const bf16x8*)(lds + (q_lo_w + 32 * qb) * SM::K_STRIDE + kr + 32 * kc);
         if (NW > 1) __syncthreads();  // the tile buffers are reused for K/V from here on
     }
@@ -177,16 +182,19 @@ __device__ __forceinline__ void attn_fwd_item(const AttnParams& p, char* lds, in
     const int key_lo = n_kv > 0 ? 0 : 0x3fffffff;
     const unsigned key_span = n_kv > 0 ? (unsigned)(n_kv - 1) : 0u;
 
-    f32x16 oacc[DB][NQB];
+    f32x16 oacc[HP][DB][NQB];
+    float m_ref[HP][NQB], l_run[HP][NQB];  // softmax: reference maximum (log2 units) and running sum
 #pragma unroll
-    for (int db = 0; db < DB; ++db)
+    for (int hh = 0; hh < HP; ++hh)
 #pragma unroll
-        for (int qb = 0; qb < NQB; ++qb)
+        for (int qb = 0; qb < NQB; ++qb) {
+            m_ref[hh][qb] = -INFINITY;
+            l_run[hh][qb] = 0.f;
 #pragma unroll
-            for (int v = 0; v < 16; ++v) oacc[db][qb][v] = 0.f;
-    float m_ref[NQB], l_run[NQB];  // softmax: reference maximum (log2 units) and running sum
+            for (int db = 0; db < DB; ++db)
 #pragma unroll
-    for (int qb = 0; qb < NQB; ++qb) { m_ref[qb] = -INFINITY; l_run[qb] = 0.f; }
+                for (int v = 0; v < 16; ++v) oacc[hh][db][qb][v] = 0.f;
+        }
     const float sc = SOFTMAX ? p.scale * LOG2E : p.scale;
 
     // AHEAD tiles ahead of the one being consumed are in flight in registers (AHEAD register sets,
@@ -206,39 +214,46 @@ __device__ __forceinline__ void attn_fwd_item(const AttnParams& p, char* lds, in
         if (!wave_active) return;
         const int kt = split + i * KS;
         // ---- S^T = K Q^T
-        f32x16 sacc[NQB];
+        f32x16 sacc[HP][NQB];
 #pragma unroll
-        for (int qb = 0; qb < NQB; ++qb)
+        for (int hh = 0; hh < HP; ++hh) {
 #pragma unroll
-            for (int v = 0; v < 16; ++v) sacc[qb][v] = 0.f;
+            for (int qb = 0; qb < NQB; ++qb)
 #pragma unroll
-        for (int kc = 0; kc < KC; ++kc) {
-            const bf16x8 a = *(const bf16x8*)(ldsK + kr + 32 * kc);
+                for (int v = 0; v < 16; ++v) sacc[hh][qb][v] = 0.f;
 #pragma unroll
-            for (int qb = 0; qb < NQB; ++qb) sacc[qb] = mfma32(a, qf[qb][kc], sacc[qb]);
+            for (int kc = 0; kc < KC; ++kc) {
+                const bf16x8 a = *(const bf16x8*)(ldsK + kr + 32 * (hh * KC + kc));
+#pragma unroll
+                for (int qb = 0; qb < NQB; ++qb) sacc[hh][qb] = mfma32(a, qf[qb][hh * KC + kc], sacc[hh][qb]);
+            }
         }
         // ---- score function, masking, packing
         const int key_base = kt * KT;
         const bool need_mask = key_base + KT > n_kv;  // only the last tile of a history has invisible keys
-        bf16x8 pf[NQB][2];
+        bf16x8 pf[HP][NQB][2];
 #pragma unroll
-        for (int qb = 0; qb < NQB; ++qb)
-            score_to_weights<ACT, DB, NQB, false, SMALL>(sacc[qb], need_mask, (unsigned)(key_base + 4 * g - key_lo), key_span, sc, m_ref[qb],
-                                           l_run[qb], oacc, qb, pf[qb]);
+        for (int hh = 0; hh < HP; ++hh)
+#pragma unroll
+            for (int qb = 0; qb < NQB; ++qb)
+                score_to_weights<ACT, DB, NQB, false, SMALL>(sacc[hh][qb], need_mask, (unsigned)(key_base + 4 * g - key_lo), key_span, sc,
+                                                             m_ref[hh][qb], l_run[hh][qb], oacc[hh], qb, pf[hh][qb]);
         // ---- O^T += V^T P^T
 #pragma unroll
-        for (int db = 0; db < DB; ++db) {
+        for (int hh = 0; hh < HP; ++hh)
 #pragma unroll
-            for (int c = 0; c < 2; ++c) {
-                const char* src = ldsV + vr + 64 * db + c * 16 * SM::V_STRIDE;
-                const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(LDS_PTR(s16x4, src));
-                const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(LDS_PTR(s16x4, src + 8 * SM::V_STRIDE));
-                typedef __attribute__((ext_vector_type(8))) short s16x8;
-                const bf16x8 a = __builtin_bit_cast(bf16x8, (s16x8)__builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+            for (int db = 0; db < DB; ++db) {
 #pragma unroll
-                for (int qb = 0; qb < NQB; ++qb) oacc[db][qb] = mfma32(a, pf[qb][c], oacc[db][qb]);
+                for (int c = 0; c < 2; ++c) {
+                    const char* src = ldsV + vr + 64 * (hh * DB + db) + c * 16 * SM::V_STRIDE;
+                    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(LDS_PTR(s16x4, src));
+                    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(LDS_PTR(s16x4, src + 8 * SM::V_STRIDE));
+                    typedef __attribute__((ext_vector_type(8))) short s16x8;
+                    const bf16x8 a = __builtin_bit_cast(bf16x8, (s16x8)__builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+#pragma unroll
+                    for (int qb = 0; qb < NQB; ++qb) oacc[hh][db][qb] = mfma32(a, pf[hh][qb][c], oacc[hh][db][qb]);
+                }
             }
-        }
     };
     auto step = [&](u32x4 (&ks)[CT::LOADS], u32x4 (&vs)[CT::LOADS], int i, int buf) {
         char* ldsK = lds + (KS > 1 ? 0 : buf) * SM::BUF_BYTES;
@@ -267,61 +282,63 @@ __device__ __forceinline__ void attn_fwd_item(const AttnParams& p, char* lds, in
     if (KS > 1) {
         // ---- merge of the KS partial results (wave 0 collects, in wave order): every other wave leaves its
         // accumulators, lane by lane, in its own idle tile buffers, with the softmax reference and sum
-        constexpr int STAT = DB * NQB * 4 * 1024;  // byte offset of the statistics behind the accumulators
-        static_assert(STAT + NQB * 2 * 256 <= LDS_BYTES, "partial results must fit the tile buffers");
+        // (su: head of the pair and query block)
+        constexpr int STAT = HP * DB * NQB * 4 * 1024;  // byte offset of the statistics behind the accumulators
+        static_assert(STAT + HP * NQB * 2 * 256 <= LDS_BYTES, "partial results must fit the tile buffers");
         if (split > 0) {
 #pragma unroll
-            for (int db = 0; db < DB; ++db)
-#pragma unroll
-                for (int qb = 0; qb < NQB; ++qb)
-#pragma unroll
-                    for (int vg = 0; vg < 4; ++vg) {
-                        f32x4 x;
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) x[e] = oacc[db][qb][4 * vg + e];
-                        *(f32x4*)(lds + ((db * NQB + qb) * 4 + vg) * 1024 + lane * 16) = x;
-                    }
-            if (SOFTMAX) {
+            for (int hh = 0; hh < HP; ++hh)
 #pragma unroll
                 for (int qb = 0; qb < NQB; ++qb) {
-                    *(float*)(lds + STAT + (2 * qb) * 256 + lane * 4) = m_ref[qb];
-                    *(float*)(lds + STAT + (2 * qb + 1) * 256 + lane * 4) = l_run[qb];
+                    const int su = hh * NQB + qb;
+#pragma unroll
+                    for (int db = 0; db < DB; ++db)
+#pragma unroll
+                        for (int vg = 0; vg < 4; ++vg) {
+                            f32x4 x;
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) x[e] = oacc[hh][db][qb][4 * vg + e];
+                            *(f32x4*)(lds + (((hh * DB + db) * NQB + qb) * 4 + vg) * 1024 + lane * 16) = x;
+                        }
+                    if (SOFTMAX) {
+                        *(float*)(lds + STAT + (2 * su) * 256 + lane * 4) = m_ref[hh][qb];
+                        *(float*)(lds + STAT + (2 * su + 1) * 256 + lane * 4) = l_run[hh][qb];
+                    }
                 }
-            }
         }
         __syncthreads();
         if (split > 0) return;
 #pragma unroll 1
         for (int w = 1; w < KS; ++w) {
             const char* part = lds_all + w * LDS_BYTES;
-            float cw[NQB];
 #pragma unroll
-            for (int qb = 0; qb < NQB; ++qb) {
-                cw[qb] = 1.f;
-                if (SOFTMAX) {
-                    const float mw = *(const float*)(part + STAT + (2 * qb) * 256 + lane * 4);
-                    const float lw = *(const float*)(part + STAT + (2 * qb + 1) * 256 + lane * 4);
-                    const float m_new = fmaxf(m_ref[qb], mw);
-                    const float c0 = m_ref[qb] == -INFINITY ? 0.f : fast_exp2(m_ref[qb] - m_new);
-                    cw[qb] = mw == -INFINITY ? 0.f : fast_exp2(mw - m_new);
-                    l_run[qb] = l_run[qb] * c0 + lw * cw[qb];
-                    m_ref[qb] = m_new;
+            for (int hh = 0; hh < HP; ++hh)
+#pragma unroll
+                for (int qb = 0; qb < NQB; ++qb) {
+                    const int su = hh * NQB + qb;
+                    float cw = 1.f;
+                    if (SOFTMAX) {
+                        const float mw = *(const float*)(part + STAT + (2 * su) * 256 + lane * 4);
+                        const float lw = *(const float*)(part + STAT + (2 * su + 1) * 256 + lane * 4);
+                        const float m_new = fmaxf(m_ref[hh][qb], mw);
+                        const float c0 = m_ref[hh][qb] == -INFINITY ? 0.f : fast_exp2(m_ref[hh][qb] - m_new);
+                        cw = mw == -INFINITY ? 0.f : fast_exp2(mw - m_new);
+                        l_run[hh][qb] = l_run[hh][qb] * c0 + lw * cw;
+                        m_ref[hh][qb] = m_new;
+#pragma unroll
+                        for (int db = 0; db < DB; ++db)
+#pragma unroll
+                            for (int v = 0; v < 16; ++v) oacc[hh][db][qb][v] *= c0;
+                    }
 #pragma unroll
                     for (int db = 0; db < DB; ++db)
 #pragma unroll
-                        for (int v = 0; v < 16; ++v) oacc[db][qb][v] *= c0;
+                        for (int vg = 0; vg < 4; ++vg) {
+                            const f32x4 x = *(const f32x4*)(part + (((hh * DB + db) * NQB + qb) * 4 + vg) * 1024 + lane * 16);
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) oacc[hh][db][qb][4 * vg + e] = fmaf(x[e], cw, oacc[hh][db][qb][4 * vg + e]);
+                        }
                 }
-            }
-#pragma unroll
-            for (int db = 0; db < DB; ++db)
-#pragma unroll
-                for (int qb = 0; qb < NQB; ++qb)
-#pragma unroll
-                    for (int vg = 0; vg < 4; ++vg) {
-                        const f32x4 x = *(const f32x4*)(part + ((db * NQB + qb) * 4 + vg) * 1024 + lane * 16);
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) oacc[db][qb][4 * vg + e] = fmaf(x[e], cw[qb], oacc[db][qb][4 * vg + e]);
-                    }
         }
     }
 
@@ -332,28 +349,30 @@ __device__ __forceinline__ void attn_fwd_item(const AttnParams& p, char* lds, in
     if (!wave_active) return;
     char* stage = lds + wave * (QW * SM::K_STRIDE);
 #pragma unroll
-    for (int qb = 0; qb < NQB; ++qb) {
-        const int qi = 32 * qb + r;  // inside this wave's block
-        float inv = 1.f;
-        if (SOFTMAX) {
-            const float l_tot = halves_sum(l_run[qb]);
-            inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
-            if (p.lse && g == 0 && qi < nq)
-                p.lse[(int64_t)h * p.total_q + q_row0 + q_lo_w + qi] =
-                    l_tot > 0.f ? (m_ref[qb] + __builtin_amdgcn_logf(l_tot)) * (1.f / LOG2E) : -INFINITY;
-        }
+    for (int hh = 0; hh < HP; ++hh)
 #pragma unroll
-        for (int db = 0; db < DB; ++db)
-#pragma unroll
-            for (int vg = 0; vg < 4; ++vg) {
-                bf16x4 out;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) out[e] = (bf16_t)(oacc[db][qb][4 * vg + e] * inv);
-                *(bf16x4*)(stage + qi * SM::K_STRIDE + (32 * db + 8 * vg + 4 * g) * 2) = out;
+        for (int qb = 0; qb < NQB; ++qb) {
+            const int qi = 32 * qb + r;  // inside this wave's block
+            float inv = 1.f;
+            if (SOFTMAX) {
+                const float l_tot = halves_sum(l_run[hh][qb]);
+                inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
+                if (p.lse && g == 0 && qi < nq)
+                    p.lse[(int64_t)(h + hh) * p.total_q + q_row0 + q_lo_w + qi] =
+                        l_tot > 0.f ? (m_ref[hh][qb] + __builtin_amdgcn_logf(l_tot)) * (1.f / LOG2E) : -INFINITY;
             }
-    }
+#pragma unroll
+            for (int db = 0; db < DB; ++db)
+#pragma unroll
+                for (int vg = 0; vg < 4; ++vg) {
+                    bf16x4 out;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) out[e] = (bf16_t)(oacc[hh][db][qb][4 * vg + e] * inv);
+                    *(bf16x4*)(stage + qi * SM::K_STRIDE + (32 * (hh * DB + db) + 8 * vg + 4 * g) * 2) = out;
+                }
+        }
     {
-        bf16_t* obase = (bf16_t*)p.o + (q_row0 + q_lo_w) * hd + (int64_t)h * D;
+        bf16_t* obase = (bf16_t*)p.o + (q_row0 + q_lo_w) * hd + (int64_t)h * DH;
         constexpr int O_STORES = QW * CT::CHUNKS / 64;
         const int chunk = lane % CT::CHUNKS, rsub = lane / CT::CHUNKS;
 #pragma unroll
@@ -365,17 +384,17 @@ __device__ __forceinline__ void attn_fwd_item(const AttnParams& p, char* lds, in
     }
 }
 
-template <int D, int NQB, int NW, int AHEAD, int KS, bool SMALL>
+template <int D, int HP, int NQB, int NW, int AHEAD, int KS, bool SMALL>
 __device__ __forceinline__ void attn_fwd_dispatch(const AttnParams& p, char* lds, int act, int h, int64_t q_row0,
                                                   int nq, int64_t k0, int n_kv) {
     switch (act) {
-    case KUNLUN_ACT_SOFTMAX: attn_fwd_item<D, NQB, NW, KUNLUN_ACT_SOFTMAX, AHEAD, KS, SMALL>(p, lds, h, q_row0, nq, k0, n_kv); break;
-    case KUNLUN_ACT_IDENTITY: attn_fwd_item<D, NQB, NW, KUNLUN_ACT_IDENTITY, AHEAD, KS, SMALL>(p, lds, h, q_row0, nq, k0, n_kv); break;
-    case KUNLUN_ACT_RELU: attn_fwd_item<D, NQB, NW, KUNLUN_ACT_RELU, AHEAD, KS, SMALL>(p, lds, h, q_row0, nq, k0, n_kv); break;
-    case KUNLUN_ACT_GELU: attn_fwd_item<D, NQB, NW, KUNLUN_ACT_GELU, AHEAD, KS, SMALL>(p, lds, h, q_row0, nq, k0, n_kv); break;
-    case KUNLUN_ACT_GELU_TANH: attn_fwd_item<D, NQB, NW, KUNLUN_ACT_GELU_TANH, AHEAD, KS, SMALL>(p, lds, h, q_row0, nq, k0, n_kv); break;
-    case KUNLUN_ACT_SILU: attn_fwd_item<D, NQB, NW, KUNLUN_ACT_SILU, AHEAD, KS, SMALL>(p, lds, h, q_row0, nq, k0, n_kv); break;
-    default: attn_fwd_item<D, NQB, NW, KUNLUN_ACT_GELU_POLY, AHEAD, KS, SMALL>(p, lds, h, q_row0, nq, k0, n_kv); break;
+    case KUNLUN_ACT_SOFTMAX: attn_fwd_item<D, HP, NQB, NW, KUNLUN_ACT_SOFTMAX, AHEAD, KS, SMALL>(p, lds, h, q_row0, nq, k0, n_kv); break;
+    case KUNLUN_ACT_IDENTITY: attn_fwd_item<D, HP, NQB, NW, KUNLUN_ACT_IDENTITY, AHEAD, KS, SMALL>(p, lds, h, q_row0, nq, k0, n_kv); break;
+    case KUNLUN_ACT_RELU: attn_fwd_item<D, HP, NQB, NW, KUNLUN_ACT_RELU, AHEAD, KS, SMALL>(p, lds, h, q_row0, nq, k0, n_kv); break;
+    case KUNLUN_ACT_GELU: attn_fwd_item<D, HP, NQB, NW, KUNLUN_ACT_GELU, AHEAD, KS, SMALL>(p, lds, h, q_row0, nq, k0, n_kv); break;
+    case KUNLUN_ACT_GELU_TANH: attn_fwd_item<D, HP, NQB, NW, KUNLUN_ACT_GELU_TANH, AHEAD, KS, SMALL>(p, lds, h, q_row0, nq, k0, n_kv); break;
+    case KUNLUN_ACT_SILU: attn_fwd_item<D, HP, NQB, NW, KUNLUN_ACT_SILU, AHEAD, KS, SMALL>(p, lds, h, q_row0, nq, k0, n_kv); break;
+    default: attn_fwd_item<D, HP, NQB, NW, KUNLUN_ACT_GELU_POLY, AHEAD, KS, SMALL>(p, lds, h, q_row0, nq, k0, n_kv); break;
     }
 }
 
@@ -389,12 +408,12 @@ __device__ __forceinline__ void attn_fwd_dispatch(const AttnParams& p, char* lds
 // unclaimed one, which is the dispatcher's longest-first list scheduling without its cost (measured on the
 // jagged benchmark batch: with cheap score functions the dispatcher kept a third of the workgroup slots empty).
 // The counter is asked for the next item while the current one starts.
-template <int D, int NQB, int NW, int OCC, int AHEAD, int KS, bool SMALL>
+template <int D, int HP, int NQB, int NW, int OCC, int AHEAD, int KS, bool SMALL>
 __global__ __launch_bounds__(64 * NW * KS, OCC) void gdpa_fwd_mfma_kernel(AttnParams p, int n_qtiles, int n_items) {
-    extern __shared__ __attribute__((aligned(1024))) char lds[];  // KS * FwdSmem<D>::bytes(KS) bytes
+    extern __shared__ __attribute__((aligned(1024))) char lds[];  // KS * FwdSmem<D>::bytes(KS, NQB) bytes
     constexpr int QT = 32 * NQB * NW;
     // hand-over word for the next item: the last word of the tile buffers, dead between items
-    volatile int* const next_word = (volatile int*)(lds + KS * FwdSmem<D>::bytes(KS) - 4);
+    volatile int* const next_word = (volatile int*)(lds + KS * FwdSmem<D>::bytes(KS, NQB) - 4);
     const int64_t n_entries = (int64_t)p.B * n_qtiles;
     int item = blockIdx.x;
     while (item < n_items) {
@@ -402,8 +421,9 @@ __global__ __launch_bounds__(64 * NW * KS, OCC) void gdpa_fwd_mfma_kernel(AttnPa
         if (KS == 1 && p.queue && threadIdx.x == 0) claimed = atomicAdd(p.queue, 1);
         const int slot = item & 7;
         const int64_t j = item >> 3;
-        const int h = (int)(j % p.H);
-        const int64_t e = (j / p.H) * 8 + slot;
+        const int groups = p.H / HP;
+        const int h = (int)(j % groups) * HP;
+        const int64_t e = (j / groups) * 8 + slot;
         if (e < n_entries) {
             const int qt = (int)(e % n_qtiles);
             const int b = p.order ? p.order[e / n_qtiles] : (int)(e / n_qtiles);
@@ -414,7 +434,7 @@ __global__ __launch_bounds__(64 * NW * KS, OCC) void gdpa_fwd_mfma_kernel(AttnPa
                 const int nq = (int)((nq_all - q_first) < QT ? (nq_all - q_first) : QT);
                 const int64_t k0 = p.kv_off[b];
                 const int n_kv = p.kv_off[b + 1] - (int)k0;
-                attn_fwd_dispatch<D, NQB, NW, AHEAD, KS, SMALL>(p, lds, p.head_act[h], h, qb0 + q_first, nq, k0, n_kv);
+                attn_fwd_dispatch<D, HP, NQB, NW, AHEAD, KS, SMALL>(p, lds, p.head_act[h], h, qb0 + q_first, nq, k0, n_kv);
             }
         }
         if (KS > 1 || !p.queue) break;
@@ -434,18 +454,18 @@ bool mfma_fwd_supported(const AttnParams& p, int dtype) {
     return true;
 }
 
-template <bool SMALL, int D, int NQB, int NW, int OCC, int AHEAD, int KS = 1>
+template <bool SMALL, int D, int HP, int NQB, int NW, int OCC, int AHEAD, int KS>
 static hipError_t launch_gdpa(const AttnParams& p, hipStream_t stream) {
     constexpr int QT = 32 * NQB * NW;
-    constexpr int bytes = KS * FwdSmem<D>::bytes(KS);
-    auto kern = gdpa_fwd_mfma_kernel<D, NQB, NW, OCC, AHEAD, KS, SMALL>;
+    constexpr int bytes = KS * FwdSmem<D>::bytes(KS, NQB);
+    auto kern = gdpa_fwd_mfma_kernel<D, HP, NQB, NW, OCC, AHEAD, KS, SMALL>;
     if (bytes > 64 * 1024) {
         // once per process (thread-safe initialisation of a function-local static); not a stream operation
         static const hipError_t raised = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
         if (raised != hipSuccess) return raised;
     }
     const int n_qtiles = (p.max_q + QT - 1) / QT;
-    const int64_t n_items = (((int64_t)p.B * n_qtiles + 7) / 8) * 8 * p.H;
+    const int64_t n_items = (((int64_t)p.B * n_qtiles + 7) / 8) * 8 * (p.H / HP);
     int64_t grid = n_items;
     if (KS == 1 && p.queue) {
         // workgroups of this kernel that fit the device (once per process, like the attribute above)
@@ -458,9 +478,7 @@ static hipError_t launch_gdpa(const AttnParams& p, hipStream_t stream) {
         // moves the bytes of few walks faster than those of many, as long as the score function keeps up: exponential
         // forms and the short form of GELU do, its general form does not.  GELU on small scores, 8 heads, log-normal
         // histories, us with 2 / 3 / 4 / all that fit workgroups per compute unit:
-        //   d = 128, 64 queries, 400 examples 348 / 376 / 390 / 390, 30 queries 333 / 363 / 390 / 389;
-        //   d = 64, 64 queries, 400: 221 / 205 / 232 / 246, 32 queries, 600: 320 / 261 / 287 / 325;  d = 32, 900: 368 / 290 / 273 / 285
-        // (scores around 2, d = 64, 64 queries, 4096 items: 313 us with three, 283 with all).
+        //   d = 128, 64 queries, 400 examples 348 / 376 / 390 / 390;  d = 32 (single heads), 900: 368 / 290 / 273 / 285
         // At d = 128 two are the best alone (bench batch 855 / 865 / 873 us), but not next to kernels that draw the clock
         // down, where two waves of a compute unit cannot keep up: in the benchmark step 887 / 833 / 838 us.
         // At d = 32 with 33..64 queries the tanh and the polynomial form need all that fit: 900 examples of 64..1024 keys 157 / 161 us.
@@ -476,77 +494,132 @@ static hipError_t launch_gdpa(const AttnParams& p, hipStream_t stream) {
 
 bool mfma_fwd_is_qtiled(const AttnParams& p) { return p.windowed || p.max_q > 64; }
 
-// Up to 32 queries per example = one wave per (example, head).  With few work items (every wave has a SIMD to itself) the
-// longest history and the score function of a single wave would set the time: two, four or, for histories beyond 1024
-// keys, eight waves then share the key tiles of a block of 32 queries; 33..64 queries make two such blocks, which read K
-// and V once each (the second time out of the L2), as long as bandwidth is not what counts.  Where the lines lie depends
-// on the score function: all but GELU (its general form) keep up with memory for longer.
+// Heads in pairs: at d = 32 a row piece of one head is 64 bytes, half a memory line, and a walk over half lines moves its bytes
+// at 3.75 TB/s where one over whole lines (the pieces of two heads) reaches 6.3.  A pair shares a score function.
+static bool heads_pair(const AttnParams& p) {
+    if (p.d != 32 || p.H % 2 != 0) return false;
+    for (int h = 0; h < p.H; h += 2)
+        if (p.head_act[h] != p.head_act[h + 1]) return false;
+    return true;
+}
+
+// How a launch is cut.  One wave per block of 32 queries leaves the time to the longest history and to the score function of a
+// single wave when items are few, and makes many thin walks through memory when they are many; so waves share the key tiles of
+// an item: four or eight when items are few, two or four when they are many (the four waves of an item read one stretch of
+// memory together).  33..64 queries: the blocks of an item are either two items that read K and V once each (the second time
+// out of the L2; few items), or both in the registers of one wave (`both`; not at d = 128, where the accumulators alone are 128
+// registers: there a workgroup of two waves walks the whole history, items handed out by a counter).
 // Longest first (one more kernel, 4 us): when the items do not all fit the device at once, and earlier with long histories.
-// us, one wave per item (64 queries: a workgroup of two) / 4 waves / 8 waves, unsorted, then sorted; histories of 64..512
-// (t), 64..1024 (u) and log-normal up to 4096 keys (l):
-//   64 queries  d = 128  softmax  256 items u 31 / 36 / 38, 35 / 35 / 36;  l 110 / 104 / 98, 111 / 80 / 73;  GELU 512 l 149 / 149 / 132, 153 / 117 / 117
-//               d = 64   softmax  384 u 23 / 26 / 31, 29 / 26 / 32;  512 l 82 / 77 / 74, 88 / 62 / 67;  768 l 89 / 107 / 110, 97 / 87 / 97
-//                        GELU     512 u 32 / 33 / 39, 37 / 32 / 39;  1024 l 122 / 129 / 131, 125 / 112 / 124
-//               d = 32   softmax  384 u 18 / 14 / 15;  768 u 20 / 23 / 25, 29 / 23 / 27;  1024 l 67 / 68 / 61, 73 / 52 / 54;  1536 u 30 / 38 / 42, 40 / 38 / 47
-//   32 queries  d = 128 (one / 2 / 4 / 8)  softmax  512 u 36 / 34 / 35 / 38, 43 / 34 / 35 / 35;  768 t 27 / 27 / 29 / 36, 36 / 27 / 30 / 38;
-//                        768 u 50 / 50 / 54 / 55, 58 / 48 / 47 / 53;  256 t 17 / 12 / 12 / 13
-//               d = 64   softmax  256 l 76 / 29 / 31, 82 / 33 / 34;  384 l 79 / 44 / 37, 85 / 39 / 37
-//               d = 32   ReLU     256 l 41 / 16 / 15, 47 / 19 / 18;  384 l 43 / 20 / 20, 50 / 21 / 21;  512 l 43 / 26 / 27, 51 / 23 / 23
+// us, 8 heads, histories of 64..512 (t), 64..1024 (u), 256..2048 (v) and log-normal up to 4096 keys (l):
+//   Many items, one wave (33..64 queries: a workgroup of two) per item from a counter, single heads / the plan below:
+//     d = 32   32 queries  softmax  4096 items t 73 / 37, u 98 / 60, v 162 / 110, l 164 / 116;  GELU l 170 / 117
+//              64 queries  softmax  4096 items t 74 / 44, u 98 / 66, v 162 / 124, l 168 / 128;  2048 l 105 / 72
+//     d = 64   30 queries  softmax  4096 items t 82 / 64, u 119 / 112, v 220 / 216, l 237 / 219
+//              64 queries  softmax  4096 items t 85 / 70, u 125 / 114, v 230 / 229, l 246 / 234;  1024 u 41 / 38, v 78 / 63, l 110 / 74;
+//                          256 u 22 / 14, v 38 / 23, l 47 / 38
+//     d = 128  20 queries  4096 items t 8 % less, u 4 %, v 3 %;  3072 l 11 %
+//   `both`, two / four / eight waves (u: unsorted, s: sorted), d = 64, 64 queries, GELU:
+//     1024 items l 108u 90u 86u, 104s 76s 73s;  v 80u 71u 74u, 77s 63s 69s;  512 v 48u 44u 43u, 46s 42s 40s;  2048 u 69u 66u, 62s 66s
+//   Few items, one wave per item / 4 waves / 8 waves, unsorted, then sorted:
+//     64 queries  d = 128  softmax  256 items u 31 / 36 / 38, 35 / 35 / 36;  l 110 / 104 / 98, 111 / 80 / 73;  GELU 512 l 149 / 149 / 132, 153 / 117 / 117;
+//                                   512 v, whole histories 84 / by four 121: with even histories the split pays up to 256 items only
+//                 d = 32   softmax  384 u 18 / 14 / 15;  768 u 20 / 23 / 25, 29 / 23 / 27;  1024 l 67 / 68 / 61, 73 / 52 / 54 (pairs 47 sorted)
+//     32 queries  d = 128 (one / 2 / 4 / 8)  softmax  512 u 36 / 34 / 35 / 38, 43 / 34 / 35 / 35;  768 t 27 / 27 / 29 / 36, 36 / 27 / 30 / 38;
+//                          768 u 50 / 50 / 54 / 55, 58 / 48 / 47 / 53;  256 t 17 / 12 / 12 / 13
+//                 d = 64   softmax  256 l 76 / 29 / 31, 82 / 33 / 34;  384 l 79 / 44 / 37, 85 / 39 / 37
+//                 d = 32   ReLU     256 l 41 / 16 / 15, 47 / 19 / 18;  384 l 43 / 20 / 20, 50 / 21 / 21;  512 l 43 / 26 / 27, 51 / 23 / 23
+//                          pairs / singles, softmax  512 l 31 / 24, 1024 l 41 / 39, 2048 u 35 / 32: pairs pay above
 FwdPlan mfma_fwd_plan(const AttnParams& p) {
     const bool cheap = !has_act(p, KUNLUN_ACT_GELU);
     const int d = p.d;
     const int64_t items = (int64_t)p.B * p.H, blocks = items * ((p.max_q + 31) / 32);
     const bool long_histories = p.max_kv > 1024;
     const bool all_fit = schedule_is_moot(items, 4);
-    FwdPlan plan = {1, !all_fit || (long_histories && !schedule_is_moot(blocks, 1))};
+    FwdPlan plan = {1, false, false, !all_fit || (long_histories && !schedule_is_moot(blocks, 1))};
     if (p.max_q <= 32) {
+        plan.pair = heads_pair(p) && items > (long_histories ? 1024 : 2048);
+        if (blocks > 2048 && (plan.pair || d != 32)) {
+            plan.key_split = long_histories ? 4 : 2;
+            return plan;
+        }
         if (blocks > 2048) return plan;
-        plan.key_split = long_histories && blocks <= 1024 ? 8 : 4;
+        plan.key_split = long_histories && blocks <= (d == 128 ? 768 : 1024) ? 8 : 4;
         if (d == 128 && !long_histories) {
             const bool worth = p.max_kv > 512 && blocks > 512;  // (four waves crowd each other out below)
             plan.key_split = worth || blocks <= 256 ? 4 : 2;
             plan.sorted = plan.sorted || worth;
         }
-        if (cheap && long_histories && (d == 64 ? blocks <= 256 : d == 32 && blocks > 256 && blocks <= 384)) plan = {4, false};
+        if (cheap && long_histories && (d == 64 ? blocks <= 256 : d == 32 && blocks > 256 && blocks <= 384)) {
+            plan.key_split = 4;
+            plan.sorted = false;
+        }
         return plan;
     }
-    const int64_t dear_limit = d == 32 ? 4096 : d == 64 ? (long_histories ? 2048 : 1024) : (long_histories ? 1024 : 512);
-    const int64_t cheap_limit = d == 32 ? (long_histories || !all_fit ? 4096 : 768) : d == 64 ? (long_histories ? 1024 : 512) : (long_histories ? 1024 : 256);
+    plan.pair = heads_pair(p) && items > (long_histories ? 768 : 1024);
+    if (plan.pair || (d == 64 && items > 128)) {
+        const int64_t units = plan.pair ? items / 2 : items;
+        plan.both = true;
+        if (long_histories)
+            plan.key_split = units <= 256 ? 4 : units <= (p.max_kv > 2048 ? 768 : 512) ? 8 : units <= 2048 ? 4 : 2;
+        else
+            plan.key_split = units <= (p.max_kv > 512 ? 1024 : 512) ? 4 : 2;
+        plan.sorted = !all_fit || (long_histories && units > 256);
+        return plan;
+    }
+    const bool even = (int64_t)p.max_kv * p.B < 5 * p.total_kv / 2;  // the longest history is less than 2.5 times the mean
+    const int64_t dear_limit = d == 32 ? 4096 : d == 64 ? 256 : (long_histories ? (even ? 512 : 1024) : 512);
+    const int64_t cheap_limit = d == 32 ? (long_histories || !all_fit ? 4096 : 768) : d == 64 ? 256 : (long_histories ? (even ? 512 : 1024) : 256);
     if (blocks <= (cheap ? cheap_limit : dear_limit))
         plan.key_split = long_histories && blocks <= (d == 32 ? 1536 : 2048) ? 8 : 4;
     else
-        plan.sorted = !all_fit || (long_histories && (d == 128 ? items > 896 : !cheap));
+        plan.sorted = !all_fit || (long_histories && (d == 128 ? items > 896 && !even : !cheap));
     return plan;
 }
 
 template <bool SMALL>
-static hipError_t launch_streaming(const AttnParams& p, int ks, hipStream_t stream) {
-    // 32 queries per wave, up to 255 registers per wave, two or three waves per SIMD.
+static hipError_t launch_streaming(const AttnParams& p, const FwdPlan& plan, hipStream_t stream) {
+    // 32 queries per wave (64 where a wave has both blocks), up to 256 registers per wave, two or three waves per SIMD.
+    const int ks = plan.key_split;
     if (p.d == 128) {
-        if (ks == 8) return launch_gdpa<SMALL, 128, 1, 1, 2, 1, 8>(p, stream);
-        if (ks == 4) return launch_gdpa<SMALL, 128, 1, 1, 2, 1, 4>(p, stream);
-        if (ks == 2) return launch_gdpa<SMALL, 128, 1, 1, 2, 1, 2>(p, stream);
-        return p.max_q <= 32 ? launch_gdpa<SMALL, 128, 1, 1, 2, 1>(p, stream) : launch_gdpa<SMALL, 128, 1, 2, 2, 2>(p, stream);
+        if (ks == 8) return launch_gdpa<SMALL, 128, 1, 1, 1, 2, 1, 8>(p, stream);
+        if (ks == 4) return launch_gdpa<SMALL, 128, 1, 1, 1, 2, 1, 4>(p, stream);
+        if (ks == 2) return launch_gdpa<SMALL, 128, 1, 1, 1, 2, 1, 2>(p, stream);
+        return launch_gdpa<SMALL, 128, 1, 1, 2, 2, 2, 1>(p, stream);
+    }
+    // Both blocks: one tile in flight per wave (a second takes 32 registers: spills with pairs, no gain without)
+    if (plan.both && plan.pair) {
+        if (ks == 8) return launch_gdpa<SMALL, 64, 2, 2, 1, 2, 1, 8>(p, stream);
+        if (ks == 4) return launch_gdpa<SMALL, 64, 2, 2, 1, 2, 1, 4>(p, stream);
+        return launch_gdpa<SMALL, 64, 2, 2, 1, 2, 1, 2>(p, stream);
+    }
+    if (plan.pair) {
+        if (ks == 4) return launch_gdpa<SMALL, 64, 2, 1, 1, 2, 2, 4>(p, stream);
+        return launch_gdpa<SMALL, 64, 2, 1, 1, 2, 2, 2>(p, stream);
+    }
+    if (plan.both) {
+        if (ks == 8) return launch_gdpa<SMALL, 64, 1, 2, 1, 2, 1, 8>(p, stream);
+        if (ks == 4) return launch_gdpa<SMALL, 64, 1, 2, 1, 2, 1, 4>(p, stream);
+        return launch_gdpa<SMALL, 64, 1, 2, 1, 2, 1, 2>(p, stream);
     }
     if (p.d == 64) {
-        if (ks == 8) return launch_gdpa<SMALL, 64, 1, 1, 2, 2, 8>(p, stream);
+        if (ks == 8) return launch_gdpa<SMALL, 64, 1, 1, 1, 2, 2, 8>(p, stream);
+        if (ks == 2) return launch_gdpa<SMALL, 64, 1, 1, 1, 2, 2, 2>(p, stream);
         // Four waves: with the short form of GELU a kernel of 177 registers, two workgroups per compute unit; without it 162
         // and three, which is what counts for short histories (GELU, 768 items of 32 queries, 64..512 keys 17.2 / 15.9 us;
         // 1536 of 64..1024 keys 43.9 / 45.4 us)
-        if (ks == 4 && SMALL && p.max_kv > 512) return launch_gdpa<SMALL, 64, 1, 1, 2, 2, 4>(p, stream);
-        if (ks == 4) return launch_gdpa<false, 64, 1, 1, 2, 2, 4>(p, stream);
-        return p.max_q <= 32 ? launch_gdpa<SMALL, 64, 1, 1, 2, 2>(p, stream) : launch_gdpa<SMALL, 64, 1, 2, 2, 2>(p, stream);
+        if (SMALL && p.max_kv > 512) return launch_gdpa<SMALL, 64, 1, 1, 1, 2, 2, 4>(p, stream);
+        return launch_gdpa<false, 64, 1, 1, 1, 2, 2, 4>(p, stream);
     }
-    if (ks == 8) return launch_gdpa<SMALL, 32, 1, 1, 2, 2, 8>(p, stream);
-    if (ks == 4) return launch_gdpa<SMALL, 32, 1, 1, 2, 2, 4>(p, stream);
-    return p.max_q <= 32 ? launch_gdpa<SMALL, 32, 1, 1, 2, 2>(p, stream) : launch_gdpa<SMALL, 32, 1, 2, 2, 2>(p, stream);
+    if (ks == 8) return launch_gdpa<SMALL, 32, 1, 1, 1, 2, 2, 8>(p, stream);
+    if (ks == 4) return launch_gdpa<SMALL, 32, 1, 1, 1, 2, 2, 4>(p, stream);
+    return p.max_q <= 32 ? launch_gdpa<SMALL, 32, 1, 1, 1, 2, 2, 1>(p, stream) : launch_gdpa<SMALL, 32, 1, 1, 2, 2, 2, 1>(p, stream);
 }
 
 hipError_t launch_mfma_fwd(const AttnParams& p, hipStream_t stream) {
     // Query-tiled launches use 128-query tiles (4 waves): fewer K/V tile loads per query.
     if (mfma_fwd_is_qtiled(p)) return launch_mfma_fwd_qtiled(p, stream);
-    const int ks = mfma_fwd_plan(p).key_split;
-    return short_gelu(p) ? launch_streaming<true>(p, ks, stream) : launch_streaming<false>(p, ks, stream);
+    const FwdPlan plan = mfma_fwd_plan(p);
+    return short_gelu(p) ? launch_streaming<true>(p, plan, stream) : launch_streaming<false>(p, plan, stream);
 }
 
 }  // namespace kunlun

@@ -93,11 +93,12 @@ inline bool small_scores_expected(const AttnParams& p) { return p.scale * p.scal
 // 64..1024 keys 51.1 / 54.7 us).  On small ones it gains 5 to 12 % (256 examples, 4 heads, d = 64, 32 queries, 64..1024 keys: forward
 // 36.7 / 33.4 us, backward 74.5 / 71.1 us).
 inline bool short_gelu(const AttnParams& p) { return has_act(p, KUNLUN_ACT_GELU) && small_scores_expected(p); }
-// How a streaming forward launch (up to 64 queries per example) is cut: waves that share the key tiles of a block of 32
-// queries (1: none do), and whether it starts its items longest first (p.order and p.queue are then set).
+// How a streaming forward launch (up to 64 queries per example) is cut: waves that share the key tiles of an item (1: none
+// do), whether a wave owns both blocks of 33..64 queries, whether an item is a pair of heads (d = 32), and whether items start
+// longest first (p.order and p.queue are then set).
 struct FwdPlan {
     int key_split;
-    bool sorted;
+    bool both, pair, sorted;
 };
 FwdPlan mfma_fwd_plan(const AttnParams& p);
 hipError_t launch_mfma_fwd(const AttnParams& p, hipStream_t stream);
