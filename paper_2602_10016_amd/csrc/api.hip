@@ -36,19 +36,6 @@ int fill_acts(AttnParams& p, int H, int act, const int32_t* head_act, bool& any_
     return KUNLUN_OK;
 }
 
-// Whether a backward launch of up to 64 queries per example starts its items longest first: when they do not all fit the
-// device at once.  That is one, two or three workgroups per compute unit by registers; at d = 32 and 64 the sorting kernel
-// pays up to four per compute unit only with long histories and an eighth more items than fit.  us, sorted / not:
-//   d = 64, 64 queries: softmax, 320 items 64..256 keys 24 / 21, 64..1024 keys 35 / 44; 264 log-normal items 104 / 101;
-//   GELU, 768 log-normal items 134 / 240;  d = 64, 20 queries, softmax: 520 items 64..1024 keys 41 / 40, 1024 items
-//   64..512 keys 41 / 38, log-normal 153 / 180;  d = 32, 64 queries, ReLU: 640 items 64..512 keys 21 / 18, 1024 log-normal 77 / 107
-bool bwd_sorts(int B, int H, int d, int max_q, int max_kv) {
-    const int64_t items = (int64_t)B * H;
-    if (d == 128) return !schedule_is_moot(items, max_q > 32 ? 2 : 1);
-    const int per_cu = d == 64 ? (max_q > 32 ? 1 : 2) : (max_q > 32 ? 2 : 3);
-    return !schedule_is_moot(items, 4) || (max_kv > 512 && !schedule_is_moot(items * 8 / 9, per_cu));
-}
-
 size_t order_bytes(int B) { return align_up((size_t)(B + 1) * sizeof(int32_t), 256); }
 
 // What a backward call cannot do without.  With more than 32 keys or up to 64 queries per example never more for fewer
@@ -331,7 +318,7 @@ int gdpa_bwd_checked(const void* q, const void* k, const void* v, const void* o,
     }
     if (mfma_bwd_supported(p, dtype)) {
         int32_t* order = (int32_t*)((char*)workspace + WS_HEADER_BYTES);
-        if (!bwd_sorts(B, H, d, max_q, max_kv)) {
+        if (!mfma_bwd_plan(p).sorted) {
             p.order = nullptr;
         } else {
             p.order = order;

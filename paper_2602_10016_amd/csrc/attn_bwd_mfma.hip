@@ -42,27 +42,31 @@ __device__ __forceinline__ int r_offset(int row, int chunk) {
     return row * D * 4 + ((chunk ^ (row & (D / 4 - 1))) << 4);
 }
 
-template <int D, int NQB, int NW, int ACT, bool SMALL>
+// HP = 2: the item is a pair of neighbouring heads of D / 2 channels each, whose row pieces are one piece of D channels; a wave
+// takes the two one after the other through the same P / dS tiles.
+template <int D, int HP, int NQB, int NW, int ACT, bool SMALL>
 __device__ __forceinline__ void attn_bwd_item(const AttnParams& p, char* smem, int h, int64_t q_row0, int nq,
                                               int64_t k0, int n_kv) {
     using L = TileLayout<D>;
     using SM = BwdSmem<D, NQB, NW>;
     constexpr bool SOFTMAX = ACT == KUNLUN_ACT_SOFTMAX;
-    constexpr int KC = D / 16;
-    constexpr int DB = D / 32;
+    constexpr int DH = D / HP;  // head dimension
+    constexpr int KC = DH / 16;
+    constexpr int DB = DH / 32;
+    static_assert(DB >= 1, "a head has at least 32 channels");
     constexpr int QROWS = SM::QROWS;
     constexpr int QCH = QROWS / 16;  // 16-query contraction chunks
     int tid = threadIdx.x;
     if (D == 128) asm volatile("" : "+v"(tid));  // opaque per item: nothing derived from it is kept across the persistent loop
     const int lane = tid & 63, wave = tid >> 6;
     const int r = lane & 31, g = lane >> 5;
-    const int64_t hd = (int64_t)p.H * D;
-    const bf16_t* Qg = (const bf16_t*)p.q + q_src_row(p, q_row0) * hd + (int64_t)h * D;
-    const bf16_t* DOg = (const bf16_t*)p.d_o + q_row0 * hd + (int64_t)h * D;
-    const bf16_t* Kg = (const bf16_t*)p.k + (k0 * p.H + h) * D;
-    const bf16_t* Vg = (const bf16_t*)p.v + (k0 * p.H + h) * D;
-    bf16_t* DKg = (bf16_t*)p.dk + (k0 * p.H + h) * D;
-    bf16_t* DVg = (bf16_t*)p.dv + (k0 * p.H + h) * D;
+    const int64_t hd = (int64_t)p.H * DH;
+    const bf16_t* Qg = (const bf16_t*)p.q + q_src_row(p, q_row0) * hd + (int64_t)h * DH;
+    const bf16_t* DOg = (const bf16_t*)p.d_o + q_row0 * hd + (int64_t)h * DH;
+    const bf16_t* Kg = (const bf16_t*)p.k + (k0 * p.H + h) * DH;
+    const bf16_t* Vg = (const bf16_t*)p.v + (k0 * p.H + h) * DH;
+    bf16_t* DKg = (bf16_t*)p.dk + (k0 * p.H + h) * DH;
+    bf16_t* DVg = (bf16_t*)p.dv + (k0 * p.H + h) * DH;
 
     char* ldsQ = smem;
     char* ldsDO = smem + SM::Q_BYTES;
@@ -85,36 +89,40 @@ __device__ __forceinline__ void attn_bwd_item(const AttnParams& p, char* smem, i
         *(u32x4*)(ldsDO + L::u_offset(row, ch * 16)) = dv;
     }
     // softmax statistics of this lane's query columns: lse (log2 units) and delta = <dO, O>
-    float lse2[NQB], delta[NQB];
+    float lse2[HP][NQB], delta[HP][NQB];
 #pragma unroll
-    for (int qb = 0; qb < NQB; ++qb) { lse2[qb] = 0.f; delta[qb] = 0.f; }
+    for (int hh = 0; hh < HP; ++hh)
+#pragma unroll
+        for (int qb = 0; qb < NQB; ++qb) { lse2[hh][qb] = 0.f; delta[hh][qb] = 0.f; }
     if (SOFTMAX) {
-        const bf16_t* Og = (const bf16_t*)p.o + q_row0 * hd + (int64_t)h * D;
+        const bf16_t* Og = (const bf16_t*)p.o + q_row0 * hd + (int64_t)h * DH;
 #pragma unroll
-        for (int qb = 0; qb < NQB; ++qb) {
-            const int qi = 32 * qb + r;
-            if (qi < nq) {
-                lse2[qb] = p.lse[(int64_t)h * p.total_q + q_row0 + qi] * LOG2E_B;
-                float acc = 0.f;
-                for (int c = 0; c < D / 16; ++c) {  // this lane half covers channels g*D/2 ..
-                    const bf16x8 a = *(const bf16x8*)(DOg + qi * hd + g * (D / 2) + c * 8);
-                    const bf16x8 b = *(const bf16x8*)(Og + qi * hd + g * (D / 2) + c * 8);
+        for (int hh = 0; hh < HP; ++hh)
 #pragma unroll
-                    for (int e = 0; e < 8; ++e) acc = fmaf((float)a[e], (float)b[e], acc);
+            for (int qb = 0; qb < NQB; ++qb) {
+                const int qi = 32 * qb + r;
+                if (qi < nq) {
+                    lse2[hh][qb] = p.lse[(int64_t)(h + hh) * p.total_q + q_row0 + qi] * LOG2E_B;
+                    float acc = 0.f;
+                    for (int c = 0; c < DH / 16; ++c) {  // this lane half covers channels g*DH/2 ..
+                        const bf16x8 a = *(const bf16x8*)(DOg + qi * hd + hh * DH + g * (DH / 2) + c * 8);
+                        const bf16x8 b = *(const bf16x8*)(Og + qi * hd + hh * DH + g * (DH / 2) + c * 8);
+#pragma unroll
+                        for (int e = 0; e < 8; ++e) acc = fmaf((float)a[e], (float)b[e], acc);
+                    }
+                    delta[hh][qb] = acc;
+                } else {
+                    lse2[hh][qb] = INFINITY;  // weight exp2(s - inf) = 0
                 }
-                delta[qb] = acc;
-            } else {
-                lse2[qb] = INFINITY;  // weight exp2(s - inf) = 0
+                delta[hh][qb] = halves_sum(delta[hh][qb]);
             }
-            delta[qb] = halves_sum(delta[qb]);
-        }
     }
     if (NW > 1) __syncthreads();
     else __builtin_amdgcn_s_waitcnt(0);
 
-    f32x16 dqacc[DB][NQB];
+    f32x16 dqacc[HP * DB][NQB];  // (channel blocks of the pair's heads, in order)
 #pragma unroll
-    for (int db = 0; db < DB; ++db)
+    for (int db = 0; db < HP * DB; ++db)
 #pragma unroll
         for (int qb = 0; qb < NQB; ++qb)
 #pragma unroll
@@ -133,12 +141,12 @@ __device__ __forceinline__ void attn_bwd_item(const AttnParams& p, char* smem, i
     int uw[L::LOADS];   // the same chunk in a swizzled LDS tile, per load
 #pragma unroll
     for (int i = 0; i < L::LOADS; ++i) uw[i] = L::u_offset(i * L::ROWS_PER_LOAD + rsub, chunk * 16);
-    int rr[KC];         // row fragment (row r, channels 16*kc + 8g ..); rows r + 32*qb add a constant
+    int rr[HP * KC];         // row fragment (row r, channels 16*kc + 8g ..); rows r + 32*qb add a constant
 #pragma unroll
-    for (int kc = 0; kc < KC; ++kc) rr[kc] = L::u_offset(r, (2 * kc + g) * 16);
-    int ktA[DB], ktB[DB], qtA[DB], qtB[DB];
+    for (int kc = 0; kc < HP * KC; ++kc) rr[kc] = L::u_offset(r, (2 * kc + g) * 16);
+    int ktA[HP * DB], ktB[HP * DB], qtA[HP * DB], qtB[HP * DB];
 #pragma unroll
-    for (int db = 0; db < DB; ++db) {
+    for (int db = 0; db < HP * DB; ++db) {
         const int colb = (32 * db + 16 * hi16 + 4 * (s16 & 3)) * 2;
         ktA[db] = L::u_offset(4 * g + (s16 >> 2), colb);          // K^T: keys 16c + 4g + 0..3 (+ 16c rows)
         ktB[db] = L::u_offset(8 + 4 * g + (s16 >> 2), colb);      //      keys 16c + 8 + 4g + 0..3
@@ -187,84 +195,88 @@ __device__ __forceinline__ void attn_bwd_item(const AttnParams& p, char* smem, i
             *(u32x4*)(ldsV + uw[i]) = vst[i];
         }
         if (kt + NW < n_tiles) fetch(kst, vst, kt + NW);
-        // ---- S^T = K Q^T and dP^T = V dO^T
-        f32x16 sacc[NQB], dpacc[NQB];
-#pragma unroll
-        for (int kc = 0; kc < KC; ++kc) {
-            const bf16x8 ka = *(const bf16x8*)(ldsK + rr[kc]);
-            const bf16x8 va = *(const bf16x8*)(ldsV + rr[kc]);
-#pragma unroll
-            for (int qb = 0; qb < NQB; ++qb) {
-                const bf16x8 qf = *(const bf16x8*)(ldsQ + qb * 32 * L::ROW_BYTES + rr[kc]);
-                const bf16x8 df = *(const bf16x8*)(ldsDO + qb * 32 * L::ROW_BYTES + rr[kc]);
-                sacc[qb] = mfma32(ka, qf, kc == 0 ? zero16 : sacc[qb]);
-                dpacc[qb] = mfma32(va, df, kc == 0 ? zero16 : dpacc[qb]);
-            }
-        }
-        // ---- P^T, dS^T in registers; bf16 copies to the P / dS tiles ([query][key])
         const int key_base = kt * KT;
         const bool need_mask = key_base + KT > n_kv;
         const unsigned keys_left = (unsigned)(n_kv - key_base - 4 * g);  // key 8*(v/4) + (v%4) + 4g < n_kv - key_base
-        bf16x8 dsf[NQB][2];
+        bf16x8 pb[HP][QCH], dsb[HP][QCH];  // P and dS with one key per lane
 #pragma unroll
-        for (int qb = 0; qb < NQB; ++qb) {
-            float pv[16], dsv[16];
-            if (SMALL && ACT == KUNLUN_ACT_GELU) {
-                gelu_tile_grad(sacc[qb], dpacc[qb], sc, pv, dsv);
-            } else {
+        for (int hh = 0; hh < HP; ++hh) {
+            // ---- S^T = K Q^T and dP^T = V dO^T
+            f32x16 sacc[NQB], dpacc[NQB];
 #pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    const float s = sacc[qb][v] * sc;
-                    float val, der;
-                    if (SOFTMAX) {
-                        val = fast_exp2(s - lse2[qb]);
-                        dsv[v] = val * (dpacc[qb][v] - delta[qb]) * p.scale;
-                    } else {
-                        act_fast_vd<ACT>(s, val, der);
-                        dsv[v] = dpacc[qb][v] * der * p.scale;
+            for (int kc = 0; kc < KC; ++kc) {
+                const bf16x8 ka = *(const bf16x8*)(ldsK + rr[hh * KC + kc]);
+                const bf16x8 va = *(const bf16x8*)(ldsV + rr[hh * KC + kc]);
+#pragma unroll
+                for (int qb = 0; qb < NQB; ++qb) {
+                    const bf16x8 qf = *(const bf16x8*)(ldsQ + qb * 32 * L::ROW_BYTES + rr[hh * KC + kc]);
+                    const bf16x8 df = *(const bf16x8*)(ldsDO + qb * 32 * L::ROW_BYTES + rr[hh * KC + kc]);
+                    sacc[qb] = mfma32(ka, qf, kc == 0 ? zero16 : sacc[qb]);
+                    dpacc[qb] = mfma32(va, df, kc == 0 ? zero16 : dpacc[qb]);
+                }
+            }
+            // ---- P^T, dS^T in registers; bf16 copies to the P / dS tiles ([query][key])
+            bf16x8 dsf[NQB][2];
+#pragma unroll
+            for (int qb = 0; qb < NQB; ++qb) {
+                float pv[16], dsv[16];
+                if (SMALL && ACT == KUNLUN_ACT_GELU) {
+                    gelu_tile_grad(sacc[qb], dpacc[qb], sc, pv, dsv);
+                } else {
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) {
+                        const float s = sacc[qb][v] * sc;
+                        float val, der;
+                        if (SOFTMAX) {
+                            val = fast_exp2(s - lse2[hh][qb]);
+                            dsv[v] = val * (dpacc[qb][v] - delta[hh][qb]) * p.scale;
+                        } else {
+                            act_fast_vd<ACT>(s, val, der);
+                            dsv[v] = dpacc[qb][v] * der * p.scale;
+                        }
+                        pv[v] = val;
                     }
-                    pv[v] = val;
+                }
+                if (need_mask) {
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) {
+                        const bool ok = (unsigned)(8 * (v >> 2) + (v & 3)) < keys_left;
+                        pv[v] = ok ? pv[v] : 0.f;
+                        dsv[v] = ok ? dsv[v] : 0.f;
+                    }
+                }
+#pragma unroll
+                for (int c = 0; c < 2; ++c)
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) dsf[qb][c][e] = (bf16_t)dsv[8 * c + e];
+                // registers 4*vg .. 4*vg+3 hold keys 8*vg + 4g + 0..3 of query 32*qb + r
+#pragma unroll
+                for (int vg = 0; vg < 4; ++vg) {
+                    bf16x4 pk, dk4;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) { pk[e] = (bf16_t)pv[4 * vg + e]; dk4[e] = (bf16_t)dsv[4 * vg + e]; }
+                    *(bf16x4*)(ldsP + qb * 32 * 64 + pw[vg]) = pk;
+                    *(bf16x4*)(ldsDS + qb * 32 * 64 + pw[vg]) = dk4;
                 }
             }
-            if (need_mask) {
+            // ---- dQ^T += K^T dS^T  (keys in the register order of the C layout)
 #pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    const bool ok = (unsigned)(8 * (v >> 2) + (v & 3)) < keys_left;
-                    pv[v] = ok ? pv[v] : 0.f;
-                    dsv[v] = ok ? dsv[v] : 0.f;
+            for (int db = hh * DB; db < (hh + 1) * DB; ++db) {
+#pragma unroll
+                for (int c = 0; c < 2; ++c) {
+                    const bf16x8 a = tr_read(ldsK + c * 16 * L::ROW_BYTES + ktA[db], ldsK + c * 16 * L::ROW_BYTES + ktB[db]);
+#pragma unroll
+                    for (int qb = 0; qb < NQB; ++qb) dqacc[db][qb] = mfma32(a, dsf[qb][c], dqacc[db][qb]);
                 }
             }
+            // (the next head of the pair overwrites the tiles behind these reads)
 #pragma unroll
-            for (int c = 0; c < 2; ++c)
-#pragma unroll
-                for (int e = 0; e < 8; ++e) dsf[qb][c][e] = (bf16_t)dsv[8 * c + e];
-            // registers 4*vg .. 4*vg+3 hold keys 8*vg + 4g + 0..3 of query 32*qb + r
-#pragma unroll
-            for (int vg = 0; vg < 4; ++vg) {
-                bf16x4 pk, dk4;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) { pk[e] = (bf16_t)pv[4 * vg + e]; dk4[e] = (bf16_t)dsv[4 * vg + e]; }
-                *(bf16x4*)(ldsP + qb * 32 * 64 + pw[vg]) = pk;
-                *(bf16x4*)(ldsDS + qb * 32 * 64 + pw[vg]) = dk4;
-            }
-        }
-        // ---- dQ^T += K^T dS^T  (keys in the register order of the C layout)
-#pragma unroll
-        for (int db = 0; db < DB; ++db) {
-#pragma unroll
-            for (int c = 0; c < 2; ++c) {
-                const bf16x8 a = tr_read(ldsK + c * 16 * L::ROW_BYTES + ktA[db], ldsK + c * 16 * L::ROW_BYTES + ktB[db]);
-#pragma unroll
-                for (int qb = 0; qb < NQB; ++qb) dqacc[db][qb] = mfma32(a, dsf[qb][c], dqacc[db][qb]);
+            for (int j = 0; j < QCH; ++j) {
+                pb[hh][j] = tr_read(ldsP + j * 16 * 64 + ptA, ldsP + j * 16 * 64 + ptB);
+                dsb[hh][j] = tr_read(ldsDS + j * 16 * 64 + ptA, ldsDS + j * 16 * 64 + ptB);
             }
         }
         // ---- dV^T = dO^T P and dK^T = Q^T dS (contraction over queries, natural order)
-        bf16x8 pb[QCH], dsb[QCH];
-#pragma unroll
-        for (int j = 0; j < QCH; ++j) {
-            pb[j] = tr_read(ldsP + j * 16 * 64 + ptA, ldsP + j * 16 * 64 + ptB);
-            dsb[j] = tr_read(ldsDS + j * 16 * 64 + ptA, ldsDS + j * 16 * 64 + ptB);
-        }
         const int rows = (n_kv - key_base) < KT ? (n_kv - key_base) : KT;
         const int out_bytes = (rows - 1) * (int)row_bytes + D * 2;
         char* stage = ldsK;  // K and V tiles are dead from here on
@@ -272,12 +284,12 @@ __device__ __forceinline__ void attn_bwd_item(const AttnParams& p, char* smem, i
         for (int which = 0; which < 2; ++which) {
             const char* src = which == 0 ? ldsDO : ldsQ;
 #pragma unroll
-            for (int db = 0; db < DB; ++db) {
+            for (int db = 0; db < HP * DB; ++db) {
                 f32x16 acc;
 #pragma unroll
                 for (int j = 0; j < QCH; ++j) {
                     const bf16x8 a = tr_read(src + j * 16 * L::ROW_BYTES + qtA[db], src + j * 16 * L::ROW_BYTES + qtB[db]);
-                    acc = mfma32(a, which == 0 ? pb[j] : dsb[j], j == 0 ? zero16 : acc);
+                    acc = mfma32(a, which == 0 ? pb[db / DB][j] : dsb[db / DB][j], j == 0 ? zero16 : acc);
                 }
                 // lane: key r, channels 32*db + 8*vg + 4g + 0..3
 #pragma unroll
@@ -305,7 +317,7 @@ __device__ __forceinline__ void attn_bwd_item(const AttnParams& p, char* smem, i
     {
         char* mine = red + wave * (QROWS * D * 4);
 #pragma unroll
-        for (int db = 0; db < DB; ++db)
+        for (int db = 0; db < HP * DB; ++db)
 #pragma unroll
             for (int qb = 0; qb < NQB; ++qb)
 #pragma unroll
@@ -319,7 +331,7 @@ __device__ __forceinline__ void attn_bwd_item(const AttnParams& p, char* smem, i
     }
     if (NW > 1) __syncthreads();
     else __builtin_amdgcn_s_waitcnt(0);
-    bf16_t* DQg = (bf16_t*)p.dq + q_row0 * hd + (int64_t)h * D;
+    bf16_t* DQg = (bf16_t*)p.dq + q_row0 * hd + (int64_t)h * DH;
     for (int idx = tid; idx < QROWS * (D / 8); idx += 64 * NW) {
         const int row = idx / (D / 8), c8 = idx % (D / 8);
         if (row >= nq) continue;
@@ -348,15 +360,16 @@ __device__ __forceinline__ void attn_bwd_item(const AttnParams& p, char* smem, i
 // persistent loop costs them 50 registers, that is, resident waves (d = 32, 64 queries: 373 -> 451 us).
 // (three workgroups per compute unit at D = 32 with one query block: without the bound the two forms of GELU take 185
 // registers where 168 allow the third; 4096 items of 64..256 keys 52 -> 41 us)
-template <int D, int NQB, int NW, bool SMALL>
+template <int D, int HP, int NQB, int NW, bool SMALL>
 __global__ __launch_bounds__(64 * NW, D == 32 && NQB == 1 ? 3 : 1) void gdpa_bwd_mfma_kernel(AttnParams p, int n_items) {
     extern __shared__ __attribute__((aligned(1024))) char smem[];
     constexpr bool PERSISTENT = D == 128;
     int item = blockIdx.x;
     while (item < n_items) {
         const int64_t j = item >> 3;
-        const int h = (int)(j % p.H);
-        const int64_t e = (j / p.H) * 8 + (item & 7);
+        const int groups = p.H / HP;
+        const int h = (int)(j % groups) * HP;
+        const int64_t e = (j / groups) * 8 + (item & 7);
         if (e < p.B) {
             const int b = p.order ? p.order[e] : (int)e;
             const int64_t q0 = q_begin(p, b);
@@ -365,22 +378,23 @@ __global__ __launch_bounds__(64 * NW, D == 32 && NQB == 1 ? 3 : 1) void gdpa_bwd
             const int n_kv = p.kv_off[b + 1] - (int)k0;
             if (nq <= 0) {
                 // no query sees these keys: their gradients are zero
-                const int64_t hd = (int64_t)p.H * D;
+                constexpr int DH = D / HP;
+                const int64_t hd = (int64_t)p.H * DH;
                 const u32x4 z = {0, 0, 0, 0};
                 for (int idx = threadIdx.x; idx < n_kv * (D / 8); idx += 64 * NW) {
                     const int row = idx / (D / 8), c8 = idx % (D / 8);
-                    *(u32x4*)((bf16_t*)p.dk + (k0 + row) * hd + (int64_t)h * D + c8 * 8) = z;
-                    *(u32x4*)((bf16_t*)p.dv + (k0 + row) * hd + (int64_t)h * D + c8 * 8) = z;
+                    *(u32x4*)((bf16_t*)p.dk + (k0 + row) * hd + (int64_t)h * DH + c8 * 8) = z;
+                    *(u32x4*)((bf16_t*)p.dv + (k0 + row) * hd + (int64_t)h * DH + c8 * 8) = z;
                 }
             } else {
                 switch (p.head_act[h]) {
-                case KUNLUN_ACT_SOFTMAX: attn_bwd_item<D, NQB, NW, KUNLUN_ACT_SOFTMAX, SMALL>(p, smem, h, q0, nq, k0, n_kv); break;
-                case KUNLUN_ACT_IDENTITY: attn_bwd_item<D, NQB, NW, KUNLUN_ACT_IDENTITY, SMALL>(p, smem, h, q0, nq, k0, n_kv); break;
-                case KUNLUN_ACT_RELU: attn_bwd_item<D, NQB, NW, KUNLUN_ACT_RELU, SMALL>(p, smem, h, q0, nq, k0, n_kv); break;
-                case KUNLUN_ACT_GELU: attn_bwd_item<D, NQB, NW, KUNLUN_ACT_GELU, SMALL>(p, smem, h, q0, nq, k0, n_kv); break;
-                case KUNLUN_ACT_GELU_TANH: attn_bwd_item<D, NQB, NW, KUNLUN_ACT_GELU_TANH, SMALL>(p, smem, h, q0, nq, k0, n_kv); break;
-                case KUNLUN_ACT_SILU: attn_bwd_item<D, NQB, NW, KUNLUN_ACT_SILU, SMALL>(p, smem, h, q0, nq, k0, n_kv); break;
-                default: attn_bwd_item<D, NQB, NW, KUNLUN_ACT_GELU_POLY, SMALL>(p, smem, h, q0, nq, k0, n_kv); break;
+                case KUNLUN_ACT_SOFTMAX: attn_bwd_item<D, HP, NQB, NW, KUNLUN_ACT_SOFTMAX, SMALL>(p, smem, h, q0, nq, k0, n_kv); break;
+                case KUNLUN_ACT_IDENTITY: attn_bwd_item<D, HP, NQB, NW, KUNLUN_ACT_IDENTITY, SMALL>(p, smem, h, q0, nq, k0, n_kv); break;
+                case KUNLUN_ACT_RELU: attn_bwd_item<D, HP, NQB, NW, KUNLUN_ACT_RELU, SMALL>(p, smem, h, q0, nq, k0, n_kv); break;
+                case KUNLUN_ACT_GELU: attn_bwd_item<D, HP, NQB, NW, KUNLUN_ACT_GELU, SMALL>(p, smem, h, q0, nq, k0, n_kv); break;
+                case KUNLUN_ACT_GELU_TANH: attn_bwd_item<D, HP, NQB, NW, KUNLUN_ACT_GELU_TANH, SMALL>(p, smem, h, q0, nq, k0, n_kv); break;
+                case KUNLUN_ACT_SILU: attn_bwd_item<D, HP, NQB, NW, KUNLUN_ACT_SILU, SMALL>(p, smem, h, q0, nq, k0, n_kv); break;
+                default: attn_bwd_item<D, HP, NQB, NW, KUNLUN_ACT_GELU_POLY, SMALL>(p, smem, h, q0, nq, k0, n_kv); break;
                 }
             }
         }
@@ -402,11 +416,11 @@ bool mfma_bwd_supported(const AttnParams& p, int dtype) {
 
 size_t mfma_bwd_workspace_tail(int, int, int, int, int64_t) { return 0; }
 
-template <int D, int NQB, int NW, bool SMALL>
+template <int D, int HP, int NQB, int NW, bool SMALL>
 static hipError_t launch_bwd_form(const AttnParams& params, hipStream_t stream) {
     AttnParams p = params;
     constexpr int bytes = BwdSmem<D, NQB, NW>::TOTAL;
-    auto kern = gdpa_bwd_mfma_kernel<D, NQB, NW, SMALL>;
+    auto kern = gdpa_bwd_mfma_kernel<D, HP, NQB, NW, SMALL>;
     if (bytes > 64 * 1024) {
         // raise the kernel's dynamic LDS limit once per process (initialisation of a function-local
         // static is thread-safe; not a stream operation, so a later call under graph capture
@@ -415,33 +429,79 @@ static hipError_t launch_bwd_form(const AttnParams& params, hipStream_t stream) 
             hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
         if (raised != hipSuccess) return raised;
     }
-    const int64_t n_items = (((int64_t)p.B + 7) / 8) * 8 * p.H;
+    const int64_t n_items = (((int64_t)p.B + 7) / 8) * 8 * (p.H / HP);
     const bool persistent = D == 128 && p.queue && n_items >= (p.max_kv > 512 ? 4 : 6) * (int64_t)compute_units();
     if (!persistent) p.queue = nullptr;
     const int64_t grid = persistent ? compute_units() : n_items;
-    // Many long histories at D = 32 with one query block: two workgroups per compute unit move their bytes faster than three
+    // Many long histories at D = 32 with one query block (heads that do not pair): two workgroups per compute unit move their bytes faster than three
     // (the memory system prefers fewer walks); LDS that is not used keeps the third away.  Softmax, 32 queries, 4096
     // log-normal items 335 -> 323 us; 64..1024 keys, 2048 items, 57 us with three, 59 with two.
-    const int lds = D == 32 && NQB == 1 && p.max_kv > 1024 && n_items > 1024 ? 56 * 1024 : bytes;
+    const int lds = D == 32 && NQB == 1 && NW == 4 && p.max_kv > 1024 && n_items > 1024 ? 56 * 1024 : bytes;
     hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(64 * NW), lds, stream, p, (int)n_items);
     return hipGetLastError();
 }
 
-template <int D, int NQB, int NW>
+template <int D, int NQB, int NW, int HP = 1>
 static hipError_t launch_bwd(const AttnParams& p, hipStream_t stream) {
-    return short_gelu(p) ? launch_bwd_form<D, NQB, NW, true>(p, stream) : launch_bwd_form<D, NQB, NW, false>(p, stream);
+    return short_gelu(p) ? launch_bwd_form<D, HP, NQB, NW, true>(p, stream) : launch_bwd_form<D, HP, NQB, NW, false>(p, stream);
+}
+
+// How a launch is cut.  The waves of an item take its key tiles in turn: eight when items are few or long (the longest history
+// then sets the time), fewer when many short ones fill the device.  At d = 32 many items go as pairs of heads: a walk over the
+// 64-byte pieces of one head moves its bytes (two reads, two writes) at 3.1 TB/s, over the 128-byte pieces of two at 4.9.
+// Longest first (one more kernel, 4 us): when the items do not all fit the device at once - one, two or three workgroups per
+// compute unit by registers and LDS - and at d = 32 and 64 only with histories beyond 512 keys and an eighth more items than
+// fit, or from four per compute unit (33..64 queries at d = 64: two).  Pairs above 1024 short items are not sorted, nor many
+// whose longest history is less than 2.5 times the mean.
+// us (u: unsorted, s: sorted), softmax, histories of 64..512 (t), 64..1024 (u), 256..2048 (v) and log-normal up to 4096 keys (l):
+//   d = 32, 32 queries   four / eight waves    256 items u 15u 13u, l 43u 32u;  512 l 55u 52u, 53s 46s;  768 l 64u 61u, 63s 56s
+//                        single heads, four waves / pairs, four / eight   4096 t 84u 73u 89u, u 158s 128u 130u, v 305s 266u 248u, l 322s 267s 268s;
+//                        1024 l 112s 115s 90s;  2048 u 82s 75u 72u, v 159s 144s 144s 136u
+//   d = 32, 60 queries   four / eight waves    256 u 21u 17u, l 66u 44u;  512 l 81u 67u, 70s 48s;  768 l 73s 61s, v 60s 59s;  1536 l 137s 145s
+//   d = 64, 20 queries   four / eight waves    256 l 86u 76u;  512 u 46u 42u, 45s 39s, l 133u 109u, 115s 96s;  1024 l 162s 137s, u 68s 68s;  2048 v 254s 251s
+//                        four / two waves      4096 t 128s 132s, u 228s 240s
+//   d = 64, 60 queries   two / four waves      512 t 36s 35s, u 60s 50s;  768 t 44s 49s, u 65s 70s;  1024 l 208s 163s;  1536 l 225s 235s;  2048 u 151s 171s
+BwdPlan mfma_bwd_plan(const AttnParams& p) {
+    const int64_t items = (int64_t)p.B * p.H;
+    const bool one_block = p.max_q <= 32, long_histories = p.max_kv > 1024;
+    BwdPlan plan = {4, false, false};
+    if (p.d == 128) {
+        plan.sorted = !schedule_is_moot(items, one_block ? 1 : 2);
+        return plan;
+    }
+    int per_cu;  // workgroups that fit a compute unit
+    if (p.d == 32) {
+        plan.pair = one_block && heads_pair(p) && items > (long_histories ? 768 : p.max_kv > 512 ? 1536 : 2048);
+        if (plan.pair) {
+            plan.waves = p.max_kv > 512 ? 8 : 4;
+            plan.sorted = long_histories && !(histories_are_even(p) && items >= 2048);
+            return plan;
+        }
+        if (items <= 256 || (long_histories && items <= 768)) plan.waves = 8;
+        per_cu = plan.waves == 8 ? 1 : one_block ? 3 : 2;
+    } else if (one_block) {
+        if (long_histories || items <= (p.max_kv > 512 ? 1024 : 256)) plan.waves = 8;
+        per_cu = plan.waves == 8 && long_histories ? 1 : 2;
+    } else {
+        if (items > (p.max_kv > 2048 ? 1024 : 512)) plan.waves = 2;
+        plan.sorted = items > 512;
+        per_cu = 1;
+    }
+    plan.sorted |= !schedule_is_moot(items, 4) || (p.max_kv > 512 && !schedule_is_moot(items * 8 / 9, per_cu));
+    return plan;
 }
 
 hipError_t launch_mfma_bwd(const AttnParams& p, void*, hipStream_t stream) {
     const bool one_block = p.max_q <= 32;
+    const BwdPlan plan = mfma_bwd_plan(p);
     if (p.d == 128) return one_block ? launch_bwd<128, 1, 4>(p, stream) : launch_mfma_bwd_pair(p, stream);
-    if (p.d == 32) return one_block ? launch_bwd<32, 1, 4>(p, stream) : launch_bwd<32, 2, 4>(p, stream);
-    // d = 64: two waves per (example, head) keep the LDS footprint small when there are many items;
-    // with few items (less than about two per SIMD) the longest history sets the time, and four
-    // waves walk it twice as fast
-    const bool few_items = (int64_t)p.B * p.H <= 2048;
-    if (few_items) return one_block ? launch_bwd<64, 1, 4>(p, stream) : launch_bwd<64, 2, 4>(p, stream);
-    return one_block ? launch_bwd<64, 1, 2>(p, stream) : launch_bwd<64, 2, 2>(p, stream);
+    if (plan.pair) return plan.waves == 8 ? launch_bwd<64, 1, 8, 2>(p, stream) : launch_bwd<64, 1, 4, 2>(p, stream);
+    if (p.d == 32) {
+        if (plan.waves == 8) return one_block ? launch_bwd<32, 1, 8>(p, stream) : launch_bwd<32, 2, 8>(p, stream);
+        return one_block ? launch_bwd<32, 1, 4>(p, stream) : launch_bwd<32, 2, 4>(p, stream);
+    }
+    if (one_block) return plan.waves == 8 ? launch_bwd<64, 1, 8>(p, stream) : launch_bwd<64, 1, 4>(p, stream);
+    return plan.waves == 4 ? launch_bwd<64, 2, 4>(p, stream) : launch_bwd<64, 2, 2>(p, stream);
 }
 
 }  // namespace kunlun

@@ -494,15 +494,6 @@ static hipError_t launch_gdpa(const AttnParams& p, hipStream_t stream) {
 
 bool mfma_fwd_is_qtiled(const AttnParams& p) { return p.windowed || p.max_q > 64; }
 
-// Heads in pairs: at d = 32 a row piece of one head is 64 bytes, half a memory line, and a walk over half lines moves its bytes
-// at 3.75 TB/s where one over whole lines (the pieces of two heads) reaches 6.3.  A pair shares a score function.
-static bool heads_pair(const AttnParams& p) {
-    if (p.d != 32 || p.H % 2 != 0) return false;
-    for (int h = 0; h < p.H; h += 2)
-        if (p.head_act[h] != p.head_act[h + 1]) return false;
-    return true;
-}
-
 // How a launch is cut.  One wave per block of 32 queries leaves the time to the longest history and to the score function of a
 // single wave when items are few, and makes many thin walks through memory when they are many; so waves share the key tiles of
 // an item: four or eight when items are few, two or four when they are many (the four waves of an item read one stretch of
@@ -511,24 +502,26 @@ static bool heads_pair(const AttnParams& p) {
 // registers: there a workgroup of two waves walks the whole history, items handed out by a counter).
 // Longest first (one more kernel, 4 us): when the items do not all fit the device at once, and earlier with long histories.
 // us, 8 heads, histories of 64..512 (t), 64..1024 (u), 256..2048 (v) and log-normal up to 4096 keys (l):
-//   Many items, one wave (33..64 queries: a workgroup of two) per item from a counter, single heads / the plan below:
-//     d = 32   32 queries  softmax  4096 items t 73 / 37, u 98 / 60, v 162 / 110, l 164 / 116;  GELU l 170 / 117
-//              64 queries  softmax  4096 items t 74 / 44, u 98 / 66, v 162 / 124, l 168 / 128;  2048 l 105 / 72
-//     d = 64   30 queries  softmax  4096 items t 82 / 64, u 119 / 112, v 220 / 216, l 237 / 219
-//              64 queries  softmax  4096 items t 85 / 70, u 125 / 114, v 230 / 229, l 246 / 234;  1024 u 41 / 38, v 78 / 63, l 110 / 74;
-//                          256 u 22 / 14, v 38 / 23, l 47 / 38
-//     d = 128  20 queries  4096 items t 8 % less, u 4 %, v 3 %;  3072 l 11 %
-//   `both`, two / four / eight waves (u: unsorted, s: sorted), d = 64, 64 queries, GELU:
-//     1024 items l 108u 90u 86u, 104s 76s 73s;  v 80u 71u 74u, 77s 63s 69s;  512 v 48u 44u 43u, 46s 42s 40s;  2048 u 69u 66u, 62s 66s
+//   (at d = 32 a walk over the 64-byte pieces of one head, half memory lines, reads 3.75 TB/s; over the pieces of two 6.3)
+//   Many items, softmax: one wave (33..64 queries: a workgroup of two) per item from a counter, single heads / the plan below:
+//     d = 32   32 queries  4096 items t 72 / 37, u 96 / 60, v 162 / 111, l 168 / 116;  2048 l 72 / 64
+//              64 queries  4096 items t 74 / 44, u 97 / 67, v 163 / 124, l 170 / 126;  2048 l 104 / 71
+//     d = 64   32 queries  4096 items t 82 / 64, u 121 / 112, v 221 / 217, l 238 / 221
+//              64 queries  4096 items t 84 / 70, u 126 / 115, v 229 / 224, l 247 / 231;  1024 u 41 / 38, v 79 / 63, l 109 / 74;
+//                          256 u 22 / 14, v 38 / 23, l 47 / 38 (two items per (example, head))
+//     d = 128  20 queries  4096 items t 126 / 117, u 213 / 203, v 410 / 400;  3072 l 342 / 313
+//   `both`, two / four / eight waves, unsorted, then sorted, d = 64, 64 queries:
+//     1024 items l 99 / 87 / 89, 91 / 74 / 77;  v 78 / 70 / 76, 74 / 63 / 72;  512 v 42 / 43 / 44, 42 / 42 / 41, l 67 / 63 / 59, 63 / 52 / 48;
+//     2048 u 67 / 65 / 92, 62 / 67 / 95
 //   Few items, one wave per item / 4 waves / 8 waves, unsorted, then sorted:
 //     64 queries  d = 128  softmax  256 items u 31 / 36 / 38, 35 / 35 / 36;  l 110 / 104 / 98, 111 / 80 / 73;  GELU 512 l 149 / 149 / 132, 153 / 117 / 117;
-//                                   512 v, whole histories 84 / by four 121: with even histories the split pays up to 256 items only
-//                 d = 32   softmax  384 u 18 / 14 / 15;  768 u 20 / 23 / 25, 29 / 23 / 27;  1024 l 67 / 68 / 61, 73 / 52 / 54 (pairs 47 sorted)
+//                                   512 v, whole histories 76 / by four 122, by eight sorted 119: with even histories the split pays up to 256 items only
+//                 d = 32   softmax  384 u 18 / 14 / 15;  768 u 20 / 23 / 25, 29 / 23 / 27;  1024 l 67 / 68 / 61, 73 / 52 / 54 (pairs, sorted, 47)
 //     32 queries  d = 128 (one / 2 / 4 / 8)  softmax  512 u 36 / 34 / 35 / 38, 43 / 34 / 35 / 35;  768 t 27 / 27 / 29 / 36, 36 / 27 / 30 / 38;
 //                          768 u 50 / 50 / 54 / 55, 58 / 48 / 47 / 53;  256 t 17 / 12 / 12 / 13
 //                 d = 64   softmax  256 l 76 / 29 / 31, 82 / 33 / 34;  384 l 79 / 44 / 37, 85 / 39 / 37
 //                 d = 32   ReLU     256 l 41 / 16 / 15, 47 / 19 / 18;  384 l 43 / 20 / 20, 50 / 21 / 21;  512 l 43 / 26 / 27, 51 / 23 / 23
-//                          pairs / singles, softmax  512 l 31 / 24, 1024 l 41 / 39, 2048 u 35 / 32: pairs pay above
+//                          pairs / singles, softmax  512 l 32 / 26, 1024 l 43 / 41, 2048 u 34 / 32: pairs pay above
 FwdPlan mfma_fwd_plan(const AttnParams& p) {
     const bool cheap = !has_act(p, KUNLUN_ACT_GELU);
     const int d = p.d;
@@ -566,7 +559,7 @@ FwdPlan mfma_fwd_plan(const AttnParams& p) {
         plan.sorted = !all_fit || (long_histories && units > 256);
         return plan;
     }
-    const bool even = (int64_t)p.max_kv * p.B < 5 * p.total_kv / 2;  // the longest history is less than 2.5 times the mean
+    const bool even = histories_are_even(p);
     const int64_t dear_limit = d == 32 ? 4096 : d == 64 ? 256 : (long_histories ? (even ? 512 : 1024) : 512);
     const int64_t cheap_limit = d == 32 ? (long_histories || !all_fit ? 4096 : 768) : d == 64 ? 256 : (long_histories ? (even ? 512 : 1024) : 256);
     if (blocks <= (cheap ? cheap_limit : dear_limit))

@@ -93,6 +93,16 @@ inline bool small_scores_expected(const AttnParams& p) { return p.scale * p.scal
 // 64..1024 keys 51.1 / 54.7 us).  On small ones it gains 5 to 12 % (256 examples, 4 heads, d = 64, 32 queries, 64..1024 keys: forward
 // 36.7 / 33.4 us, backward 74.5 / 71.1 us).
 inline bool short_gelu(const AttnParams& p) { return has_act(p, KUNLUN_ACT_GELU) && small_scores_expected(p); }
+// Whether the heads can go in pairs through one launch (d = 32: the row pieces of two neighbouring heads are one memory line of
+// 128 bytes): the two of a pair share a score function.
+inline bool heads_pair(const AttnParams& p) {
+    if (p.d != 32 || p.H % 2 != 0) return false;
+    for (int h = 0; h < p.H; h += 2)
+        if (p.head_act[h] != p.head_act[h + 1]) return false;
+    return true;
+}
+// The longest history is less than 2.5 times the mean (uniform lengths: up to 2; log-normal ones: 3.7).
+inline bool histories_are_even(const AttnParams& p) { return (int64_t)p.max_kv * p.B < 5 * p.total_kv / 2; }
 // How a streaming forward launch (up to 64 queries per example) is cut: waves that share the key tiles of an item (1: none
 // do), whether a wave owns both blocks of 33..64 queries, whether an item is a pair of heads (d = 32), and whether items start
 // longest first (p.order and p.queue are then set).
@@ -112,6 +122,13 @@ hipError_t launch_mfma_fwd_qtiled(const AttnParams& p, hipStream_t stream);
 bool swa_band_applies(const AttnParams& p);
 hipError_t launch_swa_band_fwd(const AttnParams& p, hipStream_t stream);
 bool mfma_bwd_supported(const AttnParams& p, int dtype);
+// How a backward launch of up to 64 queries per example is cut: waves per item (d = 128: always four), whether an item is a
+// pair of heads (d = 32), and whether items start longest first (p.order and p.queue are then set).
+struct BwdPlan {
+    int waves;
+    bool pair, sorted;
+};
+BwdPlan mfma_bwd_plan(const AttnParams& p);
 hipError_t launch_mfma_bwd(const AttnParams& p, void* workspace_tail, hipStream_t stream);
 size_t mfma_bwd_workspace_tail(int B, int H, int d, int max_q, int64_t total_q);
 // d = 128 with 33..64 queries per example: wave pairs share each key tile (two workgroups per compute unit).
