@@ -84,18 +84,19 @@ __device__ __forceinline__ bf16x8 tr_pair(const char* a, const char* b) {
     return __builtin_bit_cast(bf16x8, (s16x8)__builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
 }
 
-// LDS of both passes: a ring of three stages; the prologue stages the workgroup's own 128 rows
-// (4 tiles, K-tile swizzle) in the end of the ring, and the epilogue transposes the results
+// LDS of both passes: a ring of stages; the prologue stages the workgroup's own 32 NW rows
+// (NW tiles, K-tile swizzle) in the end of the ring, and the epilogue transposes the results
 // through padded rows.
-template <int D, int STAGE_EXTRA>
+template <int D, int STAGE_EXTRA, int NW>
 struct TiledSmem {
+    static constexpr int STAGES = NW == 2 ? 2 : 3;  // (four workgroups of two waves fit a compute unit with two)
     using PT = PadTiles<D>;
     static constexpr int TILE = KT * D * 2;
     static constexpr int STAGE = 2 * TILE + STAGE_EXTRA;
-    static constexpr int TOTAL = 3 * STAGE;
-    static constexpr int OWN_BYTES = 4 * TILE;
+    static constexpr int TOTAL = STAGES * STAGE;
+    static constexpr int OWN_BYTES = NW * TILE;
     static_assert(TOTAL - OWN_BYTES >= STAGE, "the staged rows must leave the first stage free");
-    static_assert(4 * PT::ROW_TILE <= TOTAL, "output staging must fit");
+    static_assert(NW * PT::ROW_TILE <= TOTAL, "output staging must fit");
 };
 
 // Per-lane LDS read offsets inside a tile in the two-way swizzle.
@@ -136,10 +137,9 @@ __device__ __forceinline__ void bwd_dq_item(const AttnParams& p, float* __restri
                                             int64_t q_row0, int nq_wg, int64_t t0_wg, int64_t k0, int n_kv) {
     using PT = PadTiles<D>;
     using L = TileLayout<D>;
-    using SM = TiledSmem<D, 0>;
+    using SM = TiledSmem<D, 0, NW>;
     constexpr bool SOFTMAX = ACT == KUNLUN_ACT_SOFTMAX;
     constexpr int KC = D / 16, DB = D / 32;
-    static_assert(NW == 4, "four waves of 32 queries");
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int r = lane & 31, g = lane >> 5;
@@ -223,7 +223,7 @@ __device__ __forceinline__ void bwd_dq_item(const AttnParams& p, float* __restri
         }
         __syncthreads();
     }
-    if (n_steps > 1) issue(kt_begin + 1, 1);
+    if (SM::STAGES > 2 && n_steps > 1) issue(kt_begin + 1, 1);
     int key_lo;
     unsigned key_span;
     {
@@ -252,13 +252,13 @@ __device__ __forceinline__ void bwd_dq_item(const AttnParams& p, float* __restri
     for (int i = 0; i < n_steps; ++i) {
         // the loads above were issued before the lse / delta loads that the compiler tracks, so
         // its own waits can only be stricter than needed
-        if (i + 1 < n_steps) wait_vmcnt<LOADS_PER_TILE>();
+        if (SM::STAGES > 2 && i + 1 < n_steps) wait_vmcnt<LOADS_PER_TILE>();
         else wait_vmcnt<0>();
         __syncthreads();  // tile i complete; every wave is done with the stage of tile i-1
-        if (i + 2 < n_steps) issue(kt_begin + i + 2, stage == 0 ? 2 : stage - 1);
+        if (i + SM::STAGES - 1 < n_steps) issue(kt_begin + i + SM::STAGES - 1, stage == 0 ? SM::STAGES - 1 : stage - 1);
         const char* ldsK = lds + stage * SM::STAGE;
         const char* ldsV = ldsK + SM::TILE;
-        stage = stage == 2 ? 0 : stage + 1;
+        stage = stage == SM::STAGES - 1 ? 0 : stage + 1;
         const int kt = kt_begin + i;
         if (!wave_active || kt < w_begin || kt >= w_end) continue;
         f32x16 sacc, dpacc;
@@ -323,7 +323,7 @@ __device__ __forceinline__ void bwd_dkdv_item(const AttnParams& p, const float* 
                                               int64_t k_row0, int nk_wg, int kpos0_wg, int64_t q0, int nq_all) {
     using PT = PadTiles<D>;
     using L = TileLayout<D>;
-    using SM = TiledSmem<D, STATS_BYTES>;
+    using SM = TiledSmem<D, STATS_BYTES, NW>;
     constexpr bool SOFTMAX = ACT == KUNLUN_ACT_SOFTMAX;
     constexpr int KC = D / 16, DB = D / 32;
     // At d = 128 the accumulators (128 registers) and the K^T, V^T fragments (64) leave too little
@@ -331,7 +331,6 @@ __device__ __forceinline__ void bwd_dkdv_item(const AttnParams& p, const float* 
     // loads inside the loop, and the compiler waits for those together with the tile loads in flight.  The last K_LDS
     // K^T fragments of every wave are parked in LDS instead, lane by lane, behind the ring.
     constexpr int K_LDS = D == 128 ? 3 : 0, K_REG = KC - K_LDS;
-    static_assert(NW == 4, "four waves of 32 keys");
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int r = lane & 31, g = lane >> 5;
@@ -409,7 +408,7 @@ __device__ __forceinline__ void bwd_dkdv_item(const AttnParams& p, const float* 
         for (int kc = 0; kc < KC; ++kc) vf[kc] = *(const bf16x8*)(own + wave * SM::TILE + L::k_offset(r, 2 * kc + g));
         __syncthreads();
     }
-    if (n_steps > 1) issue(qt_begin + 1, 1);
+    if (SM::STAGES > 2 && n_steps > 1) issue(qt_begin + 1, 1);
 
     // queries that see this lane's key: q_lo .. q_lo + q_span (empty for padding lanes)
     int q_lo;
@@ -437,16 +436,16 @@ __device__ __forceinline__ void bwd_dkdv_item(const AttnParams& p, const float* 
 
     int stage = 0;
     for (int i = 0; i < n_steps; ++i) {
-        if (i + 1 < n_steps) wait_vmcnt<LOADS_PER_TILE>();
+        if (SM::STAGES > 2 && i + 1 < n_steps) wait_vmcnt<LOADS_PER_TILE>();
         else wait_vmcnt<0>();
         __syncthreads();  // tile i complete; every wave is done with the stage of tile i-1
         const char* ldsQ = lds + stage * SM::STAGE;
         const char* ldsDO = ldsQ + SM::TILE;
         const float* stats = (const float*)(ldsDO + SM::TILE);
-        const int free_stage = stage == 0 ? 2 : stage - 1;
-        stage = stage == 2 ? 0 : stage + 1;
+        const int free_stage = stage == 0 ? SM::STAGES - 1 : stage - 1;
+        stage = stage == SM::STAGES - 1 ? 0 : stage + 1;
         const int qt = qt_begin + i;
-        if (i + 2 < n_steps) issue(qt_begin + i + 2, free_stage);
+        if (i + SM::STAGES - 1 < n_steps) issue(qt_begin + i + SM::STAGES - 1, free_stage);
         if (!wave_active || qt < w_begin || qt >= w_end) continue;
         // S = Q K^T and dP = dO V^T: lane = key column, registers = queries of the tile
         const f32x16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
@@ -537,20 +536,28 @@ __device__ __forceinline__ void bwd_dkdv_item(const AttnParams& p, const float* 
 // ------------------------------------------------------------------ kernels
 
 
-// work mapping of tile_map.h in both passes
+// work mapping of tile_map.h in both passes; PARTS workgroups share a tile of the mapping, next to each other on one XCD
+template <int PARTS>
+__device__ __forceinline__ bool locate_part(const int32_t* __restrict__ tile_start, const int32_t* __restrict__ tile_example, int B, int H,
+                                            int& b, int& h, int& t) {
+    const unsigned slot = blockIdx.x >> 3;
+    if (!locate_tile(tile_start, tile_example, B, H, (slot / PARTS) * 8 + (blockIdx.x & 7), b, h, t)) return false;
+    t = t * PARTS + (int)(slot % PARTS);
+    return true;
+}
 template <int D, int NW, bool WINDOWED>
 __global__ __launch_bounds__(64 * NW, D == 128 ? 2 : 3) void bwd_dq_kernel(AttnParams p, const int32_t* __restrict__ tile_start,
-                                                            const int32_t* __restrict__ tile_example, int runs,
+                                                            const int32_t* __restrict__ tile_example,
                                                             float* __restrict__ delta_ws) {
-    __shared__ __attribute__((aligned(1024))) char lds[TiledSmem<D, 0>::TOTAL];
-    static_assert(32 * NW == TILE_ROWS, "tile size of the work mapping");
+    __shared__ __attribute__((aligned(1024))) char lds[TiledSmem<D, 0, NW>::TOTAL];
     int b, h, qt;
-    if (!locate_tile(tile_start, tile_example, p.B, p.H, runs, b, h, qt)) return;
+    if (!locate_part<TILE_ROWS / (32 * NW)>(tile_start, tile_example, p.B, p.H, b, h, qt)) return;
     const int64_t k0 = p.kv_off[b];
     const int n_kv = p.kv_off[b + 1] - (int)k0;
     const int64_t q0 = q_begin(p, b);
     const int nq_all = (int)(q_end(p, b) - q0);
     const int q_first = qt * 32 * NW;
+    if (q_first >= nq_all) return;
     const int nq = (nq_all - q_first) < 32 * NW ? (nq_all - q_first) : 32 * NW;
     if (WINDOWED) {
         bwd_dq_item<D, NW, KUNLUN_ACT_SOFTMAX, true>(p, delta_ws, lds, h, q0 + q_first, nq, q_first, k0, n_kv);
@@ -561,16 +568,17 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 2 : 3) void bwd_dq_kernel(AttnP
 
 template <int D, int NW, bool WINDOWED>
 __global__ __launch_bounds__(64 * NW, D == 128 ? 2 : 3) void bwd_dkdv_kernel(AttnParams p, const int32_t* __restrict__ tile_start,
-                                                              const int32_t* __restrict__ tile_example, int runs,
+                                                              const int32_t* __restrict__ tile_example,
                                                               const float* __restrict__ delta_ws) {
-    __shared__ __attribute__((aligned(1024))) char lds[TiledSmem<D, STATS_BYTES>::TOTAL + (D == 128 ? 3 : 0) * NW * 1024];
+    __shared__ __attribute__((aligned(1024))) char lds[TiledSmem<D, STATS_BYTES, NW>::TOTAL + (D == 128 ? 3 : 0) * NW * 1024];
     int b, h, kt;
-    if (!locate_tile(tile_start, tile_example, p.B, p.H, runs, b, h, kt)) return;
+    if (!locate_part<TILE_ROWS / (32 * NW)>(tile_start, tile_example, p.B, p.H, b, h, kt)) return;
     const int64_t k0 = p.kv_off[b];
     const int n_kv = p.kv_off[b + 1] - (int)k0;
     const int64_t q0 = q_begin(p, b);
     const int nq_all = (int)(q_end(p, b) - q0);
     const int k_first = kt * 32 * NW;
+    if (k_first >= n_kv) return;
     const int nk = (n_kv - k_first) < 32 * NW ? (n_kv - k_first) : 32 * NW;
     if (WINDOWED) {
         bwd_dkdv_item<D, NW, KUNLUN_ACT_SOFTMAX, true>(p, delta_ws, lds, h, k0 + k_first, nk, k_first, q0, nq_all);
@@ -856,7 +864,7 @@ __global__ __launch_bounds__(256, 2) void bwd_fewkeys_kernel(AttnParams p, const
                                                           int chunk_rows) {
     extern __shared__ __attribute__((aligned(1024))) char fk_lds[];
     int b, h, qt;
-    if (!locate_tile(tile_start, tile_example, p.B, p.H, 1, b, h, qt)) return;
+    if (!locate_tile(tile_start, tile_example, p.B, p.H, blockIdx.x, b, h, qt)) return;
     const int64_t k0 = p.kv_off[b];
     int n_kv = p.kv_off[b + 1] - (int)k0;
     n_kv = n_kv > KT ? KT : n_kv;  // the launch condition (max_kv <= 32) promises this; never read past the tile
@@ -901,27 +909,37 @@ size_t mfma_bwd_tiled_workspace(int B, int H, int d, int max_q, int max_kv, int6
            (fewkeys_applies(d, max_q, max_kv, windowed) ? fewkeys_partial_bytes(B, H, d, total_q) : 0);
 }
 
-template <int D, bool WINDOWED>
-static hipError_t launch_tiled(const AttnParams& p, char* ws, bool any_softmax, hipStream_t stream) {
-    constexpr int NW = 4;
+template <int D, bool WINDOWED, int NW>
+static hipError_t launch_passes(const AttnParams& p, char* ws, bool any_softmax, hipStream_t stream) {
     int32_t* q_tiles = (int32_t*)ws;
     int32_t* k_tiles = (int32_t*)(ws + tile_table_bytes(p.B, p.total_q));
     float* delta = (float*)(ws + tile_table_bytes(p.B, p.total_q) + tile_table_bytes(p.B, p.total_kv));
-    const int runs = tile_runs(WINDOWED, p.left, p.right, p.H);
     (void)any_softmax;  // pass A computes delta of its softmax heads itself and leaves it in the workspace for pass B
     if (p.total_q > 0) {
         hipLaunchKernelGGL(tile_prefix_kernel<1>, dim3(1), dim3(1024), 0, stream, p.q_off, p.max_q, p.B, q_tiles,
                            tile_example_of(q_tiles, p.B), TILE_ROWS);
-        hipLaunchKernelGGL((bwd_dq_kernel<D, NW, WINDOWED>), dim3(tile_grid(p.B, p.H, p.total_q, runs)), dim3(64 * NW), 0,
-                           stream, p, q_tiles, tile_example_of(q_tiles, p.B), runs, delta);
+        hipLaunchKernelGGL((bwd_dq_kernel<D, NW, WINDOWED>), dim3(tile_grid(p.B, p.H, p.total_q) * (TILE_ROWS / (32 * NW))), dim3(64 * NW), 0,
+                           stream, p, q_tiles, tile_example_of(q_tiles, p.B), delta);
     }
     if (p.total_kv > 0) {
         hipLaunchKernelGGL(tile_prefix_kernel<1>, dim3(1), dim3(1024), 0, stream, p.kv_off, 0, p.B, k_tiles,
                            tile_example_of(k_tiles, p.B), TILE_ROWS);
-        hipLaunchKernelGGL((bwd_dkdv_kernel<D, NW, WINDOWED>), dim3(tile_grid(p.B, p.H, p.total_kv, runs)), dim3(64 * NW), 0,
-                           stream, p, k_tiles, tile_example_of(k_tiles, p.B), runs, delta);
+        hipLaunchKernelGGL((bwd_dkdv_kernel<D, NW, WINDOWED>), dim3(tile_grid(p.B, p.H, p.total_kv) * (TILE_ROWS / (32 * NW))), dim3(64 * NW), 0,
+                           stream, p, k_tiles, tile_example_of(k_tiles, p.B), delta);
     }
     return hipGetLastError();
+}
+
+template <int D, bool WINDOWED>
+static hipError_t launch_tiled(const AttnParams& p, char* ws, bool any_softmax, hipStream_t stream) {
+    // Narrow windows: workgroups of two waves (64 rows) and a ring of two stages, four instead of two workgroups per compute
+    // unit - fewer steps in which a wave of the workgroup is outside its own window (previous 256: a tenth instead of a
+    // quarter), for more tile loads per row, which is what counts in wide windows.  Training step, us, four / two waves:
+    // d = 128, previous 256: 635 / 623, previous 64: 505 / 503, 500 to both sides: 693 / 714;  d = 64, previous 256: 348 / 340,
+    // 50 to both sides: 570 / 560;  d = 32, previous 256: 434 / 433 (a tile is two load instructions there)
+    if constexpr (WINDOWED && D > 32)
+        if (p.left >= 0 && p.right >= 0 && (int64_t)p.left + p.right < 384) return launch_passes<D, WINDOWED, 2>(p, ws, any_softmax, stream);
+    return launch_passes<D, WINDOWED, 4>(p, ws, any_softmax, stream);
 }
 
 template <int D>

@@ -433,7 +433,7 @@ __global__ __launch_bounds__(512, 2) void gdpa_bwd_wide_range_kernel(AttnParams 
                                                                      float* __restrict__ partial, int part_floats) {
     extern __shared__ __attribute__((aligned(1024))) char smem[];
     int b, h, t;
-    if (!locate_tile(tile_start, tile_example, p.B, p.H, 1, b, h, t)) return;
+    if (!locate_tile(tile_start, tile_example, p.B, p.H, blockIdx.x, b, h, t)) return;
     const int64_t q0 = q_begin(p, b);
     const int nq = (int)(q_end(p, b) - q0);
     const int64_t k0 = p.kv_off[b];

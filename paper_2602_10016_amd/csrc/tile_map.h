@@ -5,10 +5,10 @@
 // example, then tile, then head.  tile_start[b] = number of tiles before example b and
 // tile_example[t] = example of tile t (both written by the prefix kernel), so a workgroup finds
 // its item with two dependent loads.
-// An XCD's range is further cut into `runs` contiguous runs that are issued round-robin:
-// workgroups that follow each other in a run start `runs` slots apart, so that the next tile of
-// an (example, head) starts when its predecessor is about one tile width into its window and
-// both read the rows they share at about the same time.
+// Inside its range an XCD takes the items in order: a tile and its successor, H items further on, run side by side.  (Starting a
+// tile when its predecessor is one tile width into its window, so that both read the rows they share at the same time, costs
+// up to 8 %: sliding-window forward, 128 sequences of 256..2048, 4 heads, d = 128, previous 64: in order 120 us, 32 slots
+// apart 131; 512 log-normal sequences, 8 heads, previous 64: 875 / 948, 255 to both sides 1656 / 1689.)
 #pragma once
 #include "common.h"
 
@@ -24,31 +24,19 @@ inline int32_t* tile_example_of(int32_t* tile_start, int B) {
     return (int32_t*)((char*)tile_start + align_up((size_t)(B + 1) * sizeof(int32_t), 256));
 }
 // grid size (an upper bound of the tile count sizes it; surplus workgroups exit at once)
-inline unsigned tile_grid(int B, int H, int64_t total_rows, int runs) {
+inline unsigned tile_grid(int B, int H, int64_t total_rows) {
     const int64_t per_xcd = ((total_rows / TILE_ROWS + B) * H + 7) / 8;
-    return (unsigned)((per_xcd + runs) * 8);
+    return (unsigned)((per_xcd + 1) * 8);
 }
-// Stagger for a window of finite reach: a tile shares rows with (reach / tile) neighbours on
-// each side; with about 96 workgroups resident per XCD, the next tile of an (example, head) -
-// H items further in item order - should start 96 / (neighbours + 1) slots later.
-inline int tile_runs(bool windowed, int left, int right, int H) {
-    if (!windowed || left < 0 || right < 0) return 1;
-    const int64_t span_tiles = ((int64_t)left + right + TILE_ROWS - 1) / TILE_ROWS + 1;
-    const int64_t want = 96 / span_tiles / H;
-    return (int)(want < 1 ? 1 : (want > 32 ? 32 : want));
-}
-
 #ifdef __HIPCC__
 __device__ __forceinline__ bool locate_tile(const int32_t* __restrict__ tile_start,
-                                            const int32_t* __restrict__ tile_example, int B, int H, int runs, int& b,
-                                            int& h, int& t) {
+                                            const int32_t* __restrict__ tile_example, int B, int H, unsigned block,
+                                            int& b, int& h, int& t) {
     const int64_t n_items = (int64_t)tile_start[B] * H;
     const int64_t per_xcd = (n_items + 7) / 8;
-    const int xcd = blockIdx.x & 7;
-    const int64_t slot = blockIdx.x >> 3;
-    const int64_t run_len = (per_xcd + runs - 1) / runs;
-    const int64_t in_xcd = (slot % runs) * run_len + slot / runs;
-    if (slot >= run_len * runs || in_xcd >= per_xcd) return false;
+    const int xcd = block & 7;
+    const int64_t in_xcd = block >> 3;
+    if (in_xcd >= per_xcd) return false;
     const int64_t item = xcd * per_xcd + in_xcd;
     if (item >= n_items) return false;
     const int tile = (int)(item / H);
