@@ -1,4 +1,5 @@
-"""Thin ctypes binding of libkunlun.so: argument marshalling only.
+"""Thin binding of libkunlun.so: argument marshalling only, through ctypes; the entry points hand the accepted case of a
+call to the native module _torch_call first (csrc/torch_call.cpp): 10.0 -> 4.3 us for a call whose kernel takes 4.
 
 torch is used for device memory and the current HIP stream; every step of the operators
 runs in the library's kernels.  Importing this module fails loudly when the library has not
@@ -12,10 +13,13 @@ import torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libkunlun.so")
-if not os.path.exists(LIB_PATH):
-    raise ImportError(f"{LIB_PATH} is missing: build it first (python paper_2602_10016_amd/build.py). "
-                      "There is no fallback implementation.")
+for _path in (LIB_PATH, os.path.join(_HERE, "_torch_call.so")):
+    if not os.path.exists(_path):
+        raise ImportError(f"{_path} is missing: build it first (python paper_2602_10016_amd/build.py). "
+                          "There is no fallback implementation.")
 _lib = ctypes.CDLL(LIB_PATH)
+
+from . import _torch_call as _native  # noqa: E402  (the call, or None for what is not plainly right: then the code below decides)
 
 OK = 0
 ERR_NULL, ERR_SHAPE, ERR_UNSUPPORTED, ERR_ALIGN, ERR_WORKSPACE, ERR_LAUNCH = -1, -2, -3, -4, -5, -6
@@ -94,8 +98,6 @@ def raw():
     return _lib
 
 
-# Marshalling is measured: a call whose kernels take 4 to 10 us is bound by it (14 us a call with a ctypes object per
-# pointer and a Stream object per call, 10 us with plain integers).
 def _ptr(t):
     return None if t is None else t.data_ptr()
 
@@ -210,6 +212,10 @@ def _workspace(workspace, nbytes, device):
 def gdpa_fwd(q, k, v, kv_offsets, scale, act, *, q_offsets=None, max_q=None, max_kv, head_act=None, out=None,
              lse=None, want_lse=True, workspace=None, stream=None):
     """kunlun_gdpa_fwd.  q [total_q,H,d], k/v [total_kv,H,d] device tensors; returns (o, lse)."""
+    if head_act is None and not VERIFY_OFFSETS:
+        done = _native.gdpa_fwd(q, k, v, kv_offsets, scale, act, q_offsets, max_q, max_kv, out, lse, want_lse, workspace, stream)
+        if done is not None:
+            return done
     _check_qkv(q, k, v)
     total_q, H, d = q.shape
     total_kv = k.shape[0]
@@ -274,6 +280,10 @@ def gdpa_bwd(q, k, v, d_o, kv_offsets, scale, act, *, o=None, lse=None, q_offset
              head_act=None, out=None, workspace=None, stream=None):
     """kunlun_gdpa_bwd.  Returns (dq, dk, dv) (written into the tensors of `out` when given).  o and lse are
     the forward results (read for softmax heads)."""
+    if head_act is None and not VERIFY_OFFSETS:
+        done = _native.gdpa_bwd(q, k, v, d_o, kv_offsets, scale, act, o, lse, q_offsets, max_q, max_kv, out, workspace, stream)
+        if done is not None:
+            return done
     _check_qkv(q, k, v)
     total_q, H, d = q.shape
     total_kv = k.shape[0]
@@ -304,6 +314,10 @@ def gdpa_bwd(q, k, v, d_o, kv_offsets, scale, act, *, o=None, lse=None, q_offset
 def seed_attn_fwd(e_seed, k, v, kv_offsets, scale, act=ACT_SOFTMAX, *, max_kv, head_act=None, out=None, lse=None,
                   want_lse=True, workspace=None, stream=None):
     """kunlun_seed_attn_fwd.  e_seed [n_seeds,H,d] is shared by all examples; returns (o [B*n_seeds,H,d], lse)."""
+    if head_act is None and not VERIFY_OFFSETS:
+        done = _native.seed_attn_fwd(e_seed, k, v, kv_offsets, scale, act, max_kv, out, lse, want_lse, workspace, stream)
+        if done is not None:
+            return done
     _check_qkv(e_seed, k, v)
     n_seeds, H, d = e_seed.shape
     _check_offsets("kv_offsets", kv_offsets)
@@ -329,6 +343,10 @@ def seed_attn_fwd(e_seed, k, v, kv_offsets, scale, act=ACT_SOFTMAX, *, max_kv, h
 def seed_attn_bwd(e_seed, k, v, d_o, kv_offsets, scale, act=ACT_SOFTMAX, *, o=None, lse=None, max_kv, head_act=None, out=None,
                   workspace=None, stream=None):
     """kunlun_seed_attn_bwd.  Returns (d_e [n_seeds,H,d], dk, dv); o and lse are the forward results."""
+    if head_act is None and not VERIFY_OFFSETS:
+        done = _native.seed_attn_bwd(e_seed, k, v, d_o, kv_offsets, scale, act, o, lse, max_kv, out, workspace, stream)
+        if done is not None:
+            return done
     _check_qkv(e_seed, k, v)
     n_seeds, H, d = e_seed.shape
     _check_offsets("kv_offsets", kv_offsets)
@@ -353,6 +371,10 @@ def seed_attn_bwd(e_seed, k, v, d_o, kv_offsets, scale, act=ACT_SOFTMAX, *, o=No
 def swa_fwd(q, k, v, offsets, window_left, window_right, scale, *, max_len, out=None, lse=None, want_lse=True,
             workspace=None, stream=None):
     """kunlun_swa_fwd.  q, k, v [total,H,d] share `offsets`; returns (o, lse)."""
+    if not VERIFY_OFFSETS:
+        done = _native.swa_fwd(q, k, v, offsets, window_left, window_right, scale, max_len, out, lse, want_lse, workspace, stream)
+        if done is not None:
+            return done
     _check_qkv(q, k, v)
     total, H, d = q.shape
     if k.shape[0] != total:
@@ -380,6 +402,10 @@ def swa_bwd(q, k, v, o, lse, d_o, offsets, window_left, window_right, scale, *, 
             stream=None):
     """kunlun_swa_bwd.  o and lse are the results of swa_fwd.  Returns (dq, dk, dv) (written into the tensors
     of `out` when given)."""
+    if not VERIFY_OFFSETS:
+        done = _native.swa_bwd(q, k, v, o, lse, d_o, offsets, window_left, window_right, scale, max_len, out, workspace, stream)
+        if done is not None:
+            return done
     _check_qkv(q, k, v)
     total, H, d = q.shape
     if k.shape[0] != total:
@@ -408,6 +434,9 @@ def sumkron_workspace_bytes(B, S, T, D, k, dtype=BF16) -> int:
 
 def sumkron_fwd(x, z, w, *, out=None, workspace=None, stream=None):
     """kunlun_sumkron_fwd.  x [B,S,D], z [k,S,T], w [k,D,D] device tensors; returns y [B,T,D]."""
+    done = _native.sumkron_fwd(x, z, w, out, workspace, stream)
+    if done is not None:
+        return done
     _dtype_code(x)
     _check("x", x)
     if x.dim() != 3 or z.dim() != 3:
@@ -433,6 +462,9 @@ def sumkron_bwd_workspace_bytes(B, S, T, D, k, dtype=BF16) -> int:
 
 def sumkron_bwd(x, z, w, dy, *, workspace=None, stream=None):
     """kunlun_sumkron_bwd.  x [B,S,D], z [k,S,T], w [k,D,D], dy [B,T,D] device tensors; returns (dx, dz, dw)."""
+    done = _native.sumkron_bwd(x, z, w, dy, workspace, stream)
+    if done is not None:
+        return done
     _dtype_code(x)
     _check("x", x)
     if x.dim() != 3 or z.dim() != 3:

@@ -1,12 +1,14 @@
-"""Build libkunlun.so (HIP, gfx950 only) in-tree with hipcc."""
+"""Build libkunlun.so (HIP, gfx950 only) in-tree with hipcc, and _torch_call.so (the entry points' marshalling) with g++."""
 import os
 import subprocess
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libkunlun.so")
+TORCH_CALL = os.path.join(HERE, "_torch_call.so")
 SOURCES = ["api.hip", "static_scratch.hip", "sched.hip", "stream_probe.hip", "scalar_kernels.hip", "attn_fwd_fp32_mfma.hip", "attn_fwd_mfma.hip", "attn_fwd_ring_mfma.hip", "attn_swa_band_mfma.hip", "attn_bwd_mfma.hip", "attn_bwd_pair_mfma.hip", "attn_bwd_wide_mfma.hip", "attn_bwd_tiled_mfma.hip", "sumkron.hip", "sumkron_fused.hip", "sumkron_bwd_fused.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 # -packed-fp32-ops off: the compiler must not form packed fp32 instructions on this target.
@@ -30,10 +32,22 @@ def _compile(src, extra=()):
     return obj, warn
 
 
+def _build_torch_call():
+    """The CPython module of the entry points' accepted case: host code only, against torch's C++ headers and the library."""
+    from torch.utils.cpp_extension import include_paths, library_paths
+    dirs = [*include_paths(), sysconfig.get_paths()["include"]]
+    libs = library_paths()[0]
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", *[f"-I{d}" for d in dirs], os.path.join(CSRC, "torch_call.cpp"),
+           "-o", TORCH_CALL, f"-L{HERE}", "-l:libkunlun.so", "-Wl,-rpath,$ORIGIN", f"-L{libs}", "-ltorch_python", "-ltorch_cpu", "-lc10"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"g++ failed on torch_call.cpp:\n{r.stdout}\n{r.stderr}")
+
+
 def build(force: bool = False, verbose: bool = False, extra=()) -> str:
-    """Compile every source and link libkunlun.so.  Skips the work if the library is newer
+    """Compile every source and link libkunlun.so and _torch_call.so.  Skips the work if both are newer
     than every source unless force is set."""
-    if not force and os.path.exists(LIB) and os.path.getmtime(LIB) >= _deps_mtime():
+    if not force and all(os.path.exists(f) and os.path.getmtime(f) >= _deps_mtime() for f in (LIB, TORCH_CALL)):
         return LIB
     os.makedirs(OBJ, exist_ok=True)
     with ThreadPoolExecutor(max_workers=min(8, len(SOURCES))) as ex:
@@ -44,6 +58,7 @@ def build(force: bool = False, verbose: bool = False, extra=()) -> str:
                 print(w)
     cmd = [HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *[o for o, _ in results]]
     subprocess.run(cmd, check=True)
+    _build_torch_call()
     return LIB
 
 
