@@ -420,17 +420,27 @@ __global__ __launch_bounds__(512, 2) void sumkron_batch_grads_kernel(const bf16_
         for (int v = 0; v < 16; ++v) pz[(32 * sb + c_row(v, g)) * SKB_T] = dz[sb][v];
 }
 
-// out[idx] = sum over `parts` of partial[part][idx], in order, rounded once; four values per thread
-__global__ __launch_bounds__(256) void sum_parts_kernel(const float* __restrict__ partial, bf16_t* __restrict__ out, int parts, int64_t n) {
-    const int64_t idx = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4;
-    if (idx >= n) return;
+// out[idx] = sum over `parts` of partial[part][idx], in order, rounded once; four values per thread.  Both sums in one launch
+// (one after the other took 8 us more: the sum for dZ is a chain of reads by few workgroups): the first `z_blocks`
+// workgroups add up dZ, the longer chain, the others dW.
+struct SumParts {
+    const float* partial;
+    bf16_t* out;
+    int parts;
+    int64_t n;
+};
+__global__ __launch_bounds__(256) void sum_parts_kernel(SumParts dz, SumParts dw, int z_blocks) {
+    const bool first = (int)blockIdx.x < z_blocks;
+    const SumParts p = first ? dz : dw;
+    const int64_t idx = ((int64_t)(blockIdx.x - (first ? 0 : z_blocks)) * 256 + threadIdx.x) * 4;
+    if (idx >= p.n) return;
     f32x4 sum = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll 8
-    for (int s = 0; s < parts; ++s) sum += *(const f32x4*)(partial + (int64_t)s * n + idx);
+    for (int s = 0; s < p.parts; ++s) sum += *(const f32x4*)(p.partial + (int64_t)s * p.n + idx);
     bf16x4 o;
 #pragma unroll
     for (int e = 0; e < 4; ++e) o[e] = (bf16_t)sum[e];
-    *(bf16x4*)(out + idx) = o;
+    *(bf16x4*)(p.out + idx) = o;
 }
 
 bool sumkron_bwd_fused_supported(int S, int T, int D, int k, int dtype) {
@@ -506,8 +516,9 @@ static hipError_t launch_skb(const bf16_t* x, const bf16_t* z, const bf16_t* w, 
     const int groups = splits * (D / SKB_C);
     hipLaunchKernelGGL(kern, dim3((unsigned)((groups + 7) / 8 * 8 * ((k + 1) / 2))), dim3(512), bytes, stream, x, zt, dy, gf, dw_part, dz_part, B, k,
                        splits, per_split);
-    hipLaunchKernelGGL(sum_parts_kernel, dim3((unsigned)((nw / 4 + 255) / 256)), dim3(256), 0, stream, dw_part, dw, splits, nw);
-    hipLaunchKernelGGL(sum_parts_kernel, dim3((unsigned)((nz / 4 + 255) / 256)), dim3(256), 0, stream, dz_part, dz, groups, nz);
+    const int z_blocks = (int)((nz / 4 + 255) / 256);
+    hipLaunchKernelGGL(sum_parts_kernel, dim3((unsigned)(z_blocks + (nw / 4 + 255) / 256)), dim3(256), 0, stream, SumParts{dz_part, dz, groups, nz},
+                       SumParts{dw_part, dw, splits, nw}, z_blocks);
     return hipGetLastError();
 }
 

@@ -39,29 +39,31 @@ constexpr int SKF_EX = 4;       // examples per workgroup step
 // position p of a 16-group holds channel perm(p): lane half g of a B fragment owns {4g..4g+3, 8+4g..8+4g+3}
 __host__ __device__ inline int skf_perm(int p) { return (p & 3) + 4 * (p >> 3) + 8 * ((p >> 2) & 1); }
 
-// zt[(i*T + t)*S + 16q + p] = z[(i*S + 16q + perm(p))*T + t]
-__global__ __launch_bounds__(256) void skf_prepare_z_kernel(const bf16_t* __restrict__ z, bf16_t* __restrict__ zt, int k, int S, int T) {
-    const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (idx >= (int64_t)k * S * T) return;
-    const int sp = (int)(idx % S);
-    const int t = (int)((idx / S) % T);
-    const int i = (int)(idx / ((int64_t)S * T));
-    const int s = (sp & ~15) + skf_perm(sp & 15);
-    zt[idx] = z[((int64_t)i * S + s) * T + t];
-}
-// Fragment order: fragment (i, channel block cb of 32, output block nb of 32, half cc) holds, for lane (r, g) and
+// Once per call, in one launch (two took 6 us more); eight values per thread.
+// Z: zt[(i*T + t)*S + 16q + p] = z[(i*S + 16q + perm(p))*T + t].
+// W in fragment order: fragment (i, channel block cb of 32, output block nb of 32, half cc) holds, for lane (r, g) and
 // q = 0..7, w[i][c = 32*cb + 16*cc + perm(8g + q)][n = 32*nb + r]; 512 values per fragment, lane-major.
-__global__ __launch_bounds__(256) void skf_prepare_w_kernel(const bf16_t* __restrict__ w, bf16_t* __restrict__ wp, int k, int D) {
-    const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (idx >= (int64_t)k * D * D) return;
-    const int q = (int)(idx & 7), lane = (int)((idx >> 3) & 63), cc = (int)((idx >> 9) & 1);
-    const int64_t rest = idx >> 10;  // (i * D/32 + cb) * D/32 + nb
-    const int nb = (int)(rest % (D / 32));
-    const int cb = (int)((rest / (D / 32)) % (D / 32));
-    const int i = (int)(rest / ((int64_t)(D / 32) * (D / 32)));
-    const int c = 32 * cb + 16 * cc + skf_perm(8 * (lane >> 5) + q);
-    const int n = 32 * nb + (lane & 31);
-    wp[idx] = w[((int64_t)i * D + c) * D + n];
+__global__ __launch_bounds__(256) void skf_prepare_kernel(const bf16_t* __restrict__ w, const bf16_t* __restrict__ z, bf16_t* __restrict__ wp,
+                                                          bf16_t* __restrict__ zt, int k, int D, int S, int T, int w_blocks) {
+    bf16x8 out;
+    if ((int)blockIdx.x < w_blocks) {
+        const int idx = blockIdx.x * 256 + threadIdx.x;
+        if (idx >= k * D * (D / 8)) return;
+        const int lane = idx & 63, cc = (idx >> 6) & 1, rest = idx >> 7;  // (i * D/32 + cb) * D/32 + nb
+        const int nb = rest % (D / 32), cb = (rest / (D / 32)) % (D / 32), i = rest / ((D / 32) * (D / 32));
+        const bf16_t* src = w + ((int64_t)i * D + 32 * cb + 16 * cc) * D + 32 * nb + (lane & 31);
+#pragma unroll
+        for (int q = 0; q < 8; ++q) out[q] = src[skf_perm(8 * (lane >> 5) + q) * D];
+        *(bf16x8*)(wp + (int64_t)idx * 8) = out;
+    } else {
+        const int idx = (blockIdx.x - w_blocks) * 256 + threadIdx.x;  // t fastest: the reads of a wave are contiguous
+        if (idx >= k * T * (S / 8)) return;
+        const int t = idx % T, s8 = (idx / T) % (S / 8), i = idx / (T * (S / 8));
+        const bf16_t* src = z + ((int64_t)i * S + (s8 >> 1) * 16) * T + t;
+#pragma unroll
+        for (int q = 0; q < 8; ++q) out[q] = src[skf_perm(8 * (s8 & 1) + q) * T];
+        *(bf16x8*)(zt + ((int64_t)i * T + t) * S + s8 * 8) = out;
+    }
 }
 
 template <int NBW, int S>  // D = 128 * NBW output / input channels; S rows of X per example (128 or 256)
@@ -285,8 +287,9 @@ hipError_t launch_sumkron_fused(const void* x, const void* z, const void* w, voi
     bf16_t* zt = (bf16_t*)workspace;
     bf16_t* wp = (bf16_t*)((char*)workspace + align_up((size_t)k * T * S * 2, 256));
     const int64_t nz = (int64_t)k * S * T, nw = (int64_t)k * D * D;
-    hipLaunchKernelGGL(skf_prepare_z_kernel, dim3((unsigned)((nz + 255) / 256)), dim3(256), 0, stream, (const bf16_t*)z, zt, k, S, T);
-    hipLaunchKernelGGL(skf_prepare_w_kernel, dim3((unsigned)((nw + 255) / 256)), dim3(256), 0, stream, (const bf16_t*)w, wp, k, D);
+    const int w_blocks = (int)((nw / 8 + 255) / 256);
+    hipLaunchKernelGGL(skf_prepare_kernel, dim3((unsigned)(w_blocks + (nz / 8 + 255) / 256)), dim3(256), 0, stream, (const bf16_t*)w, (const bf16_t*)z,
+                       wp, zt, k, D, S, T, w_blocks);
     const bf16_t* xb = (const bf16_t*)x;
     bf16_t* yb = (bf16_t*)y;
     const int nbw = D / 128;
