@@ -246,13 +246,16 @@ size_t kunlun_workspace_bytes(int op, int B, int H, int d, int max_q, int max_kv
  * intermediate Z_i^T X_b is rounded to bf16 once) - in ONE kernel that keeps the intermediate on the
  * compute unit when T = 32, S is 128 or 256, D <= 384 and k <= 8 (the paper's S = 256, T = 32, D = 384,
  * k = 8 among them), else as two matrix products through the workspace; other shapes and KUNLUN_FP32
- * take plain kernels that keep every intermediate and sum in fp64.  workspace: device, at least kunlun_sumkron_workspace_bytes(...) bytes, 256-byte aligned.
+ * take plain kernels that keep every intermediate and sum in fp64.  workspace: device, 256-byte aligned, of
+ * kunlun_sumkron_workspace_bytes(...) bytes; the one kernel runs with less too, down to the prepared copies of Z and W (2 k T S
+ * and 2 k D^2 bytes, each rounded up to 256, and 256), but then without the fp32 partial sums with which small batches spread
+ * over the compute units.
  * B == 0 is legal and does nothing.  Errors as for the other entry points.
  */
 int kunlun_sumkron_fwd(const void* x, const void* z, const void* w, void* y, int B, int S, int T, int D, int k,
                        int dtype, void* workspace, size_t workspace_bytes, void* stream);
 
-/* Bytes of workspace that kunlun_sumkron_fwd needs for these sizes (0 for invalid sizes). */
+/* Bytes of workspace with which kunlun_sumkron_fwd takes its fastest path for these sizes (0 for invalid sizes). */
 size_t kunlun_sumkron_workspace_bytes(int B, int S, int T, int D, int k, int dtype);
 
 /*

@@ -94,9 +94,9 @@ int kunlun_sumkron_fwd(const void* x, const void* z, const void* w, void* y, int
     if (B == 0) return KUNLUN_OK;
     if (!x || !z || !w || !y) return KUNLUN_ERR_NULL;
     if (!aligned(x, 16) || !aligned(z, 16) || !aligned(w, 16) || !aligned(y, 16)) return KUNLUN_ERR_ALIGN;
-    if (!workspace || workspace_bytes < kunlun_sumkron_workspace_bytes(B, S, T, D, k, dtype)) return KUNLUN_ERR_WORKSPACE;
+    if (!workspace || workspace_bytes < sumkron_need(B, S, T, D, k, dtype) + 256) return KUNLUN_ERR_WORKSPACE;
     if (!aligned(workspace, 256)) return KUNLUN_ERR_ALIGN;
-    const hipError_t e = launch_sumkron(x, z, w, y, B, S, T, D, k, dtype, workspace, (hipStream_t)stream);
+    const hipError_t e = launch_sumkron(x, z, w, y, B, S, T, D, k, dtype, workspace, workspace_bytes, (hipStream_t)stream);
     return e == hipSuccess ? KUNLUN_OK : KUNLUN_ERR_LAUNCH;
 }
 

@@ -66,10 +66,13 @@ __global__ __launch_bounds__(256) void skf_prepare_kernel(const bf16_t* __restri
     }
 }
 
-template <int NBW, int S>  // D = 128 * NBW output / input channels; S rows of X per example (128 or 256)
+// SPLIT: a workgroup takes one group of examples and a range of the channel blocks (the contraction of stage 2) and leaves an
+// fp32 partial sum of Y in part[range]; skf_sum_kernel adds the ranges in order.  For batches that would leave compute units
+// empty, where one group's chain of D / 32 steps sets the time.
+template <int NBW, int S, bool SPLIT>  // D = 128 * NBW output / input channels; S rows of X per example (128 or 256)
 __global__ __launch_bounds__(64 * SKF_WAVES, 1) void sumkron_fused_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ zt,
                                                                           const bf16_t* __restrict__ wp, bf16_t* __restrict__ y,
-                                                                          int B, int k) {
+                                                                          int B, int k, float* __restrict__ part, int blocks_per_range) {
     using L = TileLayout<SKF_CB>;  // 32-row tiles of 32 channels, the layout of the transposing reads
     constexpr int D = 128 * NBW;
     constexpr int KS = S / 16;                  // contraction steps of stage 1
@@ -118,9 +121,11 @@ __global__ __launch_bounds__(64 * SKF_WAVES, 1) void sumkron_fused_kernel(const 
     };
 
     const int64_t n_groups = ((int64_t)B + SKF_EX - 1) / SKF_EX;
-    int64_t group = blockIdx.x;
+    int64_t group = SPLIT ? blockIdx.x % n_groups : blockIdx.x;
     if (group >= n_groups) return;
-    send_x(group, 0);
+    const int range = SPLIT ? (int)(blockIdx.x / n_groups) : 0;
+    const int cb_first = SPLIT ? range * blocks_per_range : 0, cb_end = SPLIT ? cb_first + blocks_per_range : NCB;
+    send_x(group, cb_first);
     load_z();
     wait_vmcnt<0>();
     // W fragments travel three fragment steps ahead of their use in a ring of four register sets that runs on from
@@ -135,16 +140,16 @@ __global__ __launch_bounds__(64 * SKF_WAVES, 1) void sumkron_fused_kernel(const 
         const bool next = i >= kp;
         int ii = next ? i - kp : i;
         ii = ii < k ? ii : k - 1;
-        const int cbb = next ? (cb + 1 < NCB ? cb + 1 : 0) : cb;
+        const int cbb = next ? (cb + 1 < cb_end ? cb + 1 : cb_first) : cb;
         const bf16_t* src = wlane + cbb * wblock + ii * wfactor + cc * 512;
 #pragma unroll
         for (int j = 0; j < NBW; ++j) dst[j] = *(const bf16x8*)(src + j * 2 * 512);
         asm volatile("" ::: "memory");
     };
-    issue(0, 0, 0, wq[0]);
-    issue(0, 0, 1, wq[1]);
-    issue(0, 1, 0, wq[2]);
-    for (; group < n_groups; group += gridDim.x) {
+    issue(cb_first, 0, 0, wq[0]);
+    issue(cb_first, 0, 1, wq[1]);
+    issue(cb_first, 1, 0, wq[2]);
+    for (; group < n_groups; group += SPLIT ? n_groups : gridDim.x) {
         f32x16 yacc[2][NBW];
 #pragma unroll
         for (int e = 0; e < 2; ++e)
@@ -152,7 +157,7 @@ __global__ __launch_bounds__(64 * SKF_WAVES, 1) void sumkron_fused_kernel(const 
             for (int j = 0; j < NBW; ++j)
 #pragma unroll
                 for (int v = 0; v < 16; ++v) yacc[e][j][v] = 0.f;
-        for (int cb = 0; cb < NCB; ++cb) {
+        for (int cb = cb_first; cb < cb_end; ++cb) {
             __syncthreads();  // (A) this step's X blocks are in LDS; the exchange buffer is free
             // ---- stage 1: U^T_{e, wave} of the block, example by example.  Every MFMA needs a fresh A fragment from LDS:
             // the fragments are requested four MFMAs ahead (left to the compiler they were read one at a time, each
@@ -195,8 +200,8 @@ __global__ __launch_bounds__(64 * SKF_WAVES, 1) void sumkron_fused_kernel(const 
             }
             __syncthreads();  // (B) every U^T fragment of the step is in the exchange buffer; the X blocks are dead
             {   // the next step's blocks set out
-                const bool same = cb + 1 < NCB;
-                const int64_t ng_ = same ? group : group + gridDim.x;
+                const bool same = cb + 1 < cb_end;
+                const int64_t ng_ = same ? group : group + (SPLIT ? n_groups : gridDim.x);
                 if (ng_ < n_groups) send_x(ng_, same ? cb + 1 : 0);
             }
             // ---- stage 2: Y^T_e[channels of group ng] += W_i^T[.., block] U^T_{e, i} over all factors, e = 2 eh, 2 eh + 1.  A
@@ -244,7 +249,18 @@ __global__ __launch_bounds__(64 * SKF_WAVES, 1) void sumkron_fused_kernel(const 
 #pragma unroll
         for (int e = 0; e < 2; ++e) {
             const int64_t b = group * SKF_EX + 2 * eh + e;
-            if (b < B) {
+            if (SPLIT && b < B) {
+                float* prow = part + (((int64_t)range * B + b) * SKF_T + r) * D + 32 * NBW * ng + 4 * g;
+#pragma unroll
+                for (int j = 0; j < NBW; ++j)
+#pragma unroll
+                    for (int vg = 0; vg < 4; ++vg) {
+                        f32x4 out;
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) out[q] = yacc[e][j][4 * vg + q];
+                        *(f32x4*)(prow + 32 * j + 8 * vg) = out;
+                    }
+            } else if (b < B) {
                 bf16_t* yrow = y + (b * SKF_T + r) * D + 32 * NBW * ng + 4 * g;
 #pragma unroll
                 for (int j = 0; j < NBW; ++j)
@@ -260,40 +276,82 @@ __global__ __launch_bounds__(64 * SKF_WAVES, 1) void sumkron_fused_kernel(const 
     }
 }
 
+// y[idx] = sum of part[range][idx] over the ranges, in order, rounded once; four values per thread
+__global__ __launch_bounds__(256) void skf_sum_kernel(const float* __restrict__ part, bf16_t* __restrict__ y, int ranges, int64_t n) {
+    const int64_t idx = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4;
+    if (idx >= n) return;
+    f32x4 sum = {0.f, 0.f, 0.f, 0.f};
+    for (int s = 0; s < ranges; ++s) sum += *(const f32x4*)(part + (int64_t)s * n + idx);
+    bf16x4 o;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) o[q] = (bf16_t)sum[q];
+    *(bf16x4*)(y + idx) = o;
+}
+
+// Ranges of channel blocks: as many as fill the compute units, a divisor of D / 32.  `room`: bytes for the partial sums.
+// One group takes 95 to 110 us on its compute unit however small the batch.  Forward and backward at S = 256, D = 384, k = 8,
+// whole / split, us: 8 examples 139 / 68, 64: 154 / 95, 128: 182 / 120, 256: 240 / 187, 512: 341 / 318, 700: 415 / 412 (one range).
+constexpr int SKF_WGS = 256;  // workgroups of a split launch, at most
+static int skf_ranges(int B, int D, size_t room) {
+    const int groups = (B + SKF_EX - 1) / SKF_EX, blocks = D / SKF_CB;
+    int ranges = 1;
+    for (int d = 2; d <= blocks; ++d)
+        if (blocks % d == 0 && (int64_t)groups * d <= SKF_WGS && (size_t)d * B * SKF_T * D * sizeof(float) <= room) ranges = d;
+    return ranges;
+}
+
 bool sumkron_fused_supported(int S, int T, int D, int k, int dtype) {
     return dtype == KUNLUN_BF16 && T == SKF_T && (S == 128 || S == 256) && D % 128 == 0 && D >= 128 && D <= 384 && k >= 1 && k <= SKF_WAVES;
 }
 
-size_t sumkron_fused_workspace(int S, int T, int D, int k) {
+size_t sumkron_fused_need(int S, int T, int D, int k) {
     return align_up((size_t)k * T * S * 2, 256) + align_up((size_t)k * D * D * 2, 256);
 }
+// ... with the partial sums of any split launch (the same for every batch size, so that a kept workspace serves them all)
+size_t sumkron_fused_workspace(int S, int T, int D, int k) {
+    return sumkron_fused_need(S, T, D, k) + (size_t)SKF_WGS * SKF_EX * SKF_T * D * sizeof(float);
+}
 
-template <int NBW, int S>
-static hipError_t launch_skf(const bf16_t* x, const bf16_t* zt, const bf16_t* wp, bf16_t* y, int B, int k, hipStream_t stream) {
+template <int NBW, int S, bool SPLIT>
+static hipError_t launch_skf_form(const bf16_t* x, const bf16_t* zt, const bf16_t* wp, bf16_t* y, int B, int k, float* part, int ranges,
+                                  hipStream_t stream) {
     constexpr int bytes = SKF_EX * S * SKF_CB * 2 + SKF_EX * 8 * 2 * 1024;
-    auto kern = sumkron_fused_kernel<NBW, S>;
+    auto kern = sumkron_fused_kernel<NBW, S, SPLIT>;
     // once per process (thread-safe initialisation of a function-local static); not a stream operation
     static const hipError_t raised = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
     if (raised != hipSuccess) return raised;
     const int64_t n_groups = ((int64_t)B + SKF_EX - 1) / SKF_EX;
     const int64_t resident = compute_units();
-    hipLaunchKernelGGL(kern, dim3((unsigned)(n_groups < resident ? n_groups : resident)), dim3(64 * SKF_WAVES), bytes, stream, x, zt, wp, y, B, k);
+    const int64_t grid = SPLIT ? n_groups * ranges : n_groups < resident ? n_groups : resident;
+    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(64 * SKF_WAVES), bytes, stream, x, zt, wp, y, B, k, part, 128 * NBW / SKF_CB / ranges);
+    return hipGetLastError();
+}
+template <int NBW, int S>
+static hipError_t launch_skf(const bf16_t* x, const bf16_t* zt, const bf16_t* wp, bf16_t* y, int B, int k, float* part, size_t room, hipStream_t stream) {
+    const int ranges = skf_ranges(B, 128 * NBW, room);
+    if (ranges == 1) return launch_skf_form<NBW, S, false>(x, zt, wp, y, B, k, nullptr, 1, stream);
+    const hipError_t e = launch_skf_form<NBW, S, true>(x, zt, wp, y, B, k, part, ranges, stream);
+    if (e != hipSuccess) return e;
+    const int64_t n = (int64_t)B * SKF_T * 128 * NBW;
+    hipLaunchKernelGGL(skf_sum_kernel, dim3((unsigned)((n / 4 + 255) / 256)), dim3(256), 0, stream, part, y, ranges, n);
     return hipGetLastError();
 }
 
-// workspace: sumkron_fused_workspace(...) bytes (prepared Z, prepared W)
+// workspace: prepared Z, prepared W, and what is left of its bytes (at least sumkron_fused_need()) for partial sums
 hipError_t launch_sumkron_fused(const void* x, const void* z, const void* w, void* y, int B, int S, int T, int D, int k, void* workspace,
-                                hipStream_t stream) {
+                                size_t workspace_bytes, hipStream_t stream) {
     bf16_t* zt = (bf16_t*)workspace;
     bf16_t* wp = (bf16_t*)((char*)workspace + align_up((size_t)k * T * S * 2, 256));
     const int64_t nz = (int64_t)k * S * T, nw = (int64_t)k * D * D;
     const int w_blocks = (int)((nw / 8 + 255) / 256);
     hipLaunchKernelGGL(skf_prepare_kernel, dim3((unsigned)(w_blocks + (nz / 8 + 255) / 256)), dim3(256), 0, stream, (const bf16_t*)w, (const bf16_t*)z,
                        wp, zt, k, D, S, T, w_blocks);
+    const size_t used = sumkron_fused_need(S, T, D, k), room = workspace_bytes > used ? workspace_bytes - used : 0;
+    float* part = (float*)((char*)workspace + used);
     const bf16_t* xb = (const bf16_t*)x;
     bf16_t* yb = (bf16_t*)y;
     const int nbw = D / 128;
-#define KUNLUN_SKF(NBW_) (S == 256 ? launch_skf<NBW_, 256>(xb, zt, wp, yb, B, k, stream) : launch_skf<NBW_, 128>(xb, zt, wp, yb, B, k, stream))
+#define KUNLUN_SKF(NBW_) (S == 256 ? launch_skf<NBW_, 256>(xb, zt, wp, yb, B, k, part, room, stream) : launch_skf<NBW_, 128>(xb, zt, wp, yb, B, k, part, room, stream))
     switch (nbw) {
     case 1: return KUNLUN_SKF(1);
     case 2: return KUNLUN_SKF(2);
