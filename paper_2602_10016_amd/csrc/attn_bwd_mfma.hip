@@ -2,7 +2,7 @@
 // dQ, dK, dV of <O, dO>.  Scores are recomputed tile by tile; nothing of score size is ever
 // stored (the block-wise backward of Sec. "Efficient Attention-Style Implementation").
 //
-// One workgroup of NW wavefronts = one work item = (example, head) with up to 32*NQB queries.
+// One workgroup of NW wavefronts = one work item = (example, head), or a pair of heads of 32 channels, with up to 32*NQB queries.
 // Q and dO of the item stay in LDS (shared by the waves); the waves take the 32-key tiles of
 // the history round-robin and never synchronise inside the key loop.  Per tile, per wave:
 //     S^T  = K Q^T            dP^T = V dO^T                       (MFMA, keys x queries)

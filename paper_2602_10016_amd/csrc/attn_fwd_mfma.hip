@@ -3,11 +3,12 @@
 // (Eq. (PMA), Eq. (seed-level attention)).  Longer query sequences and the sliding window are
 // served by the query-tiled kernel (attn_fwd_ring_mfma.hip).
 //
-// A workgroup of NW wavefronts owns one work item = (example, head); each wave owns 32*NQB of
-// its queries for the whole item.  The waves stream the 32-key K/V tiles of the item together:
+// A workgroup owns one work item = (example, head), or a pair of heads of 32 channels (HP = 2); a wave owns 32*NQB of its
+// queries for the whole item.  Either NW waves with different queries stream the 32-key K/V tiles of the item together:
 // every thread fetches its share of tile t+1 (and t+2) into registers (whole rows, coalesced,
 // non-temporal) while tile t, already in LDS, is being consumed; tiles are double-buffered in
-// LDS, so there is one barrier per tile.  These operators do only Nq flops per byte of K/V (a
+// LDS, so there is one barrier per tile.  Or KS waves with the same queries take the tiles in turn, without a barrier, and
+// merge their results at the end (mfma_fwd_plan() says which).  These operators do only Nq flops per byte of K/V (a
 // key/value byte is used by the queries of its own example and head and by nobody else), far
 // below the matrix-core ridge, so the design goal is bytes in flight and enough resident waves
 // to hide latency, not MFMA occupancy.
