@@ -456,10 +456,10 @@ static hipError_t launch_bwd(const AttnParams& p, hipStream_t stream) {
 // us (u: unsorted, s: sorted), softmax, histories of 64..512 (t), 64..1024 (u), 256..2048 (v) and log-normal up to 4096 keys (l):
 //   d = 32, 32 queries   four / eight waves    256 items u 15u 13u, l 43u 32u;  512 l 55u 52u, 53s 46s;  768 l 64u 61u, 63s 56s
 //                        single heads, four waves / pairs, four / eight   4096 t 84u 73u 89u, u 158s 128u 130u, v 305s 266u 248u, l 322s 267s 268s;
-//                        1024 l 112s 115s 90s;  2048 u 82s 75u 72u, v 159s 144s 144s 136u
+//                        1024 l 112s 115s 90s;  2048 u 82s 75u 72u, v 159s 144s 144s 136u;  fewer: 1680 u 52 63, 2560 t 42 54;  64..256 keys, 4664 items 43 51
 //   d = 32, 60 queries   four / eight waves    256 u 21u 17u, l 66u 44u;  512 l 81u 67u, 70s 48s;  768 l 73s 61s, v 60s 59s;  1536 l 137s 145s
 //   d = 64, 20 queries   four / eight waves    256 l 86u 76u;  512 u 46u 42u, 45s 39s, l 133u 109u, 115s 96s;  1024 l 162s 137s, u 68s 68s;  2048 v 254s 251s
-//                        four / two waves      4096 t 128s 132s, u 228s 240s
+//                        four / two waves      4096 t 128s 132s, u 228s 240s;  64..256 keys, 2925 items 66s 63s, 8704 159s 153s
 //   d = 64, 60 queries   two / four waves      512 t 36s 35s, u 60s 50s;  768 t 44s 49s, u 65s 70s;  1024 l 208s 163s;  1536 l 225s 235s;  2048 u 151s 171s
 BwdPlan mfma_bwd_plan(const AttnParams& p) {
     const int64_t items = (int64_t)p.B * p.H;
@@ -471,7 +471,7 @@ BwdPlan mfma_bwd_plan(const AttnParams& p) {
     }
     int per_cu;  // workgroups that fit a compute unit
     if (p.d == 32) {
-        plan.pair = one_block && heads_pair(p) && items > (long_histories ? 768 : p.max_kv > 512 ? 1536 : 2048);
+        plan.pair = one_block && p.max_kv > 256 && heads_pair(p) && items > (long_histories ? 768 : p.max_kv > 512 ? 2000 : 3584);
         if (plan.pair) {
             plan.waves = p.max_kv > 512 ? 8 : 4;
             plan.sorted = long_histories && !(histories_are_even(p) && items >= 2048);
@@ -481,9 +481,10 @@ BwdPlan mfma_bwd_plan(const AttnParams& p) {
         per_cu = plan.waves == 8 ? 1 : one_block ? 3 : 2;
     } else if (one_block) {
         if (long_histories || items <= (p.max_kv > 512 ? 1024 : 256)) plan.waves = 8;
+        else if (p.max_kv <= 256 && items > 2048) plan.waves = 2;
         per_cu = plan.waves == 8 && long_histories ? 1 : 2;
     } else {
-        if (items > (p.max_kv > 2048 ? 1024 : 512)) plan.waves = 2;
+        if (items > (p.max_kv > 2048 ? 1280 : p.max_kv > 512 ? 640 : 512)) plan.waves = 2;
         plan.sorted = items > 512;
         per_cu = 1;
     }
@@ -500,7 +501,8 @@ hipError_t launch_mfma_bwd(const AttnParams& p, void*, hipStream_t stream) {
         if (plan.waves == 8) return one_block ? launch_bwd<32, 1, 8>(p, stream) : launch_bwd<32, 2, 8>(p, stream);
         return one_block ? launch_bwd<32, 1, 4>(p, stream) : launch_bwd<32, 2, 4>(p, stream);
     }
-    if (one_block) return plan.waves == 8 ? launch_bwd<64, 1, 8>(p, stream) : launch_bwd<64, 1, 4>(p, stream);
+    if (one_block)
+        return plan.waves == 8 ? launch_bwd<64, 1, 8>(p, stream) : plan.waves == 4 ? launch_bwd<64, 1, 4>(p, stream) : launch_bwd<64, 1, 2>(p, stream);
     return plan.waves == 4 ? launch_bwd<64, 2, 4>(p, stream) : launch_bwd<64, 2, 2>(p, stream);
 }
 

@@ -509,7 +509,7 @@ bool mfma_fwd_is_qtiled(const AttnParams& p) { return p.windowed || p.max_q > 64
 //              64 queries  4096 items t 74 / 44, u 97 / 67, v 163 / 124, l 170 / 126;  2048 l 104 / 71
 //     d = 64   32 queries  4096 items t 82 / 64, u 121 / 112, v 221 / 217, l 238 / 221
 //              64 queries  4096 items t 84 / 70, u 126 / 115, v 229 / 224, l 247 / 231;  1024 u 41 / 38, v 79 / 63, l 109 / 74;
-//                          256 u 22 / 14, v 38 / 23, l 47 / 38 (two items per (example, head))
+//                          256 u 22 / 14, v 38 / 23, l 47 / 38 (two items per (example, head); 171 l 34 / 40)
 //     d = 128  20 queries  4096 items t 126 / 117, u 213 / 203, v 410 / 400;  3072 l 342 / 313
 //   `both`, two / four / eight waves, unsorted, then sorted, d = 64, 64 queries:
 //     1024 items l 99 / 87 / 89, 91 / 74 / 77;  v 78 / 70 / 76, 74 / 63 / 72;  512 v 42 / 43 / 44, 42 / 42 / 41, l 67 / 63 / 59, 63 / 52 / 48;
@@ -549,8 +549,10 @@ FwdPlan mfma_fwd_plan(const AttnParams& p) {
         }
         return plan;
     }
-    plan.pair = heads_pair(p) && items > (long_histories ? 768 : 1024);
-    if (plan.pair || (d == 64 && items > 128)) {
+    // (more for GELU's general form: 1762 items l 105 / 114;  the others: 812 l 45 / 58, 1272 t 24 / 28 below the line)
+    plan.pair = heads_pair(p) && items > (!cheap && !small_scores_expected(p) ? 2048 : long_histories ? 1000 : 1500);
+    if (d == 64 && p.max_kv <= 256 && items > 512 && all_fit) return plan;  // (952 items of 64..256 keys, a workgroup of two / `both`: 12.5 / 13.7)
+    if (plan.pair || (d == 64 && items > (long_histories ? 192 : 128))) {
         const int64_t units = plan.pair ? items / 2 : items;
         plan.both = true;
         if (long_histories)
@@ -561,8 +563,8 @@ FwdPlan mfma_fwd_plan(const AttnParams& p) {
         return plan;
     }
     const bool even = histories_are_even(p);
-    const int64_t dear_limit = d == 32 ? 4096 : d == 64 ? 256 : (long_histories ? (even ? 512 : 1024) : 512);
-    const int64_t cheap_limit = d == 32 ? (long_histories || !all_fit ? 4096 : 768) : d == 64 ? 256 : (long_histories ? (even ? 512 : 1024) : 256);
+    const int64_t dear_limit = d == 32 ? 4096 : d == 64 ? 384 : (long_histories ? (even ? 512 : 1024) : 512);
+    const int64_t cheap_limit = d == 32 ? (long_histories || !all_fit ? 4096 : 768) : d == 64 ? 384 : (long_histories ? (even ? 512 : 1024) : 256);
     if (blocks <= (cheap ? cheap_limit : dear_limit))
         plan.key_split = long_histories && blocks <= (d == 32 ? 1536 : 2048) ? 8 : 4;
     else
@@ -598,6 +600,7 @@ static hipError_t launch_streaming(const AttnParams& p, const FwdPlan& plan, hip
     if (p.d == 64) {
         if (ks == 8) return launch_gdpa<SMALL, 64, 1, 1, 1, 2, 2, 8>(p, stream);
         if (ks == 2) return launch_gdpa<SMALL, 64, 1, 1, 1, 2, 2, 2>(p, stream);
+        if (ks == 1) return launch_gdpa<SMALL, 64, 1, 1, 2, 2, 2, 1>(p, stream);
         // Four waves: with the short form of GELU a kernel of 177 registers, two workgroups per compute unit; without it 162
         // and three, which is what counts for short histories (GELU, 768 items of 32 queries, 64..512 keys 17.2 / 15.9 us;
         // 1536 of 64..1024 keys 43.9 / 45.4 us)

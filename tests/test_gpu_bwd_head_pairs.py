@@ -38,8 +38,8 @@ def check(oracle, B, H, d, n, longest, act=0, head_act=None):
         assert_close(to_np(a), ref, TOL["bf16"], f"B={B} H={H} d={d} n={n} longest={longest} act={act} {name}")
 
 
-# items = B * H: pairs above 2048 items of up to 512 keys (four waves), 1536 of up to 1024, 768 of longer ones (eight)
-@pytest.mark.parametrize("B,H,n,longest", [(1030, 2, 1, 90), (520, 4, 32, 90), (770, 2, 32, 600), (200, 8, 20, 600), (100, 8, 31, 1100), (390, 2, 32, 1100),
+# items = B * H: pairs above 3584 items of 257..512 keys (four waves), 2000 of up to 1024, 768 of longer ones (eight)
+@pytest.mark.parametrize("B,H,n,longest", [(1800, 2, 1, 300), (900, 4, 32, 300), (1002, 2, 32, 600), (251, 8, 20, 600), (100, 8, 31, 1100), (390, 2, 32, 1100),
                                            (260, 8, 32, 1100)])
 @pytest.mark.parametrize("act", [0, 3, 5])
 def test_pairs_of_heads(oracle, B, H, n, longest, act):
@@ -48,7 +48,7 @@ def test_pairs_of_heads(oracle, B, H, n, longest, act):
 
 @pytest.mark.parametrize("head_act", [[0, 0, 5, 5], [3, 3, 0, 0], [0, 3, 0, 3]])
 def test_pairs_share_a_score_function_or_go_alone(oracle, head_act):
-    check(oracle, 530, 4, 32, 20, 200, act=3, head_act=head_act)
+    check(oracle, 900, 4, 32, 20, 300, act=3, head_act=head_act)
 
 
 def test_pairs_of_even_histories_unsorted(oracle):
@@ -68,11 +68,13 @@ def test_pairs_of_even_histories_unsorted(oracle):
 
 
 # eight waves: d = 32 up to 256 items (768 of long histories), d = 64 with up to 32 queries 256, 1024 beyond 512 keys, all
-# beyond 1024; two waves: d = 64 with 33..64 queries above 512 items, 1024 with histories beyond 2048 keys
+# beyond 1024; two waves: d = 64 with 33..64 queries above 512 items (640 with histories beyond 512 keys, 1280 beyond 2048),
+# and with up to 32 queries above 2048 items of up to 256 keys
 @pytest.mark.parametrize("B,H,d,n,longest", [(64, 4, 32, 32, 90), (65, 4, 32, 32, 90), (64, 4, 32, 64, 300), (65, 4, 32, 33, 300), (192, 4, 32, 20, 1100),
                                              (192, 4, 32, 64, 1100), (193, 4, 32, 40, 1100), (64, 4, 64, 32, 500), (65, 4, 64, 32, 500),
                                              (256, 4, 64, 17, 600), (257, 4, 64, 17, 600), (300, 4, 64, 32, 1100), (128, 4, 64, 64, 90),
-                                             (129, 4, 64, 33, 90), (256, 4, 64, 40, 2100), (257, 4, 64, 40, 2100)])
+                                             (129, 4, 64, 33, 90), (160, 4, 64, 40, 600), (161, 4, 64, 40, 600), (320, 4, 64, 40, 2100), (321, 4, 64, 40, 2100),
+                                             (513, 4, 64, 20, 90)])
 @pytest.mark.parametrize("act", [0, 3])
 def test_waves_per_item(oracle, B, H, d, n, longest, act):
     check(oracle, B, H, d, n, longest, act)

@@ -40,10 +40,10 @@ def check(oracle, B, H, d, n, longest, act=0, head_act=None, seed=0):
 
 
 # items = B * H.  Up to 32 queries: pairs above 2048 items, or 1024 with histories beyond 1024 keys (eight, then four waves);
-# 33..64: above 1024 or 768 (two, four or eight waves by items and longest history)
+# 33..64: above 1500 or 1000 (two, four or eight waves by items and longest history)
 @pytest.mark.parametrize("B,H,n,longest", [(1030, 2, 1, 90), (1030, 2, 32, 600), (260, 4, 31, 1100), (530, 4, 32, 1100), (330, 8, 17, 1100),
-                                           (520, 2, 33, 90), (520, 2, 64, 600), (1060, 4, 40, 600), (200, 4, 64, 1100), (600, 4, 33, 1100),
-                                           (1100, 4, 64, 1100), (390, 2, 50, 2100)])
+                                           (760, 2, 33, 90), (760, 2, 64, 600), (1060, 4, 40, 600), (255, 4, 64, 1100), (600, 4, 33, 1100),
+                                           (1100, 4, 64, 1100), (510, 2, 50, 2100)])
 @pytest.mark.parametrize("act", [0, 3])
 def test_pairs_of_heads(oracle, B, H, n, longest, act):
     check(oracle, B, H, 32, n, longest, act)
@@ -55,7 +55,7 @@ def test_pairs_share_a_score_function_or_go_alone(oracle, head_act, n):
     check(oracle, 530, 4, 32, n, 200, act=3, head_act=head_act)
 
 
-@pytest.mark.parametrize("B,H,n,longest", [(33, 4, 33, 90), (33, 4, 64, 1100), (130, 4, 64, 90), (130, 4, 40, 600), (130, 4, 64, 1100), (300, 4, 50, 600),
+@pytest.mark.parametrize("B,H,n,longest", [(33, 4, 33, 90), (49, 4, 64, 1100), (130, 4, 64, 90), (130, 4, 40, 600), (130, 4, 64, 1100), (300, 4, 50, 600),
                                            (300, 4, 64, 1100), (180, 4, 64, 2100), (520, 4, 64, 1100)])
 @pytest.mark.parametrize("act", [0, 3, 5])
 def test_both_query_blocks_in_a_wave(oracle, B, H, n, longest, act):
