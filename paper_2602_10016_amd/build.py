@@ -32,13 +32,14 @@ def _compile(src, extra=()):
     return obj, warn
 
 
-def _build_torch_call():
+def _build_torch_call(out=TORCH_CALL, library=LIB, extra=()):
     """The CPython module of the entry points' accepted case: host code only, against torch's C++ headers and the library."""
     from torch.utils.cpp_extension import include_paths, library_paths
     dirs = [*include_paths(), sysconfig.get_paths()["include"]]
     libs = library_paths()[0]
-    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", *[f"-I{d}" for d in dirs], os.path.join(CSRC, "torch_call.cpp"),
-           "-o", TORCH_CALL, f"-L{HERE}", "-l:libkunlun.so", "-Wl,-rpath,$ORIGIN", f"-L{libs}", "-ltorch_python", "-ltorch_cpu", "-lc10"]
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", *extra, *[f"-I{d}" for d in dirs], os.path.join(CSRC, "torch_call.cpp"),
+           "-o", out, f"-L{os.path.dirname(library)}", f"-l:{os.path.basename(library)}", "-Wl,-rpath,$ORIGIN", f"-L{libs}", "-ltorch_python",
+           "-ltorch_cpu", "-lc10"]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError(f"g++ failed on torch_call.cpp:\n{r.stdout}\n{r.stderr}")

@@ -9,10 +9,16 @@
 // So nothing is accepted here that is not accepted there.
 #include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
+#include <torch/csrc/utils/object_ptr.h>
 #include <ATen/ATen.h>
 #include <c10/core/impl/VirtualGuardImpl.h>
 
 #include "../../include/kunlun.h"
+
+// Device type of the tensors; the module can be built for host tensors, to run its checks in front of another library.
+#ifndef KUNLUN_CALL_DEVICE
+#define KUNLUN_CALL_DEVICE CUDA
+#endif
 
 namespace {
 
@@ -23,19 +29,20 @@ constexpr int64_t ANY = -1;
 // Arguments of one call.  Every accessor leaves ok = false where the argument is not of the plain kind.
 struct Call {
     bool ok = true;
-    int device = -1;
+    static constexpr int NONE_YET = -2;  // (-1: the index of a host tensor)
+    int device = NONE_YET;
     at::ScalarType type = at::ScalarType::Undefined;  // of the first tensor: bfloat16 or float32
 
     static bool is_plain(const at::Tensor& t) {
-        if (!t.defined() || t.layout() != at::kStrided || t.device().type() != at::kCUDA || !t.has_storage()) return false;
+        if (!t.defined() || t.layout() != at::kStrided || t.device().type() != c10::DeviceType::KUNLUN_CALL_DEVICE || !t.has_storage()) return false;
         const c10::DispatchKeySet odd({c10::DispatchKey::Python, c10::DispatchKey::FuncTorchBatched, c10::DispatchKey::FuncTorchGradWrapper,
                                        c10::DispatchKey::BatchedNestedTensor, c10::DispatchKey::Functionalize, c10::DispatchKey::ZeroTensor,
                                        c10::DispatchKey::Conjugate, c10::DispatchKey::Negative});
         return !t.key_set().has_any(odd) && t.is_contiguous();
     }
     bool same_device(const at::Tensor& t) {
-        if (device < 0) device = t.device().index();
-        return t.device().index() == device && device >= 0;
+        if (device == NONE_YET) device = t.device().index();
+        return t.device().index() == device;
     }
     // A tensor of the call's dtype (the first one sets it), shape (a, b, c); ANY: any extent.
     const at::Tensor* rows(PyObject* o, int64_t a, int64_t b, int64_t c) {
@@ -121,16 +128,17 @@ struct Out {
     }
 };
 
+// The items of a caller's list are held: another thread may replace them while the kernels are enqueued.
 struct Grads {
     Out g[3];
-    PyObject* given[3] = {Py_None, Py_None, Py_None};
+    THPObjectPtr given[3];
     // out: None or a sequence of three tensors shaped like the inputs
     void take(Call& c, PyObject* out, const at::Tensor* const (&like)[3]) {
         if (!c.ok) return;
         if (out != Py_None) {
             if (!(PyTuple_CheckExact(out) || PyList_CheckExact(out)) || PySequence_Fast_GET_SIZE(out) != 3) { c.ok = false; return; }
             for (int i = 0; i < 3; ++i) {
-                given[i] = PySequence_Fast_GET_ITEM(out, i);
+                given[i] = Py_NewRef(PySequence_Fast_GET_ITEM(out, i));
                 g[i].t = c.rows(given[i], like[i]->size(0), like[i]->size(1), like[i]->size(2));
             }
         }
@@ -143,7 +151,7 @@ struct Grads {
         PyObject* r = PyTuple_New(3);
         if (!r) return nullptr;
         for (int i = 0; i < 3; ++i) {
-            PyObject* o = g[i].object(given[i]);
+            PyObject* o = given[i] ? Py_NewRef(given[i].get()) : g[i].object(Py_None);
             if (!o) { Py_DECREF(r); return nullptr; }
             PyTuple_SET_ITEM(r, i, o);
         }

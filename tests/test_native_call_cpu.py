@@ -1,0 +1,132 @@
+"""The native marshalling (csrc/torch_call.cpp) on the CPU: built for host tensors, in front of a library of stubs that note
+their arguments, call back into Python in the middle of the call (the interpreter's lock is free there, as for another thread)
+and return the status they are told."""
+import ctypes
+import gc
+import importlib.machinery
+import importlib.util
+import os
+import re
+import subprocess
+import types
+import weakref
+
+import pytest
+import torch
+
+from paper_2602_10016_amd import build
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+H, D, N, B, T = 2, 64, 8, 3, 40
+ENTRIES = ["gdpa_fwd", "gdpa_bwd", "seed_attn_fwd", "seed_attn_bwd", "swa_fwd", "swa_bwd", "sumkron_fwd", "sumkron_bwd"]
+
+
+def stub_source():
+    """Every entry point of include/kunlun.h that returns a status: arguments as text into a buffer, then the hook."""
+    header = open(os.path.join(ROOT, "include", "kunlun.h")).read()
+    code = ['#include "kunlun.h"', "#include <stdio.h>", "char noted[4096]; int calls, status; void (*hook)(void);",
+            "size_t kunlun_workspace_bytes(int op, int B, int H, int d, int mq, int mk, int64_t tq, int64_t tk) { return 1000 + op; }",
+            "size_t kunlun_sumkron_workspace_bytes(int B, int S, int T, int D, int k, int dtype) { return 2000; }",
+            "size_t kunlun_sumkron_bwd_workspace_bytes(int B, int S, int T, int D, int k, int dtype) { return 3000; }"]
+    for name in ENTRIES:
+        args = re.search(rf"^int kunlun_{name}\(([^)]*)\);", header, flags=re.M).group(1)
+        formats, values = [], []
+        for arg in args.split(","):
+            kind, var = arg.replace("\n", " ").strip().rsplit(" ", 1)
+            var = var.lstrip("*")
+            pointer = "*" in arg
+            formats.append("%p" if pointer else {"float": "%.9g"}.get(kind, "%lld"))
+            values.append(f"(void*){var}" if pointer else f"(double){var}" if kind == "float" else f"(long long){var}")
+        code.append(f'int kunlun_{name}({args}) {{ ++calls; snprintf(noted, sizeof noted, "{" ".join(formats)}", {", ".join(values)}); '
+                    "if (hook) hook(); return status; }")
+    return "\n".join(code)
+
+
+class Stub:
+    def __init__(self, folder):
+        source, library, module = (os.path.join(folder, f) for f in ("stub.c", "libkunlun_stub.so", "_torch_call.so"))
+        with open(source, "w") as f:
+            f.write(stub_source())
+        subprocess.run(["gcc", "-shared", "-fPIC", f"-I{ROOT}/include", source, "-o", library], check=True)
+        build._build_torch_call(out=module, library=library, extra=["-O0", "-DKUNLUN_CALL_DEVICE=CPU"])
+        loader = importlib.machinery.ExtensionFileLoader("_torch_call", module)
+        self.native = importlib.util.module_from_spec(importlib.util.spec_from_loader("_torch_call", loader))
+        self.lib = ctypes.CDLL(library)
+        self.reset()
+
+    def reset(self, status=0, hook=None):
+        self.hook = ctypes.CFUNCTYPE(None)(hook) if hook else None
+        ctypes.c_void_p.in_dll(self.lib, "hook").value = ctypes.cast(self.hook, ctypes.c_void_p).value if hook else None
+        ctypes.c_int.in_dll(self.lib, "status").value = status
+        ctypes.c_int.in_dll(self.lib, "calls").value = 0
+
+    @property
+    def calls(self):
+        return ctypes.c_int.in_dll(self.lib, "calls").value
+
+    @property
+    def noted(self):
+        return (ctypes.c_char * 4096).in_dll(self.lib, "noted").value.decode().split()
+
+
+@pytest.fixture(scope="module")
+def built(tmp_path_factory):
+    return Stub(str(tmp_path_factory.mktemp("native")))
+
+
+@pytest.fixture
+def stub(built):
+    built.reset()
+    return built
+
+
+STREAM = types.SimpleNamespace(cuda_stream=0x5EED)
+
+
+def arguments(name, dtype=torch.bfloat16, **change):
+    """The arguments of a native entry point by name, in its order."""
+    r = lambda *s: torch.zeros(*s, dtype=dtype)
+    i = lambda *x: torch.tensor(x, dtype=torch.int32)
+    off, lse = i(0, 15, 15, T), torch.zeros(H, B * N)
+    kv = dict(k=r(T, H, D), v=r(T, H, D))
+    gdpa = dict(q=r(B * N, H, D), **kv)
+    seed = dict(e_seed=r(N, H, D), **kv)
+    swa = dict(q=r(T, H, D), **kv)
+    sk = dict(x=r(B, 64, 128), z=r(2, 64, 32), w=r(2, 128, 128))
+    o, d_o = r(B * N, H, D), r(B * N, H, D)
+    tail = dict(workspace=None, stream=STREAM)
+    fwd_tail = dict(out=None, lse=None, want_lse=True, **tail)
+    a = {"gdpa_fwd": dict(**gdpa, kv_offsets=off, scale=0.1, act=3, q_offsets=None, max_q=N, max_kv=25, **fwd_tail),
+         "gdpa_bwd": dict(**gdpa, d_o=d_o, kv_offsets=off, scale=0.1, act=0, o=o, lse=lse, q_offsets=None, max_q=N, max_kv=25, out=None, **tail),
+         "seed_attn_fwd": dict(**seed, kv_offsets=off, scale=0.1, act=0, max_kv=25, **fwd_tail),
+         "seed_attn_bwd": dict(**seed, d_o=d_o, kv_offsets=off, scale=0.1, act=0, o=o, lse=lse, max_kv=25, out=None, **tail),
+         "swa_fwd": dict(**swa, offsets=off, window_left=7, window_right=2, scale=0.1, max_len=25, **fwd_tail),
+         "swa_bwd": dict(**swa, o=r(T, H, D), lse=torch.zeros(H, T), d_o=r(T, H, D), offsets=off, window_left=7, window_right=2, scale=0.1,
+                         max_len=25, out=None, **tail),
+         "sumkron_fwd": dict(**sk, out=None, **tail),
+         "sumkron_bwd": dict(**sk, dy=r(B, 32, 128), **tail)}[name]
+    assert set(change) <= set(a)
+    a.update(change)
+    return a
+
+
+def gradients(a):
+    return [torch.zeros_like(t) for t in list(a.values())[:3]]
+
+
+@pytest.mark.parametrize("name", ["gdpa_bwd", "seed_attn_bwd", "swa_bwd"])
+def test_gradients_of_a_list_outlive_its_change_during_the_call(stub, name):
+    a = arguments(name)
+    a["out"] = gradients(a)
+    alive, pointers = [weakref.ref(t) for t in a["out"]], [t.data_ptr() for t in a["out"]]
+    during = []
+
+    def another_thread():
+        a["out"].clear()
+        gc.collect()
+        during.extend(w() is not None for w in alive)
+
+    stub.reset(hook=another_thread)
+    got = getattr(stub.native, name)(*a.values())
+    assert during == [True] * 3
+    assert [id(g) for g in got] == [id(w()) for w in alive] and [g.data_ptr() for g in got] == pointers
