@@ -178,13 +178,15 @@ void make_workspace(Out& ws, const at::Tensor& like, size_t nbytes) {
 
 template <typename T> const T* data(const at::Tensor* t) { return t ? (const T*)t->data_ptr() : nullptr; }
 
-template <typename F>
-int enqueue(F&& call) {  // the GIL is free while the kernels are enqueued
-    int rc;
-    Py_BEGIN_ALLOW_THREADS
-    rc = call();
-    Py_END_ALLOW_THREADS
-    return rc;
+// A call of the C ABI.  The arguments are complete before the interpreter's lock is given up: a tensor whose memory may not be
+// had throws where it can be reported, and no other thread changes a tensor between the checks and the reading of its pointer.
+template <typename... P, typename... A>
+int enqueue(int (*entry)(P...), A... arguments) {
+    struct Unlocked {
+        PyThreadState* const state = PyEval_SaveThread();
+        ~Unlocked() { PyEval_RestoreThread(state); }
+    } unlocked;
+    return entry(arguments...);
 }
 
 #define ENTRY(NAME, N)                                                              \
@@ -227,10 +229,9 @@ ENTRY(gdpa_fwd, 14)
     if (!o.t) o.make(*q, q->sizes(), q->scalar_type());
     if (!lse.t && want_lse) lse.make(*q, {H, total_q}, at::kFloat);
     make_workspace(ws, *q, ws.t ? 0 : kunlun_workspace_bytes(KUNLUN_OP_GDPA_FWD, (int)B, (int)H, (int)d, max_q, max_kv, total_q, total_kv));
-    const int rc = enqueue([&] {
-        return kunlun_gdpa_fwd(q->data_ptr(), k->data_ptr(), v->data_ptr(), o.ptr(), (float*)lse.ptr(), data<int32_t>(qo), data<int32_t>(kvo), (int)B,
-                               (int)H, (int)d, max_q, max_kv, total_q, total_kv, scale, act, nullptr, c.dtype(), ws.ptr(), (size_t)ws.t->numel(), s);
-    });
+    const int rc = enqueue(kunlun_gdpa_fwd, q->data_ptr(), k->data_ptr(), v->data_ptr(), o.ptr(), (float*)lse.ptr(),
+                           data<int32_t>(qo), data<int32_t>(kvo), (int)B, (int)H, (int)d, max_q, max_kv, total_q, total_kv,
+                           scale, act, nullptr, c.dtype(), ws.ptr(), (size_t)ws.t->numel(), s);
     DONE_OR_NONE(rc);
     return pair(o, a[9], lse, a[10]);
 END_ENTRY
@@ -263,11 +264,10 @@ ENTRY(gdpa_bwd, 15)
     PLAIN_OR_NONE;
     grads.allocate(like);
     make_workspace(ws, *q, ws.t ? 0 : kunlun_workspace_bytes(KUNLUN_OP_GDPA_BWD, (int)B, (int)H, (int)d, max_q, max_kv, total_q, total_kv));
-    const int rc = enqueue([&] {
-        return kunlun_gdpa_bwd(q->data_ptr(), k->data_ptr(), v->data_ptr(), data<void>(o), data<float>(lse), d_o->data_ptr(), grads.g[0].ptr(),
-                               grads.g[1].ptr(), grads.g[2].ptr(), data<int32_t>(qo), data<int32_t>(kvo), (int)B, (int)H, (int)d, max_q, max_kv,
-                               total_q, total_kv, scale, act, nullptr, c.dtype(), ws.ptr(), (size_t)ws.t->numel(), s);
-    });
+    const int rc = enqueue(kunlun_gdpa_bwd, q->data_ptr(), k->data_ptr(), v->data_ptr(), data<void>(o), data<float>(lse),
+                           d_o->data_ptr(), grads.g[0].ptr(), grads.g[1].ptr(), grads.g[2].ptr(), data<int32_t>(qo),
+                           data<int32_t>(kvo), (int)B, (int)H, (int)d, max_q, max_kv, total_q, total_kv, scale, act, nullptr,
+                           c.dtype(), ws.ptr(), (size_t)ws.t->numel(), s);
     DONE_OR_NONE(rc);
     return grads.result();
 END_ENTRY
@@ -298,10 +298,9 @@ ENTRY(seed_attn_fwd, 12)
     if (!o.t) o.make(*q, {total_q, H, d}, q->scalar_type());
     if (!lse.t && want_lse) lse.make(*q, {H, total_q}, at::kFloat);
     make_workspace(ws, *q, ws.t ? 0 : kunlun_workspace_bytes(KUNLUN_OP_SEED_FWD, (int)B, (int)H, (int)d, (int)seeds, max_kv, total_q, total_kv));
-    const int rc = enqueue([&] {
-        return kunlun_seed_attn_fwd(q->data_ptr(), k->data_ptr(), v->data_ptr(), o.ptr(), (float*)lse.ptr(), data<int32_t>(kvo), (int)B, (int)H, (int)d,
-                                    (int)seeds, max_kv, total_kv, scale, act, nullptr, c.dtype(), ws.ptr(), (size_t)ws.t->numel(), s);
-    });
+    const int rc = enqueue(kunlun_seed_attn_fwd, q->data_ptr(), k->data_ptr(), v->data_ptr(), o.ptr(), (float*)lse.ptr(),
+                           data<int32_t>(kvo), (int)B, (int)H, (int)d, (int)seeds, max_kv, total_kv, scale, act, nullptr,
+                           c.dtype(), ws.ptr(), (size_t)ws.t->numel(), s);
     DONE_OR_NONE(rc);
     return pair(o, a[7], lse, a[8]);
 END_ENTRY
@@ -334,11 +333,10 @@ ENTRY(seed_attn_bwd, 13)
     PLAIN_OR_NONE;
     grads.allocate(like);
     make_workspace(ws, *q, ws.t ? 0 : kunlun_workspace_bytes(KUNLUN_OP_SEED_BWD, (int)B, (int)H, (int)d, (int)seeds, max_kv, total_q, total_kv));
-    const int rc = enqueue([&] {
-        return kunlun_seed_attn_bwd(q->data_ptr(), k->data_ptr(), v->data_ptr(), data<void>(o), data<float>(lse), d_o->data_ptr(), grads.g[0].ptr(),
-                                    grads.g[1].ptr(), grads.g[2].ptr(), data<int32_t>(kvo), (int)B, (int)H, (int)d, (int)seeds, max_kv, total_kv, scale,
-                                    act, nullptr, c.dtype(), ws.ptr(), (size_t)ws.t->numel(), s);
-    });
+    const int rc = enqueue(kunlun_seed_attn_bwd, q->data_ptr(), k->data_ptr(), v->data_ptr(), data<void>(o), data<float>(lse),
+                           d_o->data_ptr(), grads.g[0].ptr(), grads.g[1].ptr(), grads.g[2].ptr(), data<int32_t>(kvo), (int)B,
+                           (int)H, (int)d, (int)seeds, max_kv, total_kv, scale, act, nullptr, c.dtype(), ws.ptr(),
+                           (size_t)ws.t->numel(), s);
     DONE_OR_NONE(rc);
     return grads.result();
 END_ENTRY
@@ -367,10 +365,9 @@ ENTRY(swa_fwd, 13)
     if (!o.t) o.make(*q, q->sizes(), q->scalar_type());
     if (!lse.t && want_lse) lse.make(*q, {H, total}, at::kFloat);
     make_workspace(ws, *q, ws.t ? 0 : kunlun_workspace_bytes(KUNLUN_OP_SWA_FWD, (int)B, (int)H, (int)d, max_len, max_len, total, total));
-    const int rc = enqueue([&] {
-        return kunlun_swa_fwd(q->data_ptr(), k->data_ptr(), v->data_ptr(), o.ptr(), (float*)lse.ptr(), data<int32_t>(off), (int)B, (int)H, (int)d, max_len,
-                              total, left, right, scale, c.dtype(), ws.ptr(), (size_t)ws.t->numel(), s);
-    });
+    const int rc = enqueue(kunlun_swa_fwd, q->data_ptr(), k->data_ptr(), v->data_ptr(), o.ptr(), (float*)lse.ptr(),
+                           data<int32_t>(off), (int)B, (int)H, (int)d, max_len, total, left, right, scale, c.dtype(), ws.ptr(),
+                           (size_t)ws.t->numel(), s);
     DONE_OR_NONE(rc);
     return pair(o, a[8], lse, a[9]);
 END_ENTRY
@@ -400,11 +397,9 @@ ENTRY(swa_bwd, 14)
     PLAIN_OR_NONE;
     grads.allocate(like);
     make_workspace(ws, *q, ws.t ? 0 : kunlun_workspace_bytes(KUNLUN_OP_SWA_BWD, (int)B, (int)H, (int)d, max_len, max_len, total, total));
-    const int rc = enqueue([&] {
-        return kunlun_swa_bwd(q->data_ptr(), k->data_ptr(), v->data_ptr(), o->data_ptr(), data<float>(lse), d_o->data_ptr(), grads.g[0].ptr(),
-                              grads.g[1].ptr(), grads.g[2].ptr(), data<int32_t>(off), (int)B, (int)H, (int)d, max_len, total, left, right, scale,
-                              c.dtype(), ws.ptr(), (size_t)ws.t->numel(), s);
-    });
+    const int rc = enqueue(kunlun_swa_bwd, q->data_ptr(), k->data_ptr(), v->data_ptr(), o->data_ptr(), data<float>(lse),
+                           d_o->data_ptr(), grads.g[0].ptr(), grads.g[1].ptr(), grads.g[2].ptr(), data<int32_t>(off), (int)B,
+                           (int)H, (int)d, max_len, total, left, right, scale, c.dtype(), ws.ptr(), (size_t)ws.t->numel(), s);
     DONE_OR_NONE(rc);
     return grads.result();
 END_ENTRY
@@ -427,10 +422,8 @@ ENTRY(sumkron_fwd, 6)
     PLAIN_OR_NONE;
     if (!y.t) y.make(*x, {B, T, D}, x->scalar_type());
     make_workspace(ws, *x, ws.t ? 0 : kunlun_sumkron_workspace_bytes((int)B, (int)S, (int)T, (int)D, (int)k, c.dtype()));
-    const int rc = enqueue([&] {
-        return kunlun_sumkron_fwd(x->data_ptr(), z->data_ptr(), w->data_ptr(), y.ptr(), (int)B, (int)S, (int)T, (int)D, (int)k, c.dtype(), ws.ptr(),
-                                  (size_t)ws.t->numel(), s);
-    });
+    const int rc = enqueue(kunlun_sumkron_fwd, x->data_ptr(), z->data_ptr(), w->data_ptr(), y.ptr(), (int)B, (int)S, (int)T,
+                           (int)D, (int)k, c.dtype(), ws.ptr(), (size_t)ws.t->numel(), s);
     DONE_OR_NONE(rc);
     return y.object(a[3]);
 END_ENTRY
@@ -455,10 +448,9 @@ ENTRY(sumkron_bwd, 6)
     const at::Tensor* const like[3] = {x, z, w};
     grads.allocate(like);
     make_workspace(ws, *x, ws.t ? 0 : kunlun_sumkron_bwd_workspace_bytes((int)B, (int)S, (int)T, (int)D, (int)k, c.dtype()));
-    const int rc = enqueue([&] {
-        return kunlun_sumkron_bwd(x->data_ptr(), z->data_ptr(), w->data_ptr(), dy->data_ptr(), grads.g[0].ptr(), grads.g[1].ptr(), grads.g[2].ptr(),
-                                  (int)B, (int)S, (int)T, (int)D, (int)k, c.dtype(), ws.ptr(), (size_t)ws.t->numel(), s);
-    });
+    const int rc = enqueue(kunlun_sumkron_bwd, x->data_ptr(), z->data_ptr(), w->data_ptr(), dy->data_ptr(), grads.g[0].ptr(),
+                           grads.g[1].ptr(), grads.g[2].ptr(), (int)B, (int)S, (int)T, (int)D, (int)k, c.dtype(), ws.ptr(),
+                           (size_t)ws.t->numel(), s);
     DONE_OR_NONE(rc);
     return grads.result();
 END_ENTRY

@@ -130,3 +130,12 @@ def test_gradients_of_a_list_outlive_its_change_during_the_call(stub, name):
     got = getattr(stub.native, name)(*a.values())
     assert during == [True] * 3
     assert [id(g) for g in got] == [id(w()) for w in alive] and [g.data_ptr() for g in got] == pointers
+
+
+@pytest.mark.parametrize("name", ENTRIES)
+def test_memory_that_may_not_be_had_is_an_error(stub, name):
+    a = arguments(name)
+    torch._C._set_throw_on_mutable_data_ptr(list(a.values())[1])
+    with pytest.raises(RuntimeError):
+        getattr(stub.native, name)(*a.values())
+    assert stub.calls == 0
