@@ -4,9 +4,10 @@
 // whose kernels take less 156 -> 124 us.
 //
 // A function returns None for everything that is not plainly right - another type or dtype, a strided view, a tensor of a
-// subclass or a transform, a wrong shape or device, an int that is no int, an error status - before anything is enqueued
-// (or, for a refused launch, after); the Python function then takes its own way, which raises what there is to raise.
-// So nothing is accepted here that is not accepted there.
+// subclass or a transform, a wrong shape or device, an int that is no int, the error status of an argument - before anything
+// is enqueued; the Python function then takes its own way, which raises what there is to raise.  So nothing is accepted here
+// that is not accepted there.  A launch that the HIP runtime refuses raises KunlunError here: work may be enqueued by then,
+// and the call is not made again.
 #include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
 #include <torch/csrc/utils/object_ptr.h>
@@ -189,6 +190,14 @@ int enqueue(int (*entry)(P...), A... arguments) {
     return entry(arguments...);
 }
 
+PyObject* raise_status(int rc) {
+    THPObjectPtr binding(PyImport_ImportModule("paper_2602_10016_amd.binding"));
+    THPObjectPtr type(binding ? PyObject_GetAttrString(binding, "KunlunError") : nullptr);
+    THPObjectPtr error(type ? PyObject_CallFunction(type, "i", rc) : nullptr);
+    if (error) PyErr_SetObject(type, error);
+    return nullptr;
+}
+
 #define ENTRY(NAME, N)                                                              \
     PyObject* NAME(PyObject*, PyObject* const* a, Py_ssize_t n) {                   \
         HANDLE_TH_ERRORS                                                            \
@@ -200,6 +209,7 @@ int enqueue(int (*entry)(P...), A... arguments) {
 #define PLAIN_OR_NONE \
     if (!c.ok) Py_RETURN_NONE
 #define DONE_OR_NONE(RC) \
+    if ((RC) == KUNLUN_ERR_LAUNCH) return raise_status(RC); \
     if ((RC) != KUNLUN_OK) Py_RETURN_NONE
 
 // q, k, v, kv_offsets, scale, act, q_offsets, max_q, max_kv, out, lse, want_lse, workspace, stream

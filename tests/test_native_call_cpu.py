@@ -139,3 +139,16 @@ def test_memory_that_may_not_be_had_is_an_error(stub, name):
     with pytest.raises(RuntimeError):
         getattr(stub.native, name)(*a.values())
     assert stub.calls == 0
+
+
+@pytest.mark.parametrize("name", ENTRIES)
+def test_a_refused_launch_raises_without_a_second_call(stub, name):
+    """The launchers report after kernels are enqueued: the Python code behind must not make the call again."""
+    from paper_2602_10016_amd import binding as kb
+    stub.reset(status=kb.ERR_LAUNCH)
+    with pytest.raises(kb.KunlunError) as error:
+        getattr(stub.native, name)(*arguments(name).values())
+    assert error.value.status == kb.ERR_LAUNCH and stub.calls == 1
+    for status in (kb.ERR_NULL, kb.ERR_SHAPE, kb.ERR_UNSUPPORTED, kb.ERR_ALIGN, kb.ERR_WORKSPACE):  # of an argument: nothing is enqueued
+        stub.reset(status=status)
+        assert getattr(stub.native, name)(*arguments(name).values()) is None and stub.calls == 1
