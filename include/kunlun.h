@@ -225,9 +225,9 @@ int kunlun_swa_bwd(const void* q, const void* k, const void* v, const void* o, c
                    size_t workspace_bytes, void* stream);
 
 /* Bytes of workspace for a call of `op` (kunlun_op) with these sizes.  A workspace of the size for some batch also
- * serves the calls with the same H, d, max_q and max_kv, no more examples and no more rows - except backward calls with
- * max_kv <= 32 and max_q > 64, whose partial sums may take more room for a smaller batch: size those for each batch.
- * (Backward calls with 65..256 queries per example at d = 128 and a history that would set their time alone also have
+ * serves the calls with the same H, d, max_q and max_kv, no more examples and no more rows.  (Backward calls with
+ * max_kv <= 32 and max_q > 64 may have a larger size for a smaller batch: with less room they keep fewer partial sums, which
+ * are added in another order.  Backward calls with 65..256 queries per example at d = 128 and a history that would set their time alone also have
  * a larger size for some smaller batches: they add partial sums over ranges of the histories where the workspace has
  * room for them, and take other kernels, which round differently, where it has not.)  Returns 0 for an unknown op or
  * negative sizes.  For the sliding-window ops pass max_len as max_q and max_kv and total as total_q and total_kv; for

@@ -38,15 +38,16 @@ int fill_acts(AttnParams& p, int H, int act, const int32_t* head_act, bool& any_
 
 size_t order_bytes(int B) { return align_up((size_t)(B + 1) * sizeof(int32_t), 256); }
 
-// What a backward call cannot do without.  With more than 32 keys or up to 64 queries per example never more for fewer
-// examples or tokens, so that a kept workspace serves smaller batches.
-size_t bwd_bytes(int B, int H, int d, int max_q, int max_kv, int64_t total_q, int64_t total_kv, bool windowed) {
-    return WS_HEADER_BYTES + order_bytes(B) + mfma_bwd_tiled_workspace(B, H, d, max_q, max_kv, total_q, total_kv, windowed);
+// What a backward call takes with these query tiles per workgroup (at most 32 keys per example; else they count for nothing).
+// With FEWKEYS_MAX_TILES it is what the call cannot do without: never more for fewer examples or tokens, so that a kept
+// workspace serves smaller batches.
+size_t bwd_bytes(int B, int H, int d, int max_q, int max_kv, int64_t total_q, int64_t total_kv, bool windowed, int chunk_tiles) {
+    return WS_HEADER_BYTES + order_bytes(B) + mfma_bwd_tiled_workspace(B, H, d, max_q, max_kv, total_q, total_kv, windowed, chunk_tiles);
 }
 // ... of shared seeds: behind that, the per-example query gradients (at most 4 bytes per element) and the partial sums
 // over the batch
-size_t seed_bwd_bytes(int B, int H, int d, int n_seeds, int max_kv, int64_t total_q, int64_t total_kv) {
-    return bwd_bytes(B, H, d, n_seeds, max_kv, total_q, total_kv, false) + seed_grad_rows_bytes(total_q, H, d, KUNLUN_FP32) +
+size_t seed_bwd_bytes(int B, int H, int d, int n_seeds, int max_kv, int64_t total_q, int64_t total_kv, int chunk_tiles) {
+    return bwd_bytes(B, H, d, n_seeds, max_kv, total_q, total_kv, false, chunk_tiles) + seed_grad_rows_bytes(total_q, H, d, KUNLUN_FP32) +
            seed_grad_partial_bytes(B, (int64_t)n_seeds * H * d);
 }
 
@@ -69,11 +70,12 @@ size_t kunlun_workspace_bytes(int op, int B, int H, int d, int max_q, int max_kv
         return WS_HEADER_BYTES + tile_table_bytes(B, total_q);
     // (+ the partial query gradients of the one-pass kernel's ranges, which a call can do without)
     case KUNLUN_OP_SEED_BWD:
-        return seed_bwd_bytes(B, H, d, max_q, max_kv, total_q, total_kv) + mfma_bwd_wide_workspace(B, H, d, max_q, max_kv, total_kv);
+        return seed_bwd_bytes(B, H, d, max_q, max_kv, total_q, total_kv, fewkeys_chunk_tiles(B, H, total_q)) + mfma_bwd_wide_workspace(B, H, d, max_q, max_kv, total_kv);
     case KUNLUN_OP_GDPA_BWD:
-        return bwd_bytes(B, H, d, max_q, max_kv, total_q, total_kv, false) + mfma_bwd_wide_workspace(B, H, d, max_q, max_kv, total_kv);
+        return bwd_bytes(B, H, d, max_q, max_kv, total_q, total_kv, false, fewkeys_chunk_tiles(B, H, total_q)) +
+               mfma_bwd_wide_workspace(B, H, d, max_q, max_kv, total_kv);
     case KUNLUN_OP_SWA_BWD:
-        return bwd_bytes(B, H, d, max_q, max_kv, total_q, total_kv, true);
+        return bwd_bytes(B, H, d, max_q, max_kv, total_q, total_kv, true, 0);
     default:
         return 0;
     }
@@ -295,8 +297,12 @@ int gdpa_bwd_checked(const void* q, const void* k, const void* v, const void* o,
         !aligned(dq, 16) || !aligned(dk, 16) || !aligned(dv, 16) || !aligned(lse, 4) || !aligned(q_offsets, 4) ||
         !aligned(kv_offsets, 4))
         return KUNLUN_ERR_ALIGN;
-    const size_t base_bytes = bwd_bytes(B, H, d, max_q, max_kv, total_q, total_kv, false);
-    const size_t need_bytes = q_shared ? seed_bwd_bytes(B, H, d, max_q, max_kv, total_q, total_kv) : base_bytes;
+    // a workspace kept from a larger batch may have room for fewer partial sums than the fastest form leaves: more tiles each
+    int chunk_tiles = fewkeys_chunk_tiles(B, H, total_q);
+    auto base = [&] { return bwd_bytes(B, H, d, max_q, max_kv, total_q, total_kv, false, chunk_tiles); };
+    auto need = [&] { return q_shared ? seed_bwd_bytes(B, H, d, max_q, max_kv, total_q, total_kv, chunk_tiles) : base(); };
+    while (workspace_bytes < need() && chunk_tiles < FEWKEYS_MAX_TILES) ++chunk_tiles;
+    const size_t base_bytes = base(), need_bytes = need();
     if (!workspace || workspace_bytes < need_bytes) return KUNLUN_ERR_WORKSPACE;
     if (!aligned(workspace, 256)) return KUNLUN_ERR_ALIGN;
 
@@ -334,7 +340,7 @@ int gdpa_bwd_checked(const void* q, const void* k, const void* v, const void* o,
         char* const order = (char*)workspace + WS_HEADER_BYTES;
         e = launch_mfma_bwd_wide(p, workspace, order, order + order_bytes(B), (char*)workspace + need_bytes, s);
     } else if (mfma_bwd_tiled_supported(p, dtype)) {
-        e = launch_mfma_bwd_tiled(p, (char*)workspace + WS_HEADER_BYTES + order_bytes(B), any_softmax, s);
+        e = launch_mfma_bwd_tiled(p, (char*)workspace + WS_HEADER_BYTES + order_bytes(B), any_softmax, chunk_tiles, s);
     } else {
         e = launch_scalar_bwd(p, dtype, s);
     }
@@ -420,7 +426,7 @@ int kunlun_swa_bwd(const void* q, const void* k, const void* v, const void* o, c
     p.right = (window_right < 0 || window_right >= max_len) ? -1 : window_right;
     hipError_t e;
     if (mfma_bwd_tiled_supported(p, dtype))
-        e = launch_mfma_bwd_tiled(p, (char*)workspace + WS_HEADER_BYTES + order_bytes(B), true, (hipStream_t)stream);
+        e = launch_mfma_bwd_tiled(p, (char*)workspace + WS_HEADER_BYTES + order_bytes(B), true, 0, (hipStream_t)stream);
     else  // one wavefront per gradient row: dQ rows over their windows, then dK/dV rows
         e = launch_scalar_bwd(p, dtype, (hipStream_t)stream);
     return e == hipSuccess ? KUNLUN_OK : KUNLUN_ERR_LAUNCH;

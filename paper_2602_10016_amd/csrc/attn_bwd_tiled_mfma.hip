@@ -645,12 +645,12 @@ struct FewKeysSmem {
 // partial sums to write and read back, fewer workgroups mean an emptier machine.  Training step, us, with 2 / 4 / 6 / 8 tiles:
 // 5120 tile-heads, d = 128: 192 / 179 / 174 / 185;  10240, d = 64: 202 / 186 / 184 / 183;  11 700 (log-normal): 244 / 225 / 222 / 223;
 // 20 000, d = 128: 708 / 658 / 654 / 652.
-inline int fewkeys_chunk_tiles(int B, int H, int64_t total_q) {
+int fewkeys_chunk_tiles(int B, int H, int64_t total_q) {
     const int64_t wgs = (total_q / TILE_ROWS + B) * H;
-    return wgs >= 16384 ? 8 : (wgs >= 4096 ? 6 : (wgs >= 2048 ? 2 : 1));
+    return wgs >= 16384 ? FEWKEYS_MAX_TILES : (wgs >= 4096 ? 6 : (wgs >= 2048 ? 2 : 1));
 }
-inline size_t fewkeys_partial_bytes(int B, int H, int d, int64_t total_q) {
-    const int chunk_rows = TILE_ROWS * fewkeys_chunk_tiles(B, H, total_q);
+inline size_t fewkeys_partial_bytes(int B, int H, int d, int64_t total_q, int chunk_tiles) {
+    const int chunk_rows = TILE_ROWS * chunk_tiles;
     return align_up((size_t)(total_q / chunk_rows + B) * H * 2 * KT * d * sizeof(float), 256);
 }
 inline bool fewkeys_applies(int d, int max_q, int max_kv, bool windowed) {
@@ -906,9 +906,9 @@ bool mfma_bwd_tiled_supported(const AttnParams& p, int dtype) {
     return dtype == KUNLUN_BF16 && (p.d == 32 || p.d == 64 || p.d == 128);
 }
 
-size_t mfma_bwd_tiled_workspace(int B, int H, int d, int max_q, int max_kv, int64_t total_q, int64_t total_kv, bool windowed) {
+size_t mfma_bwd_tiled_workspace(int B, int H, int d, int max_q, int max_kv, int64_t total_q, int64_t total_kv, bool windowed, int chunk_tiles) {
     return tile_table_bytes(B, total_q) + tile_table_bytes(B, total_kv) + align_up((size_t)H * total_q * sizeof(float), 256) +
-           (fewkeys_applies(d, max_q, max_kv, windowed) ? fewkeys_partial_bytes(B, H, d, total_q) : 0);
+           (fewkeys_applies(d, max_q, max_kv, windowed) ? fewkeys_partial_bytes(B, H, d, total_q, chunk_tiles) : 0);
 }
 
 template <int D, bool WINDOWED, int NW>
@@ -945,7 +945,7 @@ static hipError_t launch_tiled(const AttnParams& p, char* ws, bool any_softmax, 
 }
 
 template <int D>
-static hipError_t launch_fewkeys(const AttnParams& p, char* ws, bool any_softmax, hipStream_t stream) {
+static hipError_t launch_fewkeys(const AttnParams& p, char* ws, bool any_softmax, int chunk_tiles, hipStream_t stream) {
     int32_t* q_tiles = (int32_t*)ws;
     float* delta = (float*)(ws + tile_table_bytes(p.B, p.total_q) + tile_table_bytes(p.B, p.total_kv));
     float* partial = (float*)((char*)delta + align_up((size_t)p.H * p.total_q * sizeof(float), 256));
@@ -961,7 +961,7 @@ static hipError_t launch_fewkeys(const AttnParams& p, char* ws, bool any_softmax
         hipLaunchKernelGGL((delta_kernel<D>), dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, stream,
                            (const bf16_t*)p.o, (const bf16_t*)p.d_o, delta, p.total_q, p.H);
     }
-    const int chunk_rows = TILE_ROWS * fewkeys_chunk_tiles(p.B, p.H, p.total_q);
+    const int chunk_rows = TILE_ROWS * chunk_tiles;
     hipLaunchKernelGGL(tile_prefix_kernel<1>, dim3(1), dim3(1024), 0, stream, p.q_off, p.max_q, p.B, q_tiles,
                        tile_example_of(q_tiles, p.B), chunk_rows);
     if (p.total_q > 0) {
@@ -977,11 +977,11 @@ static hipError_t launch_fewkeys(const AttnParams& p, char* ws, bool any_softmax
     return hipGetLastError();
 }
 
-hipError_t launch_mfma_bwd_tiled(const AttnParams& p, void* workspace_tail, bool any_softmax, hipStream_t stream) {
+hipError_t launch_mfma_bwd_tiled(const AttnParams& p, void* workspace_tail, bool any_softmax, int chunk_tiles, hipStream_t stream) {
     char* ws = (char*)workspace_tail;
     if (fewkeys_applies(p.d, p.max_q, p.max_kv, p.windowed != 0))
-        return p.d == 128 ? launch_fewkeys<128>(p, ws, any_softmax, stream)
-               : p.d == 64 ? launch_fewkeys<64>(p, ws, any_softmax, stream) : launch_fewkeys<32>(p, ws, any_softmax, stream);
+        return p.d == 128 ? launch_fewkeys<128>(p, ws, any_softmax, chunk_tiles, stream)
+               : p.d == 64 ? launch_fewkeys<64>(p, ws, any_softmax, chunk_tiles, stream) : launch_fewkeys<32>(p, ws, any_softmax, chunk_tiles, stream);
     if (p.windowed)
         return p.d == 128 ? launch_tiled<128, true>(p, ws, true, stream)
                : p.d == 64 ? launch_tiled<64, true>(p, ws, true, stream) : launch_tiled<32, true>(p, ws, true, stream);
