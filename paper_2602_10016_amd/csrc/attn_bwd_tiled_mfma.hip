@@ -528,9 +528,13 @@ __device__ __forceinline__ void bwd_dkdv_item(const AttnParams& p, const float* 
     }
     __syncthreads();  // every wave is done with the ring
     if (!wave_active) return;
+    // (the lane again, by an opaque move: what the stores derive from it is computed here and not kept across the loop, where the
+    // workgroups of two waves had no register for it and went to scratch memory, at d = 128 inside the loop)
+    int out_lane = threadIdx.x & 63;
+    asm volatile("" : "+v"(out_lane));
     char* out_stage = lds + wave * PT::ROW_TILE;
-    store_tile_rows<D>(out_stage, dvacc, (bf16_t*)p.dv + (k_row0 + k_lo_w) * hd + (int64_t)h * D, hd, nk, lane);
-    store_tile_rows<D>(out_stage, dkacc, (bf16_t*)p.dk + (k_row0 + k_lo_w) * hd + (int64_t)h * D, hd, nk, lane);
+    store_tile_rows<D>(out_stage, dvacc, (bf16_t*)p.dv + (k_row0 + k_lo_w) * hd + (int64_t)h * D, hd, nk, out_lane);
+    store_tile_rows<D>(out_stage, dkacc, (bf16_t*)p.dk + (k_row0 + k_lo_w) * hd + (int64_t)h * D, hd, nk, out_lane);
 }
 
 // ------------------------------------------------------------------ kernels

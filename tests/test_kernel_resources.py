@@ -1,0 +1,26 @@
+"""Registers of built kernels: what the key loop of the window backward holds must not go to scratch memory, because a reload
+waits together with the tile loads in flight."""
+import os
+import re
+import subprocess
+
+from paper_2602_10016_amd import build
+
+LLVM = "/opt/rocm/llvm/bin/"
+
+
+def spilled_vector_registers(source, tmp_path):
+    """Mangled kernel name -> spilled vector registers, from the metadata of the object that was built from `source`."""
+    build.build()
+    bundle, code = tmp_path / "bundle", tmp_path / "code"
+    subprocess.run([LLVM + "llvm-objcopy", "--dump-section", f".hip_fatbin={bundle}", os.path.join(build.OBJ, source.replace(".hip", ".o")), os.devnull],
+                   check=True)
+    subprocess.run([LLVM + "clang-offload-bundler", "--type=o", "--unbundle", f"--input={bundle}", "--targets=hipv4-amdgcn-amd-amdhsa--gfx950",
+                    f"--output={code}"], check=True)
+    notes = subprocess.run([LLVM + "llvm-readelf", "--notes", str(code)], check=True, capture_output=True, text=True).stdout
+    return {name: int(n) for name, n in re.findall(r"\.name: +(\S+)\n(?:(?!\.name).)*?\.vgpr_spill_count: (\d+)", notes, flags=re.S)}
+
+
+def test_the_window_backward_keeps_its_registers(tmp_path):
+    spilled = {n: s for n, s in spilled_vector_registers("attn_bwd_tiled_mfma.hip", tmp_path).items() if re.search(r"bwd_(dq|dkdv)_kernel", n)}
+    assert len(spilled) == 16 and not any(spilled.values()), spilled
