@@ -5,10 +5,13 @@
 // example, then tile, then head.  tile_start[b] = number of tiles before example b and
 // tile_example[t] = example of tile t (both written by the prefix kernel), so a workgroup finds
 // its item with two dependent loads.
-// Inside its range an XCD takes the items in order: a tile and its successor, H items further on, run side by side.  (Starting a
-// tile when its predecessor is one tile width into its window, so that both read the rows they share at the same time, costs
-// up to 8 %: sliding-window forward, 128 sequences of 256..2048, 4 heads, d = 128, previous 64: in order 120 us, 32 slots
-// apart 131; 512 log-normal sequences, 8 heads, previous 64: 875 / 948, 255 to both sides 1656 / 1689.)
+// Inside its range an XCD takes the items in order: a tile and its successor, H items further on, run side by side.  (Cut into
+// `runs` contiguous runs that are issued in turn, a tile starts when its predecessor is one tile width into its window, and both
+// read the rows they share at the same time.  That costs up to 8 % in large launches: sliding-window forward, 128 sequences of
+// 256..2048, 4 heads, d = 128, previous 64: in order 120 us, 32 slots apart 131; 512 log-normal sequences, 8 heads, previous 64: 875 /
+// 948, 255 to both sides 1656 / 1689.  In order over in turn, 3000 random forward calls: d = 32 1.02 at every size, d = 64 1.00 up to 2000
+// tile-heads and 1.02 beyond, d = 128 1.02 up to 512, 0.99 from there to 1800 and 1.02 beyond; what is lost is lost in narrow windows over
+// long sequences, 2.5 % in the mean and up to 6 from 1024 to 1792 tile-heads, and tile_runs() cuts those.)
 #pragma once
 #include "common.h"
 
@@ -24,18 +27,33 @@ inline int32_t* tile_example_of(int32_t* tile_start, int B) {
     return (int32_t*)((char*)tile_start + align_up((size_t)(B + 1) * sizeof(int32_t), 256));
 }
 // grid size (an upper bound of the tile count sizes it; surplus workgroups exit at once)
-inline unsigned tile_grid(int B, int H, int64_t total_rows) {
+inline unsigned tile_grid(int B, int H, int64_t total_rows, int runs = 1) {
     const int64_t per_xcd = ((total_rows / TILE_ROWS + B) * H + 7) / 8;
-    return (unsigned)((per_xcd + 1) * 8);
+    return (unsigned)((per_xcd + runs) * 8);
+}
+// tiles times heads: half a tile more per example than its rows fill
+inline int64_t tiles_expected(const AttnParams& p) { return (p.total_q / TILE_ROWS + (p.B + 1) / 2) * p.H; }
+// Runs per XCD of a forward launch: with about 96 workgroups resident there, a tile and its successor start 48 slots apart.
+inline int tile_runs(const AttnParams& p) {
+    const int64_t tiles = tiles_expected(p);
+    if (!p.windowed || p.d != 128 || p.left < 0 || p.right < 0 || (int64_t)p.left + p.right > TILE_ROWS) return 1;
+    if (tiles <= 1024 || tiles > 1792 || p.total_q < (int64_t)512 * p.B) return 1;
+    const int want = 48 / p.H;
+    return want < 1 ? 1 : (want > 32 ? 32 : want);
 }
 #ifdef __HIPCC__
 __device__ __forceinline__ bool locate_tile(const int32_t* __restrict__ tile_start,
                                             const int32_t* __restrict__ tile_example, int B, int H, unsigned block,
-                                            int& b, int& h, int& t) {
+                                            int& b, int& h, int& t, int runs = 1) {
     const int64_t n_items = (int64_t)tile_start[B] * H;
     const int64_t per_xcd = (n_items + 7) / 8;
     const int xcd = block & 7;
-    const int64_t in_xcd = block >> 3;
+    int64_t in_xcd = block >> 3;
+    if (runs > 1) {
+        const unsigned slot = block >> 3, run_len = ((unsigned)per_xcd + runs - 1) / runs;
+        if (slot >= run_len * runs) return false;
+        in_xcd = (slot % runs) * run_len + slot / runs;
+    }
     if (in_xcd >= per_xcd) return false;
     const int64_t item = xcd * per_xcd + in_xcd;
     if (item >= n_items) return false;
