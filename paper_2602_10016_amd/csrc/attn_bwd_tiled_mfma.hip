@@ -938,13 +938,21 @@ static hipError_t launch_passes(const AttnParams& p, char* ws, bool any_softmax,
 
 template <int D, bool WINDOWED>
 static hipError_t launch_tiled(const AttnParams& p, char* ws, bool any_softmax, hipStream_t stream) {
-    // Narrow windows: workgroups of two waves (64 rows) and a ring of two stages, four instead of two workgroups per compute
-    // unit - fewer steps in which a wave of the workgroup is outside its own window (previous 256: a tenth instead of a
-    // quarter), for more tile loads per row, which is what counts in wide windows.  Training step, us, four / two waves:
-    // d = 128, previous 256: 635 / 623, previous 64: 505 / 503, 500 to both sides: 693 / 714;  d = 64, previous 256: 348 / 340,
-    // 50 to both sides: 570 / 560;  d = 32, previous 256: 434 / 433 (a tile is two load instructions there)
-    if constexpr (WINDOWED && D > 32)
-        if (p.left >= 0 && p.right >= 0 && (int64_t)p.left + p.right < 384) return launch_passes<D, WINDOWED, 2>(p, ws, any_softmax, stream);
+    // Narrow windows: workgroups of two waves (64 rows) and a ring of two stages, four (d = 128) or six (d = 64) instead of two or
+    // three workgroups per compute unit - fewer steps in which a wave of the workgroup is outside its own window (previous 256: a
+    // tenth instead of a quarter), for more tile loads per row, which is what counts in wide windows.  Training step, us, four /
+    // two waves: d = 128, previous 256: 635 / 623, previous 64: 505 / 503, 500 to both sides: 693 / 714;  d = 64, previous 256:
+    // 348 / 340, 50 to both sides: 570 / 560;  d = 32, previous 256: 434 / 433 (a tile is two load instructions there).
+    // Backward alone, 500 random calls, two waves over four by reach (d = 64 / d = 128): 100..199 1.12 / 1.11, 200..383 1.07 / 1.07,
+    // 384..449 1.05 / 1.06, 450..549 1.05 / 1.03 with losses of up to 4 % at d = 128, 550..699 1.03 / 1.01 - but for half to one tile
+    // of 128 rows per compute unit, where four waves have a unit to themselves and two workgroups of two share one: d = 64 1.00 from a
+    // reach of 300 on (down to 0.94), d = 128 0.99 from 200 on (down to 0.86).
+    if constexpr (WINDOWED && D > 32) {
+        const int64_t reach = (int64_t)p.left + p.right, tiles = tiles_expected(p);
+        const bool alone = 2 * tiles > compute_units() && tiles <= compute_units();
+        if (p.left >= 0 && p.right >= 0 && reach < (alone ? (D == 64 ? 320 : 200) : D == 64 ? 704 : 448))
+            return launch_passes<D, WINDOWED, 2>(p, ws, any_softmax, stream);
+    }
     return launch_passes<D, WINDOWED, 4>(p, ws, any_softmax, stream);
 }
 
