@@ -70,9 +70,9 @@ size_t kunlun_workspace_bytes(int op, int B, int H, int d, int max_q, int max_kv
         return WS_HEADER_BYTES + tile_table_bytes(B, total_q);
     // (+ the partial query gradients of the one-pass kernel's ranges, which a call can do without)
     case KUNLUN_OP_SEED_BWD:
-        return seed_bwd_bytes(B, H, d, max_q, max_kv, total_q, total_kv, fewkeys_chunk_tiles(B, H, total_q)) + mfma_bwd_wide_workspace(B, H, d, max_q, max_kv, total_kv);
+        return seed_bwd_bytes(B, H, d, max_q, max_kv, total_q, total_kv, fewkeys_chunk_tiles(B, H, d, total_q)) + mfma_bwd_wide_workspace(B, H, d, max_q, max_kv, total_kv);
     case KUNLUN_OP_GDPA_BWD:
-        return bwd_bytes(B, H, d, max_q, max_kv, total_q, total_kv, false, fewkeys_chunk_tiles(B, H, total_q)) +
+        return bwd_bytes(B, H, d, max_q, max_kv, total_q, total_kv, false, fewkeys_chunk_tiles(B, H, d, total_q)) +
                mfma_bwd_wide_workspace(B, H, d, max_q, max_kv, total_kv);
     case KUNLUN_OP_SWA_BWD:
         return bwd_bytes(B, H, d, max_q, max_kv, total_q, total_kv, true, 0);
@@ -298,7 +298,7 @@ int gdpa_bwd_checked(const void* q, const void* k, const void* v, const void* o,
         !aligned(kv_offsets, 4))
         return KUNLUN_ERR_ALIGN;
     // a workspace kept from a larger batch may have room for fewer partial sums than the fastest form leaves: more tiles each
-    int chunk_tiles = fewkeys_chunk_tiles(B, H, total_q);
+    int chunk_tiles = fewkeys_chunk_tiles(B, H, d, total_q);
     auto base = [&] { return bwd_bytes(B, H, d, max_q, max_kv, total_q, total_kv, false, chunk_tiles); };
     auto need = [&] { return q_shared ? seed_bwd_bytes(B, H, d, max_q, max_kv, total_q, total_kv, chunk_tiles) : base(); };
     while (workspace_bytes < need() && chunk_tiles < FEWKEYS_MAX_TILES) ++chunk_tiles;

@@ -648,10 +648,14 @@ struct FewKeysSmem {
 // Query tiles that one workgroup walks (accumulating dK / dV in registers): more tiles mean fewer
 // partial sums to write and read back, fewer workgroups mean an emptier machine.  Training step, us, with 2 / 4 / 6 / 8 tiles:
 // 5120 tile-heads, d = 128: 192 / 179 / 174 / 185;  10240, d = 64: 202 / 186 / 184 / 183;  11 700 (log-normal): 244 / 225 / 222 / 223;
-// 20 000, d = 128: 708 / 658 / 654 / 652.
-int fewkeys_chunk_tiles(int B, int H, int64_t total_q) {
+// 20 000, d = 128: 708 / 658 / 654 / 652.  Six instead of four, backward alone, 210 random calls from 4096 to 16 383 tile-heads with 900
+// and more queries in the mean: d = 64 and 128 up to 5200 +3 % (two rounds of workgroups instead of three), to 7700 -2 to -4 %, beyond
+// +1 to +3 %; d = 32 and shorter examples, of which six tiles are one workgroup, -1 to -4 %.
+int fewkeys_chunk_tiles(int B, int H, int d, int64_t total_q) {
     const int64_t wgs = (total_q / TILE_ROWS + B) * H;
-    return wgs >= 16384 ? FEWKEYS_MAX_TILES : (wgs >= 4096 ? 6 : (wgs >= 2048 ? 2 : 1));
+    if (wgs < 4096) return wgs >= 2048 ? 2 : 1;
+    if (wgs >= 16384) return FEWKEYS_MAX_TILES;
+    return d >= 64 && total_q >= (int64_t)900 * B && (wgs <= 5200 || wgs >= 7700) ? 6 : 4;
 }
 inline size_t fewkeys_partial_bytes(int B, int H, int d, int64_t total_q, int chunk_tiles) {
     const int chunk_rows = TILE_ROWS * chunk_tiles;

@@ -144,7 +144,7 @@ bool mfma_bwd_tiled_supported(const AttnParams& p, int dtype);
 // chunk_tiles: query tiles per workgroup with at most 32 keys per example (partial sums are kept per workgroup), the fastest
 // number up to the largest; no other call depends on it.
 constexpr int FEWKEYS_MAX_TILES = 8;
-int fewkeys_chunk_tiles(int B, int H, int64_t total_q);
+int fewkeys_chunk_tiles(int B, int H, int d, int64_t total_q);
 size_t mfma_bwd_tiled_workspace(int B, int H, int d, int max_q, int max_kv, int64_t total_q, int64_t total_kv, bool windowed, int chunk_tiles);
 hipError_t launch_mfma_bwd_tiled(const AttnParams& p, void* workspace_tail, bool any_softmax, int chunk_tiles, hipStream_t stream);
 
