@@ -523,21 +523,31 @@ bool mfma_fwd_is_qtiled(const AttnParams& p) { return p.windowed || p.max_q > 64
 //                 d = 64   softmax  256 l 76 / 29 / 31, 82 / 33 / 34;  384 l 79 / 44 / 37, 85 / 39 / 37
 //                 d = 32   ReLU     256 l 41 / 16 / 15, 47 / 19 / 18;  384 l 43 / 20 / 20, 50 / 21 / 21;  512 l 43 / 26 / 27, 51 / 23 / 23
 //                          pairs / singles, softmax  512 l 32 / 26, 1024 l 43 / 41, 2048 u 34 / 32: pairs pay above
+//   The lines themselves come from 800 random calls beside them, new form over old in time, by items (E: the longest history less than
+//   2.5 times the mean; the three forms of GELU, "general" its exact form on scores that may be large):
+//     pairs, up to 32 queries, long histories   E 1040..1720 1.03..1.12;  l 1036..1112 0.88..1.00, 1144..1270 softmax and SiLU 1.03..1.10, GELU 0.93..1.03,
+//                                               1300..1450 GELU 0.91..1.07, 1464..1760 all 1.02..1.16
+//     pairs, 33..64 queries                     long 1008..2256 1.13..1.66, general GELU to 1956 0.98..1.00;  short 1552..1800 1.06..1.22, tanh 0.93..1.02
+//     `both` at d = 64                          E 212..464 1.3..1.7;  l 200..252 0.70..1.06, 256..508 1.05..1.44 but general GELU to 300 0.77, 416 1.04;
+//                                               short 130..138 0.91..1.06, 142..300 1.02..1.53 but general GELU to 162 0.88..1.03, 168..288 0.96..1.21
+//     four waves instead of eight, d = 128      up to 32 queries, E 784..1003 1.03..1.11;  l 776..928 0.90..0.99, 944..1017 1.00..1.03
 FwdPlan mfma_fwd_plan(const AttnParams& p) {
-    const bool cheap = !has_act(p, KUNLUN_ACT_GELU);
+    const bool cheap = !has_act(p, KUNLUN_ACT_GELU), general_gelu = !cheap && !small_scores_expected(p);
+    const bool tanh_gelu = has_act(p, KUNLUN_ACT_GELU_TANH), any_gelu = !cheap || tanh_gelu || has_act(p, KUNLUN_ACT_GELU_POLY);
+    const bool even = histories_are_even(p);
     const int d = p.d;
     const int64_t items = (int64_t)p.B * p.H, blocks = items * ((p.max_q + 31) / 32);
     const bool long_histories = p.max_kv > 1024;
     const bool all_fit = schedule_is_moot(items, 4);
     FwdPlan plan = {1, false, false, !all_fit || (long_histories && !schedule_is_moot(blocks, 1))};
     if (p.max_q <= 32) {
-        plan.pair = heads_pair(p) && items > (long_histories ? 1024 : 2048);
+        plan.pair = heads_pair(p) && items > (!long_histories ? 2048 : even ? 1024 : any_gelu ? 1456 : 1216);
         if (blocks > 2048 && (plan.pair || d != 32)) {
             plan.key_split = long_histories ? 4 : 2;
             return plan;
         }
         if (blocks > 2048) return plan;
-        plan.key_split = long_histories && blocks <= (d == 128 ? 768 : 1024) ? 8 : 4;
+        plan.key_split = long_histories && blocks <= (d != 128 ? 1024 : even ? 768 : 936) ? 8 : 4;
         if (d == 128 && !long_histories) {
             const bool worth = p.max_kv > 512 && blocks > 512;  // (four waves crowd each other out below)
             plan.key_split = worth || blocks <= 256 ? 4 : 2;
@@ -549,10 +559,10 @@ FwdPlan mfma_fwd_plan(const AttnParams& p) {
         }
         return plan;
     }
-    // (more for GELU's general form: 1762 items l 105 / 114;  the others: 812 l 45 / 58, 1272 t 24 / 28 below the line)
-    plan.pair = heads_pair(p) && items > (!cheap && !small_scores_expected(p) ? 2048 : long_histories ? 1000 : 1500);
+    plan.pair = heads_pair(p) && items > (general_gelu ? 2048 : long_histories ? 1000 : tanh_gelu ? 1800 : 1500);
     if (d == 64 && p.max_kv <= 256 && items > 512 && all_fit) return plan;  // (952 items of 64..256 keys, a workgroup of two / `both`: 12.5 / 13.7)
-    if (plan.pair || (d == 64 && items > (long_histories ? 192 : 128))) {
+    const int both_limit = !long_histories ? (general_gelu ? 170 : 140) : even ? 192 : general_gelu ? 400 : 256;
+    if (plan.pair || (d == 64 && items > both_limit)) {
         const int64_t units = plan.pair ? items / 2 : items;
         plan.both = true;
         if (long_histories)
@@ -562,9 +572,8 @@ FwdPlan mfma_fwd_plan(const AttnParams& p) {
         plan.sorted = !all_fit || (long_histories && units > 256);
         return plan;
     }
-    const bool even = histories_are_even(p);
-    const int64_t dear_limit = d == 32 ? 4096 : d == 64 ? 384 : (long_histories ? (even ? 512 : 1024) : 512);
-    const int64_t cheap_limit = d == 32 ? (long_histories || !all_fit ? 4096 : 768) : d == 64 ? 384 : (long_histories ? (even ? 512 : 1024) : 256);
+    const int64_t dear_limit = d == 32 ? 4096 : d == 64 ? (long_histories ? 2048 : 1024) : (long_histories ? (even ? 512 : 1024) : 512);
+    const int64_t cheap_limit = d == 32 ? (long_histories || !all_fit ? 4096 : 768) : d == 64 ? (long_histories ? 1024 : 512) : (long_histories ? (even ? 512 : 1024) : 256);
     if (blocks <= (cheap ? cheap_limit : dear_limit))
         plan.key_split = long_histories && blocks <= (d == 32 ? 1536 : 2048) ? 8 : 4;
     else
