@@ -464,6 +464,11 @@ static hipError_t launch_bwd(const AttnParams& p, hipStream_t stream) {
 //   d = 64, 20 queries   four / eight waves    256 l 86u 76u;  512 u 46u 42u, 45s 39s, l 133u 109u, 115s 96s;  1024 l 162s 137s, u 68s 68s;  2048 v 254s 251s
 //                        four / two waves      4096 t 128s 132s, u 228s 240s;  64..256 keys, 2925 items 66s 63s, 8704 159s 153s
 //   d = 64, 60 queries   two / four waves      512 t 36s 35s, u 60s 50s;  768 t 44s 49s, u 65s 70s;  1024 l 208s 163s;  1536 l 225s 235s;  2048 u 151s 171s
+//   Lines from 600 random calls beside them, new form over old in time (E: the longest history less than 2.5 times the mean):
+//     eight waves instead of four   d = 32, 33..64 queries  E 440..564 1.24..1.42, 600..666 0.92..0.99;  l 514..744 1.27..1.97
+//                                   d = 64, up to 32 queries, u 200..574 1.03..1.27, 680..1016 softmax 0.93..1.06, others 0.99..1.03
+//     two waves instead of four     d = 64, 33..64 queries  t 532..1720 1.10..1.36;  u 740..1600 1.04..1.16;  v 656..676 0.95..0.98, 732..1756 1.00..1.08;
+//                                   l 1284..1359 0.93..0.95, 1754 1.06
 BwdPlan mfma_bwd_plan(const AttnParams& p) {
     const int64_t items = (int64_t)p.B * p.H;
     const bool one_block = p.max_q <= 32, long_histories = p.max_kv > 1024;
@@ -480,14 +485,14 @@ BwdPlan mfma_bwd_plan(const AttnParams& p) {
             plan.sorted = long_histories && !(histories_are_even(p) && items >= 2048);
             return plan;
         }
-        if (items <= 256 || (long_histories && items <= 768)) plan.waves = 8;
+        if (items <= 256 || (long_histories && items <= (one_block || !histories_are_even(p) ? 768 : 576))) plan.waves = 8;
         per_cu = plan.waves == 8 ? 1 : one_block ? 3 : 2;
     } else if (one_block) {
-        if (long_histories || items <= (p.max_kv > 512 ? 1024 : 256)) plan.waves = 8;
+        if (long_histories || items <= (p.max_kv > 512 ? 640 : 256)) plan.waves = 8;
         else if (p.max_kv <= 256 && items > 2048) plan.waves = 2;
         per_cu = plan.waves == 8 && long_histories ? 1 : 2;
     } else {
-        if (items > (p.max_kv > 2048 ? 1280 : p.max_kv > 512 ? 640 : 512)) plan.waves = 2;
+        if (items > (p.max_kv > 2048 ? 1400 : long_histories ? 704 : p.max_kv > 512 ? 640 : 512)) plan.waves = 2;
         plan.sorted = items > 512;
         per_cu = 1;
     }
