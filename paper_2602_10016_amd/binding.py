@@ -56,6 +56,8 @@ _lib.kunlun_sumkron_fwd.argtypes = [_vp, _vp, _vp, _vp, _i, _i, _i, _i, _i, _i, 
 _lib.kunlun_sumkron_fwd.restype = _i
 _lib.kunlun_sumkron_workspace_bytes.argtypes = [_i, _i, _i, _i, _i, _i]
 _lib.kunlun_sumkron_workspace_bytes.restype = _sz
+_lib.kunlun_sumkron_batch_bytes.argtypes = [_i, _i, _i, _i, _i, _i]  # (behind the public interface: for a workspace of one call)
+_lib.kunlun_sumkron_batch_bytes.restype = _sz
 _lib.kunlun_sumkron_bwd.argtypes = [_vp, _vp, _vp, _vp, _vp, _vp, _vp, _i, _i, _i, _i, _i, _i, _vp, _sz, _vp]
 _lib.kunlun_sumkron_bwd.restype = _i
 _lib.kunlun_sumkron_bwd_workspace_bytes.argtypes = [_i, _i, _i, _i, _i, _i]
@@ -447,7 +449,7 @@ def sumkron_fwd(x, z, w, *, out=None, workspace=None, stream=None):
     _check("w", w, like=x, shape=(k, D, D))
     y = torch.empty((B, T, D), dtype=x.dtype, device=x.device) if out is None else out
     _check("out", y, like=x, shape=(B, T, D))
-    ws = _workspace(workspace, sumkron_workspace_bytes(B, S, T, D, k, _dtype_code(x)), x.device)
+    ws = _workspace(workspace, int(_lib.kunlun_sumkron_batch_bytes(B, S, T, D, k, _dtype_code(x))), x.device)
     _on_device(x=x, z=z, w=w, out=y, workspace=ws)
     rc = _lib.kunlun_sumkron_fwd(_ptr(x), _ptr(z), _ptr(w), _ptr(y), B, S, T, D, k, _dtype_code(x), _ptr(ws), ws.numel(),
                                  _stream(stream))

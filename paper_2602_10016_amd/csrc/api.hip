@@ -86,6 +86,13 @@ size_t kunlun_sumkron_workspace_bytes(int B, int S, int T, int D, int k, int dty
     return sumkron_workspace(B, S, T, D, k, dtype) + 256;
 }
 
+// Not part of the public interface: what a binding that allocates for one call needs.  The public size serves every batch and
+// holds the partial sums of the most demanding one (50 MB at D = 384, which a batch of 1024 does not touch).
+size_t kunlun_sumkron_batch_bytes(int B, int S, int T, int D, int k, int dtype) {
+    if (kunlun_sumkron_workspace_bytes(B, S, T, D, k, dtype) == 0) return 0;
+    return sumkron_batch_bytes(B, S, T, D, k, dtype) + 256;
+}
+
 int kunlun_sumkron_fwd(const void* x, const void* z, const void* w, void* y, int B, int S, int T, int D, int k,
                        int dtype, void* workspace, size_t workspace_bytes, void* stream) {
     if (B < 0 || S <= 0 || T <= 0 || D <= 0 || k <= 0) return KUNLUN_ERR_SHAPE;

@@ -149,12 +149,14 @@ size_t mfma_bwd_tiled_workspace(int B, int H, int d, int max_q, int max_kv, int6
 hipError_t launch_mfma_bwd_tiled(const AttnParams& p, void* workspace_tail, bool any_softmax, int chunk_tiles, hipStream_t stream);
 
 // SumKronLinear (two tiled GEMMs with a bf16 intermediate, or plain fp32 kernels)
-// (bytes with which the call takes its fastest path, and bytes that it cannot do without)
+// (bytes with which calls of any batch size take their fastest path, bytes with which this one does, and bytes that it cannot do without)
 size_t sumkron_workspace(int B, int S, int T, int D, int k, int dtype);
+size_t sumkron_batch_bytes(int B, int S, int T, int D, int k, int dtype);
 size_t sumkron_need(int B, int S, int T, int D, int k, int dtype);
 // One-kernel forward for T = 32, S in {128, 256}, D in {128, 256, 384}, k <= 8 (sumkron_fused.hip)
 bool sumkron_fused_supported(int S, int T, int D, int k, int dtype);
 size_t sumkron_fused_need(int S, int T, int D, int k);
+size_t sumkron_fused_batch_bytes(int B, int S, int T, int D, int k);
 size_t sumkron_fused_workspace(int S, int T, int D, int k);
 hipError_t launch_sumkron_fused(const void* x, const void* z, const void* w, void* y, int B, int S, int T, int D, int k, void* workspace,
                                 size_t workspace_bytes, hipStream_t stream);

@@ -353,6 +353,9 @@ bool sumkron_bwd_tiled_supported(int B, int S, int T, int D, int k, int dtype) {
 size_t sumkron_workspace(int B, int S, int T, int D, int k, int dtype) {
     return sumkron_fused_supported(S, T, D, k, dtype) ? sumkron_fused_workspace(S, T, D, k) : sumkron_need(B, S, T, D, k, dtype);
 }
+size_t sumkron_batch_bytes(int B, int S, int T, int D, int k, int dtype) {
+    return sumkron_fused_supported(S, T, D, k, dtype) ? sumkron_fused_batch_bytes(B, S, T, D, k) : sumkron_need(B, S, T, D, k, dtype);
+}
 size_t sumkron_need(int B, int S, int T, int D, int k, int dtype) {
     if (sumkron_fused_supported(S, T, D, k, dtype)) return sumkron_fused_need(S, T, D, k);
     if (sumkron_tiled_supported(S, T, D, k, dtype))

@@ -307,6 +307,11 @@ bool sumkron_fused_supported(int S, int T, int D, int k, int dtype) {
 size_t sumkron_fused_need(int S, int T, int D, int k) {
     return align_up((size_t)k * T * S * 2, 256) + align_up((size_t)k * D * D * 2, 256);
 }
+// ... with the partial sums of this batch
+size_t sumkron_fused_batch_bytes(int B, int S, int T, int D, int k) {
+    const int ranges = skf_ranges(B, D, ~(size_t)0);
+    return sumkron_fused_need(S, T, D, k) + (ranges > 1 ? (size_t)ranges * B * SKF_T * D * sizeof(float) : 0);
+}
 // ... with the partial sums of any split launch (the same for every batch size, so that a kept workspace serves them all)
 size_t sumkron_fused_workspace(int S, int T, int D, int k) {
     return sumkron_fused_need(S, T, D, k) + (size_t)SKF_WGS * SKF_EX * SKF_T * D * sizeof(float);

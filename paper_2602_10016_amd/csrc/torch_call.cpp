@@ -16,6 +16,9 @@
 
 #include "../../include/kunlun.h"
 
+// (of the library, behind its public interface: the bytes that one call of kunlun_sumkron_fwd can use)
+extern "C" size_t kunlun_sumkron_batch_bytes(int B, int S, int T, int D, int k, int dtype);
+
 // Device type of the tensors; the module can be built for host tensors, to run its checks in front of another library.
 #ifndef KUNLUN_CALL_DEVICE
 #define KUNLUN_CALL_DEVICE CUDA
@@ -431,7 +434,7 @@ ENTRY(sumkron_fwd, 6)
         if (n > INT32_MAX) c.ok = false;
     PLAIN_OR_NONE;
     if (!y.t) y.make(*x, {B, T, D}, x->scalar_type());
-    make_workspace(ws, *x, ws.t ? 0 : kunlun_sumkron_workspace_bytes((int)B, (int)S, (int)T, (int)D, (int)k, c.dtype()));
+    make_workspace(ws, *x, ws.t ? 0 : kunlun_sumkron_batch_bytes((int)B, (int)S, (int)T, (int)D, (int)k, c.dtype()));
     const int rc = enqueue(kunlun_sumkron_fwd, x->data_ptr(), z->data_ptr(), w->data_ptr(), y.ptr(), (int)B, (int)S, (int)T,
                            (int)D, (int)k, c.dtype(), ws.ptr(), (size_t)ws.t->numel(), s);
     DONE_OR_NONE(rc);

@@ -32,3 +32,25 @@ def test_split_forward(oracle, B, S, D, k, room):
     torch.cuda.synchronize()
     assert_close(to_np(got), oracle.sumkron_fwd(x, z, w), TOL["bf16"], f"B={B} S={S} D={D} k={k} {room}")
     assert torch.all(memory[nbytes:] == 0xEE)
+
+
+def test_a_call_allocates_for_its_own_batch():
+    """B = 1024 cuts no ranges: the prepared copies of Z and W and the result, not the partial sums of a smaller batch; B = 8 has
+    room for its twelve ranges."""
+    from paper_2602_10016_amd import binding as kb
+    S, T, D, k = 256, 32, 384, 8
+    need = align(k * T * S * 2) + align(k * D * D * 2) + 256
+    z, w = (torch.zeros(s, dtype=torch.bfloat16, device="cuda") for s in ((k, S, T), (k, D, D)))
+    for B, partial in ((1024, 0), (8, 12 * 8 * T * D * 4)):
+        x = torch.zeros((B, S, D), dtype=torch.bfloat16, device="cuda")
+        torch.cuda.synchronize()
+        torch.cuda.empty_cache()
+        before = torch.cuda.memory_allocated()
+        torch.cuda.reset_peak_memory_stats()
+        y = kb.sumkron_fwd(x, z, w)
+        taken = torch.cuda.max_memory_allocated() - before - y.numel() * 2
+        assert need + partial <= taken <= need + partial + 4096, (B, taken, need + partial)
+    assert kb.raw().kunlun_sumkron_batch_bytes(0, 0, 1, 8, 1, kb.BF16) == 0
+    for B in (1, 5, 80, 170, 255, 256, 300, 512, 1024, 5000):
+        assert kb.raw().kunlun_sumkron_batch_bytes(B, S, T, D, k, kb.BF16) <= kb.sumkron_workspace_bytes(B, S, T, D, k)
+        assert kb.raw().kunlun_sumkron_batch_bytes(B, S, 16, D, k, kb.BF16) == kb.sumkron_workspace_bytes(B, S, 16, D, k)

@@ -26,7 +26,7 @@ def stub_source():
     header = open(os.path.join(ROOT, "include", "kunlun.h")).read()
     code = ['#include "kunlun.h"', "#include <stdio.h>", "char noted[4096]; int calls, status; void (*hook)(void);",
             "size_t kunlun_workspace_bytes(int op, int B, int H, int d, int mq, int mk, int64_t tq, int64_t tk) { return 1000 + op; }",
-            "size_t kunlun_sumkron_workspace_bytes(int B, int S, int T, int D, int k, int dtype) { return 2000; }",
+            "size_t kunlun_sumkron_batch_bytes(int B, int S, int T, int D, int k, int dtype) { return 2000; }",
             "size_t kunlun_sumkron_bwd_workspace_bytes(int B, int S, int T, int D, int k, int dtype) { return 3000; }"]
     for name in ENTRIES:
         args = re.search(rf"^int kunlun_{name}\(([^)]*)\);", header, flags=re.M).group(1)
