@@ -70,6 +70,26 @@ def test_same_results(monkeypatch, dtype, stream):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+def test_every_entry_point_goes_the_native_way(monkeypatch, dtype):
+    a, native, taken = arguments("cuda", dtype), kb._native, []
+
+    class Recorder:
+        def __getattr__(self, name):
+            def call(*args):
+                done = getattr(native, name)(*args)
+                assert done is not None, name
+                taken.append(name)
+                return done
+            return call
+
+    monkeypatch.setattr(kb, "_native", Recorder())
+    calls(a)
+    torch.cuda.synchronize()
+    assert sorted(set(taken)) == sorted(["gdpa_fwd", "gdpa_bwd", "seed_attn_fwd", "seed_attn_bwd", "swa_fwd", "swa_bwd", "sumkron_fwd", "sumkron_bwd"])
+
+
+@pytest.mark.gpu
 def test_given_outputs_come_back_themselves():
     a = arguments("cuda")
     out, lse = torch.empty_like(a["q"]), torch.empty((H, B * N), device="cuda")

@@ -152,3 +152,117 @@ def test_a_refused_launch_raises_without_a_second_call(stub, name):
     for status in (kb.ERR_NULL, kb.ERR_SHAPE, kb.ERR_UNSUPPORTED, kb.ERR_ALIGN, kb.ERR_WORKSPACE):  # of an argument: nothing is enqueued
         stub.reset(status=status)
         assert getattr(stub.native, name)(*arguments(name).values()) is None and stub.calls == 1
+
+
+def parameters(name):
+    """Names of the C parameters, in order."""
+    header = open(os.path.join(ROOT, "include", "kunlun.h")).read()
+    return [p.rsplit(" ", 1)[1].lstrip("*") for p in re.search(rf"^int kunlun_{name}\(([^)]*)\);", header, flags=re.M).group(1).replace("\n", " ").split(",")]
+
+
+def expected(name, a, result, dtype):
+    """C parameter -> value that the call must have received."""
+    pointer = lambda t: 0 if t is None else t.data_ptr()
+    given = {k: pointer(v) if isinstance(v, torch.Tensor) or v is None else v for k, v in a.items() if k not in ("out", "want_lse", "stream", "workspace")}
+    results = [pointer(t) for t in (result if isinstance(result, tuple) else (result,))]
+    want = dict(given, stream=0x5EED, dtype=1 if dtype == torch.float32 else 0, head_act=0, H=H, d=D, B=B, total_q=B * N, total_kv=T, n_seeds=N, total=T)
+    if name.startswith("sumkron"):
+        want.update(S=64, T=32, D=128, k_=2, y=results[0])
+        want.update(zip(("dx", "dz", "dw"), results) if name == "sumkron_bwd" else ())
+    elif name.endswith("fwd"):
+        want.update(o=results[0], lse=results[1])
+    else:
+        want.update(zip(("d_e" if name == "seed_attn_bwd" else "dq", "dk", "dv"), results))
+    return want
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("given", [False, True])
+@pytest.mark.parametrize("name", ENTRIES)
+def test_every_entry_point_takes_its_plain_arguments(stub, name, given, dtype):
+    """The call is made, once, with every argument in its place; outputs and workspace that are given are the ones that are used."""
+    a = arguments(name, dtype)
+    if given:
+        a["workspace"] = torch.zeros(5000, dtype=torch.uint8)
+        if "q_offsets" in a:
+            a["q_offsets"] = torch.tensor([0, N, 2 * N, 3 * N], dtype=torch.int32)
+        if name.endswith("bwd") and "out" in a:
+            a["out"] = gradients(a)
+        elif "out" in a:
+            rows = T if name == "swa_fwd" else B * N
+            a["out"] = torch.zeros(B, 32, 128, dtype=dtype) if name == "sumkron_fwd" else torch.zeros(rows, H, D, dtype=dtype)
+            if "lse" in a:
+                a["lse"] = torch.zeros(H, rows)
+    result = getattr(stub.native, name)(*a.values())
+    assert result is not None and stub.calls == 1
+    flat = list(result) if isinstance(result, tuple) else [result]
+    if given and "out" in a:
+        outs = a["out"] if isinstance(a["out"], list) else [a["out"]]
+        assert [id(x) for x in flat[:len(outs)]] == [id(x) for x in outs]
+    want, got = expected(name, a, result, dtype), dict(zip(parameters(name), stub.noted))
+    if name.startswith("sumkron"):  # (there k is a number, not a tensor)
+        want["k"] = want.pop("k_")
+    for parameter, text in got.items():
+        if parameter == "workspace":
+            assert int(text, 16) == a["workspace"].data_ptr() if given else int(text, 16) != 0
+        elif parameter == "workspace_bytes":
+            assert int(text) == (5000 if given else {"gdpa_fwd": 1000, "gdpa_bwd": 1001, "swa_fwd": 1002, "swa_bwd": 1003, "seed_attn_fwd": 1004,
+                                                     "seed_attn_bwd": 1005, "sumkron_fwd": 2000, "sumkron_bwd": 3000}[name])
+        elif parameter == "scale":
+            assert float(text) == pytest.approx(0.1, rel=1e-7)
+        else:
+            value = 0 if text == "(nil)" else int(text, 16) if text.startswith("0x") else int(text)
+            assert value == want[parameter], parameter
+
+
+class Sub(torch.Tensor):
+    pass
+
+
+def odd(x):
+    """Arguments of other kinds in the place of x."""
+    if isinstance(x, torch.Tensor):
+        yield from (None, "x", x.double(), x.half(), x.long(), x.float() if x.dtype != torch.float32 else x.bfloat16(), x.unsqueeze(0), x[:-1],
+                    torch.cat([x, x[:1]]), torch.stack([x, x], -1)[..., 0], x.as_subclass(Sub), x[:0])
+        if x.dim() > 1:
+            yield from (x.transpose(0, 1), x.transpose(0, 1).contiguous(), x[:, :1].contiguous(), x[..., :-8].contiguous())
+    elif isinstance(x, (int, float)) and not isinstance(x, bool):
+        yield from (None, "x", [], 1 << 40, 2.5, torch.zeros(2))
+
+
+@pytest.mark.parametrize("name", ENTRIES)
+def test_nothing_is_accepted_that_the_python_code_refuses(stub, name, monkeypatch):
+    """Every argument in turn replaced by others: what the Python code refuses for any other reason than the device, the native
+    call leaves to it, without making the call."""
+    from paper_2602_10016_amd import binding as kb
+    monkeypatch.setattr(kb, "_native", types.SimpleNamespace(**{n: lambda *args: None for n in ENTRIES}))
+
+    def refused(a):
+        try:
+            getattr(kb, name)(**a)
+        except Exception as e:
+            return "CUDA" not in str(e)
+        raise AssertionError("host tensors were accepted")
+
+    assert not refused(arguments(name))
+    cases = [(key, value) for key, x in arguments(name).items() for value in odd(x)]
+    grads = lambda i, value: [value if i == j else g for j, g in enumerate(gradients(arguments(name)))]
+    if name.endswith("bwd") and "out" in arguments(name):
+        cases += [("out", grads(i, value)) for i in range(3) for value in odd(gradients(arguments(name))[i])]
+        cases += [("out", gradients(arguments(name))[:2]), ("out", 5)]
+    elif "out" in arguments(name):
+        shape = (B, 32, 128) if name == "sumkron_fwd" else (T if name == "swa_fwd" else B * N, H, D)
+        cases += [("out", value) for value in odd(torch.zeros(shape, dtype=torch.bfloat16)) if value is not None]
+        if "lse" in arguments(name):
+            cases += [("lse", value) for value in odd(torch.zeros(H, shape[0])) if value is not None]
+    cases += [("workspace", value) for value in ("x", torch.zeros(5000), torch.zeros(5000, 2, dtype=torch.uint8)[:, 0])]
+    if "q_offsets" in arguments(name):
+        cases += [("q_offsets", value) for value in odd(torch.tensor([0, N, 2 * N, 3 * N], dtype=torch.int32)) if value is not None]
+    n = 0
+    for key, value in cases:
+        a = arguments(name, **{key: value})
+        stub.reset()
+        if refused(a):
+            n += 1
+            assert getattr(stub.native, name)(*a.values()) is None and stub.calls == 0, (key, value)
+    assert n > 20
