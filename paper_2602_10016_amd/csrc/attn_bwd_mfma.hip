@@ -76,15 +76,13 @@ __device__ __forceinline__ void attn_bwd_item(const AttnParams& p, char* smem, i
     char* ldsP = wbase + 2 * SM::TILE_BYTES;
     char* ldsDS = ldsP + SM::P_BYTES;
 
-    // ---- prologue: Q and dO of the item into LDS; rows past nq are zero (they then add
-    // nothing to dK, dV, and their dQ rows are never stored)
+    // ---- prologue: Q and dO of the item into LDS.  Rows past nq repeat the last query, with a zero dO: they add nothing to dK, dV,
+    // and their dQ rows are never stored.  (Zero queries would score 0 * -inf = NaN at a key with a channel of -inf.)
     for (int idx = tid; idx < QROWS * L::CHUNKS; idx += 64 * NW) {
         const int row = idx / L::CHUNKS, ch = idx % L::CHUNKS;
-        u32x4 qv = {0, 0, 0, 0}, dv = {0, 0, 0, 0};
-        if (row < nq) {
-            qv = *(const u32x4*)(Qg + row * hd + ch * 8);
-            dv = *(const u32x4*)(DOg + row * hd + ch * 8);
-        }
+        const u32x4 qv = *(const u32x4*)(Qg + (row < nq ? row : nq - 1) * hd + ch * 8);
+        u32x4 dv = {0, 0, 0, 0};
+        if (row < nq) dv = *(const u32x4*)(DOg + row * hd + ch * 8);
         *(u32x4*)(ldsQ + L::u_offset(row, ch * 16)) = qv;
         *(u32x4*)(ldsDO + L::u_offset(row, ch * 16)) = dv;
     }

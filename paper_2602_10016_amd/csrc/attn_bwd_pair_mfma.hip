@@ -73,15 +73,15 @@ __device__ __forceinline__ void attn_bwd_pair_item(const AttnParams& p, char* sm
     char* ldsP = pbase + 2 * SM::TILE_BYTES;
     char* ldsDS = ldsP + SM::P_BYTES;
 
-    // ---- prologue: Q and dO of the item into LDS (rows past nq read as zero: they add nothing
-    // to dK, dV and their dQ rows are never stored)
+    // ---- prologue: Q and dO of the item into LDS.  Rows past nq repeat the last query, with a zero dO: they add nothing to dK,
+    // dV and their dQ rows are never stored.  (Zero queries would score 0 * -inf = NaN at a key with a channel of -inf.)
     {
         const __amdgpu_buffer_rsrc_t qr = __builtin_amdgcn_make_buffer_rsrc((void*)Qg, 0, (nq - 1) * (int)row_bytes + D * 2, 0x00020000);
         const __amdgpu_buffer_rsrc_t dr = __builtin_amdgcn_make_buffer_rsrc((void*)DOg, 0, (nq - 1) * (int)row_bytes + D * 2, 0x00020000);
 #pragma unroll
         for (int i = 0; i < 4; ++i) {  // 64 rows x 16 chunks over 256 threads
             const int row = i * 16 + (tid >> 4), ch = tid & 15;
-            const u32x4 qv = __builtin_amdgcn_raw_buffer_load_b128(qr, (uint32_t)row * row_bytes + ch * 16, 0, 0);
+            const u32x4 qv = __builtin_amdgcn_raw_buffer_load_b128(qr, (uint32_t)(row < nq ? row : nq - 1) * row_bytes + ch * 16, 0, 0);
             const u32x4 dv = __builtin_amdgcn_raw_buffer_load_b128(dr, (uint32_t)row * row_bytes + ch * 16, 0, 0);
             *(u32x4*)(ldsQ + L::u_offset(row, ch * 16)) = qv;
             *(u32x4*)(ldsDO + L::u_offset(row, ch * 16)) = dv;
