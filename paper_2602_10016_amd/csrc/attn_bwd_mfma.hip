@@ -486,7 +486,8 @@ BwdPlan mfma_bwd_plan(const AttnParams& p) {
         if (items <= 256 || (long_histories && items <= (one_block || !histories_are_even(p) ? 768 : 576))) plan.waves = 8;
         per_cu = plan.waves == 8 ? 1 : one_block ? 3 : 2;
     } else if (one_block) {
-        if (long_histories || items <= (p.max_kv > 512 ? 640 : 256)) plan.waves = 8;
+        const int64_t eight_up_to = p.max_kv <= 512 ? 256 : has_act(p, KUNLUN_ACT_SOFTMAX) ? 640 : 1024;
+        if (long_histories || items <= eight_up_to) plan.waves = 8;
         else if (p.max_kv <= 256 && items > 2048) plan.waves = 2;
         per_cu = plan.waves == 8 && long_histories ? 1 : 2;
     } else {
