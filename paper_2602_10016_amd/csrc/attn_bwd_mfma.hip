@@ -80,9 +80,10 @@ __device__ __forceinline__ void attn_bwd_item(const AttnParams& p, char* smem, i
     // and their dQ rows are never stored.  (Zero queries would score 0 * -inf = NaN at a key with a channel of -inf.)
     for (int idx = tid; idx < QROWS * L::CHUNKS; idx += 64 * NW) {
         const int row = idx / L::CHUNKS, ch = idx % L::CHUNKS;
-        const u32x4 qv = *(const u32x4*)(Qg + (row < nq ? row : nq - 1) * hd + ch * 8);
-        u32x4 dv = {0, 0, 0, 0};
-        if (row < nq) dv = *(const u32x4*)(DOg + row * hd + ch * 8);
+        const int64_t src = (row < nq ? row : nq - 1) * hd + ch * 8;
+        const u32x4 qv = *(const u32x4*)(Qg + src);
+        u32x4 dv = *(const u32x4*)(DOg + src);
+        if (row >= nq) dv = (u32x4){0, 0, 0, 0};
         *(u32x4*)(ldsQ + L::u_offset(row, ch * 16)) = qv;
         *(u32x4*)(ldsDO + L::u_offset(row, ch * 16)) = dv;
     }
