@@ -950,11 +950,13 @@ static hipError_t launch_tiled(const AttnParams& p, char* ws, bool any_softmax, 
     // Backward alone, 500 random calls, two waves over four by reach (d = 64 / d = 128): 100..199 1.12 / 1.11, 200..383 1.07 / 1.07,
     // 384..449 1.05 / 1.06, 450..549 1.05 / 1.03 with losses of up to 4 % at d = 128, 550..699 1.03 / 1.01 - but for half to one tile
     // of 128 rows per compute unit, where four waves have a unit to themselves and two workgroups of two share one: d = 64 1.00 from a
-    // reach of 300 on (down to 0.94), d = 128 0.99 from 200 on (down to 0.86).
+    // reach of 300 on (down to 0.94), d = 128 0.99 from 200 on (down to 0.86), and sequences of up to 256 rows 0.95 from about 112 on.
+    // (The number of tiles is known to about 3 %: up to 33/32 of the units.)
     if constexpr (WINDOWED && D > 32) {
-        const int64_t reach = (int64_t)p.left + p.right, tiles = tiles_expected(p);
-        const bool alone = 2 * tiles > compute_units() && tiles <= compute_units();
-        if (p.left >= 0 && p.right >= 0 && reach < (alone ? (D == 64 ? 320 : 200) : D == 64 ? 704 : 448))
+        const int64_t reach = (int64_t)p.left + p.right, tiles = tiles_expected(p), units = compute_units();
+        const bool alone = 2 * tiles > units && 32 * tiles <= 33 * units;
+        const int alone_limit = p.max_kv <= 256 ? 112 : D == 64 ? 320 : 200;
+        if (p.left >= 0 && p.right >= 0 && reach < (alone ? alone_limit : D == 64 ? 704 : 448))
             return launch_passes<D, WINDOWED, 2>(p, ws, any_softmax, stream);
     }
     return launch_passes<D, WINDOWED, 4>(p, ws, any_softmax, stream);
