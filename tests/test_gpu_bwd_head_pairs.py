@@ -51,10 +51,12 @@ def test_pairs_share_a_score_function_or_go_alone(oracle, head_act):
     check(oracle, 900, 4, 32, 20, 300, act=3, head_act=head_act)
 
 
-def test_pairs_of_even_histories_unsorted(oracle):
-    """Histories beyond 1024 keys whose longest is less than 2.5 times the mean: issued in memory order."""
+# ... and eight waves for 33..64 queries up to 576 items of them
+@pytest.mark.parametrize("B,n", [(1024, 3), (288, 40), (289, 40)])
+def test_even_histories(oracle, B, n):
+    """Histories beyond 1024 keys whose longest is less than 2.5 times the mean: many pairs are issued in memory order."""
     from paper_2602_10016_amd import binding as kb
-    B, H, d, n = 1024, 2, 32, 3
+    H, d = 2, 32
     lengths = np.full(B, 500)
     lengths[[1, 7]] = [1025, 0]
     wl = W.make("cfg5", 5, B=B, H=H, d=d, Nq=n, lengths=("list", lengths), scale=0.2)
@@ -67,14 +69,15 @@ def test_pairs_of_even_histories_unsorted(oracle):
         assert_close(to_np(a), ref, TOL["bf16"], name)
 
 
-# eight waves: d = 32 up to 256 items (768 of long histories), d = 64 with up to 32 queries 256, 1024 beyond 512 keys, all
-# beyond 1024; two waves: d = 64 with 33..64 queries above 512 items (640 with histories beyond 512 keys, 1280 beyond 2048),
-# and with up to 32 queries above 2048 items of up to 256 keys
+# eight waves: d = 32 up to 256 items (768 of long histories), d = 64 with up to 32 queries 256, beyond 512 keys 640 with softmax
+# heads and 1024 without, all beyond 1024; two waves: d = 64 with 33..64 queries above 512 items (640 with histories beyond 512
+# keys, 704 beyond 1024, 1400 beyond 2048), and with up to 32 queries above 2048 items of up to 256 keys
 @pytest.mark.parametrize("B,H,d,n,longest", [(64, 4, 32, 32, 90), (65, 4, 32, 32, 90), (64, 4, 32, 64, 300), (65, 4, 32, 33, 300), (192, 4, 32, 20, 1100),
                                              (192, 4, 32, 64, 1100), (193, 4, 32, 40, 1100), (64, 4, 64, 32, 500), (65, 4, 64, 32, 500),
                                              (256, 4, 64, 17, 600), (257, 4, 64, 17, 600), (300, 4, 64, 32, 1100), (128, 4, 64, 64, 90),
                                              (129, 4, 64, 33, 90), (160, 4, 64, 40, 600), (161, 4, 64, 40, 600), (320, 4, 64, 40, 2100), (321, 4, 64, 40, 2100),
-                                             (513, 4, 64, 20, 90)])
+                                             (513, 4, 64, 20, 90), (160, 4, 64, 17, 600), (161, 4, 64, 17, 600), (176, 4, 64, 40, 1100), (177, 4, 64, 40, 1100),
+                                             (350, 4, 64, 40, 2100), (351, 4, 64, 40, 2100)])
 @pytest.mark.parametrize("act", [0, 3])
 def test_waves_per_item(oracle, B, H, d, n, longest, act):
     check(oracle, B, H, d, n, longest, act)

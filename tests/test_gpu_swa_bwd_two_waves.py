@@ -1,5 +1,5 @@
 """Sliding-window backward in workgroups of two waves (64 rows; bounded windows reaching fewer than 704 rows at d = 64 and 448 at
-d = 128, for half to one tile of 128 rows per compute unit 320 and 200) and of four (wider or unbounded windows, d = 32), against
+d = 128, for half to one tile of 128 rows per compute unit 320 and 200, 112 for sequences of up to 256 rows) and of four (wider or unbounded windows, d = 32), against
 the CPU oracle: sequences around 32, 64 and 128 rows, windows on both sides of the lines."""
 import numpy as np
 import pytest
@@ -33,7 +33,8 @@ def test_swa_backward_around_the_two_wave_rule(oracle, d, left, right):
 
 # 4 sequences of up to 1100 rows, 2 heads (40 tiles), and 20 of up to 900, 2 heads (about 240 tiles: one per compute unit)
 @pytest.mark.parametrize("d,B,longest,left,right", [(64, 4, 1100, 703, 0), (64, 4, 1100, 352, 352), (128, 4, 1100, 447, 0), (128, 4, 1100, 0, 448),
-                                                    (64, 20, 900, 319, 0), (64, 20, 900, 160, 160), (128, 20, 900, 199, 0), (128, 20, 900, 100, 100)])
+                                                    (64, 20, 900, 319, 0), (64, 20, 900, 160, 160), (128, 20, 900, 199, 0), (128, 20, 900, 100, 100),
+                                                    (64, 70, 256, 111, 0), (128, 70, 256, 112, 0)])
 def test_swa_backward_around_the_lines_by_reach_and_size(oracle, d, B, longest, left, right):
     from paper_2602_10016_amd import binding as kb
     rng = np.random.default_rng(d + B)
