@@ -18,14 +18,14 @@
 //            examples.
 // What sets the shape: W (2.4 MB) is read by every workgroup for every group of examples, so the L2 traffic per example
 // is W / (examples that share a fragment load).  With two examples per workgroup and one per wave the kernel was bound
-// by exactly that (2.4 GB at the 12 TB/s the L2s sustained: 192 us); two examples per wave need twice the accumulators,
-// and the registers for them are those of the Z fragments, which are therefore re-read from L2 for every step (dead
-// during stage 2) - a third of the W traffic that is saved.
+// by exactly that (2.4 GB at the 12 TB/s the L2s sustained: 192 us).  Two examples per wave need twice the accumulators; the Z
+// fragments stay in registers beside them, read once per workgroup (at D = 384 and S = 256 that is all 256 registers, and two
+// addresses go to scratch memory).
 // W is prepared once per call in fragment order: the 64 x 16 bytes that the lanes of a wave need for one MFMA are
 // 1 KB contiguous (read the other way - 16 bytes per lane from 32 different rows - every load touched 32 cache
 // lines and the kernel ran at a third of its speed).  Z likewise transposed, in the c order of the register layout.
-// X blocks of the next step are fetched into registers at the end of stage 2 (last, so that no wait for a W fragment
-// covers them) and stored to LDS as soon as stage 1 has read the old ones.
+// X blocks of the next step set out for LDS at the start of stage 2, as soon as stage 1 has read the old ones, without
+// passing through registers.
 // Per example: 3840 MFMAs of 32x32x16 (the 126 MFLOP of the operator), X read once.
 #include "lds_ring.h"
 
@@ -89,7 +89,7 @@ __global__ __launch_bounds__(64 * SKF_WAVES, 1) void sumkron_fused_kernel(const 
     const int r = lane & 31, g = lane >> 5;
     const int ng = wave & 3, eh = wave >> 2;    // stage 2: channel group and pair of examples
 
-    // ---- stage-1 B fragments: column t = r of Z_wave, rows in the fragment order (prepared); re-read for every step
+    // ---- stage-1 B fragments: column t = r of Z_wave, rows in the fragment order (prepared); read once
     bf16x8 zf[KS];
     auto load_z = [&]() {
 #pragma unroll

@@ -1,7 +1,7 @@
 // The accepted case of the Python entry points, in native code: unpacks the tensors, makes the binding's checks on them,
 // allocates what the caller left out and calls the C ABI.  Small calls were bound by marshalling through ctypes: two fp32
 // examples of 8 queries and 64 keys (kernel 4 us) 10.0 -> 4.3 us a pass, 27 -> 17 us alone; a training step through autograd
-// whose kernels take less 156 -> 124 us.
+// whose kernels take less: 124 to 144 -> 82 to 96 us on the host, most of it torch's own.
 //
 // A function returns None for everything that is not plainly right - another type or dtype, a strided view, a tensor of a
 // subclass or a transform, a wrong shape or device, an int that is no int, the error status of an argument - before anything
