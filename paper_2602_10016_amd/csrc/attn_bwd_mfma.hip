@@ -470,6 +470,10 @@ static hipError_t launch_bwd(const AttnParams& p, hipStream_t stream) {
 //                                   l 1284..1359 0.93..0.95, 1754 1.06
 BwdPlan mfma_bwd_plan(const AttnParams& p) {
     const int64_t items = (int64_t)p.B * p.H;
+    // (items that run side by side; short ones only if the launch, whole groups of eight examples, leaves no workgroup over: 81
+    // examples, 3 heads, d = 64, 64..256 keys, 264 workgroups of eight waves for 256 compute units 14.3 us, of four 10.4; from 512 keys on eight
+    // are better even so, up to 1.32)
+    const bool side_by_side = (p.max_kv > 256 ? items : ((int64_t)p.B + 7) / 8 * 8 * p.H) <= compute_units();
     const bool one_block = p.max_q <= 32, long_histories = p.max_kv > 1024;
     BwdPlan plan = {4, false, false};
     if (p.d == 128) {
@@ -484,11 +488,11 @@ BwdPlan mfma_bwd_plan(const AttnParams& p) {
             plan.sorted = long_histories && !(histories_are_even(p) && items >= 2048);
             return plan;
         }
-        if (items <= 256 || (long_histories && items <= (one_block || !histories_are_even(p) ? 768 : 576))) plan.waves = 8;
+        if (side_by_side || (long_histories && items <= (one_block || !histories_are_even(p) ? 768 : 576))) plan.waves = 8;
         per_cu = plan.waves == 8 ? 1 : one_block ? 3 : 2;
     } else if (one_block) {
-        const int64_t eight_up_to = p.max_kv <= 512 ? 256 : has_act(p, KUNLUN_ACT_SOFTMAX) ? 640 : 1024;
-        if (long_histories || items <= eight_up_to) plan.waves = 8;
+        const int64_t eight_up_to = has_act(p, KUNLUN_ACT_SOFTMAX) ? 640 : 1024;
+        if (long_histories || side_by_side || (p.max_kv > 512 && items <= eight_up_to)) plan.waves = 8;
         else if (p.max_kv <= 256 && items > 2048) plan.waves = 2;
         per_cu = plan.waves == 8 && long_histories ? 1 : 2;
     } else {

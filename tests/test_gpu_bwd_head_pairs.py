@@ -69,7 +69,7 @@ def test_even_histories(oracle, B, n):
         assert_close(to_np(a), ref, TOL["bf16"], name)
 
 
-# eight waves: d = 32 up to 256 items (768 of long histories), d = 64 with up to 32 queries 256, beyond 512 keys 640 with softmax
+# eight waves: d = 32 up to 256 items in whole groups of eight examples (768 of long histories), d = 64 with up to 32 queries 256 so, beyond 512 keys 640 with softmax
 # heads and 1024 without, all beyond 1024; two waves: d = 64 with 33..64 queries above 512 items (640 with histories beyond 512
 # keys, 704 beyond 1024, 1400 beyond 2048), and with up to 32 queries above 2048 items of up to 256 keys
 @pytest.mark.parametrize("B,H,d,n,longest", [(64, 4, 32, 32, 90), (65, 4, 32, 32, 90), (64, 4, 32, 64, 300), (65, 4, 32, 33, 300), (192, 4, 32, 20, 1100),
@@ -77,7 +77,7 @@ def test_even_histories(oracle, B, n):
                                              (256, 4, 64, 17, 600), (257, 4, 64, 17, 600), (300, 4, 64, 32, 1100), (128, 4, 64, 64, 90),
                                              (129, 4, 64, 33, 90), (160, 4, 64, 40, 600), (161, 4, 64, 40, 600), (320, 4, 64, 40, 2100), (321, 4, 64, 40, 2100),
                                              (513, 4, 64, 20, 90), (160, 4, 64, 17, 600), (161, 4, 64, 17, 600), (176, 4, 64, 40, 1100), (177, 4, 64, 40, 1100),
-                                             (350, 4, 64, 40, 2100), (351, 4, 64, 40, 2100)])
+                                             (350, 4, 64, 40, 2100), (351, 4, 64, 40, 2100), (81, 3, 64, 20, 90), (80, 3, 32, 40, 90), (81, 3, 32, 40, 90)])
 @pytest.mark.parametrize("act", [0, 3])
 def test_waves_per_item(oracle, B, H, d, n, longest, act):
     check(oracle, B, H, d, n, longest, act)
