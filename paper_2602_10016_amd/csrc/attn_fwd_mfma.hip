@@ -531,7 +531,7 @@ bool mfma_fwd_is_qtiled(const AttnParams& p) { return p.windowed || p.max_q > 64
 //     pairs, 33..64 queries                     long 1008..2256 1.13..1.66, general GELU to 1956 0.98..1.00;  short 1552..1800 1.06..1.22, tanh 0.93..1.02
 //     `both` at d = 64                          E 212..464 1.3..1.7;  l 200..252 0.70..1.06, 256..508 1.05..1.44 but general GELU to 300 0.77, 416 1.04;
 //                                               short 130..138 0.91..1.06, 142..300 1.02..1.53 but general GELU to 162 0.88..1.03, 168..288 0.96..1.21
-//     one walk instead of eight waves, d = 128  33..64 queries, E 280..472 1.09..1.47 but general GELU 268..272 0.76, 368 0.95
+//     one walk instead of eight waves, d = 128  33..64 queries, E 280..472 1.09..1.47 but GELU on small scores 274 0.94, in general 268..272 0.76, 368 0.95
 //     four waves instead of eight, d = 128      up to 32 queries, E 784..1003 1.03..1.11;  l 776..928 0.90..0.99, 944..1017 1.00..1.03
 FwdPlan mfma_fwd_plan(const AttnParams& p) {
     const bool cheap = !has_act(p, KUNLUN_ACT_GELU), general_gelu = !cheap && !small_scores_expected(p);
@@ -574,7 +574,7 @@ FwdPlan mfma_fwd_plan(const AttnParams& p) {
         plan.sorted = !all_fit || (long_histories && units > 256);
         return plan;
     }
-    const int64_t dear_limit = d == 32 ? 4096 : d == 64 ? (long_histories ? 2048 : 1024) : (long_histories ? (!even ? 1024 : general_gelu ? 800 : 512) : 512);
+    const int64_t dear_limit = d == 32 ? 4096 : d == 64 ? (long_histories ? 2048 : 1024) : (long_histories ? (!even ? 1024 : general_gelu ? 800 : 600) : 512);
     const int64_t cheap_limit = d == 32 ? (long_histories || !all_fit ? 4096 : 768) : d == 64 ? (long_histories ? 1024 : 512) : (long_histories ? (even ? 512 : 1024) : 256);
     if (blocks <= (cheap ? cheap_limit : dear_limit))
         plan.key_split = long_histories && blocks <= (d == 32 ? 1536 : 2048) ? 8 : 4;
