@@ -8,7 +8,7 @@ Workspace layout relied on here (csrc/common.h, csrc/tile_map.h): a 256-byte hea
   query-tiled launches    int32 tile_start[B+1] (exclusive prefix sums of ceil(n_b / 128)), padded to 256
                           bytes, then int32 tile_example[tile] = example of every tile.
 The sorting kernel runs when the launch has more workgroups than are resident at once: forward more than 1024
-(example, head) items, or, with histories beyond 1024 keys, more than 256 blocks of 32 queries (d = 64, 33..64 queries: items; d = 32
+(example, head) items, or, with histories beyond 1024 keys, more than 256 blocks of 32 queries (d = 64, both blocks in a wave: items; d = 32
 in pairs of heads with 33..64 queries: pairs; d = 128, up to 32 queries: more than 512 blocks with histories beyond 512 keys); backward
 more than 1024 items, or, with histories beyond 512 keys, an eighth more than fit, and at d = 64 with 33..64 queries more than 512; at
 d = 128 more than 512 (more than 32 queries) or 256 items whatever the histories; pairs of heads only with histories beyond 1024 keys.
