@@ -204,9 +204,12 @@ def _head_act(head_act, H):
     return (ctypes.c_int32 * len(head_act))(*[int(a) for a in head_act])
 
 
-def _workspace(workspace, nbytes, device):
+def _workspace(workspace, nbytes, device, stream):
     if workspace is None:
-        return torch.empty(max(nbytes, 256), dtype=torch.uint8, device=device)
+        ws = torch.empty(max(nbytes, 256), dtype=torch.uint8, device=device)
+        if isinstance(stream, torch.Stream) and ws.is_cuda:  # given back when the call returns, perhaps before the stream reaches it
+            ws.record_stream(stream)
+        return ws
     _check("workspace", workspace, dtype=torch.uint8)
     return workspace
 
@@ -233,7 +236,7 @@ def gdpa_fwd(q, k, v, kv_offsets, scale, act, *, q_offsets=None, max_q=None, max
     _check("lse", lse, dtype=torch.float32, like=None, shape=(H, total_q), optional=True)
     nbytes = workspace_bytes(OP_GDPA_FWD, B, H, d, max_q, max_kv, total_q, total_kv)
     ha = _head_act(head_act, H)
-    ws = _workspace(workspace, nbytes, q.device)
+    ws = _workspace(workspace, nbytes, q.device, stream)
     _on_device(q=q, k=k, v=v, kv_offsets=kv_offsets, q_offsets=q_offsets, out=o, lse=lse, workspace=ws)
     _verify("kv_offsets", kv_offsets, total_kv, max_kv, stream)
     _verify("q_offsets", q_offsets, total_q, max_q, stream)
@@ -300,7 +303,7 @@ def gdpa_bwd(q, k, v, d_o, kv_offsets, scale, act, *, o=None, lse=None, q_offset
     dq, dk, dv = _grads(out, q, k, v)
     nbytes = workspace_bytes(OP_GDPA_BWD, B, H, d, max_q, max_kv, total_q, total_kv)
     ha = _head_act(head_act, H)
-    ws = _workspace(workspace, nbytes, q.device)
+    ws = _workspace(workspace, nbytes, q.device, stream)
     _on_device(q=q, k=k, v=v, d_o=d_o, o=o, lse=lse, kv_offsets=kv_offsets, q_offsets=q_offsets, dq=dq, dk=dk, dv=dv,
                workspace=ws)
     _verify("kv_offsets", kv_offsets, total_kv, max_kv, stream)
@@ -331,7 +334,7 @@ def seed_attn_fwd(e_seed, k, v, kv_offsets, scale, act=ACT_SOFTMAX, *, max_kv, h
         lse = torch.empty((H, total_q), dtype=torch.float32, device=e_seed.device)
     _check("lse", lse, dtype=torch.float32, shape=(H, total_q), optional=True)
     ha = _head_act(head_act, H)
-    ws = _workspace(workspace, workspace_bytes(OP_SEED_FWD, B, H, d, n_seeds, max_kv, total_q, k.shape[0]), e_seed.device)
+    ws = _workspace(workspace, workspace_bytes(OP_SEED_FWD, B, H, d, n_seeds, max_kv, total_q, k.shape[0]), e_seed.device, stream)
     _on_device(e_seed=e_seed, k=k, v=v, kv_offsets=kv_offsets, out=o, lse=lse, workspace=ws)
     _verify("kv_offsets", kv_offsets, k.shape[0], max_kv, stream)
     rc = _lib.kunlun_seed_attn_fwd(_ptr(e_seed), _ptr(k), _ptr(v), _ptr(o), _ptr(lse), _ptr(kv_offsets), B, H, d, n_seeds,
@@ -359,7 +362,7 @@ def seed_attn_bwd(e_seed, k, v, d_o, kv_offsets, scale, act=ACT_SOFTMAX, *, o=No
     _check("lse", lse, dtype=torch.float32, shape=(H, total_q), optional=True)
     d_e, dk, dv = _grads(out, e_seed, k, v)
     ha = _head_act(head_act, H)
-    ws = _workspace(workspace, workspace_bytes(OP_SEED_BWD, B, H, d, n_seeds, max_kv, total_q, k.shape[0]), e_seed.device)
+    ws = _workspace(workspace, workspace_bytes(OP_SEED_BWD, B, H, d, n_seeds, max_kv, total_q, k.shape[0]), e_seed.device, stream)
     _on_device(e_seed=e_seed, k=k, v=v, d_o=d_o, o=o, lse=lse, kv_offsets=kv_offsets, d_e=d_e, dk=dk, dv=dv, workspace=ws)
     _verify("kv_offsets", kv_offsets, k.shape[0], max_kv, stream)
     rc = _lib.kunlun_seed_attn_bwd(_ptr(e_seed), _ptr(k), _ptr(v), _ptr(o), _ptr(lse), _ptr(d_o), _ptr(d_e), _ptr(dk), _ptr(dv),
@@ -389,7 +392,7 @@ def swa_fwd(q, k, v, offsets, window_left, window_right, scale, *, max_len, out=
         lse = torch.empty((H, total), dtype=torch.float32, device=q.device)
     _check("lse", lse, dtype=torch.float32, shape=(H, total), optional=True)
     nbytes = workspace_bytes(OP_SWA_FWD, B, H, d, max_len, max_len, total, total)
-    ws = _workspace(workspace, nbytes, q.device)
+    ws = _workspace(workspace, nbytes, q.device, stream)
     _on_device(q=q, k=k, v=v, offsets=offsets, out=o, lse=lse, workspace=ws)
     _verify("offsets", offsets, total, max_len, stream)
     rc = _lib.kunlun_swa_fwd(_ptr(q), _ptr(k), _ptr(v), _ptr(o), _ptr(lse), _ptr(offsets), B, H, d, int(max_len),
@@ -419,7 +422,7 @@ def swa_bwd(q, k, v, o, lse, d_o, offsets, window_left, window_right, scale, *, 
     B = offsets.numel() - 1
     dq, dk, dv = _grads(out, q, k, v)
     nbytes = workspace_bytes(OP_SWA_BWD, B, H, d, max_len, max_len, total, total)
-    ws = _workspace(workspace, nbytes, q.device)
+    ws = _workspace(workspace, nbytes, q.device, stream)
     _on_device(q=q, k=k, v=v, o=o, lse=lse, d_o=d_o, offsets=offsets, dq=dq, dk=dk, dv=dv, workspace=ws)
     _verify("offsets", offsets, q.shape[0], max_len, stream)
     rc = _lib.kunlun_swa_bwd(_ptr(q), _ptr(k), _ptr(v), _ptr(o), _ptr(lse), _ptr(d_o), _ptr(dq), _ptr(dk), _ptr(dv),
@@ -449,7 +452,7 @@ def sumkron_fwd(x, z, w, *, out=None, workspace=None, stream=None):
     _check("w", w, like=x, shape=(k, D, D))
     y = torch.empty((B, T, D), dtype=x.dtype, device=x.device) if out is None else out
     _check("out", y, like=x, shape=(B, T, D))
-    ws = _workspace(workspace, int(_lib.kunlun_sumkron_batch_bytes(B, S, T, D, k, _dtype_code(x))), x.device)
+    ws = _workspace(workspace, int(_lib.kunlun_sumkron_batch_bytes(B, S, T, D, k, _dtype_code(x))), x.device, stream)
     _on_device(x=x, z=z, w=w, out=y, workspace=ws)
     rc = _lib.kunlun_sumkron_fwd(_ptr(x), _ptr(z), _ptr(w), _ptr(y), B, S, T, D, k, _dtype_code(x), _ptr(ws), ws.numel(),
                                  _stream(stream))
@@ -477,7 +480,7 @@ def sumkron_bwd(x, z, w, dy, *, workspace=None, stream=None):
     _check("w", w, like=x, shape=(k, D, D))
     _check("dy", dy, like=x, shape=(B, T, D))
     dx, dz, dw = torch.empty_like(x), torch.empty_like(z), torch.empty_like(w)
-    ws = _workspace(workspace, sumkron_bwd_workspace_bytes(B, S, T, D, k, _dtype_code(x)), x.device)
+    ws = _workspace(workspace, sumkron_bwd_workspace_bytes(B, S, T, D, k, _dtype_code(x)), x.device, stream)
     _on_device(x=x, z=z, w=w, dy=dy, workspace=ws)
     rc = _lib.kunlun_sumkron_bwd(_ptr(x), _ptr(z), _ptr(w), _ptr(dy), _ptr(dx), _ptr(dz), _ptr(dw), B, S, T, D, k,
                                  _dtype_code(x), _ptr(ws), ws.numel(), _stream(stream))
@@ -513,9 +516,7 @@ def jagged_stream_probe(a, b, c, out_a, out_b, offsets, max_len, reads, writes, 
     _check_offsets("offsets", offsets)
     B = offsets.numel() - 1
     need = 256 + (4 * (B + 1) + 255) // 256 * 256
-    if workspace is None:
-        workspace = torch.empty(need, dtype=torch.uint8, device=a.device)
-    _check("workspace", workspace, dtype=torch.uint8)
+    workspace = _workspace(workspace, need, a.device, stream)
     _on_device(a=a, b=b, c=c, out_a=out_a, out_b=out_b, offsets=offsets, workspace=workspace)
     rc = _lib.kunlun_jagged_stream_probe(_ptr(a), _ptr(b), _ptr(c), _ptr(out_a), _ptr(out_b), _ptr(offsets), B, H, d, int(max_len),
                                          total, int(reads), int(writes), int(workgroups_per_cu), _ptr(workspace),

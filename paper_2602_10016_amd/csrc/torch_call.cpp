@@ -9,6 +9,7 @@
 // that is not accepted there.  A launch that the HIP runtime refuses raises KunlunError here: work may be enqueued by then,
 // and the call is not made again.
 #include <torch/csrc/Exceptions.h>
+#include <torch/csrc/Stream.h>
 #include <torch/csrc/autograd/python_variable.h>
 #include <torch/csrc/utils/object_ptr.h>
 #include <ATen/ATen.h>
@@ -176,8 +177,14 @@ PyObject* pair(const Out& a, PyObject* given_a, const Out& b, PyObject* given_b)
 void take_workspace(Call& c, PyObject* o, Out& ws) {
     if (o != Py_None) ws.t = c.bytes(o);
 }
-void make_workspace(Out& ws, const at::Tensor& like, size_t nbytes) {
-    if (!ws.t) ws.make(like, {(int64_t)(nbytes > 256 ? nbytes : 256)}, at::kByte);
+// (given back when the call returns: the allocator is told of the caller's stream, on which its kernels may still be to run)
+void make_workspace(Out& ws, const at::Tensor& like, size_t nbytes, PyObject* stream) {
+    if (ws.t) return;
+    ws.make(like, {(int64_t)(nbytes > 256 ? nbytes : 256)}, at::kByte);
+    if (stream != Py_None && THPStream_Check(stream)) {
+        const THPStream* s = (THPStream*)stream;
+        ws.fresh.record_stream(c10::Stream::unpack3(s->stream_id, (c10::DeviceIndex)s->device_index, (c10::DeviceType)s->device_type));
+    }
 }
 
 template <typename T> const T* data(const at::Tensor* t) { return t ? (const T*)t->data_ptr() : nullptr; }
@@ -241,7 +248,7 @@ ENTRY(gdpa_fwd, 14)
     PLAIN_OR_NONE;
     if (!o.t) o.make(*q, q->sizes(), q->scalar_type());
     if (!lse.t && want_lse) lse.make(*q, {H, total_q}, at::kFloat);
-    make_workspace(ws, *q, ws.t ? 0 : kunlun_workspace_bytes(KUNLUN_OP_GDPA_FWD, (int)B, (int)H, (int)d, max_q, max_kv, total_q, total_kv));
+    make_workspace(ws, *q, ws.t ? 0 : kunlun_workspace_bytes(KUNLUN_OP_GDPA_FWD, (int)B, (int)H, (int)d, max_q, max_kv, total_q, total_kv), a[13]);
     const int rc = enqueue(kunlun_gdpa_fwd, q->data_ptr(), k->data_ptr(), v->data_ptr(), o.ptr(), (float*)lse.ptr(),
                            data<int32_t>(qo), data<int32_t>(kvo), (int)B, (int)H, (int)d, max_q, max_kv, total_q, total_kv,
                            scale, act, nullptr, c.dtype(), ws.ptr(), (size_t)ws.t->numel(), s);
@@ -276,7 +283,7 @@ ENTRY(gdpa_bwd, 15)
     void* s = c.stream(a[14]);
     PLAIN_OR_NONE;
     grads.allocate(like);
-    make_workspace(ws, *q, ws.t ? 0 : kunlun_workspace_bytes(KUNLUN_OP_GDPA_BWD, (int)B, (int)H, (int)d, max_q, max_kv, total_q, total_kv));
+    make_workspace(ws, *q, ws.t ? 0 : kunlun_workspace_bytes(KUNLUN_OP_GDPA_BWD, (int)B, (int)H, (int)d, max_q, max_kv, total_q, total_kv), a[14]);
     const int rc = enqueue(kunlun_gdpa_bwd, q->data_ptr(), k->data_ptr(), v->data_ptr(), data<void>(o), data<float>(lse),
                            d_o->data_ptr(), grads.g[0].ptr(), grads.g[1].ptr(), grads.g[2].ptr(), data<int32_t>(qo),
                            data<int32_t>(kvo), (int)B, (int)H, (int)d, max_q, max_kv, total_q, total_kv, scale, act, nullptr,
@@ -310,7 +317,7 @@ ENTRY(seed_attn_fwd, 12)
     PLAIN_OR_NONE;
     if (!o.t) o.make(*q, {total_q, H, d}, q->scalar_type());
     if (!lse.t && want_lse) lse.make(*q, {H, total_q}, at::kFloat);
-    make_workspace(ws, *q, ws.t ? 0 : kunlun_workspace_bytes(KUNLUN_OP_SEED_FWD, (int)B, (int)H, (int)d, (int)seeds, max_kv, total_q, total_kv));
+    make_workspace(ws, *q, ws.t ? 0 : kunlun_workspace_bytes(KUNLUN_OP_SEED_FWD, (int)B, (int)H, (int)d, (int)seeds, max_kv, total_q, total_kv), a[11]);
     const int rc = enqueue(kunlun_seed_attn_fwd, q->data_ptr(), k->data_ptr(), v->data_ptr(), o.ptr(), (float*)lse.ptr(),
                            data<int32_t>(kvo), (int)B, (int)H, (int)d, (int)seeds, max_kv, total_kv, scale, act, nullptr,
                            c.dtype(), ws.ptr(), (size_t)ws.t->numel(), s);
@@ -345,7 +352,7 @@ ENTRY(seed_attn_bwd, 13)
     void* s = c.stream(a[12]);
     PLAIN_OR_NONE;
     grads.allocate(like);
-    make_workspace(ws, *q, ws.t ? 0 : kunlun_workspace_bytes(KUNLUN_OP_SEED_BWD, (int)B, (int)H, (int)d, (int)seeds, max_kv, total_q, total_kv));
+    make_workspace(ws, *q, ws.t ? 0 : kunlun_workspace_bytes(KUNLUN_OP_SEED_BWD, (int)B, (int)H, (int)d, (int)seeds, max_kv, total_q, total_kv), a[12]);
     const int rc = enqueue(kunlun_seed_attn_bwd, q->data_ptr(), k->data_ptr(), v->data_ptr(), data<void>(o), data<float>(lse),
                            d_o->data_ptr(), grads.g[0].ptr(), grads.g[1].ptr(), grads.g[2].ptr(), data<int32_t>(kvo), (int)B,
                            (int)H, (int)d, (int)seeds, max_kv, total_kv, scale, act, nullptr, c.dtype(), ws.ptr(),
@@ -377,7 +384,7 @@ ENTRY(swa_fwd, 13)
     PLAIN_OR_NONE;
     if (!o.t) o.make(*q, q->sizes(), q->scalar_type());
     if (!lse.t && want_lse) lse.make(*q, {H, total}, at::kFloat);
-    make_workspace(ws, *q, ws.t ? 0 : kunlun_workspace_bytes(KUNLUN_OP_SWA_FWD, (int)B, (int)H, (int)d, max_len, max_len, total, total));
+    make_workspace(ws, *q, ws.t ? 0 : kunlun_workspace_bytes(KUNLUN_OP_SWA_FWD, (int)B, (int)H, (int)d, max_len, max_len, total, total), a[12]);
     const int rc = enqueue(kunlun_swa_fwd, q->data_ptr(), k->data_ptr(), v->data_ptr(), o.ptr(), (float*)lse.ptr(),
                            data<int32_t>(off), (int)B, (int)H, (int)d, max_len, total, left, right, scale, c.dtype(), ws.ptr(),
                            (size_t)ws.t->numel(), s);
@@ -409,7 +416,7 @@ ENTRY(swa_bwd, 14)
     void* s = c.stream(a[13]);
     PLAIN_OR_NONE;
     grads.allocate(like);
-    make_workspace(ws, *q, ws.t ? 0 : kunlun_workspace_bytes(KUNLUN_OP_SWA_BWD, (int)B, (int)H, (int)d, max_len, max_len, total, total));
+    make_workspace(ws, *q, ws.t ? 0 : kunlun_workspace_bytes(KUNLUN_OP_SWA_BWD, (int)B, (int)H, (int)d, max_len, max_len, total, total), a[13]);
     const int rc = enqueue(kunlun_swa_bwd, q->data_ptr(), k->data_ptr(), v->data_ptr(), o->data_ptr(), data<float>(lse),
                            d_o->data_ptr(), grads.g[0].ptr(), grads.g[1].ptr(), grads.g[2].ptr(), data<int32_t>(off), (int)B,
                            (int)H, (int)d, max_len, total, left, right, scale, c.dtype(), ws.ptr(), (size_t)ws.t->numel(), s);
@@ -434,7 +441,7 @@ ENTRY(sumkron_fwd, 6)
         if (n > INT32_MAX) c.ok = false;
     PLAIN_OR_NONE;
     if (!y.t) y.make(*x, {B, T, D}, x->scalar_type());
-    make_workspace(ws, *x, ws.t ? 0 : kunlun_sumkron_batch_bytes((int)B, (int)S, (int)T, (int)D, (int)k, c.dtype()));
+    make_workspace(ws, *x, ws.t ? 0 : kunlun_sumkron_batch_bytes((int)B, (int)S, (int)T, (int)D, (int)k, c.dtype()), a[5]);
     const int rc = enqueue(kunlun_sumkron_fwd, x->data_ptr(), z->data_ptr(), w->data_ptr(), y.ptr(), (int)B, (int)S, (int)T,
                            (int)D, (int)k, c.dtype(), ws.ptr(), (size_t)ws.t->numel(), s);
     DONE_OR_NONE(rc);
@@ -460,7 +467,7 @@ ENTRY(sumkron_bwd, 6)
     Grads grads;
     const at::Tensor* const like[3] = {x, z, w};
     grads.allocate(like);
-    make_workspace(ws, *x, ws.t ? 0 : kunlun_sumkron_bwd_workspace_bytes((int)B, (int)S, (int)T, (int)D, (int)k, c.dtype()));
+    make_workspace(ws, *x, ws.t ? 0 : kunlun_sumkron_bwd_workspace_bytes((int)B, (int)S, (int)T, (int)D, (int)k, c.dtype()), a[5]);
     const int rc = enqueue(kunlun_sumkron_bwd, x->data_ptr(), z->data_ptr(), w->data_ptr(), dy->data_ptr(), grads.g[0].ptr(),
                            grads.g[1].ptr(), grads.g[2].ptr(), (int)B, (int)S, (int)T, (int)D, (int)k, c.dtype(), ws.ptr(),
                            (size_t)ws.t->numel(), s);
