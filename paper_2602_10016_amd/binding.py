@@ -533,4 +533,6 @@ def check_offsets(offsets, total, max_len, *, stream=None) -> int:
     rc = _lib.kunlun_check_offsets(_ptr(offsets), offsets.numel() - 1, int(total), int(max_len), _ptr(out), _stream(stream))
     if rc != OK:
         raise KunlunError(rc)
+    if isinstance(stream, torch.Stream):  # (the read follows the kernel only on the kernel's stream)
+        stream.synchronize()
     return int(out.item())

@@ -36,3 +36,12 @@ def test_a_workspace_is_kept_until_its_stream_has_used_it(monkeypatch, native):
     assert other.data_ptr() != address
     torch.cuda.synchronize()
     assert torch.equal(got, want)
+
+
+def test_the_count_of_violations_is_read_behind_its_kernel():
+    offsets = torch.tensor([0, 5, 3, 9], dtype=torch.int32, device="cuda")
+    torch.cuda.synchronize()
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        torch.cuda._sleep(100_000_000)
+    assert kb.check_offsets(offsets, 9, 5, stream=stream) > 0
