@@ -431,11 +431,18 @@ int kunlun_swa_bwd(const void* q, const void* k, const void* v, const void* o, c
     // 32-bit window arithmetic (position + reach) far from overflow
     p.left = (window_left < 0 || window_left >= max_len) ? -1 : window_left;
     p.right = (window_right < 0 || window_right >= max_len) ? -1 : window_right;
+    hipStream_t s = (hipStream_t)stream;
     hipError_t e;
-    if (mfma_bwd_tiled_supported(p, dtype))
-        e = launch_mfma_bwd_tiled(p, (char*)workspace + WS_HEADER_BYTES + order_bytes(B), true, 0, (hipStream_t)stream);
-    else  // one wavefront per gradient row: dQ rows over their windows, then dK/dV rows
-        e = launch_scalar_bwd(p, dtype, (hipStream_t)stream);
+    if (swa_bwd_band_applies(p, dtype)) {
+        int32_t* order = (int32_t*)((char*)workspace + WS_HEADER_BYTES);  // sequences, longest first
+        p.order = order;
+        e = launch_schedule(offsets, B, max_len, order, (int32_t*)workspace, s);
+        if (e == hipSuccess) e = launch_swa_bwd_band(p, s);
+    } else if (mfma_bwd_tiled_supported(p, dtype)) {
+        e = launch_mfma_bwd_tiled(p, (char*)workspace + WS_HEADER_BYTES + order_bytes(B), true, 0, s);
+    } else {  // one wavefront per gradient row: dQ rows over their windows, then dK/dV rows
+        e = launch_scalar_bwd(p, dtype, s);
+    }
     return e == hipSuccess ? KUNLUN_OK : KUNLUN_ERR_LAUNCH;
 }
 

@@ -1,5 +1,6 @@
-// bf16 matrix-core backward in two passes, for the shapes the fused backward kernel does not
-// take: sliding-window self-attention (Eq. (sliding window)) and GDPA / softmax attention with
+// bf16 matrix-core backward in two passes, for the shapes the fused backward kernels do not
+// take: sliding-window self-attention (Eq. (sliding window); attn_swa_bwd_band_mfma.hip serves d = 128 with narrow windows over many
+// sequences) and GDPA / softmax attention with
 // more than 64 queries per example (the PFFN direction of Eq. (GDPA): sequence tokens are the
 // queries).  Scores are recomputed tile by tile in both passes; nothing of score size is stored.
 //
@@ -76,14 +77,6 @@ __device__ __forceinline__ void store_tile_rows(char* stage, const f32x16 (&acc)
     store_staged_rows<D>(stage, out_rows, hd, n_rows, lane);
 }
 
-// One 8-element fragment from two transposing reads (rows .. +3 at a, rows .. +3 at b).
-__device__ __forceinline__ bf16x8 tr_pair(const char* a, const char* b) {
-    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(LDS_PTR(s16x4, a));
-    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(LDS_PTR(s16x4, b));
-    typedef __attribute__((ext_vector_type(8))) short s16x8;
-    return __builtin_bit_cast(bf16x8, (s16x8)__builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
-}
-
 // LDS of both passes: a ring of stages; the prologue stages the workgroup's own 32 NW rows
 // (NW tiles, K-tile swizzle) in the end of the ring, and the epilogue transposes the results
 // through padded rows.
@@ -97,26 +90,6 @@ struct TiledSmem {
     static constexpr int OWN_BYTES = NW * TILE;
     static_assert(TOTAL - OWN_BYTES >= STAGE, "the staged rows must leave the first stage free");
     static_assert(NW * PT::ROW_TILE <= TOTAL, "output staging must fit");
-};
-
-// Per-lane LDS read offsets inside a tile in the two-way swizzle.
-template <int D>
-struct UFrag {
-    int row0, trA, trB;
-    __device__ __forceinline__ void init(int lane) {
-        using L = TileLayout<D>;
-        const int r = lane & 31, g = lane >> 5, s16 = lane & 15, hi16 = (lane >> 4) & 1;
-        const int colb = (16 * hi16 + 4 * (s16 & 3)) * 2;
-        row0 = L::u_offset(r, g * 16);                      // row fragment: row r, channels 16*kc + 8g ..: row0 ^ (kc << 5)
-        trA = L::u_offset(4 * g + (s16 >> 2), colb);         // transposed: rows 16c + 4g + 0..3, channel block db: trA ^ (db << 6)
-        trB = L::u_offset(8 + 4 * g + (s16 >> 2), colb);     //             rows 16c + 8 + 4g + 0..3
-    }
-    __device__ __forceinline__ bf16x8 row(const char* tile, int kc) const { return *(const bf16x8*)(tile + (row0 ^ (kc << 5))); }
-    // A operand (row = channel 32*db + lane%32) for the 16 tile rows that the C layout puts in registers 8c .. 8c+7
-    __device__ __forceinline__ bf16x8 transposed(const char* tile, int db, int c) const {
-        const char* base = tile + c * 16 * D * 2;
-        return tr_pair(base + (trA ^ (db << 6)), base + (trB ^ (db << 6)));
-    }
 };
 
 #define KUNLUN_ACT_SWITCH(ACTV, CALL)                                   \

@@ -55,11 +55,6 @@ struct WideSmem {
 
 static bool wide_applies(int d, int max_q, int max_kv) { return d == WideSmem::D && max_q > 64 && max_q <= WideSmem::NQ && max_kv > KT; }
 
-// P / dS image, and a wave's output block: rows of 64 bytes, 16-byte chunk swizzled by the row.
-__device__ __forceinline__ int w64_offset(int row, int byte_in_row) {
-    return row * 64 + ((((byte_in_row >> 4) ^ (row >> 2)) & 3) << 4) + (byte_in_row & 15);
-}
-
 // kt0 .. kt1-1: key tiles of the item.  dq_part: null = the item covers all tiles, dQ rows go out rounded;
 // else the fp32 dQ partial sums of this range go there, lane by lane (launch_wide_dq_sum adds them).
 template <int ACT>

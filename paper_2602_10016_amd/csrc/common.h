@@ -121,6 +121,10 @@ hipError_t launch_mfma_fwd_qtiled(const AttnParams& p, hipStream_t stream);
 // its waves rotate through the query blocks (attn_swa_band_mfma.hip).  p.order: sequences, longest first.
 bool swa_band_applies(const AttnParams& p);
 hipError_t launch_swa_band_fwd(const AttnParams& p, hipStream_t stream);
+// The backward of a bounded window over many (sequence, head) items: one workgroup walks one item, its waves own the key tiles
+// under the window (attn_swa_bwd_band_mfma.hip).  p.order: sequences, longest first.
+bool swa_bwd_band_applies(const AttnParams& p, int dtype);
+hipError_t launch_swa_bwd_band(const AttnParams& p, hipStream_t stream);
 bool mfma_bwd_supported(const AttnParams& p, int dtype);
 // How a backward launch of up to 64 queries per example is cut: waves per item (d = 128: always four), whether an item is a
 // pair of heads (d = 32), and whether items start longest first (p.order and p.queue are then set).

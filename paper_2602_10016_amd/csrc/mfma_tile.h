@@ -171,6 +171,39 @@ __device__ __forceinline__ bf16x8 read_tr_frag(const char* lds, OFFSET offset, i
     return __builtin_bit_cast(bf16x8, both);
 }
 
+// One 8-element fragment from two transposing reads (rows .. +3 at a, rows .. +3 at b).
+__device__ __forceinline__ bf16x8 tr_pair(const char* a, const char* b) {
+    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(LDS_PTR(s16x4, a));
+    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(LDS_PTR(s16x4, b));
+    typedef __attribute__((ext_vector_type(8))) short s16x8;
+    return __builtin_bit_cast(bf16x8, (s16x8)__builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+}
+
+// Per-lane LDS read offsets inside a tile in the two-way swizzle.
+template <int D>
+struct UFrag {
+    int row0, trA, trB;
+    __device__ __forceinline__ void init(int lane) {
+        using L = TileLayout<D>;
+        const int r = lane & 31, g = lane >> 5, s16 = lane & 15, hi16 = (lane >> 4) & 1;
+        const int colb = (16 * hi16 + 4 * (s16 & 3)) * 2;
+        row0 = L::u_offset(r, g * 16);                      // row fragment: row r, channels 16*kc + 8g ..: row0 ^ (kc << 5)
+        trA = L::u_offset(4 * g + (s16 >> 2), colb);         // transposed: rows 16c + 4g + 0..3, channel block db: trA ^ (db << 6)
+        trB = L::u_offset(8 + 4 * g + (s16 >> 2), colb);     //             rows 16c + 8 + 4g + 0..3
+    }
+    __device__ __forceinline__ bf16x8 row(const char* tile, int kc) const { return *(const bf16x8*)(tile + (row0 ^ (kc << 5))); }
+    // A operand (row = channel 32*db + lane%32) for the 16 tile rows that the C layout puts in registers 8c .. 8c+7
+    __device__ __forceinline__ bf16x8 transposed(const char* tile, int db, int c) const {
+        const char* base = tile + c * 16 * D * 2;
+        return tr_pair(base + (trA ^ (db << 6)), base + (trB ^ (db << 6)));
+    }
+};
+
+// P / dS images and 32-channel output blocks of the backward kernels: rows of 64 bytes, 16-byte chunk swizzled by the row.
+__device__ __forceinline__ int w64_offset(int row, int byte_in_row) {
+    return row * 64 + ((((byte_in_row >> 4) ^ (row >> 2)) & 3) << 4) + (byte_in_row & 15);
+}
+
 // Value of x in the lane 32 further (or 32 back), paired with the lane's own: the gfx950
 // half-wave swap is a VALU operation, where a shuffle would take an LDS round trip.
 // Returns both values in an order that depends on the lane half; use for symmetric reductions.
