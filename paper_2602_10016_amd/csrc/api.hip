@@ -240,9 +240,9 @@ int kunlun::gdpa_fwd_checked(const void* q, const void* k, const void* v, void* 
     hipError_t e;
     if (mfma_fwd_supported(p, dtype)) {
         int32_t* order = (int32_t*)((char*)workspace + WS_HEADER_BYTES);
-        if (mfma_fwd_is_qtiled(p)) {
+        if (mfma_fwd_is_qtiled(p) && !dense_tiles_sorted(p)) {
             p.order = order;  // holds the query-tile prefix sums
-        } else if (!mfma_fwd_plan(p).sorted) {
+        } else if (!mfma_fwd_is_qtiled(p) && !mfma_fwd_plan(p).sorted) {
             p.order = nullptr;
         } else {
             p.order = order;
@@ -347,6 +347,12 @@ int gdpa_bwd_checked(const void* q, const void* k, const void* v, const void* o,
         char* const order = (char*)workspace + WS_HEADER_BYTES;
         e = launch_mfma_bwd_wide(p, workspace, order, order + order_bytes(B), (char*)workspace + need_bytes, s);
     } else if (mfma_bwd_tiled_supported(p, dtype)) {
+        if (dense_tiles_sorted(p)) {
+            int32_t* order = (int32_t*)((char*)workspace + WS_HEADER_BYTES);  // examples, longest history first
+            p.order = order;
+            e = launch_schedule(kv_offsets, B, max_kv, order, (int32_t*)workspace, s);
+            if (e != hipSuccess) return KUNLUN_ERR_LAUNCH;
+        }
         e = launch_mfma_bwd_tiled(p, (char*)workspace + WS_HEADER_BYTES + order_bytes(B), any_softmax, chunk_tiles, s);
     } else {
         e = launch_scalar_bwd(p, dtype, s);

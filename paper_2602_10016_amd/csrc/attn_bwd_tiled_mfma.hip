@@ -522,13 +522,19 @@ __device__ __forceinline__ bool locate_part(const int32_t* __restrict__ tile_sta
     t = t * PARTS + (int)(slot % PARTS);
     return true;
 }
-template <int D, int NW, bool WINDOWED>
+// SORTED: dense queries, examples by p.order
+template <int D, int NW, bool WINDOWED, bool SORTED>
 __global__ __launch_bounds__(64 * NW, D == 128 ? 2 : 3) void bwd_dq_kernel(AttnParams p, const int32_t* __restrict__ tile_start,
                                                             const int32_t* __restrict__ tile_example,
                                                             float* __restrict__ delta_ws) {
     __shared__ __attribute__((aligned(1024))) char lds[TiledSmem<D, 0, NW>::TOTAL];
     int b, h, qt;
-    if (!locate_part<TILE_ROWS / (32 * NW)>(tile_start, tile_example, p.B, p.H, b, h, qt)) return;
+    if (SORTED) {
+        static_assert(!SORTED || 32 * NW == TILE_ROWS, "whole tiles of the mapping");
+        if (!locate_dense_tile(p.order, p.B, p.H, p.max_q, blockIdx.x, b, h, qt)) return;
+    } else if (!locate_part<TILE_ROWS / (32 * NW)>(tile_start, tile_example, p.B, p.H, b, h, qt)) {
+        return;
+    }
     const int64_t k0 = p.kv_off[b];
     const int n_kv = p.kv_off[b + 1] - (int)k0;
     const int64_t q0 = q_begin(p, b);
@@ -898,10 +904,16 @@ static hipError_t launch_passes(const AttnParams& p, char* ws, bool any_softmax,
     int32_t* k_tiles = (int32_t*)(ws + tile_table_bytes(p.B, p.total_q));
     float* delta = (float*)(ws + tile_table_bytes(p.B, p.total_q) + tile_table_bytes(p.B, p.total_kv));
     (void)any_softmax;  // pass A computes delta of its softmax heads itself and leaves it in the workspace for pass B
-    if (p.total_q > 0) {
+    bool sorted = false;
+    if constexpr (!WINDOWED) {
+        sorted = p.total_q > 0 && dense_tiles_sorted(p);
+        if (sorted)
+            hipLaunchKernelGGL((bwd_dq_kernel<D, NW, false, true>), dim3((unsigned)dense_tile_grid(p)), dim3(64 * NW), 0, stream, p, nullptr, nullptr, delta);
+    }
+    if (p.total_q > 0 && !sorted) {
         hipLaunchKernelGGL(tile_prefix_kernel<1>, dim3(1), dim3(1024), 0, stream, p.q_off, p.max_q, p.B, q_tiles,
                            tile_example_of(q_tiles, p.B), TILE_ROWS);
-        hipLaunchKernelGGL((bwd_dq_kernel<D, NW, WINDOWED>), dim3(tile_grid(p.B, p.H, p.total_q) * (TILE_ROWS / (32 * NW))), dim3(64 * NW), 0,
+        hipLaunchKernelGGL((bwd_dq_kernel<D, NW, WINDOWED, false>), dim3(tile_grid(p.B, p.H, p.total_q) * (TILE_ROWS / (32 * NW))), dim3(64 * NW), 0,
                            stream, p, q_tiles, tile_example_of(q_tiles, p.B), delta);
     }
     if (p.total_kv > 0) {

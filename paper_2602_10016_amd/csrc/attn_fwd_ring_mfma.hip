@@ -228,15 +228,19 @@ __device__ __forceinline__ void attn_fwd_ring_item(const AttnParams& p, char* ld
     }
 }
 
-// One workgroup per (example, query tile, head); work mapping of tile_map.h.
-template <int D, int NW, int OCC, bool WINDOWED>
+// One workgroup per (example, query tile, head); work mapping of tile_map.h (SORTED: dense queries, examples by p.order).
+template <int D, int NW, int OCC, bool WINDOWED, bool SORTED>
 __global__ __launch_bounds__(64 * NW, OCC) void qtile_fwd_mfma_kernel(AttnParams p, const int32_t* __restrict__ tile_start,
                                                                       const int32_t* __restrict__ tile_example, int runs) {
     __shared__ __attribute__((aligned(1024))) char lds[RingSmem<D, NW>::TOTAL];
     constexpr int QT = 32 * NW;
     static_assert(QT == TILE_ROWS, "tile size of the work mapping");
     int b, h, qt;
-    if (!locate_tile(tile_start, tile_example, p.B, p.H, blockIdx.x, b, h, qt, runs)) return;
+    if (SORTED) {
+        if (!locate_dense_tile(p.order, p.B, p.H, p.max_q, blockIdx.x, b, h, qt)) return;
+    } else if (!locate_tile(tile_start, tile_example, p.B, p.H, blockIdx.x, b, h, qt, runs)) {
+        return;
+    }
     const int64_t k0 = p.kv_off[b];
     const int n_kv = p.kv_off[b + 1] - (int)k0;
     const int64_t q0 = q_begin(p, b);
@@ -260,17 +264,24 @@ __global__ __launch_bounds__(64 * NW, OCC) void qtile_fwd_mfma_kernel(AttnParams
 
 template <int D, int NW, int OCC, bool WINDOWED>
 static hipError_t launch_qtiled(const AttnParams& p, hipStream_t stream) {
+    if constexpr (!WINDOWED) {
+        if (dense_tiles_sorted(p)) {
+            hipLaunchKernelGGL((qtile_fwd_mfma_kernel<D, NW, OCC, false, true>), dim3((unsigned)dense_tile_grid(p)), dim3(64 * NW), 0, stream, p, nullptr,
+                               nullptr, 1);
+            return hipGetLastError();
+        }
+    }
     const int runs = tile_runs(p);
     int32_t* tile_start = const_cast<int32_t*>(p.order);
     int32_t* tile_example = tile_example_of(tile_start, p.B);
     hipLaunchKernelGGL(tile_prefix_kernel<0>, dim3(1), dim3(1024), 0, stream, p.q_off, p.max_q, p.B, tile_start,
                        tile_example, TILE_ROWS);
-    hipLaunchKernelGGL((qtile_fwd_mfma_kernel<D, NW, OCC, WINDOWED>), dim3(tile_grid(p.B, p.H, p.total_q, runs)),
+    hipLaunchKernelGGL((qtile_fwd_mfma_kernel<D, NW, OCC, WINDOWED, false>), dim3(tile_grid(p.B, p.H, p.total_q, runs)),
                        dim3(64 * NW), 0, stream, p, tile_start, tile_example, runs);
     return hipGetLastError();
 }
 
-// p.order points at tile_table_bytes(B, total_q) bytes of workspace.
+// p.order points at tile_table_bytes(B, total_q) bytes of workspace, or at the sorted examples (dense_tiles_sorted()).
 hipError_t launch_mfma_fwd_qtiled(const AttnParams& p, hipStream_t stream) {
     // 128-query tiles (4 waves of 32 queries)
     if (p.windowed)

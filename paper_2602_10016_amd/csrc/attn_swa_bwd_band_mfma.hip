@@ -24,6 +24,7 @@
 #include <type_traits>
 
 #include "lds_ring.h"
+#include "tile_map.h"
 
 namespace kunlun {
 
@@ -423,7 +424,7 @@ __global__ __launch_bounds__(64 * SWB_WAVES, 2) void swa_bwd_band_kernel(AttnPar
     extern __shared__ __attribute__((aligned(1024))) char swb_lds[];
     const unsigned slot = blockIdx.x >> 3;
     const int h = (int)(slot % (unsigned)p.H);
-    const int64_t e = (int64_t)(slot / (unsigned)p.H) * 8 + (blockIdx.x & 7);
+    const int64_t e = dealt_rank(slot / (unsigned)p.H, blockIdx.x & 7);
     if (e >= p.B) return;
     const int b = p.order[e];
     const int64_t row0 = p.kv_off[b];
