@@ -522,15 +522,17 @@ __device__ __forceinline__ bool locate_part(const int32_t* __restrict__ tile_sta
     t = t * PARTS + (int)(slot % PARTS);
     return true;
 }
-// SORTED: dense queries, examples by p.order
-template <int D, int NW, bool WINDOWED, bool SORTED>
+// (without tables: dense queries, examples by p.order, or, without an order, tiles numbered by the offsets)
+template <int D, int NW, bool WINDOWED>
 __global__ __launch_bounds__(64 * NW, D == 128 ? 2 : 3) void bwd_dq_kernel(AttnParams p, const int32_t* __restrict__ tile_start,
                                                             const int32_t* __restrict__ tile_example,
                                                             float* __restrict__ delta_ws) {
     __shared__ __attribute__((aligned(1024))) char lds[TiledSmem<D, 0, NW>::TOTAL];
     int b, h, qt;
-    if (SORTED) {
-        static_assert(!SORTED || 32 * NW == TILE_ROWS, "whole tiles of the mapping");
+    if (!tile_start && !p.order) {
+        if (!locate_spread_tile(p.q_off, p.B, p.H, p.total_q, 32 * NW, blockIdx.x, b, h, qt)) return;
+    } else if (!WINDOWED && !tile_start) {
+        static_assert(WINDOWED || 32 * NW == TILE_ROWS, "whole tiles of the mapping");
         if (!locate_dense_tile(p.order, p.B, p.H, p.max_q, blockIdx.x, b, h, qt)) return;
     } else if (!locate_part<TILE_ROWS / (32 * NW)>(tile_start, tile_example, p.B, p.H, b, h, qt)) {
         return;
@@ -555,7 +557,11 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 2 : 3) void bwd_dkdv_kernel(Att
                                                               const float* __restrict__ delta_ws) {
     __shared__ __attribute__((aligned(1024))) char lds[TiledSmem<D, STATS_BYTES, NW>::TOTAL + (D == 128 ? 3 : 0) * NW * 1024];
     int b, h, kt;
-    if (!locate_part<TILE_ROWS / (32 * NW)>(tile_start, tile_example, p.B, p.H, b, h, kt)) return;
+    if (!tile_start) {
+        if (!locate_spread_tile(p.kv_off, p.B, p.H, p.total_kv, 32 * NW, blockIdx.x, b, h, kt)) return;
+    } else if (!locate_part<TILE_ROWS / (32 * NW)>(tile_start, tile_example, p.B, p.H, b, h, kt)) {
+        return;
+    }
     const int64_t k0 = p.kv_off[b];
     const int n_kv = p.kv_off[b + 1] - (int)k0;
     const int64_t q0 = q_begin(p, b);
@@ -846,29 +852,35 @@ __device__ __forceinline__ void bwd_fewkeys_item(const AttnParams& p, const floa
     }
 }
 
-template <int D>
+// SPREAD: chunks numbered by the offsets, without tables
+template <int D, bool SPREAD>
 __global__ __launch_bounds__(256, 2) void bwd_fewkeys_kernel(AttnParams p, const int32_t* __restrict__ tile_start,
                                                           const int32_t* __restrict__ tile_example,
                                                           const float* __restrict__ delta_ws, float* __restrict__ partial,
                                                           int chunk_rows) {
     extern __shared__ __attribute__((aligned(1024))) char fk_lds[];
     int b, h, qt;
-    if (!locate_tile(tile_start, tile_example, p.B, p.H, blockIdx.x, b, h, qt)) return;
+    if (SPREAD) {
+        if (!locate_spread_tile(p.q_off, p.B, p.H, p.total_q, chunk_rows, blockIdx.x, b, h, qt)) return;
+    } else if (!locate_tile(tile_start, tile_example, p.B, p.H, blockIdx.x, b, h, qt)) {
+        return;
+    }
     const int64_t k0 = p.kv_off[b];
     int n_kv = p.kv_off[b + 1] - (int)k0;
     n_kv = n_kv > KT ? KT : n_kv;  // the launch condition (max_kv <= 32) promises this; never read past the tile
     const int64_t q0 = q_begin(p, b);
     const int nq_all = (int)(q_end(p, b) - q0);
-    const int q_first = qt * chunk_rows;  // the tile table counts chunks of chunk_rows queries here
+    const int q_first = qt * chunk_rows;  // the tiles of the mapping are chunks of chunk_rows queries here
     const int nq = (nq_all - q_first) < chunk_rows ? (nq_all - q_first) : chunk_rows;
-    float* part_out = partial + ((size_t)(tile_start[b] + qt) * p.H + h) * (2 * KT * D);
+    const int first = SPREAD ? spread_tile(p.q_off, b, chunk_rows) : tile_start[b];
+    float* part_out = partial + ((size_t)(first + qt) * p.H + h) * (2 * KT * D);
     KUNLUN_ACT_SWITCH(p.head_act[h], (bwd_fewkeys_item<D, A>(p, delta_ws, fk_lds, h, q0 + q_first, nq, k0, n_kv, part_out)));
 }
 
 // dK, dV rows of every example = sum of the partial tiles of its query tiles, in tile order; 4 channels per thread.
-template <int D>
+template <int D, bool SPREAD>
 __global__ __launch_bounds__(256) void fewkeys_reduce_kernel(AttnParams p, const int32_t* __restrict__ tile_start,
-                                                             const float* __restrict__ partial) {
+                                                             const float* __restrict__ partial, int chunk_rows) {
     constexpr int PER_ROW = D / 4;
     const int64_t gid = (int64_t)blockIdx.x * 256 + threadIdx.x;  // (((b*H + h)*2 + which)*32 + key)*PER_ROW + c4
     if (gid >= (int64_t)p.B * p.H * 2 * KT * PER_ROW) return;
@@ -880,7 +892,9 @@ __global__ __launch_bounds__(256) void fewkeys_reduce_kernel(AttnParams p, const
     const int64_t k0 = p.kv_off[b];
     if (key >= p.kv_off[b + 1] - (int)k0) return;
     f32x4 sum = {0.f, 0.f, 0.f, 0.f};
-    for (int t = tile_start[b]; t < tile_start[b + 1]; ++t)
+    const int first = SPREAD ? spread_tile(p.q_off, b, chunk_rows) : tile_start[b];
+    const int last = SPREAD ? first + (int)((q_end(p, b) - q_begin(p, b) + chunk_rows - 1) / chunk_rows) : tile_start[b + 1];
+    for (int t = first; t < last; ++t)
         sum += *(const f32x4*)(partial + (((size_t)t * p.H + h) * 2 + which) * (KT * D) + key * D + c4 * 4);
     bf16x4 out;
 #pragma unroll
@@ -904,19 +918,22 @@ static hipError_t launch_passes(const AttnParams& p, char* ws, bool any_softmax,
     int32_t* k_tiles = (int32_t*)(ws + tile_table_bytes(p.B, p.total_q));
     float* delta = (float*)(ws + tile_table_bytes(p.B, p.total_q) + tile_table_bytes(p.B, p.total_kv));
     (void)any_softmax;  // pass A computes delta of its softmax heads itself and leaves it in the workspace for pass B
-    bool sorted = false;
-    if constexpr (!WINDOWED) {
-        sorted = p.total_q > 0 && dense_tiles_sorted(p);
-        if (sorted)
-            hipLaunchKernelGGL((bwd_dq_kernel<D, NW, false, true>), dim3((unsigned)dense_tile_grid(p)), dim3(64 * NW), 0, stream, p, nullptr, nullptr, delta);
-    }
-    if (p.total_q > 0 && !sorted) {
+    // Small launches: the two kernels that write tables cost 5 to 7 us.  By offsets over by tables, 260 random calls, sliding windows and 33..64 keys: up
+    // to 500 tile-heads 1.1 to 1.4, to 1500 1.04 to 1.2, at d = 32 and 64 to 3500 1.04 to 1.14, beyond (d = 128: from 1600 on) 0.92 to 1.04.
+    const bool spread = p.q_off && tiles_expected(p) <= (p.d == 128 ? 1536 : 3600);
+    if (p.total_q > 0 && (spread || dense_tiles_sorted(p))) {
+        hipLaunchKernelGGL((bwd_dq_kernel<D, NW, WINDOWED>), dim3(spread ? spread_grid(p.B, p.H, p.total_q, 32 * NW) : (unsigned)dense_tile_grid(p)),
+                           dim3(64 * NW), 0, stream, p, nullptr, nullptr, delta);
+    } else if (p.total_q > 0) {
         hipLaunchKernelGGL(tile_prefix_kernel<1>, dim3(1), dim3(1024), 0, stream, p.q_off, p.max_q, p.B, q_tiles,
                            tile_example_of(q_tiles, p.B), TILE_ROWS);
-        hipLaunchKernelGGL((bwd_dq_kernel<D, NW, WINDOWED, false>), dim3(tile_grid(p.B, p.H, p.total_q) * (TILE_ROWS / (32 * NW))), dim3(64 * NW), 0,
+        hipLaunchKernelGGL((bwd_dq_kernel<D, NW, WINDOWED>), dim3(tile_grid(p.B, p.H, p.total_q) * (TILE_ROWS / (32 * NW))), dim3(64 * NW), 0,
                            stream, p, q_tiles, tile_example_of(q_tiles, p.B), delta);
     }
-    if (p.total_kv > 0) {
+    if (p.total_kv > 0 && spread) {
+        hipLaunchKernelGGL((bwd_dkdv_kernel<D, NW, WINDOWED>), dim3(spread_grid(p.B, p.H, p.total_kv, 32 * NW)), dim3(64 * NW), 0, stream, p, nullptr,
+                           nullptr, delta);
+    } else if (p.total_kv > 0) {
         hipLaunchKernelGGL(tile_prefix_kernel<1>, dim3(1), dim3(1024), 0, stream, p.kv_off, 0, p.B, k_tiles,
                            tile_example_of(k_tiles, p.B), TILE_ROWS);
         hipLaunchKernelGGL((bwd_dkdv_kernel<D, NW, WINDOWED>), dim3(tile_grid(p.B, p.H, p.total_kv) * (TILE_ROWS / (32 * NW))), dim3(64 * NW), 0,
@@ -947,7 +964,7 @@ static hipError_t launch_tiled(const AttnParams& p, char* ws, bool any_softmax, 
     return launch_passes<D, WINDOWED, 4>(p, ws, any_softmax, stream);
 }
 
-template <int D>
+template <int D, bool SPREAD>
 static hipError_t launch_fewkeys(const AttnParams& p, char* ws, bool any_softmax, int chunk_tiles, hipStream_t stream) {
     int32_t* q_tiles = (int32_t*)ws;
     float* delta = (float*)(ws + tile_table_bytes(p.B, p.total_q) + tile_table_bytes(p.B, p.total_kv));
@@ -956,7 +973,7 @@ static hipError_t launch_fewkeys(const AttnParams& p, char* ws, bool any_softmax
     if (bytes > 64 * 1024) {
         // once per process (thread-safe initialisation of a function-local static); not a stream operation
         static const hipError_t raised =
-            hipFuncSetAttribute((const void*)bwd_fewkeys_kernel<D>, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+            hipFuncSetAttribute((const void*)bwd_fewkeys_kernel<D, SPREAD>, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
         if (raised != hipSuccess) return raised;
     }
     if (any_softmax && p.total_q > 0) {
@@ -965,17 +982,18 @@ static hipError_t launch_fewkeys(const AttnParams& p, char* ws, bool any_softmax
                            (const bf16_t*)p.o, (const bf16_t*)p.d_o, delta, p.total_q, p.H);
     }
     const int chunk_rows = TILE_ROWS * chunk_tiles;
-    hipLaunchKernelGGL(tile_prefix_kernel<1>, dim3(1), dim3(1024), 0, stream, p.q_off, p.max_q, p.B, q_tiles,
-                       tile_example_of(q_tiles, p.B), chunk_rows);
+    if (!SPREAD)
+        hipLaunchKernelGGL(tile_prefix_kernel<1>, dim3(1), dim3(1024), 0, stream, p.q_off, p.max_q, p.B, q_tiles,
+                           tile_example_of(q_tiles, p.B), chunk_rows);
     if (p.total_q > 0) {
         const int64_t per_xcd = ((p.total_q / chunk_rows + p.B) * p.H + 7) / 8;  // an upper bound of the chunk count sizes the grid
-        hipLaunchKernelGGL((bwd_fewkeys_kernel<D>), dim3((unsigned)((per_xcd + 1) * 8)), dim3(256), bytes, stream, p, q_tiles,
+        hipLaunchKernelGGL((bwd_fewkeys_kernel<D, SPREAD>), dim3((unsigned)((per_xcd + 1) * 8)), dim3(256), bytes, stream, p, q_tiles,
                            tile_example_of(q_tiles, p.B), delta, partial, chunk_rows);
     }
     if (p.total_kv > 0) {
         const int64_t threads = (int64_t)p.B * p.H * 2 * KT * (D / 4);
-        hipLaunchKernelGGL((fewkeys_reduce_kernel<D>), dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, stream, p, q_tiles,
-                           partial);
+        hipLaunchKernelGGL((fewkeys_reduce_kernel<D, SPREAD>), dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, stream, p, q_tiles,
+                           partial, chunk_rows);
     }
     return hipGetLastError();
 }
@@ -983,8 +1001,12 @@ static hipError_t launch_fewkeys(const AttnParams& p, char* ws, bool any_softmax
 hipError_t launch_mfma_bwd_tiled(const AttnParams& p, void* workspace_tail, bool any_softmax, int chunk_tiles, hipStream_t stream) {
     char* ws = (char*)workspace_tail;
     if (fewkeys_applies(p.d, p.max_q, p.max_kv, p.windowed != 0))
-        return p.d == 128 ? launch_fewkeys<128>(p, ws, any_softmax, chunk_tiles, stream)
-               : p.d == 64 ? launch_fewkeys<64>(p, ws, any_softmax, chunk_tiles, stream) : launch_fewkeys<32>(p, ws, any_softmax, chunk_tiles, stream);
+        // (as in the forward: 1.04 to 1.25 up to 2600 tile-heads, at d = 32 and 64 1.02 to 1.1 up to 7000, about 1 beyond)
+        return p.q_off && tiles_expected(p) <= (p.d == 128 ? 2600 : 7000)
+                   ? (p.d == 128 ? launch_fewkeys<128, true>(p, ws, any_softmax, chunk_tiles, stream)
+                      : p.d == 64 ? launch_fewkeys<64, true>(p, ws, any_softmax, chunk_tiles, stream) : launch_fewkeys<32, true>(p, ws, any_softmax, chunk_tiles, stream))
+                   : (p.d == 128 ? launch_fewkeys<128, false>(p, ws, any_softmax, chunk_tiles, stream)
+                      : p.d == 64 ? launch_fewkeys<64, false>(p, ws, any_softmax, chunk_tiles, stream) : launch_fewkeys<32, false>(p, ws, any_softmax, chunk_tiles, stream));
     if (p.windowed)
         return p.d == 128 ? launch_tiled<128, true>(p, ws, true, stream)
                : p.d == 64 ? launch_tiled<64, true>(p, ws, true, stream) : launch_tiled<32, true>(p, ws, true, stream);

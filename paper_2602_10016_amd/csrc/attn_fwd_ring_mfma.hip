@@ -228,15 +228,19 @@ __device__ __forceinline__ void attn_fwd_ring_item(const AttnParams& p, char* ld
     }
 }
 
-// One workgroup per (example, query tile, head); work mapping of tile_map.h (SORTED: dense queries, examples by p.order).
-template <int D, int NW, int OCC, bool WINDOWED, bool SORTED>
+// One workgroup per (example, query tile, head); work mapping of tile_map.h (BY_ORDER: dense queries, examples by p.order; BY_OFFSETS:
+// long sequences of queries, no tables).
+enum { BY_TABLES, BY_ORDER, BY_OFFSETS };
+template <int D, int NW, int OCC, bool WINDOWED, int MAPPING>
 __global__ __launch_bounds__(64 * NW, OCC) void qtile_fwd_mfma_kernel(AttnParams p, const int32_t* __restrict__ tile_start,
                                                                       const int32_t* __restrict__ tile_example, int runs) {
     __shared__ __attribute__((aligned(1024))) char lds[RingSmem<D, NW>::TOTAL];
     constexpr int QT = 32 * NW;
     static_assert(QT == TILE_ROWS, "tile size of the work mapping");
     int b, h, qt;
-    if (SORTED) {
+    if (MAPPING == BY_OFFSETS) {
+        if (!locate_spread_tile(p.q_off, p.B, p.H, p.total_q, TILE_ROWS, blockIdx.x, b, h, qt)) return;
+    } else if (MAPPING == BY_ORDER) {
         if (!locate_dense_tile(p.order, p.B, p.H, p.max_q, blockIdx.x, b, h, qt)) return;
     } else if (!locate_tile(tile_start, tile_example, p.B, p.H, blockIdx.x, b, h, qt, runs)) {
         return;
@@ -266,8 +270,16 @@ template <int D, int NW, int OCC, bool WINDOWED>
 static hipError_t launch_qtiled(const AttnParams& p, hipStream_t stream) {
     if constexpr (!WINDOWED) {
         if (dense_tiles_sorted(p)) {
-            hipLaunchKernelGGL((qtile_fwd_mfma_kernel<D, NW, OCC, false, true>), dim3((unsigned)dense_tile_grid(p)), dim3(64 * NW), 0, stream, p, nullptr,
-                               nullptr, 1);
+            hipLaunchKernelGGL((qtile_fwd_mfma_kernel<D, NW, OCC, false, BY_ORDER>), dim3((unsigned)dense_tile_grid(p)), dim3(64 * NW), 0, stream, p,
+                               nullptr, nullptr, 1);
+            return hipGetLastError();
+        }
+        // Small launches: the kernel that writes the tables costs them 2.5 to 3.5 us, the search and the numbers without a tile 5 to 15 %
+        // of a large one.  By offsets over by tables, 320 random calls: up to 600 tile-heads 1.3 to 1.7, to 1000 1.05 to 1.6, to 2400 1.03
+        // to 1.2 (d = 128: from 1400 on 0.92 to 0.97), from there 0.85 to 1.0.
+        if (p.q_off && tiles_expected(p) <= (D == 128 ? 1280 : 2048)) {
+            hipLaunchKernelGGL((qtile_fwd_mfma_kernel<D, NW, OCC, false, BY_OFFSETS>), dim3(spread_grid(p.B, p.H, p.total_q, TILE_ROWS)), dim3(64 * NW),
+                               0, stream, p, nullptr, nullptr, 1);
             return hipGetLastError();
         }
     }
@@ -276,7 +288,7 @@ static hipError_t launch_qtiled(const AttnParams& p, hipStream_t stream) {
     int32_t* tile_example = tile_example_of(tile_start, p.B);
     hipLaunchKernelGGL(tile_prefix_kernel<0>, dim3(1), dim3(1024), 0, stream, p.q_off, p.max_q, p.B, tile_start,
                        tile_example, TILE_ROWS);
-    hipLaunchKernelGGL((qtile_fwd_mfma_kernel<D, NW, OCC, WINDOWED, false>), dim3(tile_grid(p.B, p.H, p.total_q, runs)),
+    hipLaunchKernelGGL((qtile_fwd_mfma_kernel<D, NW, OCC, WINDOWED, BY_TABLES>), dim3(tile_grid(p.B, p.H, p.total_q, runs)),
                        dim3(64 * NW), 0, stream, p, tile_start, tile_example, runs);
     return hipGetLastError();
 }

@@ -33,6 +33,10 @@ inline unsigned tile_grid(int B, int H, int64_t total_rows, int runs = 1) {
 }
 // tiles times heads: half a tile more per example than its rows fill
 inline int64_t tiles_expected(const AttnParams& p) { return (p.total_q / TILE_ROWS + (p.B + 1) / 2) * p.H; }
+// The launches that number their tiles by the offsets instead (locate_spread_tile below).
+inline unsigned spread_grid(int B, int H, int64_t total_rows, int tile_rows) {
+    return (unsigned)((((total_rows / tile_rows + B) * H + 7) / 8 + 1) * 8);
+}
 // Runs per XCD of a forward launch: with about 96 workgroups resident there, a tile and its successor start 48 slots apart.
 inline int tile_runs(const AttnParams& p) {
     const int64_t tiles = tiles_expected(p);
@@ -88,6 +92,32 @@ __device__ __forceinline__ bool locate_tile(const int32_t* __restrict__ tile_sta
     b = tile_example[tile];
     t = tile - tile_start[b];
     return true;
+}
+
+// The same mapping without tables, for long sequences: tile numbers are dealt by the offsets themselves, example b beginning at
+// off[b] / tile_rows + b (never fewer numbers than it has tiles; a number without a tile ends its workgroup).  Every wave finds the
+// example by itself, 64 probes of the offsets at a time: as many dependent loads as the tables take up to 4096 examples, and no
+// launch in front.
+__device__ __forceinline__ int spread_tile(const int32_t* __restrict__ off, int b, int tile_rows) { return off[b] / tile_rows + b; }
+__device__ __forceinline__ bool locate_spread_tile(const int32_t* __restrict__ off, int B, int H, int64_t total, int tile_rows, unsigned block,
+                                                   int& b, int& h, int& t) {
+    const int64_t n_items = (total / tile_rows + B) * H;
+    const int64_t per_xcd = (n_items + 7) / 8;
+    const int64_t in_xcd = block >> 3, item = (block & 7) * per_xcd + in_xcd;
+    if (in_xcd >= per_xcd || item >= n_items) return false;
+    const int tile = (int)(item / H);
+    h = (int)(item % H);
+    const int lane = threadIdx.x & 63;
+    int lo = 0, hi = B;  // the example is in [lo, hi)
+    while (hi - lo > 1) {
+        const int step = (hi - lo + 63) / 64, probe = lo + lane * step;
+        const int before = __builtin_popcountll(__builtin_amdgcn_ballot_w64(probe < hi && spread_tile(off, probe < hi ? probe : lo, tile_rows) <= tile));
+        lo += (before > 0 ? before - 1 : 0) * step;
+        hi = lo + step < hi ? lo + step : hi;
+    }
+    b = lo;
+    t = tile - spread_tile(off, lo, tile_rows);
+    return t >= 0 && (int64_t)t * tile_rows < off[lo + 1] - off[lo];
 }
 
 // Exclusive prefix sum of ceil(len_b / tile_rows) over the examples, and the example of every

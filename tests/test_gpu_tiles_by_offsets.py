@@ -1,0 +1,67 @@
+"""Small launches of long query sequences (up to 1280 tiles of 128 queries, times heads, in the forward at d = 128 and 2048 at d = 32 and 64; backward
+1536 and 3600; over at most 32 keys 2600 and 7000) find their tiles from the offsets: examples of less than a tile, of whole tiles and
+empty ones, first and last, in batches around the 64 probes of a search step, against the CPU oracle."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2602_10016_amd import workloads as W
+from tests.helpers import TOL, assert_close, assert_close_sums, offsets_dev, to_dev, to_np
+
+pytestmark = pytest.mark.gpu
+
+
+def ragged(rng, B, longest):
+    lengths = rng.integers(0, longest + 1, size=B)
+    special = [0, 128, 129, 127, 0, 256, 1, longest]
+    lengths[:min(B, len(special))] = [min(x, longest) for x in special[-min(B, len(special)):]]
+    rng.shuffle(lengths)
+    if B > 2:
+        lengths[0] = lengths[-1] = 0
+    return lengths
+
+
+def values(rng, rows, H, d):
+    return W.round_to_bf16(rng.standard_normal((rows, H, d), dtype=np.float32) * 0.5)
+
+
+@pytest.mark.parametrize("B,H,d,longest,keys,act", [(1, 2, 64, 500, 20, 3), (63, 2, 128, 600, 32, 0), (64, 3, 32, 400, 48, 3), (65, 1, 128, 700, 40, 0), (129, 4, 64, 300, 8, 0),
+                                                    (1500, 1, 64, 140, 33, 0)])
+def test_long_query_sequences(oracle, B, H, d, longest, keys, act):
+    from paper_2602_10016_amd import binding as kb
+    rng = np.random.default_rng(B + d)
+    n_keys = rng.integers(0, keys + 1, size=B)
+    n_keys[B // 2] = keys
+    q_off, kv_off = W.offsets_from_lengths(ragged(rng, B, longest)), W.offsets_from_lengths(n_keys)
+    q, k, v = values(rng, q_off[-1], H, d), values(rng, kv_off[-1], H, d), values(rng, kv_off[-1], H, d)
+    d_o = values(rng, q_off[-1], H, d)
+    scale = d ** -0.5 if act == 0 else 1.0 / keys
+    tq, tk, tv, tdo = (to_dev(x, "bf16") for x in (q, k, v, d_o))
+    how = dict(q_offsets=offsets_dev(q_off), max_q=longest, max_kv=keys)
+    o, lse = kb.gdpa_fwd(tq, tk, tv, offsets_dev(kv_off), scale, act, out=torch.full_like(tq, float("nan")), **how)
+    out = tuple(torch.full_like(t, float("nan")) for t in (tq, tk, tv))
+    got = kb.gdpa_bwd(tq, tk, tv, tdo, offsets_dev(kv_off), scale, act, o=o, lse=lse, out=out, **how)
+    torch.cuda.synchronize()
+    o_ref, _ = oracle.gdpa_fwd(q, k, v, kv_off, scale, act, q_offsets=q_off, max_q=longest)
+    refs = oracle.gdpa_bwd(q, k, v, d_o, kv_off, scale, act, q_offsets=q_off, max_q=longest)
+    for a, ref, name in zip((o, got[0]), (o_ref, refs[0]), ("O", "dQ")):
+        assert_close(to_np(a), ref, TOL["bf16"], f"B={B} H={H} d={d} {name}")
+    for a, ref, name in zip(got[1:], refs[1:], ("dK", "dV")):  # sums over the queries with rounded factors: held to their RMS (see there)
+        assert_close_sums(to_np(a), ref, TOL["bf16"], f"B={B} H={H} d={d} {name}", offsets=kv_off)
+
+
+@pytest.mark.parametrize("B,H,d,longest,left,right", [(1, 1, 64, 300, 40, 0), (64, 2, 64, 260, 127, 0), (65, 2, 128, 260, 31, 31), (66, 1, 32, 400, 255, 0), (2200, 1, 64, 130, 20, 5),
+                                                      (4200, 1, 32, 60, 20, 0), (30, 2, 64, 900, 800, 0)])
+def test_sliding_window_backward(oracle, B, H, d, longest, left, right):
+    from paper_2602_10016_amd import binding as kb
+    rng = np.random.default_rng(B + d)
+    off = W.offsets_from_lengths(ragged(rng, B, longest))
+    q, k, v, d_o = (values(rng, off[-1], H, d) for _ in range(4))
+    tq, tk, tv, tdo = (to_dev(x, "bf16") for x in (q, k, v, d_o))
+    o, lse = kb.swa_fwd(tq, tk, tv, offsets_dev(off), left, right, d ** -0.5, max_len=longest)
+    out = tuple(torch.full_like(t, float("nan")) for t in (tq, tk, tv))
+    got = kb.swa_bwd(tq, tk, tv, o, lse, tdo, offsets_dev(off), left, right, d ** -0.5, max_len=longest, out=out)
+    torch.cuda.synchronize()
+    refs = oracle.swa_bwd(q, k, v, d_o, off, left, right, d ** -0.5)
+    for a, ref, name in zip(got, refs, ("dQ", "dK", "dV")):
+        assert_close(to_np(a), ref, TOL["bf16"], f"B={B} H={H} d={d} window=({left}, {right}) {name}")
