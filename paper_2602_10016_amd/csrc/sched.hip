@@ -101,8 +101,9 @@ namespace kunlun {
 // V consecutive elements per thread (16-byte loads when the row length allows it); the additions of one element
 // happen in example order whatever V is.  What bounds it: the rows are read once, 134 MB for 256 examples of 256 seeds (8 heads,
 // d = 128); with streaming loads 26 us = 5.2 TB/s, with plain ones 34 (eight or sixteen examples in flight instead of four 28, 29).
+// Rows that the caches still hold (up to 32 MB) are read with plain loads (127 examples of 128 seeds, 1 head, d = 32: backward 27.5 / 29.0 us).
 // LAST: the only group, its sums are the result.
-template <typename T, int V, bool LAST>
+template <typename T, int V, bool LAST, bool STREAM>
 __global__ __launch_bounds__(256) void seed_grad_group_kernel(const T* __restrict__ rows, float* __restrict__ partial, T* __restrict__ d_e, int B,
                                                               int64_t n_elems) {
     typedef T vec_t __attribute__((ext_vector_type(V)));
@@ -115,7 +116,8 @@ __global__ __launch_bounds__(256) void seed_grad_group_kernel(const T* __restric
     for (int q = 0; q < V; ++q) acc[q] = 0.f;
 #pragma unroll 4
     for (int b = b0; b < b1; ++b) {
-        const vec_t x = __builtin_nontemporal_load((const vec_t*)(rows + (int64_t)b * n_elems + n));
+        const vec_t* at = (const vec_t*)(rows + (int64_t)b * n_elems + n);
+        const vec_t x = STREAM ? __builtin_nontemporal_load(at) : *at;
 #pragma unroll
         for (int q = 0; q < V; ++q) acc[q] += to_float((T)x[q]);
     }
@@ -140,10 +142,13 @@ static hipError_t launch_seed_grad(const T* rows, T* d_e, float* partial, int B,
     const int groups = (B + SEED_GROUP - 1) / SEED_GROUP;
     const dim3 grid((unsigned)((n_elems / V + 255) / 256), (unsigned)groups);
     if (groups == 1) {  // up to SEED_GROUP examples: one launch (5 examples of 108 seeds, backward 22.6 / 20.4 us)
-        hipLaunchKernelGGL((seed_grad_group_kernel<T, V, true>), grid, dim3(256), 0, stream, rows, partial, d_e, B, n_elems);
+        hipLaunchKernelGGL((seed_grad_group_kernel<T, V, true, false>), grid, dim3(256), 0, stream, rows, partial, d_e, B, n_elems);
         return hipGetLastError();
     }
-    hipLaunchKernelGGL((seed_grad_group_kernel<T, V, false>), grid, dim3(256), 0, stream, rows, partial, d_e, B, n_elems);
+    if ((int64_t)B * n_elems * (int64_t)sizeof(T) > (int64_t)32 << 20)
+        hipLaunchKernelGGL((seed_grad_group_kernel<T, V, false, true>), grid, dim3(256), 0, stream, rows, partial, d_e, B, n_elems);
+    else
+        hipLaunchKernelGGL((seed_grad_group_kernel<T, V, false, false>), grid, dim3(256), 0, stream, rows, partial, d_e, B, n_elems);
     hipLaunchKernelGGL(seed_grad_final_kernel<T>, dim3((unsigned)((n_elems + 255) / 256)), dim3(256), 0, stream, partial, d_e, groups, n_elems);
     return hipGetLastError();
 }

@@ -34,6 +34,16 @@ inline unsigned tile_grid(int B, int H, int64_t total_rows, int runs = 1) {
 // tiles times heads: half a tile more per example than its rows fill
 inline int64_t tiles_expected(const AttnParams& p) { return (p.total_q / TILE_ROWS + (p.B + 1) / 2) * p.H; }
 // The launches that number their tiles by the offsets instead (locate_spread_tile below).
+// The numbers without a tile are up to one per example, and not the same share of every XCD: where the tiles fill so many rounds of the
+// workgroups that the device holds (`slots`, of the kernel without tables; that with them, of fewer registers, `table_slots`) and the
+// numbers one more, some compute units get a round more than others.  Backward, by offsets over by tables: 34 to 64
+// keys, 231 examples, 1 head (231 key tiles, 314 numbers) 119 / 97 us; few keys, 13 x 4 (496 chunks, 520) 27.0 / 24.3; windows 49.8 / 47.
+// From the fifth round on it is not seen.
+inline bool spread_keeps_rounds(int B, int H, int64_t total_rows, int max_rows, int tile_rows, int slots, int table_slots) {
+    const int64_t numbers = (total_rows / tile_rows + B) * H;
+    const int64_t tiles = (max_rows <= tile_rows ? B : total_rows / tile_rows + (B + 1) / 2) * H;
+    return tiles > 4 * (int64_t)slots || (numbers + slots - 1) / slots <= (tiles - tiles / 32 + table_slots - 1) / table_slots;
+}
 inline unsigned spread_grid(int B, int H, int64_t total_rows, int tile_rows) {
     return (unsigned)((((total_rows / tile_rows + B) * H + 7) / 8 + 1) * 8);
 }

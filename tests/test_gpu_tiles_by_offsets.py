@@ -1,5 +1,5 @@
 """Small launches of long query sequences (up to 1280 tiles of 128 queries, times heads, in the forward at d = 128 and 2048 at d = 32 and 64; backward
-1536 and 3600; over at most 32 keys 2600 and 7000) find their tiles from the offsets: examples of less than a tile, of whole tiles and
+1536 and 3600; over at most 32 keys 2600 and 4096; where the numbers without a tile cost no round) find their tiles from the offsets: examples of less than a tile, of whole tiles and
 empty ones, first and last, in batches around the 64 probes of a search step, against the CPU oracle."""
 import numpy as np
 import pytest
