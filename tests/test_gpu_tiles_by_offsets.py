@@ -25,7 +25,7 @@ def values(rng, rows, H, d):
     return W.round_to_bf16(rng.standard_normal((rows, H, d), dtype=np.float32) * 0.5)
 
 
-@pytest.mark.parametrize("B,H,d,longest,keys,act", [(1, 2, 64, 500, 20, 3), (63, 2, 128, 600, 32, 0), (64, 3, 32, 400, 48, 3), (65, 1, 128, 700, 40, 0), (129, 4, 64, 300, 8, 0),
+@pytest.mark.parametrize("B,H,d,longest,keys,act", [(1, 2, 64, 500, 20, 3), (63, 2, 128, 600, 32, 0), (64, 3, 32, 400, 48, 3), (65, 1, 128, 700, 40, 0), (129, 4, 64, 300, 8, 0), (231, 1, 32, 150, 46, 0),
                                                     (1500, 1, 64, 140, 33, 0)])
 def test_long_query_sequences(oracle, B, H, d, longest, keys, act):
     from paper_2602_10016_amd import binding as kb
