@@ -11,6 +11,7 @@
 //         dV^T += dO^T P,  dK^T += Q^T dS,  and behind a barrier (dQ_{i-1} is done) a bf16 image of dS, [key][query], to LDS
 //     two waves of the other half have sent the loads of step i + 1 at the start (buffer-load-to-LDS, lds_ring.h) and wait for them
 //         here; they compute delta = rowsum(dO * O) of the rows that they loaded themselves;  barrier
+// Every sum is made in the order of the two-pass kernels, so that a sequence has the same gradients to the bit whatever batch it comes in.
 // A window of nine tiles (256 rows) makes one wave a step hand its key tile over: it finishes tile i - L, sends out its rows and
 // takes tile i + R (L, R: tiles to the left and right) within the step.
 //
@@ -40,7 +41,7 @@ struct SwbSmem {
     static constexpr int TILE = KT * D * 2;
     static constexpr int RING = SWB_MAX_TILES + 1;  // K tiles under the window, and the next one on its way
     static constexpr int IMAGE = KT * KT * 2;
-    static constexpr int STATS = 2 * KT * 4;        // of a query tile: -lse / scale, then -delta
+    static constexpr int STATS = 2 * KT * 4;        // of a query tile: -lse log2 e, then delta
     static constexpr int V = RING * TILE;           // two tiles: read by its owner when it takes up the key tile
     static constexpr int QD = V + 2 * TILE;         // two stages of a Q and a dO tile
     static constexpr int O = QD + 4 * TILE;
@@ -49,18 +50,6 @@ struct SwbSmem {
     static constexpr int LSE = ST + 2 * STATS;      // lse as loaded, for each loading wave
     static constexpr int TOTAL = LSE + SWB_LOADERS * 256;  // d = 128: 157 KB
 };
-
-// The sum of a value over 16 neighbouring lanes, in all of them.
-__device__ __forceinline__ float sum_of_16_lanes(float x) {
-    auto add = [&](auto ctrl) {
-        x += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), decltype(ctrl)::value, 0xf, 0xf, true));
-    };
-    add(std::integral_constant<int, 0xB1>{});   // quad_perm [1,0,3,2]
-    add(std::integral_constant<int, 0x4E>{});   // quad_perm [2,3,0,1]
-    add(std::integral_constant<int, 0x141>{});  // row_half_mirror
-    add(std::integral_constant<int, 0x140>{});  // row_mirror
-    return x;
-}
 
 // A 32 x 32 block in the C layout (lane: output row r, registers: channels 8*(v/4) + 4g + v%4) to bf16 rows of the buffer, 16
 // bytes per lane: the lane halves exchange the channels that make them whole.  voff: r * row_bytes + channel block + 16 g bytes.
@@ -100,9 +89,8 @@ __device__ __forceinline__ void swa_bwd_band_item(const AttnParams& p, char* lds
     const float sc = p.scale * LOG2E_B;
 
     const u32x4 lse_rsrc = make_rsrc_words(p.lse + (int64_t)h * p.total_q + row0, (uint32_t)n * 4);
-    const float neg_inv_scale = -1.f / p.scale;
     using DmaQ = TileDma<D, SWB_LOADERS, SWZ_U>;
-    static_assert(DmaQ::CHUNKS == 16, "lanes of a row in row_stats");
+    constexpr int ROWS = DmaQ::RPI * DmaQ::IPW;  // rows of a query tile that a wave loads, one after the other
     using DmaK = TileDma<D, SWB_WAVES / 2, SWZ_U>;
     // Q, dO, O and lse of query tile i, by SWB_LOADERS waves
     auto issue_queries = [&](int i, int part) {
@@ -134,26 +122,25 @@ __device__ __forceinline__ void swa_bwd_band_item(const AttnParams& p, char* lds
         asm volatile("" : "+v"(lane));
         const char* dot = lds + SM::QD + (i & 1) * 2 * SM::TILE + SM::TILE;
         float* st = (float*)(lds + SM::ST + (i & 1) * SM::STATS);
-        float sum[DmaQ::IPW], l[DmaQ::IPW];
+        // Two neighbouring lanes per row and half (every other 8 channels): each multiplies half of the channels, and the even one adds all
+        // of them up in the order of the two-pass kernels (a product of two bf16 is exact).
+        const int row = part * ROWS + (lane >> 1) % ROWS, odd = lane & 1, at = L::u_offset(row, (lane >> 5) * 16) ^ (odd * (KC / 2) << 5);
+        const float lse = *(const float*)(lds + SM::LSE + part * 256 + row * 4);
+        float term[KC / 2 * 8], sum = 0.f;
 #pragma unroll
-        for (int x = 0; x < DmaQ::IPW; ++x) {
-            const int piece = (part * DmaQ::IPW + x) * 1024 + lane * 16;
-            const bf16x8 of = *(const bf16x8*)(lds + SM::O + piece);
-            const bf16x8 df = *(const bf16x8*)(dot + piece);
-            l[x] = *(const float*)(lds + SM::LSE + part * 256 + DmaQ::row_of(lane, part, x) * 4);
-            sum[x] = 0.f;
+        for (int kc = 0; kc < KC / 2; ++kc) {
+            const bf16x8 of = *(const bf16x8*)(lds + SM::O + (at ^ (kc << 5)));
+            const bf16x8 df = *(const bf16x8*)(dot + (at ^ (kc << 5)));
 #pragma unroll
-            for (int e = 0; e < 8; ++e) sum[x] = fmaf((float)of[e], (float)df[e], sum[x]);
+            for (int e = 0; e < 8; ++e) sum += term[kc * 8 + e] = (float)of[e] * (float)df[e];
         }
 #pragma unroll
-        for (int x = 0; x < DmaQ::IPW; ++x) sum[x] = sum_of_16_lanes(sum[x]);
-        if (lane % DmaQ::CHUNKS == 0) {
-#pragma unroll
-            for (int x = 0; x < DmaQ::IPW; ++x) {
-                const int row = DmaQ::row_of(lane, part, x);
-                st[row] = l[x] * neg_inv_scale;
-                st[KT + row] = -sum[x];
-            }
+        for (int x = 0; x < KC / 2 * 8; ++x)  // quad_perm [1,0,3,2]: the neighbour's
+            sum += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, term[x]), 0xB1, 0xf, 0xf, true));
+        sum = halves_sum(sum);
+        if (lane < 2 * ROWS && !odd) {
+            st[row] = lse * -LOG2E_B;
+            st[KT + row] = sum;
         }
     };
 
@@ -189,43 +176,37 @@ __device__ __forceinline__ void swa_bwd_band_item(const AttnParams& p, char* lds
         uf.init(lane);
         const int slot = cur % SM::RING;
         const char* ldsK = lds + slot * SM::TILE;
-        // S - lse / scale = Q K^T + .., then dP - delta = dO V^T + ..: lane = key column, registers = queries of the tile.
+        // S = Q K^T, then dP = dO V^T: lane = key column, registers = queries of the tile.
         // The matrix instructions of dP run beside the exponentials of S; fragments are read AHEAD instructions before their use.
         constexpr int AHEAD = 3;
         f32x16 sacc, dpacc;
         bf16x8 fr[AHEAD], kr = kf[0];
-        auto start = [&](const float* from) {
-            f32x16 x;
-#pragma unroll
-            for (int vg = 0; vg < 4; ++vg) {
-                const f32x4 y = *(const f32x4*)(from + 8 * vg + 4 * g);
-#pragma unroll
-                for (int e = 0; e < 4; ++e) x[4 * vg + e] = y[e];
-            }
-            return x;
-        };
+        f32x4 lse[2], del[4];
+        auto stat = [&](int vg, int which) { return *(const f32x4*)(stats + which * KT + 8 * vg + 4 * g); };
         auto frag = [&](int j) { return j < KC ? uf.row(ldsQ, j) : uf.row(ldsDO, j - KC); };
-        sacc = start(stats);
 #pragma unroll
         for (int j = 0; j < AHEAD; ++j) fr[j] = frag(j);
         PIN();
         float pv[16], dsv[16];
 #pragma unroll
         for (int j = 0; j < 2 * KC; ++j) {
-            if (j < KC) sacc = mfma32(fr[j % AHEAD], j < K_REG ? kf[j < K_REG ? j : 0] : kr, sacc);
-            else dpacc = mfma32(fr[j % AHEAD], vf[j < KC ? 0 : j - KC], dpacc);
+            if (j < KC) sacc = mfma32(fr[j % AHEAD], j < K_REG ? kf[j < K_REG ? j : 0] : kr, j == 0 ? zero16 : sacc);
+            else dpacc = mfma32(fr[j % AHEAD], vf[j < KC ? 0 : j - KC], j == KC ? zero16 : dpacc);
             if (j + 1 >= K_REG && j + 1 < KC) kr = uf.row(ldsK, j + 1);
-            if (j == KC - 2) dpacc = start(stats + KT);
             if (j + AHEAD < 2 * KC) fr[j % AHEAD] = frag(j + AHEAD);
             if (j >= KC) {
                 constexpr int W = 16 / KC;  // weights beside each matrix instruction
 #pragma unroll
-                for (int v = W * (j - KC); v < W * (j - KC) + W; ++v) pv[v] = fast_exp2(sacc[v] * sc);
+                for (int v = W * (j - KC); v < W * (j - KC) + W; ++v) pv[v] = fast_exp2(fmaf(sacc[v], sc, lse[(v >> 2) & 1][v & 3]));
             }
+            if (j >= KC - 2 && j % 2 == 0 && j < 2 * KC - 2) lse[((j - KC + 2) >> 1) & 1] = stat((j - KC + 2) >> 1, 0);
+            if (j >= 2 * KC - 3) del[j - 2 * KC + 3] = stat(j - 2 * KC + 3, 1);
             PIN();
         }
+        del[3] = stat(3, 1);
+        PIN();
 #pragma unroll
-        for (int v = 0; v < 16; ++v) dsv[v] = pv[v] * dpacc[v] * p.scale;
+        for (int v = 0; v < 16; ++v) dsv[v] = pv[v] * (dpacc[v] - del[v >> 2][v & 3]) * p.scale;
         // Interior tiles - every (query, key) pair inside the sequence and the window - skip the visibility test.
         // (Padding key lanes repeat the last key and are never stored.)
         const int q_base = i * KT, k_lo = cur * KT, k_hi = k_lo + KT - 1;
@@ -308,8 +289,9 @@ __device__ __forceinline__ void swa_bwd_band_item(const AttnParams& p, char* lds
         asm volatile("" : "+v"(dq_lane));
         const int s16 = dq_lane & 15, r = dq_lane & 31, g = dq_lane >> 5;
         const int colb = (16 * ((dq_lane >> 4) & 1) + 4 * (s16 & 3)) * 2;
-        int ka = L::u_offset(8 * g + (s16 >> 2), colb) ^ (db << 6), kb = L::u_offset(8 * g + 4 + (s16 >> 2), colb) ^ (db << 6);
-        int ia = w64_offset(8 * g + (s16 >> 2), colb), ib = w64_offset(8 * g + 4 + (s16 >> 2), colb);
+        // (the keys of a matrix instruction in the order of the two-pass kernels, which have them from the C layout)
+        int ka = L::u_offset(4 * g + (s16 >> 2), colb) ^ (db << 6), kb = L::u_offset(8 + 4 * g + (s16 >> 2), colb) ^ (db << 6);
+        int ia = w64_offset(4 * g + (s16 >> 2), colb), ib = w64_offset(8 + 4 * g + (s16 >> 2), colb);
         // two matrix instructions per key tile; their operands are read two tiles ahead (past the window: slots that
         // are not used)
         bf16x8 kfr[4], ifr[4];
@@ -439,9 +421,9 @@ static int64_t tiles_reached(int reach, int max_len) { return ((int64_t)(reach <
 // two-pass kernels spread the tiles of every sequence.  In units of the mean: the longest sequence, or, for lengths that are nearly
 // equal, the rounds that they leave incomplete.  One pass against two, 220 random launches: with up to 1.2 times the mean 1.14 to 1.39
 // times as fast, at 1.35 1.14 (three tiles), at 1.45 1.17 (nine) and 1.06 (three to five), at 1.6 0.95 (two) and 1.09 (nine), at 1.9
-// 0.8 to 0.95.  The smallest scales, by which the statistics are divided, stay with the two-pass kernels.
+// 0.8 to 0.95.
 bool swa_bwd_band_applies(const AttnParams& p, int dtype) {
-    if (!p.windowed || dtype != KUNLUN_BF16 || p.d != SwbSmem::D || !(p.scale >= 1e-6f)) return false;
+    if (!p.windowed || dtype != KUNLUN_BF16 || p.d != SwbSmem::D) return false;
     const int64_t tiles = tiles_reached(p.left, p.max_kv) + tiles_reached(p.right, p.max_kv) + 1;
     if (tiles > SWB_MAX_TILES) return false;
     const float units = (float)compute_units(), items = (float)p.B * p.H / units;

@@ -43,6 +43,53 @@ def test_swa_backward_one_pass_unbounded_short_and_long(oracle, B, H, longest, l
     check(oracle, B, H, longest, left, right, seed=B + longest)
 
 
+def prepared(kind, lengths, H, left, right):
+    """Inputs and the forward's results; q[..., 0] = 1 under "masked keys", so that K[key, h, 0] = -inf masks a key."""
+    from paper_2602_10016_amd import binding as kb
+    rng = np.random.default_rng(left + 3 * right + len(kind))
+    total = int(lengths.sum())
+    q, k, v, d_o = (W.round_to_bf16(rng.standard_normal((total, H, 128), dtype=np.float32) * (4 if kind == "large scores" else 0.5)) for _ in range(4))
+    if kind == "masked keys":
+        q[..., 0] = 1
+        k[rng.random(k.shape[:2]) < 0.3, 0] = -np.inf
+        k[rng.random(k.shape[0]) < 0.002] = -np.inf  # (in every head)
+    scale = {"tiny scale": 1e-7, "negative scale": -0.2}.get(kind, 128 ** -0.5)
+    off = W.offsets_from_lengths(lengths)
+    dev = [to_dev(x, "bf16") for x in (q, k, v)]
+    o, lse = kb.swa_fwd(*dev, offsets_dev(off), left, right, scale, max_len=int(lengths.max()))
+    return off, scale, (*dev, o, lse, to_dev(d_o, "bf16"))
+
+
+def bits(t):
+    return torch.where(t.isnan(), torch.full_like(t, float("nan")), t).view(torch.int16)
+
+
+# 512 items: one pass; a sequence by itself has too few of them and goes through the two-pass kernels
+@pytest.mark.gpu
+@pytest.mark.parametrize("kind,left,right", [("ordinary", 255, 0), ("ordinary", 128, 128), ("ordinary", 40, 0), ("ordinary", 0, 0), ("ordinary", 100, 31),
+                                             ("tiny scale", 255, 0), ("negative scale", 100, 31), ("large scores", 255, 0), ("large scores", 20, 20),
+                                             ("masked keys", 255, 0), ("masked keys", 60, 60)])
+def test_one_pass_and_two_passes_give_the_same_bits(kind, left, right):
+    from paper_2602_10016_amd import binding as kb
+    B, H = 128, 4
+    lengths = np.random.default_rng(left).integers(200, 331, size=B)
+    some = [0, 1, 17, 40, 63, 90, B - 1]
+    lengths[some] = [330, 1, 31, 33, 288, 289, 64]
+    off, scale, (q, k, v, o, lse, d_o) = prepared(kind, lengths, H, left, right)
+    total, order_end = int(off[-1]), 256 + ((B + 1) * 4 + 255) // 256 * 256
+    ws = torch.full((kb.workspace_bytes(kb.OP_SWA_BWD, B, H, 128, 330, 330, total, total),), 0xEE, dtype=torch.uint8, device="cuda")
+    got = kb.swa_bwd(q, k, v, o, lse, d_o, offsets_dev(off), left, right, scale, max_len=330, workspace=ws)
+    assert torch.all(ws[order_end:] == 0xEE), "the two passes leave delta here: the one-pass kernel did not run"
+    for b in some:
+        n, at = int(lengths[b]), slice(int(off[b]), int(off[b + 1]))
+        ws = torch.full((kb.workspace_bytes(kb.OP_SWA_BWD, 1, H, 128, n, n, n, n),), 0xEE, dtype=torch.uint8, device="cuda")
+        own = kb.swa_bwd(*(x[at].contiguous() for x in (q, k, v, o)), lse[:, at].contiguous(), d_o[at].contiguous(), offsets_dev(np.array([0, n])),
+                         left, right, scale, max_len=n, workspace=ws)
+        assert torch.any(ws[512:] != 0xEE), "the one-pass kernel ran"
+        for a, ref, name in zip(got, own, ("dQ", "dK", "dV")):
+            assert torch.equal(bits(a[at]), bits(ref)), f"{kind} window=({left}, {right}) sequence of {n} rows {name}"
+
+
 def test_the_one_pass_window_backward_keeps_its_registers(tmp_path):
     """A reload from scratch memory would also count among the vector-memory operations that the kernel's waits number."""
     spilled = spilled_vector_registers("attn_swa_bwd_band_mfma.hip", tmp_path)
