@@ -105,7 +105,10 @@ struct TiledSmem {
 
 // ------------------------------------------------------------------ pass A: dQ
 
-template <int D, int NW, int ACT, bool WINDOWED>
+// (MAPPING in the items of both passes: an instance for each kernel.  Shared by kernels of several mappings, or with the mapping chosen at
+// run time, an item comes out in another order of instructions and of more registers: backward of 75 to 400 seeds at d = 64 and 32, 54
+// calls, 1.011.)
+template <int D, int NW, int ACT, bool WINDOWED, int MAPPING>
 __device__ __forceinline__ void bwd_dq_item(const AttnParams& p, float* __restrict__ delta_ws, char* lds, int h,
                                             int64_t q_row0, int nq_wg, int64_t t0_wg, int64_t k0, int n_kv) {
     using PT = PadTiles<D>;
@@ -291,7 +294,7 @@ __device__ __forceinline__ void bwd_dq_item(const AttnParams& p, float* __restri
 
 constexpr int STATS_BYTES = 512;  // per stage: lse of 64 queries (32 used), then delta of 64 queries
 
-template <int D, int NW, int ACT, bool WINDOWED>
+template <int D, int NW, int ACT, bool WINDOWED, int MAPPING>
 __device__ __forceinline__ void bwd_dkdv_item(const AttnParams& p, const float* __restrict__ delta_ws, char* lds, int h,
                                               int64_t k_row0, int nk_wg, int kpos0_wg, int64_t q0, int nq_all) {
     using PT = PadTiles<D>;
@@ -522,20 +525,20 @@ __device__ __forceinline__ bool locate_part(const int32_t* __restrict__ tile_sta
     t = t * PARTS + (int)(slot % PARTS);
     return true;
 }
-// (without tables: dense queries, examples by p.order, or, without an order, tiles numbered by the offsets)
-template <int D, int NW, bool WINDOWED>
+// (BY_ORDER: dense queries, examples by p.order; BY_OFFSETS: tiles numbered by the offsets, no tables)
+template <int D, int NW, bool WINDOWED, int MAPPING>
 __global__ __launch_bounds__(64 * NW, D == 128 ? 2 : 3) void bwd_dq_kernel(AttnParams p, const int32_t* __restrict__ tile_start,
                                                             const int32_t* __restrict__ tile_example,
                                                             float* __restrict__ delta_ws) {
     __shared__ __attribute__((aligned(1024))) char lds[TiledSmem<D, 0, NW>::TOTAL];
     int b, h, qt;
-    if (!tile_start && !p.order) {
+    if constexpr (MAPPING == BY_OFFSETS) {
         if (!locate_spread_tile(p.q_off, p.B, p.H, p.total_q, 32 * NW, blockIdx.x, b, h, qt)) return;
-    } else if (!WINDOWED && !tile_start) {
-        static_assert(WINDOWED || 32 * NW == TILE_ROWS, "whole tiles of the mapping");
+    } else if constexpr (MAPPING == BY_ORDER) {
+        static_assert(!WINDOWED && 32 * NW == TILE_ROWS, "whole tiles of the mapping");
         if (!locate_dense_tile(p.order, p.B, p.H, p.max_q, blockIdx.x, b, h, qt)) return;
-    } else if (!locate_part<TILE_ROWS / (32 * NW)>(tile_start, tile_example, p.B, p.H, b, h, qt)) {
-        return;
+    } else {
+        if (!locate_part<TILE_ROWS / (32 * NW)>(tile_start, tile_example, p.B, p.H, b, h, qt)) return;
     }
     const int64_t k0 = p.kv_off[b];
     const int n_kv = p.kv_off[b + 1] - (int)k0;
@@ -545,22 +548,22 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 2 : 3) void bwd_dq_kernel(AttnP
     if (q_first >= nq_all) return;
     const int nq = (nq_all - q_first) < 32 * NW ? (nq_all - q_first) : 32 * NW;
     if (WINDOWED) {
-        bwd_dq_item<D, NW, KUNLUN_ACT_SOFTMAX, true>(p, delta_ws, lds, h, q0 + q_first, nq, q_first, k0, n_kv);
+        bwd_dq_item<D, NW, KUNLUN_ACT_SOFTMAX, true, MAPPING>(p, delta_ws, lds, h, q0 + q_first, nq, q_first, k0, n_kv);
     } else {
-        KUNLUN_ACT_SWITCH(p.head_act[h], (bwd_dq_item<D, NW, A, false>(p, delta_ws, lds, h, q0 + q_first, nq, q_first, k0, n_kv)));
+        KUNLUN_ACT_SWITCH(p.head_act[h], (bwd_dq_item<D, NW, A, false, MAPPING>(p, delta_ws, lds, h, q0 + q_first, nq, q_first, k0, n_kv)));
     }
 }
 
-template <int D, int NW, bool WINDOWED>
+template <int D, int NW, bool WINDOWED, int MAPPING>
 __global__ __launch_bounds__(64 * NW, D == 128 ? 2 : 3) void bwd_dkdv_kernel(AttnParams p, const int32_t* __restrict__ tile_start,
                                                               const int32_t* __restrict__ tile_example,
                                                               const float* __restrict__ delta_ws) {
     __shared__ __attribute__((aligned(1024))) char lds[TiledSmem<D, STATS_BYTES, NW>::TOTAL + (D == 128 ? 3 : 0) * NW * 1024];
     int b, h, kt;
-    if (!tile_start) {
+    if constexpr (MAPPING == BY_OFFSETS) {
         if (!locate_spread_tile(p.kv_off, p.B, p.H, p.total_kv, 32 * NW, blockIdx.x, b, h, kt)) return;
-    } else if (!locate_part<TILE_ROWS / (32 * NW)>(tile_start, tile_example, p.B, p.H, b, h, kt)) {
-        return;
+    } else {
+        if (!locate_part<TILE_ROWS / (32 * NW)>(tile_start, tile_example, p.B, p.H, b, h, kt)) return;
     }
     const int64_t k0 = p.kv_off[b];
     const int n_kv = p.kv_off[b + 1] - (int)k0;
@@ -570,9 +573,9 @@ __global__ __launch_bounds__(64 * NW, D == 128 ? 2 : 3) void bwd_dkdv_kernel(Att
     if (k_first >= n_kv) return;
     const int nk = (n_kv - k_first) < 32 * NW ? (n_kv - k_first) : 32 * NW;
     if (WINDOWED) {
-        bwd_dkdv_item<D, NW, KUNLUN_ACT_SOFTMAX, true>(p, delta_ws, lds, h, k0 + k_first, nk, k_first, q0, nq_all);
+        bwd_dkdv_item<D, NW, KUNLUN_ACT_SOFTMAX, true, MAPPING>(p, delta_ws, lds, h, k0 + k_first, nk, k_first, q0, nq_all);
     } else {
-        KUNLUN_ACT_SWITCH(p.head_act[h], (bwd_dkdv_item<D, NW, A, false>(p, delta_ws, lds, h, k0 + k_first, nk, k_first, q0, nq_all)));
+        KUNLUN_ACT_SWITCH(p.head_act[h], (bwd_dkdv_item<D, NW, A, false, MAPPING>(p, delta_ws, lds, h, k0 + k_first, nk, k_first, q0, nq_all)));
     }
 }
 
@@ -660,7 +663,7 @@ __device__ __forceinline__ int part_offset(int row, int chunk) {
     return row * D * 4 + ((chunk ^ (row & (D / 4 - 1))) << 4);
 }
 
-template <int D, int ACT>
+template <int D, int ACT, bool SPREAD>
 __device__ __forceinline__ void bwd_fewkeys_item(const AttnParams& p, const float* __restrict__ delta_ws, char* lds, int h,
                                                  int64_t q_row0, int nq_chunk, int64_t k0, int n_kv,
                                                  float* __restrict__ part_out) {
@@ -874,7 +877,7 @@ __global__ __launch_bounds__(256, 2) void bwd_fewkeys_kernel(AttnParams p, const
     const int nq = (nq_all - q_first) < chunk_rows ? (nq_all - q_first) : chunk_rows;
     const int first = SPREAD ? spread_tile(p.q_off, b, chunk_rows) : tile_start[b];
     float* part_out = partial + ((size_t)(first + qt) * p.H + h) * (2 * KT * D);
-    KUNLUN_ACT_SWITCH(p.head_act[h], (bwd_fewkeys_item<D, A>(p, delta_ws, fk_lds, h, q0 + q_first, nq, k0, n_kv, part_out)));
+    KUNLUN_ACT_SWITCH(p.head_act[h], (bwd_fewkeys_item<D, A, SPREAD>(p, delta_ws, fk_lds, h, q0 + q_first, nq, k0, n_kv, part_out)));
 }
 
 // dK, dV rows of every example = sum of the partial tiles of its query tiles, in tile order; 4 channels per thread.
@@ -924,22 +927,32 @@ static hipError_t launch_passes(const AttnParams& p, char* ws, bool any_softmax,
     const bool spread = p.q_off && tiles_expected(p) <= (p.d == 128 ? 1536 : 3600) &&
                         spread_keeps_rounds(p.B, p.H, p.total_q, p.max_q, 32 * NW, cus, cus) &&
                         spread_keeps_rounds(p.B, p.H, p.total_kv, p.max_kv, 32 * NW, cus, cus);
-    if (p.total_q > 0 && (spread || dense_tiles_sorted(p))) {
-        hipLaunchKernelGGL((bwd_dq_kernel<D, NW, WINDOWED>), dim3(spread ? spread_grid(p.B, p.H, p.total_q, 32 * NW) : (unsigned)dense_tile_grid(p)),
-                           dim3(64 * NW), 0, stream, p, nullptr, nullptr, delta);
-    } else if (p.total_q > 0) {
+    if (spread) {
+        if (p.total_q > 0)
+            hipLaunchKernelGGL((bwd_dq_kernel<D, NW, WINDOWED, BY_OFFSETS>), dim3(spread_grid(p.B, p.H, p.total_q, 32 * NW)), dim3(64 * NW), 0, stream, p,
+                               nullptr, nullptr, delta);
+        if (p.total_kv > 0)
+            hipLaunchKernelGGL((bwd_dkdv_kernel<D, NW, WINDOWED, BY_OFFSETS>), dim3(spread_grid(p.B, p.H, p.total_kv, 32 * NW)), dim3(64 * NW), 0, stream,
+                               p, nullptr, nullptr, delta);
+        return hipGetLastError();
+    }
+    bool sorted = false;
+    if constexpr (!WINDOWED) {
+        sorted = dense_tiles_sorted(p);
+        if (sorted && p.total_q > 0)
+            hipLaunchKernelGGL((bwd_dq_kernel<D, NW, false, BY_ORDER>), dim3((unsigned)dense_tile_grid(p)), dim3(64 * NW), 0, stream, p, nullptr, nullptr,
+                               delta);
+    }
+    if (p.total_q > 0 && !sorted) {
         hipLaunchKernelGGL(tile_prefix_kernel<1>, dim3(1), dim3(1024), 0, stream, p.q_off, p.max_q, p.B, q_tiles,
                            tile_example_of(q_tiles, p.B), TILE_ROWS);
-        hipLaunchKernelGGL((bwd_dq_kernel<D, NW, WINDOWED>), dim3(tile_grid(p.B, p.H, p.total_q) * (TILE_ROWS / (32 * NW))), dim3(64 * NW), 0,
+        hipLaunchKernelGGL((bwd_dq_kernel<D, NW, WINDOWED, BY_TABLES>), dim3(tile_grid(p.B, p.H, p.total_q) * (TILE_ROWS / (32 * NW))), dim3(64 * NW), 0,
                            stream, p, q_tiles, tile_example_of(q_tiles, p.B), delta);
     }
-    if (p.total_kv > 0 && spread) {
-        hipLaunchKernelGGL((bwd_dkdv_kernel<D, NW, WINDOWED>), dim3(spread_grid(p.B, p.H, p.total_kv, 32 * NW)), dim3(64 * NW), 0, stream, p, nullptr,
-                           nullptr, delta);
-    } else if (p.total_kv > 0) {
+    if (p.total_kv > 0) {
         hipLaunchKernelGGL(tile_prefix_kernel<1>, dim3(1), dim3(1024), 0, stream, p.kv_off, 0, p.B, k_tiles,
                            tile_example_of(k_tiles, p.B), TILE_ROWS);
-        hipLaunchKernelGGL((bwd_dkdv_kernel<D, NW, WINDOWED>), dim3(tile_grid(p.B, p.H, p.total_kv) * (TILE_ROWS / (32 * NW))), dim3(64 * NW), 0,
+        hipLaunchKernelGGL((bwd_dkdv_kernel<D, NW, WINDOWED, BY_TABLES>), dim3(tile_grid(p.B, p.H, p.total_kv) * (TILE_ROWS / (32 * NW))), dim3(64 * NW), 0,
                            stream, p, k_tiles, tile_example_of(k_tiles, p.B), delta);
     }
     return hipGetLastError();

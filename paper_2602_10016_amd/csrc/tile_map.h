@@ -17,6 +17,8 @@
 
 namespace kunlun {
 
+enum { BY_TABLES, BY_ORDER, BY_OFFSETS };  // how a workgroup finds its tile
+
 constexpr int TILE_ROWS = 128;  // rows (queries or keys) per tile of every tiled launch: 4 waves x 32
 
 inline size_t tile_table_bytes(int B, int64_t total_rows) {
