@@ -925,8 +925,8 @@ static hipError_t launch_passes(const AttnParams& p, char* ws, bool any_softmax,
     // to 500 tile-heads 1.1 to 1.4, to 1500 1.04 to 1.2, at d = 32 and 64 to 3500 1.04 to 1.14, beyond (d = 128: from 1600 on) 0.92 to 1.04.
     const int cus = compute_units();
     const bool spread = p.q_off && tiles_expected(p) <= (p.d == 128 ? 1536 : 3600) &&
-                        spread_keeps_rounds(p.B, p.H, p.total_q, p.max_q, 32 * NW, cus, cus) &&
-                        spread_keeps_rounds(p.B, p.H, p.total_kv, p.max_kv, 32 * NW, cus, cus);
+                        spread_keeps_rounds(p.B, p.H, p.total_q, p.max_q, 32 * NW, cus) &&
+                        spread_keeps_rounds(p.B, p.H, p.total_kv, p.max_kv, 32 * NW, cus);
     if (spread) {
         if (p.total_q > 0)
             hipLaunchKernelGGL((bwd_dq_kernel<D, NW, WINDOWED, BY_OFFSETS>), dim3(spread_grid(p.B, p.H, p.total_q, 32 * NW)), dim3(64 * NW), 0, stream, p,
@@ -1019,7 +1019,7 @@ hipError_t launch_mfma_bwd_tiled(const AttnParams& p, void* workspace_tail, bool
     if (fewkeys_applies(p.d, p.max_q, p.max_kv, p.windowed != 0))
         // (as in the forward: 1.04 to 1.25 up to 2600 tile-heads, at d = 32 and 64 1.02 to 1.1 up to 4096, about 1 beyond)
         return p.q_off && tiles_expected(p) <= (p.d == 128 ? 2600 : 4096) &&
-                       spread_keeps_rounds(p.B, p.H, p.total_q, p.max_q, TILE_ROWS * chunk_tiles, 2 * compute_units(), 2 * compute_units())
+                       spread_keeps_rounds(p.B, p.H, p.total_q, p.max_q, TILE_ROWS * chunk_tiles, 2 * compute_units())
                    ? (p.d == 128 ? launch_fewkeys<128, true>(p, ws, any_softmax, chunk_tiles, stream)
                       : p.d == 64 ? launch_fewkeys<64, true>(p, ws, any_softmax, chunk_tiles, stream) : launch_fewkeys<32, true>(p, ws, any_softmax, chunk_tiles, stream))
                    : (p.d == 128 ? launch_fewkeys<128, false>(p, ws, any_softmax, chunk_tiles, stream)

@@ -278,11 +278,11 @@ static hipError_t launch_qtiled(const AttnParams& p, hipStream_t stream) {
         }
         // Small launches: the kernel that writes the tables costs them 2.5 to 3.5 us, the search and the numbers without a tile 5 to 15 %
         // of a large one.  By offsets over by tables, 320 random calls: up to 600 tile-heads 1.3 to 1.7, to 1000 1.05 to 1.6, to 2400 1.03
-        // to 1.2 (d = 128: from 1400 on 0.92 to 0.97), from there 0.85 to 1.0.
-        // (The search takes registers: 191 / 133 / 108 instead of 159 / 102 / 77.  Held to fewer, the kernel spills: 126 x 2 at d = 128 24.9 / 22.2 us.)
-        const int cus = compute_units(), slots = (D == 128 ? 2 : D == 64 ? 3 : 4) * cus, table_slots = (D == 128 ? 3 : D == 64 ? 4 : 6) * cus;
+        // to 1.2 (d = 128: from 1400 on 0.92 to 0.97), from there 0.85 to 1.0.  (Timed with a search of 31 registers more, a
+        // quarter to a third of the wavefronts; 244 more calls of up to so many tile-heads are 1.06 times as fast without them, and those lines.)
+        const int slots = (D == 128 ? 3 : D == 64 ? 4 : 6) * compute_units();  // (160 / 102 / 77 registers)
         if (p.q_off && tiles_expected(p) <= (D == 128 ? 1280 : 2048) &&
-            spread_keeps_rounds(p.B, p.H, p.total_q, p.max_q, TILE_ROWS, slots, table_slots)) {
+            spread_keeps_rounds(p.B, p.H, p.total_q, p.max_q, TILE_ROWS, slots)) {
             hipLaunchKernelGGL((qtile_fwd_mfma_kernel<D, NW, OCC, false, BY_OFFSETS>), dim3(spread_grid(p.B, p.H, p.total_q, TILE_ROWS)), dim3(64 * NW),
                                0, stream, p, nullptr, nullptr, 1);
             return hipGetLastError();

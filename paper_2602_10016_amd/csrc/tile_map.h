@@ -36,15 +36,14 @@ inline unsigned tile_grid(int B, int H, int64_t total_rows, int runs = 1) {
 // tiles times heads: half a tile more per example than its rows fill
 inline int64_t tiles_expected(const AttnParams& p) { return (p.total_q / TILE_ROWS + (p.B + 1) / 2) * p.H; }
 // The launches that number their tiles by the offsets instead (locate_spread_tile below).
-// The numbers without a tile are up to one per example, and not the same share of every XCD: where the tiles fill so many rounds of the
-// workgroups that the device holds (`slots`, of the kernel without tables; that with them, of fewer registers, `table_slots`) and the
-// numbers one more, some compute units get a round more than others.  Backward, by offsets over by tables: 34 to 64
+// The numbers without a tile are up to one per example, and not the same share of every XCD: where the tiles fill so many rounds of
+// `slots` workgroups and the numbers one more, some compute units get a round more than others.  Backward, by offsets over by tables: 34 to 64
 // keys, 231 examples, 1 head (231 key tiles, 314 numbers) 119 / 97 us; few keys, 13 x 4 (496 chunks, 520) 27.0 / 24.3; windows 49.8 / 47.
 // From the fifth round on it is not seen.
-inline bool spread_keeps_rounds(int B, int H, int64_t total_rows, int max_rows, int tile_rows, int slots, int table_slots) {
+inline bool spread_keeps_rounds(int B, int H, int64_t total_rows, int max_rows, int tile_rows, int slots) {
     const int64_t numbers = (total_rows / tile_rows + B) * H;
     const int64_t tiles = (max_rows <= tile_rows ? B : total_rows / tile_rows + (B + 1) / 2) * H;
-    return tiles > 4 * (int64_t)slots || (numbers + slots - 1) / slots <= (tiles - tiles / 32 + table_slots - 1) / table_slots;
+    return tiles > 4 * (int64_t)slots || (numbers + slots - 1) / slots <= (tiles - tiles / 32 + slots - 1) / slots;
 }
 inline unsigned spread_grid(int B, int H, int64_t total_rows, int tile_rows) {
     return (unsigned)((((total_rows / tile_rows + B) * H + 7) / 8 + 1) * 8);
@@ -110,6 +109,7 @@ __device__ __forceinline__ bool locate_tile(const int32_t* __restrict__ tile_sta
 // off[b] / tile_rows + b (never fewer numbers than it has tiles; a number without a tile ends its workgroup).  Every wave finds the
 // example by itself, 64 probes of the offsets at a time: as many dependent loads as the tables take up to 4096 examples, and no
 // launch in front.
+constexpr int SPREAD_STEPS = 3;  // 64^3 examples; launches with as many as 8192 take this path (half a tile each in tiles_expected())
 __device__ __forceinline__ int spread_tile(const int32_t* __restrict__ off, int b, int tile_rows) { return off[b] / tile_rows + b; }
 __device__ __forceinline__ bool locate_spread_tile(const int32_t* __restrict__ off, int B, int H, int64_t total, int tile_rows, unsigned block,
                                                    int& b, int& h, int& t) {
@@ -121,15 +121,21 @@ __device__ __forceinline__ bool locate_spread_tile(const int32_t* __restrict__ o
     h = (int)(item % H);
     const int lane = threadIdx.x & 63;
     int lo = 0, hi = B;  // the example is in [lo, hi)
-    while (hi - lo > 1) {
+    // Steps of a known number, and the result as scalars: with a loop of unknown length in front of the item the forward kernels take
+    // 191 / 133 / 108 registers (d = 128 / 64 / 32) instead of 160 / 102 / 77, two, three and four workgroups per compute unit instead of
+    // three, four and six.
+#pragma unroll
+    for (int i = 0; i < SPREAD_STEPS; ++i) {
+        if (hi - lo <= 1) break;
         const int step = (hi - lo + 63) / 64, probe = lo + lane * step;
         const int before = __builtin_popcountll(__builtin_amdgcn_ballot_w64(probe < hi && spread_tile(off, probe < hi ? probe : lo, tile_rows) <= tile));
         lo += (before > 0 ? before - 1 : 0) * step;
         hi = lo + step < hi ? lo + step : hi;
     }
-    b = lo;
-    t = tile - spread_tile(off, lo, tile_rows);
-    return t >= 0 && (int64_t)t * tile_rows < off[lo + 1] - off[lo];
+    b = __builtin_amdgcn_readfirstlane(lo);
+    t = __builtin_amdgcn_readfirstlane(tile) - spread_tile(off, b, tile_rows);
+    h = __builtin_amdgcn_readfirstlane(h);
+    return t >= 0 && (int64_t)t * tile_rows < off[b + 1] - off[b];
 }
 
 // Exclusive prefix sum of ceil(len_b / tile_rows) over the examples, and the example of every

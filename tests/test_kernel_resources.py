@@ -34,3 +34,11 @@ def test_tile_tables_cost_the_backward_no_registers_of_the_other_mappings(tmp_pa
     """115 since before there was another mapping; 118 with the search for an example in the same kernel."""
     found = {n: r for n, r in metadata("attn_bwd_tiled_mfma.hip", tmp_path, "vgpr_count").items() if "bwd_dkdv_kernelILi32ELi4ELb0E" in n}
     assert len(found) == 2 and min(found.values()) <= 115, found
+
+
+def test_the_search_for_an_example_costs_no_workgroup_per_compute_unit(tmp_path):
+    """Query-tiled forward, tiles by offsets (mapping 2) beside by tables (0): 512 registers per SIMD, granted by eights."""
+    found = metadata("attn_fwd_ring_mfma.hip", tmp_path, "vgpr_count")
+    for d in (32, 64, 128):
+        tables, offsets = ([512 // ((r + 7) // 8 * 8) for n, r in found.items() if f"qtile_fwd_mfma_kernelILi{d}ELi4ELi2ELb0ELi{m}E" in n] for m in (0, 2))
+        assert len(tables) == 1 and tables == offsets, (d, found)
