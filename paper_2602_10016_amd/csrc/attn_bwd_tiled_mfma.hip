@@ -1016,14 +1016,18 @@ static hipError_t launch_fewkeys(const AttnParams& p, char* ws, bool any_softmax
 
 hipError_t launch_mfma_bwd_tiled(const AttnParams& p, void* workspace_tail, bool any_softmax, int chunk_tiles, hipStream_t stream) {
     char* ws = (char*)workspace_tail;
-    if (fewkeys_applies(p.d, p.max_q, p.max_kv, p.windowed != 0))
-        // (as in the forward: 1.04 to 1.25 up to 2600 tile-heads, at d = 32 and 64 1.02 to 1.1 up to 4096, about 1 beyond)
-        return p.q_off && tiles_expected(p) <= (p.d == 128 ? 2600 : 4096) &&
-                       spread_keeps_rounds(p.B, p.H, p.total_q, p.max_q, TILE_ROWS * chunk_tiles, 2 * compute_units())
-                   ? (p.d == 128 ? launch_fewkeys<128, true>(p, ws, any_softmax, chunk_tiles, stream)
-                      : p.d == 64 ? launch_fewkeys<64, true>(p, ws, any_softmax, chunk_tiles, stream) : launch_fewkeys<32, true>(p, ws, any_softmax, chunk_tiles, stream))
-                   : (p.d == 128 ? launch_fewkeys<128, false>(p, ws, any_softmax, chunk_tiles, stream)
-                      : p.d == 64 ? launch_fewkeys<64, false>(p, ws, any_softmax, chunk_tiles, stream) : launch_fewkeys<32, false>(p, ws, any_softmax, chunk_tiles, stream));
+    if (fewkeys_applies(p.d, p.max_q, p.max_kv, p.windowed != 0)) {
+        // By offsets over by tables, 330 random calls: up to 1300 tile-heads 1.0 to 1.17, beyond 1.0 to 1.12 where an example fills a tile and
+        // more, down to 0.93 (0.97 in the mean) where it does not, at d = 64 and 128: the search and what it makes spill are paid per workgroup.
+        const int64_t limit = p.d > 32 && p.total_q < (int64_t)TILE_ROWS * p.B ? 1280 : p.d == 128 ? 2600 : 4096;
+        const bool spread = p.q_off && tiles_expected(p) <= limit &&
+                            spread_keeps_rounds(p.B, p.H, p.total_q, p.max_q, TILE_ROWS * chunk_tiles, 2 * compute_units());
+        if (spread)
+            return p.d == 128 ? launch_fewkeys<128, true>(p, ws, any_softmax, chunk_tiles, stream)
+                   : p.d == 64 ? launch_fewkeys<64, true>(p, ws, any_softmax, chunk_tiles, stream) : launch_fewkeys<32, true>(p, ws, any_softmax, chunk_tiles, stream);
+        return p.d == 128 ? launch_fewkeys<128, false>(p, ws, any_softmax, chunk_tiles, stream)
+               : p.d == 64 ? launch_fewkeys<64, false>(p, ws, any_softmax, chunk_tiles, stream) : launch_fewkeys<32, false>(p, ws, any_softmax, chunk_tiles, stream);
+    }
     if (p.windowed)
         return p.d == 128 ? launch_tiled<128, true>(p, ws, true, stream)
                : p.d == 64 ? launch_tiled<64, true>(p, ws, true, stream) : launch_tiled<32, true>(p, ws, true, stream);

@@ -65,3 +65,24 @@ def test_sliding_window_backward(oracle, B, H, d, longest, left, right):
     refs = oracle.swa_bwd(q, k, v, d_o, off, left, right, d ** -0.5)
     for a, ref, name in zip(got, refs, ("dQ", "dK", "dV")):
         assert_close(to_np(a), ref, TOL["bf16"], f"B={B} H={H} d={d} window=({left}, {right}) {name}")
+
+
+def tables_written(ws, at):
+    """Whether a launch has left tile tables at byte `at` of a workspace that was filled with 0xEE."""
+    return bool(torch.any(ws[at:at + 4] != 0xEE))
+
+
+# 2 x 1700 and 2 x 1100 examples of less than a tile (3490 and 2260 tile-heads), 2 x 150 (300) and 2 x 200 of several tiles (1840); the line of d = 32 is 4096
+@pytest.mark.parametrize("d,B,H,longest,tables", [(64, 1700, 2, 90, True), (128, 1100, 2, 90, True), (32, 1700, 2, 90, False), (64, 150, 2, 90, False), (128, 150, 2, 90, False),
+                                                  (64, 200, 2, 700, False), (128, 200, 2, 700, False)])
+def test_few_keys_of_short_examples_keep_the_tables(d, B, H, longest, tables):
+    from paper_2602_10016_amd import binding as kb
+    rng = np.random.default_rng(B + d)
+    lengths = rng.integers(longest // 2, longest + 1, size=B)
+    lengths[0] = longest
+    q_off, kv_off = W.offsets_from_lengths(lengths), W.offsets_from_lengths(np.full(B, 8))
+    q, k, v, d_o = (to_dev(values(rng, int(n), H, d), "bf16") for n in (q_off[-1], kv_off[-1], kv_off[-1], q_off[-1]))
+    ws = torch.full((kb.workspace_bytes(kb.OP_GDPA_BWD, B, H, d, longest, 8, q.shape[0], k.shape[0]),), 0xEE, dtype=torch.uint8, device="cuda")
+    kb.gdpa_bwd(q, k, v, d_o, offsets_dev(kv_off), 0.1, 3, q_offsets=offsets_dev(q_off), max_q=longest, max_kv=8, workspace=ws)
+    torch.cuda.synchronize()
+    assert tables_written(ws, 256 + ((B + 1) * 4 + 255) // 256 * 256) == tables
