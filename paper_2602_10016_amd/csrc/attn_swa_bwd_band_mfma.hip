@@ -86,6 +86,8 @@ __device__ __forceinline__ void swa_bwd_band_item(const AttnParams& p, char* lds
     const char* DO = (const char*)p.d_o + base;
     const uint32_t lds0 = lds_address(lds);
     const int nt = (n + KT - 1) / KT;
+    L_tiles = L_tiles < nt - 1 ? L_tiles : nt - 1;  // (a reach past the sequence's other end would only add steps without a key tile)
+    R_tiles = R_tiles < nt - 1 ? R_tiles : nt - 1;
     const float sc = p.scale * LOG2E_B;
 
     const u32x4 lse_rsrc = make_rsrc_words(p.lse + (int64_t)h * p.total_q + row0, (uint32_t)n * 4);
