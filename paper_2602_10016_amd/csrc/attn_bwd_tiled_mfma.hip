@@ -915,18 +915,23 @@ size_t mfma_bwd_tiled_workspace(int B, int H, int d, int max_q, int max_kv, int6
            (fewkeys_applies(d, max_q, max_kv, windowed) ? fewkeys_partial_bytes(B, H, d, total_q, chunk_tiles) : 0);
 }
 
+// Small launches: the two kernels that write tables cost 5 to 7 us.  By offsets over by tables, 260 random calls, sliding windows and 33..64 keys: up
+// to 500 tile-heads 1.1 to 1.4, to 1500 1.04 to 1.2, at d = 32 and 64 to 3500 1.04 to 1.14, beyond (d = 128: from 1600 on) 0.92 to 1.04.
+// Rounds are counted as of one workgroup per compute unit, where two to six fit: with those 400 window backwards at d = 32 and 64 of up to
+// 1000 tile-heads would be 1.04 to 1.1 times as fast and those from there to 3600 0.92 to 0.97.
+static bool tiled_by_offsets(const AttnParams& p, int waves) {
+    const int cus = compute_units();
+    return p.q_off && tiles_expected(p) <= (p.d == 128 ? 1536 : 3600) && spread_keeps_rounds(p.B, p.H, p.total_q, p.max_q, 32 * waves, cus) &&
+           spread_keeps_rounds(p.B, p.H, p.total_kv, p.max_kv, 32 * waves, cus);
+}
+
 template <int D, bool WINDOWED, int NW>
 static hipError_t launch_passes(const AttnParams& p, char* ws, bool any_softmax, hipStream_t stream) {
     int32_t* q_tiles = (int32_t*)ws;
     int32_t* k_tiles = (int32_t*)(ws + tile_table_bytes(p.B, p.total_q));
     float* delta = (float*)(ws + tile_table_bytes(p.B, p.total_q) + tile_table_bytes(p.B, p.total_kv));
     (void)any_softmax;  // pass A computes delta of its softmax heads itself and leaves it in the workspace for pass B
-    // Small launches: the two kernels that write tables cost 5 to 7 us.  By offsets over by tables, 260 random calls, sliding windows and 33..64 keys: up
-    // to 500 tile-heads 1.1 to 1.4, to 1500 1.04 to 1.2, at d = 32 and 64 to 3500 1.04 to 1.14, beyond (d = 128: from 1600 on) 0.92 to 1.04.
-    const int cus = compute_units();
-    const bool spread = p.q_off && tiles_expected(p) <= (p.d == 128 ? 1536 : 3600) &&
-                        spread_keeps_rounds(p.B, p.H, p.total_q, p.max_q, 32 * NW, cus) &&
-                        spread_keeps_rounds(p.B, p.H, p.total_kv, p.max_kv, 32 * NW, cus);
+    const bool spread = tiled_by_offsets(p, NW);
     if (spread) {
         if (p.total_q > 0)
             hipLaunchKernelGGL((bwd_dq_kernel<D, NW, WINDOWED, BY_OFFSETS>), dim3(spread_grid(p.B, p.H, p.total_q, 32 * NW)), dim3(64 * NW), 0, stream, p,
@@ -958,24 +963,28 @@ static hipError_t launch_passes(const AttnParams& p, char* ws, bool any_softmax,
     return hipGetLastError();
 }
 
+// Narrow windows: workgroups of two waves (64 rows) and a ring of two stages, four (d = 128) or six (d = 64) instead of two or
+// three workgroups per compute unit - fewer steps in which a wave of the workgroup is outside its own window (previous 256: a
+// tenth instead of a quarter), for more tile loads per row, which is what counts in wide windows.  Training step, us, four /
+// two waves: d = 128, previous 256: 635 / 623, previous 64: 505 / 503, 500 to both sides: 693 / 714;  d = 64, previous 256:
+// 348 / 340, 50 to both sides: 570 / 560;  d = 32, previous 256: 434 / 433 (a tile is two load instructions there).
+// Backward alone, 500 random calls, two waves over four by reach (d = 64 / d = 128): 100..199 1.12 / 1.11, 200..383 1.07 / 1.07,
+// 384..449 1.05 / 1.06, 450..549 1.05 / 1.03 with losses of up to 4 % at d = 128, 550..699 1.03 / 1.01 - but for half to one tile
+// of 128 rows per compute unit, where four waves have a unit to themselves and two workgroups of two share one: d = 64 1.00 from a
+// reach of 300 on (down to 0.94), d = 128 0.99 from 200 on (down to 0.86), and sequences of up to 256 rows 0.95 from about 112 on.
+// (The number of tiles is known to about 3 %: up to 33/32 of the units.)
+static bool window_in_two_waves(const AttnParams& p) {
+    const int64_t reach = (int64_t)p.left + p.right, tiles = tiles_expected(p), units = compute_units();
+    const bool alone = 2 * tiles > units && 32 * tiles <= 33 * units;
+    const int alone_limit = p.max_kv <= 256 ? 112 : p.d == 64 ? 320 : 200;
+    return p.d > 32 && p.left >= 0 && p.right >= 0 && reach < (alone ? alone_limit : p.d == 64 ? 704 : 448);
+}
+bool mfma_bwd_tiled_small_window(const AttnParams& p) { return window_in_two_waves(p) && tiled_by_offsets(p, 2); }
+
 template <int D, bool WINDOWED>
 static hipError_t launch_tiled(const AttnParams& p, char* ws, bool any_softmax, hipStream_t stream) {
-    // Narrow windows: workgroups of two waves (64 rows) and a ring of two stages, four (d = 128) or six (d = 64) instead of two or
-    // three workgroups per compute unit - fewer steps in which a wave of the workgroup is outside its own window (previous 256: a
-    // tenth instead of a quarter), for more tile loads per row, which is what counts in wide windows.  Training step, us, four /
-    // two waves: d = 128, previous 256: 635 / 623, previous 64: 505 / 503, 500 to both sides: 693 / 714;  d = 64, previous 256:
-    // 348 / 340, 50 to both sides: 570 / 560;  d = 32, previous 256: 434 / 433 (a tile is two load instructions there).
-    // Backward alone, 500 random calls, two waves over four by reach (d = 64 / d = 128): 100..199 1.12 / 1.11, 200..383 1.07 / 1.07,
-    // 384..449 1.05 / 1.06, 450..549 1.05 / 1.03 with losses of up to 4 % at d = 128, 550..699 1.03 / 1.01 - but for half to one tile
-    // of 128 rows per compute unit, where four waves have a unit to themselves and two workgroups of two share one: d = 64 1.00 from a
-    // reach of 300 on (down to 0.94), d = 128 0.99 from 200 on (down to 0.86), and sequences of up to 256 rows 0.95 from about 112 on.
-    // (The number of tiles is known to about 3 %: up to 33/32 of the units.)
     if constexpr (WINDOWED && D > 32) {
-        const int64_t reach = (int64_t)p.left + p.right, tiles = tiles_expected(p), units = compute_units();
-        const bool alone = 2 * tiles > units && 32 * tiles <= 33 * units;
-        const int alone_limit = p.max_kv <= 256 ? 112 : D == 64 ? 320 : 200;
-        if (p.left >= 0 && p.right >= 0 && reach < (alone ? alone_limit : D == 64 ? 704 : 448))
-            return launch_passes<D, WINDOWED, 2>(p, ws, any_softmax, stream);
+        if (window_in_two_waves(p)) return launch_passes<D, WINDOWED, 2>(p, ws, any_softmax, stream);
     }
     return launch_passes<D, WINDOWED, 4>(p, ws, any_softmax, stream);
 }

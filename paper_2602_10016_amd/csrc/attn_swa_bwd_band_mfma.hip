@@ -429,6 +429,10 @@ bool swa_bwd_band_applies(const AttnParams& p, int dtype) {
     const int64_t tiles = tiles_reached(p.left, p.max_kv) + tiles_reached(p.right, p.max_kv) + 1;
     if (tiles > SWB_MAX_TILES) return false;
     const float units = (float)compute_units(), items = (float)p.B * p.H / units;
+    // Sequences of a few tiles: a workgroup of 157 KB is a prologue to most of its item.  1000 random launches, one pass over two: 1.15 in the
+    // mean; 0.85 (0.69 to 1.04) over sequences of up to 128 rows where the two passes run as small launches, 0.96 (0.92 to 1.01) for 9 to
+    // 16 items per compute unit of up to 128 rows and 60 and more on average; other sequences of less than 128 rows 1.12 (0.89 to 1.71).
+    if (p.max_kv <= 4 * KT && (mfma_bwd_tiled_small_window(p) || (items > 8 && items <= 16 && p.total_q >= (int64_t)60 * p.B))) return false;
     const float longest = (float)p.max_kv, each = (float)p.total_q / p.B, mean = items * each;
     // the rounds that equal lengths leave incomplete
     const float shortest = fmaxf(0.f, 2.f * each - longest);

@@ -145,6 +145,8 @@ hipError_t launch_mfma_bwd_wide(const AttnParams& p, void* counters, void* order
 size_t mfma_bwd_wide_workspace(int B, int H, int d, int max_q, int max_kv, int64_t total_kv);
 // Two-pass matrix-core backward (sliding window, or more than 64 queries per example).
 bool mfma_bwd_tiled_supported(const AttnParams& p, int dtype);
+// Window backward: whether the two passes run as small launches do (workgroups of two waves, tiles by offsets).
+bool mfma_bwd_tiled_small_window(const AttnParams& p);
 // chunk_tiles: query tiles per workgroup with at most 32 keys per example (partial sums are kept per workgroup), the fastest
 // number up to the largest; no other call depends on it.
 constexpr int FEWKEYS_MAX_TILES = 8;

@@ -90,6 +90,23 @@ def test_one_pass_and_two_passes_give_the_same_bits(kind, left, right):
             assert torch.equal(bits(a[at]), bits(ref)), f"{kind} window=({left}, {right}) sequence of {n} rows {name}"
 
 
+# 1384 items of up to 22 rows: the two passes by offsets, in workgroups of two waves; 2400 of 100 to 120 rows and 2080 of 73 to 91: two
+# passes by tables; short sequences in one pass: few and many items, up to 32 rows, and beside one of 130 rows
+@pytest.mark.gpu
+@pytest.mark.parametrize("B,H,lo,hi,left,right,one_pass", [(346, 4, 1, 22, 20, 20, False), (600, 4, 100, 120, 63, 0, False), (520, 4, 73, 91, 90, 90, False),
+                                                           (256, 2, 100, 120, 255, 0, True), (1536, 4, 100, 120, 63, 0, True), (4096, 1, 8, 32, 31, 0, True),
+                                                           (600, 4, 100, 130, 63, 0, True)])
+def test_which_short_sequences_take_one_pass(B, H, lo, hi, left, right, one_pass):
+    from paper_2602_10016_amd import binding as kb
+    lengths = np.random.default_rng(B).integers(lo, hi + 1, size=B)
+    lengths[B // 2] = hi
+    off, scale, (q, k, v, o, lse, d_o) = prepared("ordinary", lengths, H, left, right)
+    total, order_end = int(off[-1]), 256 + ((B + 1) * 4 + 255) // 256 * 256
+    ws = torch.full((kb.workspace_bytes(kb.OP_SWA_BWD, B, H, 128, hi, hi, total, total),), 0xEE, dtype=torch.uint8, device="cuda")
+    kb.swa_bwd(q, k, v, o, lse, d_o, offsets_dev(off), left, right, scale, max_len=hi, workspace=ws)
+    assert bool(torch.all(ws[order_end:] == 0xEE)) == one_pass
+
+
 def test_the_one_pass_window_backward_keeps_its_registers(tmp_path):
     """A reload from scratch memory would also count among the vector-memory operations that the kernel's waits number."""
     spilled = spilled_vector_registers("attn_swa_bwd_band_mfma.hip", tmp_path)
