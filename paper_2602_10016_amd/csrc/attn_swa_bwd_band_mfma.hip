@@ -417,6 +417,7 @@ __global__ __launch_bounds__(64 * SWB_WAVES, 2) void swa_bwd_band_kernel(AttnPar
     swa_bwd_band_item(p, swb_lds, h, row0, n, L_tiles, R_tiles);
 }
 
+static int64_t band_items(const AttnParams& p) { return (((int64_t)p.B + 7) / 8) * 8 * p.H; }
 static int64_t tiles_reached(int reach, int max_len) { return ((int64_t)(reach < 0 || reach > max_len ? max_len : reach) + KT - 1) / KT; }
 
 // A step takes as long whatever the other compute units do, so a launch lasts as long as the compute unit with the most steps, where the
@@ -427,7 +428,7 @@ static int64_t tiles_reached(int reach, int max_len) { return ((int64_t)(reach <
 bool swa_bwd_band_applies(const AttnParams& p, int dtype) {
     if (!p.windowed || dtype != KUNLUN_BF16 || p.d != SwbSmem::D) return false;
     const int64_t tiles = tiles_reached(p.left, p.max_kv) + tiles_reached(p.right, p.max_kv) + 1;
-    if (tiles > SWB_MAX_TILES) return false;
+    if (tiles > SWB_MAX_TILES || band_items(p) > largest_grid(64 * SWB_WAVES)) return false;
     const float units = (float)compute_units(), items = (float)p.B * p.H / units;
     // Sequences of a few tiles: a workgroup of 157 KB is a prologue to most of its item.  1000 random launches, one pass over two: 1.15 in the
     // mean; 0.85 (0.69 to 1.04) over sequences of up to 128 rows where the two passes run as small launches, 0.96 (0.92 to 1.01) for 9 to
@@ -446,8 +447,7 @@ hipError_t launch_swa_bwd_band(const AttnParams& p, hipStream_t stream) {
     // once per process (thread-safe initialisation of a function-local static); not a stream operation
     static const hipError_t raised = hipFuncSetAttribute((const void*)swa_bwd_band_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
     if (raised != hipSuccess) return raised;
-    const int64_t n_items = (((int64_t)p.B + 7) / 8) * 8 * p.H;
-    hipLaunchKernelGGL(swa_bwd_band_kernel, dim3((unsigned)n_items), dim3(64 * SWB_WAVES), bytes, stream, p,
+    hipLaunchKernelGGL(swa_bwd_band_kernel, dim3((unsigned)band_items(p)), dim3(64 * SWB_WAVES), bytes, stream, p,
                        (int)tiles_reached(p.left, p.max_kv), (int)tiles_reached(p.right, p.max_kv));
     return hipGetLastError();
 }

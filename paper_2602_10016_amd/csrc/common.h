@@ -60,6 +60,8 @@ hipError_t launch_seed_grad_sum(const void* rows, void* d_e, float* partial, int
 hipError_t launch_schedule(const int32_t* kv_off, int B, int max_kv, int32_t* order, int32_t* counters, hipStream_t stream);
 // Compute units of the current device (cached per process).
 int compute_units();
+// Workgroups that one launch may have: its work items are counted in 32 bits.
+inline int64_t largest_grid(int threads) { return (((int64_t)1 << 32) - 1) / threads; }
 typedef __attribute__((ext_vector_type(4))) unsigned int u32x4_t;
 hipError_t launch_stream_probe(const void* a, const void* b, const void* c, void* out, size_t bytes, int reads, int write,
                                hipStream_t stream);

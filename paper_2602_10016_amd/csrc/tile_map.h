@@ -68,7 +68,7 @@ inline int64_t dense_tile_grid(const AttnParams& p) { return ((int64_t)p.B + 7) 
 // 1.45 and 1.18, 900..1024 keys 0.96 to 1.0, 30..120 keys 0.91 to 0.97.  256 seeds over 256 log-normal histories, 8 heads, d = 128: forward 500 / 440 us.
 inline bool dense_tiles_sorted(const AttnParams& p) {
     return !p.windowed && !p.q_off && p.max_kv > 256 && (int64_t)p.max_kv * p.B > 5 * p.total_kv / 4 && dense_tile_grid(p) > 2 * compute_units() &&
-           dense_tile_grid(p) <= (int64_t)1 << 30;
+           dense_tile_grid(p) <= largest_grid(256);
 }
 #ifdef __HIPCC__
 // Rank in the issue order of item group k (one example) of an XCD: dealt forth and back, so that no XCD has the longer one of every

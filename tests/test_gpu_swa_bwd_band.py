@@ -107,6 +107,22 @@ def test_which_short_sequences_take_one_pass(B, H, lo, hi, left, right, one_pass
     assert bool(torch.all(ws[order_end:] == 0xEE)) == one_pass
 
 
+# 8.4 million sequences, most of them empty: as workgroups of 512 threads more work items than one launch may have
+@pytest.mark.gpu
+def test_more_sequences_than_one_pass_can_launch():
+    from paper_2602_10016_amd import binding as kb
+    B, rows = 8_400_000, 100_000
+    rng = np.random.default_rng(0)
+    lengths = np.zeros(B, dtype=np.int64)
+    lengths[rng.choice(B, size=rows, replace=False)] = 1
+    q, k, v, d_o = (to_dev(W.round_to_bf16(rng.standard_normal((rows, 1, 128), dtype=np.float32)), "bf16") for _ in range(4))
+    lse = ((q.float() * k.float()).sum(dim=2) * 0.1).T.contiguous()
+    dq, dk, dv = kb.swa_bwd(q, k, v, v.clone(), lse, d_o, offsets_dev(W.offsets_from_lengths(lengths)), 31, 0, 0.1, max_len=1)
+    torch.cuda.synchronize()
+    # one key each: P = 1 up to the rounding of a score of a few units in 32 bits, dS = 0 up to that of dP
+    assert torch.allclose(dv.float(), d_o.float(), rtol=1e-2, atol=0) and max(float(t.abs().max()) for t in (dq, dk)) < 1e-3
+
+
 def test_the_one_pass_window_backward_keeps_its_registers(tmp_path):
     """A reload from scratch memory would also count among the vector-memory operations that the kernel's waits number."""
     spilled = spilled_vector_registers("attn_swa_bwd_band_mfma.hip", tmp_path)
