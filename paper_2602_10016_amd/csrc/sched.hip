@@ -101,7 +101,8 @@ namespace kunlun {
 // V consecutive elements per thread (16-byte loads when the row length allows it); the additions of one element
 // happen in example order whatever V is.  What bounds it: the rows are read once, 134 MB for 256 examples of 256 seeds (8 heads,
 // d = 128); with streaming loads 26 us = 5.2 TB/s, with plain ones 34 (eight or sixteen examples in flight instead of four 28, 29).
-// Rows that the caches still hold (up to 32 MB) are read with plain loads (127 examples of 128 seeds, 1 head, d = 32: backward 27.5 / 29.0 us).
+// Rows of up to 4 MB, which one XCD's L2 holds, are read with plain loads: whole backward calls, streaming over plain, 70 of 0.2 to 4 MB 0.994
+// (0.945 to 1.006), from 6 to 16 MB 1.01 (0.99 to 1.05), to 80 MB 1.015 (0.98 to 1.085), beyond 1.02.
 // LAST: the only group, its sums are the result.
 template <typename T, int V, bool LAST, bool STREAM>
 __global__ __launch_bounds__(256) void seed_grad_group_kernel(const T* __restrict__ rows, float* __restrict__ partial, T* __restrict__ d_e, int B,
@@ -145,7 +146,7 @@ static hipError_t launch_seed_grad(const T* rows, T* d_e, float* partial, int B,
         hipLaunchKernelGGL((seed_grad_group_kernel<T, V, true, false>), grid, dim3(256), 0, stream, rows, partial, d_e, B, n_elems);
         return hipGetLastError();
     }
-    if ((int64_t)B * n_elems * (int64_t)sizeof(T) > (int64_t)32 << 20)
+    if ((int64_t)B * n_elems * (int64_t)sizeof(T) > (int64_t)4 << 20)
         hipLaunchKernelGGL((seed_grad_group_kernel<T, V, false, true>), grid, dim3(256), 0, stream, rows, partial, d_e, B, n_elems);
     else
         hipLaunchKernelGGL((seed_grad_group_kernel<T, V, false, false>), grid, dim3(256), 0, stream, rows, partial, d_e, B, n_elems);

@@ -14,6 +14,17 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("dtype,H,d,n_seeds", [("bf16", 2, 32, 8), ("bf16", 1, 24, 3), ("fp32", 1, 32, 5), ("fp32", 3, 24, 3)])
 @pytest.mark.parametrize("B", [1, 31, 32, 33, 64, 65])
 def test_seed_gradient_is_the_sum_in_order(B, dtype, H, d, n_seeds):
+    check(B, dtype, H, d, n_seeds)
+
+
+# rows of 3.7, 4.1 and 33 MiB in bf16, 4.1 in fp32 and 4.3 of the generic kernels: read with streaming loads above 4 MiB
+@pytest.mark.parametrize("B,dtype,H,d,n_seeds", [(34, "bf16", 4, 64, 224), (37, "bf16", 4, 64, 225), (65, "bf16", 8, 128, 256), (33, "fp32", 4, 64, 128),
+                                                 (36, "bf16", 1, 24, 2600)])
+def test_seed_gradient_of_many_rows(B, dtype, H, d, n_seeds):
+    check(B, dtype, H, d, n_seeds)
+
+
+def check(B, dtype, H, d, n_seeds):
     rng = np.random.default_rng(B * 100 + d)
     t = torch.bfloat16 if dtype == "bf16" else torch.float32
     off = np.concatenate([[0], np.cumsum(rng.integers(0, 70, size=B))]).astype(np.int32)
