@@ -158,11 +158,10 @@ __device__ __forceinline__ void swa_bwd_band_item(const AttnParams& p, char* lds
     // In every step the waves meet where dQ of the last step is done and its images are free, and the key tile that the widest
     // window takes up in this step has arrived.
     auto meet = [&]() {
-        if (behind == 0) wait_vmcnt<0>();
-        else if (behind == 2) wait_vmcnt<2>();
+        if (behind == 2) wait_vmcnt<2>();
         else if (behind == LOADS) wait_vmcnt<LOADS>();
         else if (behind == STORES) wait_vmcnt<STORES>();
-        else if (behind == STORES + 2) wait_vmcnt<STORES + 2>();
+        else if (behind >= 0) wait_vmcnt<0>();
         __syncthreads();
     };
     bf16x8 dsf[2];
@@ -285,6 +284,7 @@ __device__ __forceinline__ void swa_bwd_band_item(const AttnParams& p, char* lds
 
     // dQ rows of query tile i, a channel block per wave
     auto query_gradient = [&](int i) {
+        static_assert(DB == 4, "a channel block per helping wave");
         const int db = wave & 3;
         const int j0 = i - L_tiles > 0 ? i - L_tiles : 0, j1 = i + R_tiles < nt - 1 ? i + R_tiles : nt - 1;
         int dq_lane = threadIdx.x & 63;
@@ -328,7 +328,6 @@ __device__ __forceinline__ void swa_bwd_band_item(const AttnParams& p, char* lds
     // Key tiles are loaded a step before they are taken up; where the widest window has no slot for that yet, at the end of it, which
     // is soon enough: its waves take them up late in their step.
     const bool early = L_tiles + R_tiles + 1 < SWB_MAX_TILES;
-    const bool late = false;  // a wave has a step without a key tile in which its rows can go out
     if (wave >= SWB_WAVES / 2) issue_keys(0);
     if (wave < SWB_LOADERS && i0 >= 0) issue_queries(i0, wave);
     wait_vmcnt<0>();
@@ -338,16 +337,16 @@ __device__ __forceinline__ void swa_bwd_band_item(const AttnParams& p, char* lds
         // the half of the waves without the one that takes up a key tile computes dQ of the last step
         const int taker = (i + R_tiles) & (SWB_WAVES - 1);
         const bool helper = (wave ^ taker) >> 2;
-        // two of its neighbours load for the next step
+        // two of its neighbours load for the next step.  (Helpers, loaders and the taker are different waves, and the wave that sends out
+        // its rows in front of the meeting is the taker, so that `behind` counts one kind of operation.)
         const int part = i + 1 >= 0 && i + 1 < nt && !helper ? ((wave - taker) & 3) - 1 : -1;
         const bool loader = part >= 0 && part < SWB_LOADERS;
         const bool keys = helper && i + 1 + R_tiles < nt;
-        if (late && cur >= 0 && cur + L_tiles < i) retire();
         behind = !helper && early ? -1 : loader ? LOADS : 0;
         if (loader) issue_queries(i + 1, part);
         if (helper) {
             if (keys && early) issue_keys(i + 1 + R_tiles);
-            if (i > 0 && (wave & 3) < DB) {
+            if (i > 0) {
                 query_gradient(i - 1);
                 behind = 2;
             }
