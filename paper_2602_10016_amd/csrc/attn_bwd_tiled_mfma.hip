@@ -965,8 +965,9 @@ static hipError_t launch_passes(const AttnParams& p, char* ws, bool any_softmax,
 
 // Narrow windows: workgroups of two waves (64 rows) and a ring of two stages, four (d = 128) or six (d = 64) instead of two or
 // three workgroups per compute unit - fewer steps in which a wave of the workgroup is outside its own window (previous 256: a
-// tenth instead of a quarter), for more tile loads per row, which is what counts in wide windows.  Training step, us, four /
-// two waves: d = 128, previous 256: 635 / 623, previous 64: 505 / 503, 500 to both sides: 693 / 714;  d = 64, previous 256:
+// tenth instead of a quarter), for more tile loads per row, which is what counts in wide windows.  (At d = 128 the one-pass kernel is
+// asked first, swa_bwd_band_applies(); what it takes, windows of up to nine tiles over many even sequences, is in these figures.)  Training
+// step, us, four / two waves: d = 128, previous 256: 635 / 623, previous 64: 505 / 503, 500 to both sides: 693 / 714;  d = 64, previous 256:
 // 348 / 340, 50 to both sides: 570 / 560;  d = 32, previous 256: 434 / 433 (a tile is two load instructions there).
 // Backward alone, 500 random calls, two waves over four by reach (d = 64 / d = 128): 100..199 1.12 / 1.11, 200..383 1.07 / 1.07,
 // 384..449 1.05 / 1.06, 450..549 1.05 / 1.03 with losses of up to 4 % at d = 128, 550..699 1.03 / 1.01 - but for half to one tile

@@ -1,4 +1,5 @@
-"""Sliding-window backward in workgroups of two waves (64 rows; bounded windows reaching fewer than 704 rows at d = 64 and 448 at
+"""Sliding-window backward in two passes (at d = 128 the launches that the one-pass kernel is not asked for: few items, uneven lengths, or windows
+of more than nine key tiles) in workgroups of two waves (64 rows; bounded windows reaching fewer than 704 rows at d = 64 and 448 at
 d = 128, for half to one tile of 128 rows per compute unit 320 and 200, 112 for sequences of up to 256 rows) and of four (wider or unbounded windows, d = 32), against
 the CPU oracle: sequences around 32, 64 and 128 rows, windows on both sides of the lines."""
 import numpy as np
