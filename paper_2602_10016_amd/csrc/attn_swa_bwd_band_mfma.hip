@@ -429,11 +429,24 @@ bool swa_bwd_band_applies(const AttnParams& p, int dtype) {
     const int64_t tiles = tiles_reached(p.left, p.max_kv) + tiles_reached(p.right, p.max_kv) + 1;
     if (tiles > SWB_MAX_TILES || band_items(p) > largest_grid(64 * SWB_WAVES)) return false;
     const float units = (float)compute_units(), items = (float)p.B * p.H / units;
-    // Sequences of a few tiles: a workgroup of 157 KB is a prologue to most of its item.  1000 random launches, one pass over two: 1.15 in the
-    // mean; 0.85 (0.69 to 1.04) over sequences of up to 128 rows where the two passes run as small launches, 0.96 (0.92 to 1.01) for 9 to
-    // 16 items per compute unit of up to 128 rows and 60 and more on average; other sequences of less than 128 rows 1.12 (0.89 to 1.71).
-    if (p.max_kv <= 4 * KT && (mfma_bwd_tiled_small_window(p) || (items > 8 && items <= 16 && p.total_q >= (int64_t)60 * p.B))) return false;
     const float longest = (float)p.max_kv, each = (float)p.total_q / p.B, mean = items * each;
+    // Sequences of a few tiles: a workgroup of 157 KB is a prologue to most of its item, and the steps in front of the first query tile, one for
+    // each tile that the window reaches to the right, are a good part of its steps (`lead`).  One pass over two, 1191 random launches over
+    // sequences of up to 320 rows:
+    //     up to 128 rows, and the two passes run as small launches                                     0.85 (0.63 to 1.12)
+    //     up to 128 rows, 9 to 16 items per compute unit of 48 rows and more, 13 to 20 of 33 to 47     0.99 (0.89 to 1.16)
+    //     lead of 0.3 and more, 9 to 21 and 13 to 25 of these items                                    0.96 (0.84 to 1.16)
+    //     lead of 0.6 and more                                                                         0.93 (0.79 to 1.25)
+    //     any lead, 5 to 8 items of 80 rows and more                                                   0.95 (0.84 to 1.12)
+    //     the others                                                                                   1.15 (30 of 928 below 0.97)
+    if (p.max_kv <= 8 * KT) {
+        const int64_t first = tiles_reached(p.right, p.max_kv), tiles_each = tiles_reached((int)each, p.max_kv);
+        const float lead = tiles_each > 0 ? (float)(first < tiles_each - 1 ? first : tiles_each - 1) / tiles_each : 0.f;
+        const float from = each < 48 ? 12.f : 8.f, to = (each < 48 ? 20.f : 16.f) + (lead >= 0.3f ? 5.f : 0.f);
+        const bool between = each >= 33 && items > from && items <= to;
+        if (p.max_kv <= 4 * KT && (between || mfma_bwd_tiled_small_window(p))) return false;
+        if (lead >= 0.6f || (lead >= 0.3f && between) || (lead > 0 && each >= 80 && items > 4 && items <= 8)) return false;
+    }
     // the rounds that equal lengths leave incomplete
     const float shortest = fmaxf(0.f, 2.f * each - longest);
     const float whole = fmaxf(longest, mean + shortest * (ceilf(items) - items));

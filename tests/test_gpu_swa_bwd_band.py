@@ -91,11 +91,15 @@ def test_one_pass_and_two_passes_give_the_same_bits(kind, left, right):
 
 
 # 1384 items of up to 22 rows: the two passes by offsets, in workgroups of two waves; 2400 of 100 to 120 rows and 2080 of 73 to 91: two
-# passes by tables; short sequences in one pass: few and many items, up to 32 rows, and beside one of 130 rows
+# passes by tables; short sequences in one pass: few and many items, up to 32 rows, and beside one of 130 rows.  Windows to the right over short
+# sequences, whose first steps only take up key tiles: 19 items per compute unit of four tiles, of two, six of four tiles, and few of
+# three in two passes; seven of two tiles and 30 of two in one
 @pytest.mark.gpu
 @pytest.mark.parametrize("B,H,lo,hi,left,right,one_pass", [(346, 4, 1, 22, 20, 20, False), (600, 4, 100, 120, 63, 0, False), (520, 4, 73, 91, 90, 90, False),
                                                            (256, 2, 100, 120, 255, 0, True), (1536, 4, 100, 120, 63, 0, True), (4096, 1, 8, 32, 31, 0, True),
-                                                           (600, 4, 100, 130, 63, 0, True)])
+                                                           (600, 4, 100, 130, 63, 0, True), (1659, 3, 91, 114, -1, 122, False), (674, 8, 36, 42, -1, 1, False),
+                                                           (194, 8, 98, 122, 40, 20, False), (300, 2, 130, 160, 20, 120, False), (450, 4, 40, 60, 20, 20, True),
+                                                           (3840, 2, 56, 62, 40, 40, True)])
 def test_which_short_sequences_take_one_pass(B, H, lo, hi, left, right, one_pass):
     from paper_2602_10016_amd import binding as kb
     lengths = np.random.default_rng(B).integers(lo, hi + 1, size=B)
