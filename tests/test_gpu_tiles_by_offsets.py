@@ -95,13 +95,23 @@ def test_sliding_window_backward(oracle, B, H, d, longest, left, right, tables):
 @pytest.mark.parametrize("d,B,H,longest,tables", [(64, 1700, 2, 90, True), (128, 1100, 2, 90, True), (32, 1700, 2, 90, False), (64, 150, 2, 90, False), (128, 150, 2, 90, False),
                                                   (64, 200, 2, 700, False), (128, 200, 2, 700, False)])
 def test_few_keys_of_short_examples_keep_the_tables(d, B, H, longest, tables):
+    assert few_keys_by_tables(d, B, H, longest // 2, longest) == tables
+
+
+# chunks of nearly equal lengths: one round of two workgroups per compute unit by tables and two of numbers; one of either
+@pytest.mark.parametrize("d,B,H,shortest,longest,tables", [(128, 401, 1, 103, 129, True), (64, 217, 2, 104, 131, True), (128, 150, 1, 103, 129, False)])
+def test_few_keys_of_nearly_equal_lengths(d, B, H, shortest, longest, tables):
+    assert few_keys_by_tables(d, B, H, shortest, longest) == tables
+
+
+def few_keys_by_tables(d, B, H, shortest, longest):
     from paper_2602_10016_amd import binding as kb
     rng = np.random.default_rng(B + d)
-    lengths = rng.integers(longest // 2, longest + 1, size=B)
+    lengths = rng.integers(shortest, longest + 1, size=B)
     lengths[0] = longest
     q_off, kv_off = W.offsets_from_lengths(lengths), W.offsets_from_lengths(np.full(B, 8))
     q, k, v, d_o = (to_dev(values(rng, int(n), H, d), "bf16") for n in (q_off[-1], kv_off[-1], kv_off[-1], q_off[-1]))
     ws = workspace(kb, kb.OP_GDPA_BWD, B, H, d, longest, 8, q.shape[0], k.shape[0])
     kb.gdpa_bwd(q, k, v, d_o, offsets_dev(kv_off), 0.1, 3, q_offsets=offsets_dev(q_off), max_q=longest, max_kv=8, workspace=ws)
     torch.cuda.synchronize()
-    assert tables_written(ws, behind_order(B)) == tables
+    return tables_written(ws, behind_order(B))
