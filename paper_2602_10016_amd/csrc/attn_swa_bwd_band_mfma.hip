@@ -15,13 +15,14 @@
 // A window of nine tiles (256 rows) makes one wave a step hand its key tile over: it finishes tile i - L, sends out its rows and
 // takes tile i + R (L, R: tiles to the left and right) within the step.
 //
-// What bounds it: the chain of a step, not bytes or flops.  Previous 256, 128 sequences of 256..2048 rows, 4 heads: 72 steps per
-// compute unit of 4.6 us (9800 cycles: 3500 for the first tile, 1900 for the rows of the finished one, 2700 for the tile taken up,
-// 1000 between them), 335 us = 3.6 TB/s and 550 TFLOP/s; without its loads and stores 275 us.  The two-pass kernels
-// (attn_bwd_tiled_mfma.hip), which compute S and dP twice and load every row of the window for each tile of 64, take 482.  Windows of
-// two to five tiles: 270 to 280 against 363 to 396.  At d = 64 the same kernel gains nothing (230 against 260 us at nine tiles, 205
-// against 208 at five), at d = 32 it loses: the chain does not shrink with the bytes.  Rows through LDS instead of straight from
-// registers (whole rows per store instruction) and the masks beside the matrix instructions changed less than 2 %.
+// What bounds it: the chain of a step, not bytes or flops.  Previous 256, 128 sequences of 256..2048 rows, 4 heads: 73 steps per
+// compute unit in the mean, 4.7 us each (at nine tiles the longest chain is that of the wave that finishes one key tile, sends out its
+// rows and takes the next): 340 to 359 us = 3.5 TB/s and 490 TFLOP/s (ten flops per pair and channel).  The two-pass kernels
+// (attn_bwd_tiled_mfma.hip), which compute S and dP twice and load every row of the window for each tile of 64, take 470 to 485.  Windows of
+// two to five tiles: 266 to 278 against 352 to 388.  Tried with sums in another order (2 % faster in the whole kernel): at d = 64 the same
+// kernel gains nothing (230 against 260 us at nine tiles, 205 against 208 at five), at d = 32 it loses, as the chain does not shrink with
+// the bytes; rows through LDS instead of straight from registers (whole rows per store instruction) and the masks beside the matrix
+// instructions changed less than 2 %.
 #include <type_traits>
 
 #include "lds_ring.h"
