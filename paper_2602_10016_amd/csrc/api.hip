@@ -240,7 +240,7 @@ int kunlun::gdpa_fwd_checked(const void* q, const void* k, const void* v, void* 
     hipError_t e;
     if (mfma_fwd_supported(p, dtype)) {
         int32_t* order = (int32_t*)((char*)workspace + WS_HEADER_BYTES);
-        if (mfma_fwd_is_qtiled(p) && !dense_tiles_sorted(p)) {
+        if (mfma_fwd_is_qtiled(p) && !dense_tiles_sorted_fwd(p)) {
             p.order = order;  // holds the query-tile prefix sums
         } else if (!mfma_fwd_is_qtiled(p) && !mfma_fwd_plan(p).sorted) {
             p.order = nullptr;

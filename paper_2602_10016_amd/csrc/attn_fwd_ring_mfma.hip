@@ -271,7 +271,7 @@ __global__ __launch_bounds__(64 * NW, OCC) void qtile_fwd_mfma_kernel(AttnParams
 template <int D, int NW, int OCC, bool WINDOWED>
 static hipError_t launch_qtiled(const AttnParams& p, hipStream_t stream) {
     if constexpr (!WINDOWED) {
-        if (dense_tiles_sorted(p)) {
+        if (dense_tiles_sorted_fwd(p)) {
             hipLaunchKernelGGL((qtile_fwd_mfma_kernel<D, NW, OCC, false, BY_ORDER>), dim3((unsigned)dense_tile_grid(p)), dim3(64 * NW), 0, stream, p,
                                nullptr, nullptr, 1);
             return hipGetLastError();
@@ -298,7 +298,7 @@ static hipError_t launch_qtiled(const AttnParams& p, hipStream_t stream) {
     return hipGetLastError();
 }
 
-// p.order points at tile_table_bytes(B, total_q) bytes of workspace, or at the sorted examples (dense_tiles_sorted()).
+// p.order points at tile_table_bytes(B, total_q) bytes of workspace, or at the sorted examples (dense_tiles_sorted_fwd()).
 hipError_t launch_mfma_fwd_qtiled(const AttnParams& p, hipStream_t stream) {
     // 128-query tiles (4 waves of 32 queries)
     if (p.windowed)

@@ -35,3 +35,30 @@ def test_dense_queries_over_uneven_histories(oracle, B, H, d, n, longest, act):
     refs = oracle.gdpa_bwd(wl.q, wl.k, wl.v, d_o.double().numpy(), wl.kv_offsets, wl.scale, act, max_q=n)
     for a, ref, name in zip((o, *got), (o_ref, *refs), ("O", "dQ", "dK", "dV")):
         assert_close(to_np(a), ref, TOL["bf16"], f"B={B} H={H} d={d} n={n} act={act} {name}")
+
+
+# one tile per example: the forward at d = 128 over up to 352 keys leaves more than 4608 of them (256 compute units) in the order of the tables where
+# the longest history is at most 2.5 times the mean, and more than 7168 of any histories; a part of the batch is sorted, with the same bits
+@pytest.mark.parametrize("B,d,n,shortest,longest,tables", [(5000, 128, 70, 1, 280, True), (5000, 128, 70, 150, 352, True), (5000, 64, 70, 1, 280, False), (2504, 128, 130, 1, 280, False),
+                                                           (5000, 128, 65, 1, 360, False), (4600, 128, 65, 1, 280, False), (7400, 128, 65, -300, 300, True),
+                                                           (7000, 128, 65, -300, 300, False)])
+def test_many_short_histories_keep_the_tables(B, d, n, shortest, longest, tables):
+    from paper_2602_10016_amd import binding as kb
+    rng = np.random.default_rng(B + n)
+    lengths = np.maximum(1, rng.integers(shortest, longest + 1, size=B))
+    some = 64 * (8 if n <= 128 else 4) + 8  # more than 512 workgroups
+    lengths[[0, some - 1]] = longest
+    offsets = np.concatenate([[0], np.cumsum(lengths)])
+    normal = lambda rows: torch.from_numpy(rng.standard_normal((rows, 1, d), dtype=np.float32)).to(torch.bfloat16).cuda()
+    q, k, v = normal(B * n), normal(int(offsets[-1])), normal(int(offsets[-1]))
+
+    def forward(examples):
+        keys = int(offsets[examples])
+        ws = torch.zeros(kb.workspace_bytes(kb.OP_GDPA_FWD, examples, 1, d, n, longest, examples * n, keys), dtype=torch.uint8, device="cuda")
+        o, _ = kb.gdpa_fwd(q[:examples * n], k[:keys], v[:keys], offsets_dev(offsets[:examples + 1]), d ** -0.5, 0, max_q=n, max_kv=longest, workspace=ws)
+        listed = ws[256:256 + 4 * examples].view(torch.int32).cpu()  # the first tile of every example, or the examples, longest history first
+        return o, torch.equal(listed, torch.arange(examples, dtype=torch.int32) * ((n + 127) // 128))
+
+    (o, by_tables), (part, part_by_tables) = forward(B), forward(some)
+    assert by_tables == tables and not part_by_tables
+    assert torch.equal(o[:some * n].view(torch.int16), part.view(torch.int16))
